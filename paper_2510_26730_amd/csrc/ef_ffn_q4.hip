@@ -64,6 +64,84 @@ __device__ __forceinline__ q4_half2 q4_scale(uint16_t b) {
 template <int TT> constexpr int q4_depth() { return 6; }
 constexpr int kQ4Lds = 4;     // LDS ring of shared token / activation fragments (stages)
 
+// K loop of the first half for NTL live token tiles of a pass of TT: stages [k0, k0 + nloc) of 64 inputs each, `xs` the
+// LDS ring of the four waves that share these stages.  The number of live tiles is the same for a whole workgroup.
+template <int TT, int NTL, int D>
+__device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, const uint16_t *__restrict__ sA,
+                                             const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int k0, int nloc,
+                                             int wave, int lane, floatx16 (&G)[TT], floatx16 (&U)[TT]) {
+    u32x4_t qa[D], qb[D], xr[D][NTL];
+    uint16_t sa[D], sb[D];
+#define EF_Q4U_LOAD(slot, kq)                                                                             \
+    {                                                                                                     \
+        const int kc_ = k0 + min((kq), nloc - 1);                                                         \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                   \
+            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64);    \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+        qa[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w13 + (size_t)kc_ * 128));       \
+        qb[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w13 + (size_t)kc_ * 128 + 64));  \
+        sa[slot] = sA[(size_t)(kc_ >> 1) * 64];                                                           \
+        sb[slot] = sA[(size_t)(kc_ >> 1) * 64 + 32];                                                      \
+    }
+#define EF_Q4U_SHARE(slot, st)                                                                            \
+    {                                                                                                     \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
+    }
+    // The MFMAs of a k-step are issued between the vector instructions that dequantise the next
+    // k-step's fragments (one MFMA, then a share of the ~40 vector instructions), so the matrix
+    // cores work while the wave converts: a wave issues in order and has the SIMD to itself, nothing
+    // else would overlap the two.
+#define EF_Q4U_COMPUTE(slot, st)                                                                          \
+    {                                                                                                     \
+        const q4_half2 f1_ = q4_scale(sa[slot]), f3_ = q4_scale(sb[slot]);                                \
+        u32x4_t xb_[NTL][4];                                                                              \
+        _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt)                                                \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j) xb_[tt][j] = xs[(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
+        u32x4_t a1_ = dequant_q4(qa[slot][0], f1_), a3_ = dequant_q4(qb[slot][0], f3_);                   \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                   \
+            u32x4_t n1_ = a1_, n3_ = a3_;                                                                 \
+            if (j < 3) { n1_ = dequant_q4(qa[slot][j + 1], f1_); n3_ = dequant_q4(qb[slot][j + 1], f3_); } \
+            _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) {                                           \
+                G[tt] = mfma32h(a1_, xb_[tt][j], G[tt]);                                                  \
+                U[tt] = mfma32h(a3_, xb_[tt][j], U[tt]);                                                  \
+            }                                                                                             \
+            if (j < 3) {                                                                                  \
+                _Pragma("unroll") for (int q_ = 0; q_ < 2 * NTL; ++q_) {                                  \
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
+                    __builtin_amdgcn_sched_group_barrier(0x002, 40 / (2 * NTL), 0);                       \
+                }                                                                                         \
+            }                                                                                             \
+            a1_ = n1_; a3_ = n3_;                                                                         \
+        }                                                                                                 \
+    }
+    // one stage: hand the next stage's token fragments to the workgroup, compute this one, refill the
+    // register slot just used, barrier (the next stage's fragments are visible; this stage's LDS
+    // buffer is overwritten three stages from now)
+#define EF_Q4U_STAGE(slot, next_slot, st)                                                                 \
+    {                                                                                                     \
+        EF_Q4U_SHARE(next_slot, (st) + 1)                                                                 \
+        EF_Q4U_COMPUTE(slot, st)                                                                          \
+        EF_Q4U_LOAD(slot, (st) + D)                                                                       \
+        __syncthreads();                                                                                  \
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_LOAD(ring_, ring_)
+    EF_Q4U_SHARE(0, 0)
+    __syncthreads();
+    int st = 0;
+    for (; st + D <= nloc; st += D) {
+#pragma unroll
+        for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_STAGE(ring_, (ring_ + 1) % D, st + ring_)
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D - 1; ++ring_)
+        if (st + ring_ < nloc) EF_Q4U_STAGE(ring_, ring_ + 1, st + ring_)
+#undef EF_Q4U_LOAD
+#undef EF_Q4U_SHARE
+#undef EF_Q4U_COMPUTE
+#undef EF_Q4U_STAGE
+}
+
 // ------------------------------------------------------------------------------------------
 // first half: act = silu(X W1^T) * (X W3^T).  Workgroup = (group, pass of TT token tiles, four
 // consecutive 32-row blocks of F), wave = one row block and one of KH halves of the K range.
@@ -112,76 +190,11 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
 
-    u32x4_t qa[D], qb[D], xr[D][TT];
-    uint16_t sa[D], sb[D];
-#define EF_Q4U_LOAD(slot, kq)                                                                             \
-    {                                                                                                     \
-        const int kc_ = k0 + min((kq), nloc - 1);                                                         \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u)                                                    \
-            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64);    \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-        qa[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w13 + (size_t)kc_ * 128));       \
-        qb[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w13 + (size_t)kc_ * 128 + 64));  \
-        sa[slot] = sA[(size_t)(kc_ >> 1) * 64];                                                           \
-        sb[slot] = sA[(size_t)(kc_ >> 1) * 64 + 32];                                                      \
-    }
-#define EF_Q4U_SHARE(slot, st)                                                                            \
-    {                                                                                                     \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u) xs[kh][(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
-    }
-    // The MFMAs of a k-step are issued between the vector instructions that dequantise the next
-    // k-step's fragments (one MFMA, then a share of the ~40 vector instructions), so the matrix
-    // cores work while the wave converts: a wave issues in order and has the SIMD to itself, nothing
-    // else would overlap the two.
-#define EF_Q4U_COMPUTE(slot, st)                                                                          \
-    {                                                                                                     \
-        const q4_half2 f1_ = q4_scale(sa[slot]), f3_ = q4_scale(sb[slot]);                                \
-        u32x4_t xb_[TT][4];                                                                               \
-        _Pragma("unroll") for (int tt = 0; tt < TT; ++tt)                                                 \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) xb_[tt][j] = xs[kh][(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
-        u32x4_t a1_ = dequant_q4(qa[slot][0], f1_), a3_ = dequant_q4(qb[slot][0], f3_);                   \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                   \
-            u32x4_t n1_ = a1_, n3_ = a3_;                                                                 \
-            if (j < 3) { n1_ = dequant_q4(qa[slot][j + 1], f1_); n3_ = dequant_q4(qb[slot][j + 1], f3_); } \
-            _Pragma("unroll") for (int tt = 0; tt < TT; ++tt) {                                           \
-                G[tt] = mfma32h(a1_, xb_[tt][j], G[tt]);                                                  \
-                U[tt] = mfma32h(a3_, xb_[tt][j], U[tt]);                                                  \
-            }                                                                                             \
-            if (j < 3) {                                                                                  \
-                _Pragma("unroll") for (int q_ = 0; q_ < 2 * TT; ++q_) {                                   \
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
-                    __builtin_amdgcn_sched_group_barrier(0x002, 40 / (2 * TT), 0);                        \
-                }                                                                                         \
-            }                                                                                             \
-            a1_ = n1_; a3_ = n3_;                                                                         \
-        }                                                                                                 \
-    }
-    // one stage: hand the next stage's token fragments to the workgroup, compute this one, refill the
-    // register slot just used, barrier (the next stage's fragments are visible; this stage's LDS
-    // buffer is overwritten three stages from now)
-#define EF_Q4U_STAGE(slot, next_slot, st)                                                                 \
-    {                                                                                                     \
-        EF_Q4U_SHARE(next_slot, (st) + 1)                                                                 \
-        EF_Q4U_COMPUTE(slot, st)                                                                          \
-        EF_Q4U_LOAD(slot, (st) + D)                                                                       \
-        __syncthreads();                                                                                  \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_LOAD(ring_, ring_)
-    EF_Q4U_SHARE(0, 0)
-    __syncthreads();
-    int st = 0;
-    for (; st + D <= nloc; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < nloc) EF_Q4U_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_Q4U_LOAD
-#undef EF_Q4U_SHARE
-#undef EF_Q4U_COMPUTE
-#undef EF_Q4U_STAGE
+    // Groups of one live token tile take a loop of their own: half of the matrix-core work, LDS reads and token loads.
+    // In a launch of passes of two most experts have one (eight Mixtral-shaped experts, 64 tokens: 157 -> 131 us; passes
+    // of one tile for everybody instead dequantise twice where there are two: 412 against 399 us for two layers).
+    if (TT == 1 || ntl == 1) q4_up_stream<TT, 1, D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    else q4_up_stream<TT, TT, D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
 
     if constexpr (KH == 2) {
         // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
@@ -255,6 +268,79 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     return hipGetLastError();
 }
 
+// K loop of the second half, as q4_up_stream: stages [q0, q1) of the nq stages of F
+template <int TT, int NTL, int D, int CBW>
+__device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, size_t qstride,
+                                               const uint16_t *__restrict__ sB, size_t sstride,
+                                               const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
+                                               int q1, int wave, int lane, floatx16 (&acc)[CBW][TT]) {
+    u32x4_t qw[D][CBW], ar[D][NTL];
+    uint16_t sc[D][CBW];
+#define EF_Q4D_LOAD(slot, kq)                                                                             \
+    {                                                                                                     \
+        const int kc_ = min((kq), nq - 1);                                                                \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                   \
+            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64);    \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw) {                                              \
+            qw[slot][cw] = __builtin_nontemporal_load(                                                    \
+                reinterpret_cast<const u32x4_t *>(w2q + cw * qstride + (size_t)kc_ * 64));                \
+            sc[slot][cw] = sB[cw * sstride + (size_t)(kc_ >> 1) * 32];                                    \
+        }                                                                                                 \
+    }
+#define EF_Q4D_SHARE(slot, st)                                                                            \
+    {                                                                                                     \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u) as[(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = ar[slot][u]; \
+    }
+    // as in the first half: the MFMAs of one weight fragment are issued between the vector
+    // instructions that dequantise the next one
+#define EF_Q4D_COMPUTE(slot, st)                                                                          \
+    {                                                                                                     \
+        u32x4_t af_[NTL][4];                                                                              \
+        _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt)                                                \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j) af_[tt][j] = as[(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
+        q4_half2 f_[CBW];                                                                                 \
+        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw) f_[cw] = q4_scale(sc[slot][cw]);               \
+        u32x4_t w_ = dequant_q4(qw[slot][0][0], f_[0]);                                                   \
+        _Pragma("unroll") for (int idx = 0; idx < CBW * 4; ++idx) {                                       \
+            const int cw = idx >> 2, j = idx & 3;                                                         \
+            u32x4_t n_ = w_;                                                                              \
+            if (idx + 1 < CBW * 4) n_ = dequant_q4(qw[slot][(idx + 1) >> 2][(idx + 1) & 3], f_[(idx + 1) >> 2]); \
+            _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) acc[cw][tt] = mfma32h(w_, af_[tt][j], acc[cw][tt]); \
+            if (idx + 1 < CBW * 4) {                                                                      \
+                _Pragma("unroll") for (int q_ = 0; q_ < NTL; ++q_) {                                      \
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
+                    __builtin_amdgcn_sched_group_barrier(0x002, 20 / NTL, 0);                             \
+                }                                                                                         \
+            }                                                                                             \
+            w_ = n_;                                                                                      \
+        }                                                                                                 \
+    }
+#define EF_Q4D_STAGE(slot, next_slot, st)                                                                 \
+    {                                                                                                     \
+        EF_Q4D_SHARE(next_slot, (st) + 1)                                                                 \
+        EF_Q4D_COMPUTE(slot, st)                                                                          \
+        EF_Q4D_LOAD(slot, (st) + D)                                                                       \
+        __syncthreads();                                                                                  \
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_LOAD(ring_, q0 + ring_)
+    EF_Q4D_SHARE(0, q0)
+    __syncthreads();
+    int st = q0;
+    for (; st + D <= q1; st += D) {
+#pragma unroll
+        for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_STAGE(ring_, (ring_ + 1) % D, st + ring_)
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D - 1; ++ring_)
+        if (st + ring_ < q1) EF_Q4D_STAGE(ring_, ring_ + 1, st + ring_)
+#undef EF_Q4D_LOAD
+#undef EF_Q4D_SHARE
+#undef EF_Q4D_COMPUTE
+#undef EF_Q4D_STAGE
+}
+
 // ------------------------------------------------------------------------------------------
 // second half: Y = act W2^T.  Workgroup = (group, pass of TT token tiles, eight consecutive
 // 32-column blocks of d, one of `ksg` K-slices), wave = two column blocks.  Activations are operand
@@ -300,71 +386,8 @@ __global__ __launch_bounds__(256, 1) void ffn_down_q4_kernel(GroupTable gt, cons
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
 
-    u32x4_t qw[D][CBW], ar[D][TT];
-    uint16_t sc[D][CBW];
-#define EF_Q4D_LOAD(slot, kq)                                                                             \
-    {                                                                                                     \
-        const int kc_ = min((kq), nq - 1);                                                                \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u)                                                    \
-            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64);    \
-        __builtin_amdgcn_sched_barrier(0);                                                                \
-        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw) {                                              \
-            qw[slot][cw] = __builtin_nontemporal_load(                                                    \
-                reinterpret_cast<const u32x4_t *>(w2q + cw * qstride + (size_t)kc_ * 64));                \
-            sc[slot][cw] = sB[cw * sstride + (size_t)(kc_ >> 1) * 32];                                    \
-        }                                                                                                 \
-    }
-#define EF_Q4D_SHARE(slot, st)                                                                            \
-    {                                                                                                     \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u) as[(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = ar[slot][u]; \
-    }
-    // as in the first half: the MFMAs of one weight fragment are issued between the vector
-    // instructions that dequantise the next one
-#define EF_Q4D_COMPUTE(slot, st)                                                                          \
-    {                                                                                                     \
-        u32x4_t af_[TT][4];                                                                               \
-        _Pragma("unroll") for (int tt = 0; tt < TT; ++tt)                                                 \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) af_[tt][j] = as[(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
-        q4_half2 f_[CBW];                                                                                 \
-        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw) f_[cw] = q4_scale(sc[slot][cw]);               \
-        u32x4_t w_ = dequant_q4(qw[slot][0][0], f_[0]);                                                   \
-        _Pragma("unroll") for (int idx = 0; idx < CBW * 4; ++idx) {                                       \
-            const int cw = idx >> 2, j = idx & 3;                                                         \
-            u32x4_t n_ = w_;                                                                              \
-            if (idx + 1 < CBW * 4) n_ = dequant_q4(qw[slot][(idx + 1) >> 2][(idx + 1) & 3], f_[(idx + 1) >> 2]); \
-            _Pragma("unroll") for (int tt = 0; tt < TT; ++tt) acc[cw][tt] = mfma32h(w_, af_[tt][j], acc[cw][tt]); \
-            if (idx + 1 < CBW * 4) {                                                                      \
-                _Pragma("unroll") for (int q_ = 0; q_ < TT; ++q_) {                                       \
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
-                    __builtin_amdgcn_sched_group_barrier(0x002, 20 / TT, 0);                              \
-                }                                                                                         \
-            }                                                                                             \
-            w_ = n_;                                                                                      \
-        }                                                                                                 \
-    }
-#define EF_Q4D_STAGE(slot, next_slot, st)                                                                 \
-    {                                                                                                     \
-        EF_Q4D_SHARE(next_slot, (st) + 1)                                                                 \
-        EF_Q4D_COMPUTE(slot, st)                                                                          \
-        EF_Q4D_LOAD(slot, (st) + D)                                                                       \
-        __syncthreads();                                                                                  \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_LOAD(ring_, q0 + ring_)
-    EF_Q4D_SHARE(0, q0)
-    __syncthreads();
-    int st = q0;
-    for (; st + D <= q1; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < q1) EF_Q4D_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_Q4D_LOAD
-#undef EF_Q4D_SHARE
-#undef EF_Q4D_COMPUTE
-#undef EF_Q4D_STAGE
+    if (TT == 1 || ntl == 1) q4_down_stream<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+    else q4_down_stream<TT, TT, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
 
     if (!valid) return;
     const int g = lane >> 5;

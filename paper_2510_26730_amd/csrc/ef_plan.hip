@@ -462,6 +462,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     int ksg = 1, ksg_tiled = 1, split_expert = kNoSplit, split_ksg = 1;
     if (T > 0) {
         long long base_wgs = 0;
+        double streamed_w2_bytes = 0.0;   // second-half weights of the routed groups that stream (4-bit blobs)
         // token tiles per pass of the streamed launch: from the groups that stream (the tiled ones have kernels of
         // their own), with the same rule launch_phase applies to a phase's streamed groups
         int tmax = 1;
@@ -479,6 +480,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             if (counts_host[e] > 0) {
                 const int nt = (counts_host[e] + ef::kTile - 1) / ef::kTile;
                 if (use_tiled && ef::ffn_tiled_ok(d, c->cfg.d_ff, nt) && nt >= c->tune.tiled_min_tiles) continue;
+                streamed_w2_bytes += (0.5 + 2.0 / 128.0) * d * c->cfg.d_ff;
                 base_wgs += c->q4 ? ef::ffn_down_q4_wgs(d, nt, tpp, 1)
                             : tpp == 4 ? ef::ffn_down_shared_wgs(d, nt, tpp, 1) : ef::ffn_down_wgs(d, nt, tpp, 1);
             }
@@ -494,6 +496,14 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         const int units = c->q4 ? nkb_min / 4 / 6 : tpp == 4 ? nkb_min / 4 / 8 : nkb_min / 4 / 32;
         while (ksg < 8 && base_wgs * ksg < want && units / (ksg * 2) >= 1 && y_plane * (ksg * 2) <= c->y_floats)
             ksg *= 2;
+        // 4-bit: two workgroups per compute unit (their waves stall at different times) while the planes this adds
+        // cost little beside the weights, at most a quarter of their bytes written and read: eight Mixtral-shaped
+        // experts 64 tokens 416 -> 390 us per two layers, 64 DeepSeek-shaped 100 tokens 210 -> 204 us; past that
+        // the planes cost more than they gain (300 tokens, 0.4 of the weights' bytes: 385 -> 394 us)
+        if (c->q4 && c->tune.down_want_wgs == 0)
+            while (ksg < 8 && base_wgs * ksg < 512 && units / (ksg * 2) >= 1 && y_plane * (ksg * 2) <= c->y_floats &&
+                   8.0 * y_plane * ksg <= 0.25 * streamed_w2_bytes)
+                ksg *= 2;
         // A streamed launch of a little more than one round of workgroups (two fit a compute unit: 512 at a time)
         // ends in a round that is mostly empty: 544 workgroups took 28 us where 512 took 22.5.  Twice the slices make
         // the rounds half as long; taken when that saves at least a tenth of a round and a wave keeps >= 8 fragments.

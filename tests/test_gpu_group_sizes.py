@@ -1,0 +1,76 @@
+"""The grouped FFN at chosen group sizes: every number of live token tiles in a pass, full and ragged last tiles, against
+the CPU oracle.  The routing is the caller's (ef_moe_ffn takes ids, weights and permutation), so each expert gets exactly
+the tokens the case names.  Bounds as in the other parity tests: max-abs 2e-2, relative L2 1e-2 (one fp16 rounding of the
+intermediate activation; observed relative L2 2e-4)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_26730_amd import binding as ef
+from paper_2510_26730_amd import synth
+
+from helpers import LayerStack, dev_u16, float_close
+
+pytestmark = pytest.mark.gpu
+
+# tokens per expert (eight experts, one each)
+SIZES = {
+    "one tile": [1, 31, 32, 7, 0, 2, 16, 30],
+    "one and two tiles": [33, 64, 1, 32, 63, 0, 31, 2],
+    "up to four tiles": [97, 128, 65, 96, 33, 1, 0, 127],
+    "second passes": [129, 160, 193, 224, 225, 32, 1, 161],
+    "tiled beside streamed": [320, 300, 33, 1, 100, 513, 64, 0],
+}
+
+
+def run_groups(oracle_mod, cfg, sizes, q4, tune):
+    T, E = sum(sizes), cfg.E
+    st = LayerStack(cfg, 1, slots_total=E, max_tokens=T, q4=q4)
+    try:
+        if tune:
+            ef.ef_set_tuning(st.ctx, **tune)
+        for e in range(E):
+            ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        rng = np.random.default_rng(sum(sizes) + 1)
+        ids = np.repeat(np.arange(E, dtype=np.int32), sizes)
+        rng.shuffle(ids)
+        w = rng.uniform(0.2, 1.0, size=(T, 1)).astype(np.float32)
+        perm = np.argsort(ids, kind="stable").astype(np.int32)
+        inv = np.empty(T, np.int32)
+        inv[perm] = np.arange(T, dtype=np.int32)
+        counts = np.bincount(ids, minlength=E).astype(np.int32)
+        offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+        h = synth.hidden(cfg, 0, T)
+        dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        out = torch.full((T, cfg.d), float("nan"), dtype=torch.float32, device="cuda")
+        hd, d_ids, d_w, d_off, d_perm, d_inv = dev_u16(h), dev(ids), dev(w), dev(offsets), dev(perm), dev(inv)
+        ef.ef_moe_ffn(st.ctx, 0, hd, T, d_ids, d_w, counts, d_off, d_perm, d_inv, out, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        ffn = oracle_mod.expert_ffn_q4 if q4 else oracle_mod.expert_ffn
+        y = ffn(h, st.experts[0], ids.reshape(T, 1), perm)
+        shared = None
+        if cfg.F_shared:
+            if q4:
+                shared = oracle_mod.expert_ffn_q4(h, [st.shared[0]], np.zeros((T, 1), np.int32), np.arange(T))
+            else:
+                shared = oracle_mod.dense_ffn(h, *st.shared[0])
+        ref = oracle_mod.combine(y, w.astype(np.float64), inv, shared)
+        print(sizes, tune, float_close(out.cpu().numpy(), ref), flush=True)
+    finally:
+        st.close()
+
+
+@pytest.mark.parametrize("q4", [False, True], ids=["bf16", "int4"])
+@pytest.mark.parametrize("d,F,F_shared", [(256, 128, 0), (512, 640, 256)])
+@pytest.mark.parametrize("sizes", list(SIZES), ids=[s.replace(" ", "_") for s in SIZES])
+def test_group_sizes(oracle_mod, sizes, d, F, F_shared, q4):
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups", d=d, F=F, F_shared=F_shared, k=1)
+    run_groups(oracle_mod, cfg, SIZES[sizes], q4, {})
+
+
+@pytest.mark.parametrize("tune", [dict(lds_shared_occupancy=2), dict(lds_shared_occupancy=1, down_k_slices=3)], ids=str)
+def test_group_sizes_of_the_shared_forms(oracle_mod, tune):
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups", d=512, F=640, k=1)
+    run_groups(oracle_mod, cfg, SIZES["second passes"], False, tune)
