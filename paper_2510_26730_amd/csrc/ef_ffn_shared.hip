@@ -17,6 +17,70 @@ constexpr int kShDepth = 3;   // register ring: stages in flight per wave (one w
                               // fit two workgroups per CU (<= 256 registers) keep two stages
 constexpr int kShLds = 4;     // LDS ring of shared token / activation fragments (stages, power of two)
 
+// K loop of the first half for NTL live token tiles of a pass of TT (the same number for the whole workgroup): the token
+// loads, LDS traffic and matrix-core work of tiles that do not exist are left out (Mixtral-shaped chunk of 300 tokens,
+// passes of one to four live tiles: first half 369 -> 360 us, second 227 -> 207 us).
+template <int TT, int NTL, int D>
+__device__ __forceinline__ void shared_up_stream(const uint4 *__restrict__ w1, const uint4 *__restrict__ w3,
+                                                 const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int nq, int wave,
+                                                 int lane, floatx16 (&G)[TT], floatx16 (&U)[TT]) {
+    u32x4_t wa[D][4], wb[D][4], xr[D][NTL];
+    // every load is unconditional (past the end the last stage is re-read, in bounds).  The token fragments are
+    // requested before the weights: they are handed to the workgroup one stage before the weights of their
+    // stage are used, and loads return in issue order, so waiting for them must not mean waiting for those weights
+#define EF_SHU_LOAD(slot, kq)                                                                            \
+    {                                                                                                    \
+        const int kc_ = min((kq), nq - 1);                                                               \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                  \
+            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64);   \
+        __builtin_amdgcn_sched_barrier(0);                                                               \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
+            wa[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w1 + (size_t)(4 * kc_ + j) * 64)); \
+            wb[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w3 + (size_t)(4 * kc_ + j) * 64)); \
+        }                                                                                                \
+    }
+#define EF_SHU_SHARE(slot, st)                                                                           \
+    {                                                                                                    \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[(st) & (kShLds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
+    }
+#define EF_SHU_COMPUTE(slot, st)                                                                         \
+    {                                                                                                    \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
+            _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) {                                         \
+                const u32x4_t xb_ = xs[(st) & (kShLds - 1)][tt * 4 + j][lane];                           \
+                G[tt] = mfma32v(wa[slot][j], xb_, G[tt]);                                                \
+                U[tt] = mfma32v(wb[slot][j], xb_, U[tt]);                                                \
+            }                                                                                            \
+        }                                                                                                \
+    }
+    // one stage: hand the next stage's token fragments to the workgroup, compute this one, refill the
+    // register slot just used, barrier (the next stage's fragments are visible; this stage's LDS
+    // buffer is overwritten three stages from now)
+#define EF_SHU_STAGE(slot, next_slot, st)                                                                \
+    {                                                                                                    \
+        EF_SHU_SHARE(next_slot, (st) + 1)                                                                \
+        EF_SHU_COMPUTE(slot, st)                                                                         \
+        EF_SHU_LOAD(slot, (st) + D)                                                                      \
+        __syncthreads();                                                                                 \
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D; ++ring_) EF_SHU_LOAD(ring_, ring_)
+    EF_SHU_SHARE(0, 0)
+    __syncthreads();
+    int st = 0;
+    for (; st + D <= nq; st += D) {
+#pragma unroll
+        for (int ring_ = 0; ring_ < D; ++ring_) EF_SHU_STAGE(ring_, (ring_ + 1) % D, st + ring_)
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D - 1; ++ring_)
+        if (st + ring_ < nq) EF_SHU_STAGE(ring_, ring_ + 1, st + ring_)
+#undef EF_SHU_LOAD
+#undef EF_SHU_SHARE
+#undef EF_SHU_COMPUTE
+#undef EF_SHU_STAGE
+}
+
 // ------------------------------------------------------------------------------------------
 // first half: act = silu(X W1^T) * (X W3^T).  Workgroup = (group, pass of TT token tiles, four
 // consecutive 32-row blocks of F), wave = one row block, whole K range in stages of four k-blocks.
@@ -51,61 +115,10 @@ __global__ __launch_bounds__(256, OCC) void ffn_gate_up_shared_kernel(GroupTable
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
 
-    u32x4_t wa[D][4], wb[D][4], xr[D][TT];
-    // every load is unconditional (past the end the last stage is re-read, in bounds).  The token fragments are
-    // requested before the weights: they are handed to the workgroup one stage before the weights of their
-    // stage are used, and loads return in issue order, so waiting for them must not mean waiting for those weights
-#define EF_SHU_LOAD(slot, kq)                                                                            \
-    {                                                                                                    \
-        const int kc_ = min((kq), nq - 1);                                                               \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u)                                                   \
-            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64);   \
-        __builtin_amdgcn_sched_barrier(0);                                                               \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            wa[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w1 + (size_t)(4 * kc_ + j) * 64)); \
-            wb[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w3 + (size_t)(4 * kc_ + j) * 64)); \
-        }                                                                                                \
-    }
-#define EF_SHU_SHARE(slot, st)                                                                           \
-    {                                                                                                    \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u) xs[(st) & (kShLds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
-    }
-#define EF_SHU_COMPUTE(slot, st)                                                                         \
-    {                                                                                                    \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            _Pragma("unroll") for (int tt = 0; tt < TT; ++tt) {                                          \
-                const u32x4_t xb_ = xs[(st) & (kShLds - 1)][tt * 4 + j][lane];                           \
-                G[tt] = mfma32v(wa[slot][j], xb_, G[tt]);                                                \
-                U[tt] = mfma32v(wb[slot][j], xb_, U[tt]);                                                \
-            }                                                                                            \
-        }                                                                                                \
-    }
-    // one stage: hand the next stage's token fragments to the workgroup, compute this one, refill the
-    // register slot just used, barrier (the next stage's fragments are visible; this stage's LDS
-    // buffer is overwritten three stages from now)
-#define EF_SHU_STAGE(slot, next_slot, st)                                                                \
-    {                                                                                                    \
-        EF_SHU_SHARE(next_slot, (st) + 1)                                                                \
-        EF_SHU_COMPUTE(slot, st)                                                                         \
-        EF_SHU_LOAD(slot, (st) + D)                                                                      \
-        __syncthreads();                                                                                 \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_SHU_LOAD(ring_, ring_)
-    EF_SHU_SHARE(0, 0)
-    __syncthreads();
-    int st = 0;
-    for (; st + D <= nq; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_SHU_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < nq) EF_SHU_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_SHU_LOAD
-#undef EF_SHU_SHARE
-#undef EF_SHU_COMPUTE
-#undef EF_SHU_STAGE
+    if (TT == 1 || ntl == 1) shared_up_stream<TT, 1, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
+    else if (TT == 2 || ntl == 2) shared_up_stream<TT, 2, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
+    else if (ntl == 3) shared_up_stream<TT, (TT > 2 ? 3 : TT), D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
+    else shared_up_stream<TT, TT, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
 
     // a lane holds 16 F-values of one token: the two paired-order fragments the second half consumes
     const int nkb2 = F >> 4;
@@ -147,6 +160,62 @@ hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int ti
         hipLaunchKernelGGL((ffn_gate_up_shared_kernel<4, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
     else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+// K loop of the second half, as shared_up_stream: stages [q0, q1) of the nq stages of F
+template <int TT, int NTL, int D, int CBW>
+__device__ __forceinline__ void shared_down_stream(const uint4 *__restrict__ w2, size_t cb_stride,
+                                                   const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
+                                                   int q1, int wave, int lane, floatx16 (&acc)[CBW][TT]) {
+    u32x4_t wq[D][CBW][4], ar[D][NTL];
+#define EF_SHD_LOAD(slot, kq)                                                                            \
+    {                                                                                                    \
+        const int kc_ = min((kq), nq - 1);                                                               \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                  \
+            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64);   \
+        __builtin_amdgcn_sched_barrier(0);                                                               \
+        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                               \
+            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                \
+                wq[slot][cw][j] = __builtin_nontemporal_load(                                            \
+                    reinterpret_cast<const u32x4_t *>(w2 + cw * cb_stride + (size_t)(4 * kc_ + j) * 64)); \
+    }
+#define EF_SHD_SHARE(slot, st)                                                                           \
+    {                                                                                                    \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u) as[(st) & (kShLds - 1)][u * 4 + wave][lane] = ar[slot][u]; \
+    }
+#define EF_SHD_COMPUTE(slot, st)                                                                         \
+    {                                                                                                    \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
+            _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) {                                         \
+                const u32x4_t af_ = as[(st) & (kShLds - 1)][tt * 4 + j][lane];                           \
+                _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                       \
+                    acc[cw][tt] = mfma32h(wq[slot][cw][j], af_, acc[cw][tt]);                            \
+            }                                                                                            \
+        }                                                                                                \
+    }
+#define EF_SHD_STAGE(slot, next_slot, st)                                                                \
+    {                                                                                                    \
+        EF_SHD_SHARE(next_slot, (st) + 1)                                                                \
+        EF_SHD_COMPUTE(slot, st)                                                                         \
+        EF_SHD_LOAD(slot, (st) + D)                                                                      \
+        __syncthreads();                                                                                 \
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D; ++ring_) EF_SHD_LOAD(ring_, q0 + ring_)
+    EF_SHD_SHARE(0, q0)
+    __syncthreads();
+    int st = q0;
+    for (; st + D <= q1; st += D) {
+#pragma unroll
+        for (int ring_ = 0; ring_ < D; ++ring_) EF_SHD_STAGE(ring_, (ring_ + 1) % D, st + ring_)
+    }
+#pragma unroll
+    for (int ring_ = 0; ring_ < D - 1; ++ring_)
+        if (st + ring_ < q1) EF_SHD_STAGE(ring_, ring_ + 1, st + ring_)
+#undef EF_SHD_LOAD
+#undef EF_SHD_SHARE
+#undef EF_SHD_COMPUTE
+#undef EF_SHD_STAGE
 }
 
 // ------------------------------------------------------------------------------------------
@@ -192,55 +261,10 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
 
-    u32x4_t wq[D][CBW][4], ar[D][TT];
-#define EF_SHD_LOAD(slot, kq)                                                                            \
-    {                                                                                                    \
-        const int kc_ = min((kq), nq - 1);                                                               \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u)                                                   \
-            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64);   \
-        __builtin_amdgcn_sched_barrier(0);                                                               \
-        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                               \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                \
-                wq[slot][cw][j] = __builtin_nontemporal_load(                                            \
-                    reinterpret_cast<const u32x4_t *>(w2 + cw * cb_stride + (size_t)(4 * kc_ + j) * 64)); \
-    }
-#define EF_SHD_SHARE(slot, st)                                                                           \
-    {                                                                                                    \
-        _Pragma("unroll") for (int u = 0; u < TT; ++u) as[(st) & (kShLds - 1)][u * 4 + wave][lane] = ar[slot][u]; \
-    }
-#define EF_SHD_COMPUTE(slot, st)                                                                         \
-    {                                                                                                    \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            _Pragma("unroll") for (int tt = 0; tt < TT; ++tt) {                                          \
-                const u32x4_t af_ = as[(st) & (kShLds - 1)][tt * 4 + j][lane];                           \
-                _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                       \
-                    acc[cw][tt] = mfma32h(wq[slot][cw][j], af_, acc[cw][tt]);                            \
-            }                                                                                            \
-        }                                                                                                \
-    }
-#define EF_SHD_STAGE(slot, next_slot, st)                                                                \
-    {                                                                                                    \
-        EF_SHD_SHARE(next_slot, (st) + 1)                                                                \
-        EF_SHD_COMPUTE(slot, st)                                                                         \
-        EF_SHD_LOAD(slot, (st) + D)                                                                      \
-        __syncthreads();                                                                                 \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_SHD_LOAD(ring_, q0 + ring_)
-    EF_SHD_SHARE(0, q0)
-    __syncthreads();
-    int st = q0;
-    for (; st + D <= q1; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_SHD_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < q1) EF_SHD_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_SHD_LOAD
-#undef EF_SHD_SHARE
-#undef EF_SHD_COMPUTE
-#undef EF_SHD_STAGE
+    if (TT == 1 || ntl == 1) shared_down_stream<TT, 1, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
+    else if (TT == 2 || ntl == 2) shared_down_stream<TT, 2, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
+    else if (ntl == 3) shared_down_stream<TT, (TT > 2 ? 3 : TT), D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
+    else shared_down_stream<TT, TT, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
 
     if (!valid) return;
     const int g = lane >> 5;
