@@ -515,7 +515,7 @@ typedef struct ef_tuning {
                                         that fill the launch's last, partly empty round: 0 = never, 1 = as many as a
                                         model of the launch finds best, 2 / 4 / 8 = that many (1) */
     int32_t dist_form;               /* ef_token_dist: 0 = by batch size (up to 256 tokens: differences summed directly,
-                                        no Gram matrix), 1 = Gram blocks of 128 x 256 fed from registers, 2 = Gram blocks
+                                        no Gram matrix; up to 3584: Gram blocks of 32 x 32 or 64 x 64), 1 = Gram blocks of 128 x 256 fed from registers, 2 = Gram blocks
                                         of 256 x 256 staged through LDS; 1 and 2 give the same bits (0) */
 } ef_tuning;
 int ef_get_tuning(ef_ctx *ctx, ef_tuning *out);

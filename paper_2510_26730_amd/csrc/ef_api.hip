@@ -421,11 +421,13 @@ extern "C" int ef_token_dist(ef_ctx *c, const void *hidden, int T, float *tok_di
     pt.tile_start[1] = ntiles;
     pt.row_offset[0] = -1;   // identity: packed row = token
     pt.count[0] = T;
-    // flops of the strict upper triangle; bytes: tokens read once, packed copy written and read once
+    // flops of the strict upper triangle; bytes: tokens read once, the packed copy of the forms that have one written
+    // and read once
+    const bool packed = ef::dist_needs_packed(T, c->tune.dist_form);
     const double flops = (double)T * (T - 1) * d;
-    const double bytes = 6.0 * T * d + 8.0 * T;
+    const double bytes = (packed ? 6.0 : 2.0) * T * d + 8.0 * T;
     KernelTimer kt(c, s, EF_K_DIST, bytes, flops);
-    if (ef::dist_needs_packed(T, c->tune.dist_form))
+    if (packed)
         EF_HIP(c, ef::launch_pack_x(pt, ntiles, static_cast<const uint16_t *>(hidden), d, 1, nullptr, c->xp, false, s));
     EF_HIP(c, ef::launch_token_dist(static_cast<const uint16_t *>(hidden), T, d, c->xp, c->y, tok_dist, dist,
                                     c->tune.dist_form, s));

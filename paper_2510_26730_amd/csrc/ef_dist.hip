@@ -1,5 +1,7 @@
 // Intra-batch diversity Dist(t) = sum over token pairs of the Euclidean distance between their
-// embeddings (paper Sec. 2.2), computed per token: s[j] = sum_{i<j} ||v_i - v_j||_2.
+// embeddings (paper Sec. 2.2), computed per token: s[j] = sum_{i<j} ||v_i - v_j||_2.  Three families of kernels by batch
+// size: the squared differences themselves (up to kDistSmallMaxTokens), Gram blocks of 32 x 32 or 64 x 64 (up to
+// kDistBlockMaxTokens), and, described here, large Gram blocks over a packed copy.
 //
 // ||v_i - v_j||^2 = n_i + n_j - 2 <v_i, v_j>: the inner products are one T x T Gram matrix, a dense
 // contraction over d that runs on the matrix cores from the packed (operand-fragment) copy of the
@@ -43,13 +45,13 @@ __global__ __launch_bounds__(256) void dist_norm_kernel(const uint16_t *__restri
     if (lane == 0) norms[t] = acc;   // rows of the padding up to whole tiles get 0
 }
 
-// Decode-sized batches (a few hundred tokens at most): the Gram route would be one or two workgroups walking all of
+// Decode-sized batches (up to kDistRowMaxTokens tokens): the Gram route would be one or two workgroups walking all of
 // d in sequence behind five launches.  Here workgroup j owns token j: wave w of 16 takes the rows i = w, w + 16, ...
 // < j, two at a time (their loads are independent), the lanes stride the row pair in 16-byte pieces and add
 // (x_i - x_j)^2 in fp32 (no norms, no cancellation), a shuffle tree adds the lanes, the root is added to the wave's
 // sum in fp64 in ascending i; the waves' sums are added in order.  Everything in a fixed order: the result does not
 // depend on scheduling.
-constexpr int kDistSmallWaves = 16;
+constexpr int kDistRowWaves = 16;
 __device__ __forceinline__ float dist_sq_piece(uint4 a, uint4 b) {
     const uint32_t wa[4] = {a.x, a.y, a.z, a.w}, wb[4] = {b.x, b.y, b.z, b.w};
     float acc = 0.f;
@@ -62,16 +64,16 @@ __device__ __forceinline__ float dist_sq_piece(uint4 a, uint4 b) {
     }
     return acc;
 }
-__global__ __launch_bounds__(64 * kDistSmallWaves) void dist_small_kernel(const uint16_t *__restrict__ h, int T, int d,
+__global__ __launch_bounds__(64 * kDistRowWaves) void dist_row_kernel(const uint16_t *__restrict__ h, int T, int d,
                                                                            float *__restrict__ tok_dist,
                                                                            double *__restrict__ wg_sums) {
-    __shared__ double red[kDistSmallWaves];
+    __shared__ double red[kDistRowWaves];
     const int j = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint4 *rj = reinterpret_cast<const uint4 *>(h + (size_t)j * d);
     const int nc = d >> 3;
     double s = 0.0;
-    for (int i = wave; i < j; i += 2 * kDistSmallWaves) {
-        const int i2 = i + kDistSmallWaves;
+    for (int i = wave; i < j; i += 2 * kDistRowWaves) {
+        const int i2 = i + kDistRowWaves;
         const bool two = i2 < j;
         const uint4 *r0 = reinterpret_cast<const uint4 *>(h + (size_t)i * d);
         const uint4 *r1 = reinterpret_cast<const uint4 *>(h + (size_t)(two ? i2 : i) * d);
@@ -93,10 +95,249 @@ __global__ __launch_bounds__(64 * kDistSmallWaves) void dist_small_kernel(const 
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int w = 0; w < kDistSmallWaves; ++w) t += red[w];
+        for (int w = 0; w < kDistRowWaves; ++w) t += red[w];
         if (tok_dist) tok_dist[j] = (float)t;
         wg_sums[j] = t;
     }
+}
+
+// Batches up to a few hundred tokens: the squared differences themselves, no norms and no cancellation.
+// Bound by vector instructions (two per pair and element, one more to unpack each bf16) and, at a few dozen tokens, by
+// launch latency.  A workgroup owns 8 tokens j and a chunk of 16 rows i, one wave two of the rows: a lane holds its
+// 16-byte piece of the eight tokens unpacked and meets two rows with it, so a piece is loaded and unpacked once for two
+// (eight) pairs.  The lanes' sums of a wave's 16 pairs meet in a butterfly that halves the number of values per step (31
+// exchanges instead of 96); the roots are added in fp64 in ascending i, one partial per (chunk, j).  Fixed order
+// throughout.  d = 4096, the call, against one workgroup per token j that walks every row before it: T = 256 46 -> 23 us,
+// T = 128 22.5 -> 16 us; at 64 tokens both take 14 us, below that the other form is ahead (T = 16: 7 against 13 us).
+constexpr int kDistSmallCols = 8, kDistSmallRows = 16, kDistSmallWaves = 8;
+__device__ __forceinline__ void dist_unpack(uint4 v, float (&f)[8]) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f[2 * q] = __builtin_bit_cast(float, w[q] << 16);
+        f[2 * q + 1] = __builtin_bit_cast(float, w[q] & 0xFFFF0000u);
+    }
+}
+__global__ __launch_bounds__(64 * kDistSmallWaves) void dist_small_kernel(const uint16_t *__restrict__ h, int T, int d,
+                                                                           double *__restrict__ part) {
+    constexpr int NC = kDistSmallCols, RW = kDistSmallRows / kDistSmallWaves;   // rows per wave
+    static_assert(RW * NC == 16, "the butterfly reduces 16 values");
+    __shared__ float sq[kDistSmallRows][NC];
+    const int i0 = blockIdx.x * kDistSmallRows, j0 = blockIdx.y * NC;
+    if (i0 >= j0 + NC) return;   // every row past every token of the group
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int nc = d >> 3;
+    const uint4 *rj[NC], *ri[RW];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) rj[j] = reinterpret_cast<const uint4 *>(h + (size_t)min(j0 + j, T - 1) * d);
+#pragma unroll
+    for (int r = 0; r < RW; ++r) ri[r] = reinterpret_cast<const uint4 *>(h + (size_t)min(i0 + wave * RW + r, T - 1) * d);
+    float acc[16];   // [row][token]
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[q] = 0.f;
+    for (int c = lane; c < nc; c += 64) {
+        uint4 vi[RW], vj[NC];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) vi[r] = ri[r][c];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) vj[j] = rj[j][c];
+        float fi[RW][8];
+#pragma unroll
+        for (int r = 0; r < RW; ++r) dist_unpack(vi[r], fi[r]);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            float fj[8];
+            dist_unpack(vj[j], fj);
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float x = fi[r][e] - fj[e];
+                    acc[r * NC + j] += x * x;
+                }
+        }
+    }
+    // 16 values x 64 lanes: step s exchanges half of the values left between lanes that differ in bit s, so lane l ends
+    // with value l % 16 summed over the lanes that agree with it in the low four bits; two plain steps add those
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const bool up = (lane >> s) & 1;
+#pragma unroll
+        for (int q = 0; q < (8 >> s); ++q) {
+            const float keep = up ? acc[2 * q + 1] : acc[2 * q], give = up ? acc[2 * q] : acc[2 * q + 1];
+            acc[q] = keep + __shfl_xor(give, 1 << s);
+        }
+    }
+    float v = acc[0];
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (lane < 16) sq[wave * RW + (lane >> 3)][lane & 7] = v;
+    __syncthreads();
+    if (threadIdx.x < NC) {
+        const int j = j0 + threadIdx.x;
+        double t = 0.0;
+        for (int r = 0; r < kDistSmallRows; ++r)
+            if (i0 + r < j) t += (double)__builtin_sqrtf(sq[r][threadIdx.x]);
+        if (j < T) part[(size_t)blockIdx.x * T + j] = t;
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// Gram blocks of batches between the two sizes above and below (a few hundred to about two thousand tokens): too few
+// 256 x 256 (or 128 x 256) blocks to fill the chip, each walking all of d alone: 25 workgroups and 49 us at T = 1056,
+// d = 2048.  Here a workgroup owns a block of 32B x 32B pairs (B = 1 or 2) and its four waves a quarter of d each: their
+// partial products meet in LDS in a fixed order.  Rows are read as they are, whole 128-byte lines by eight lanes each,
+// and turned into operand fragments through a wave's own LDS buffer, pieces of a row rotated by an exclusive or so that
+// neither side meets bank conflicts (read straight into operand registers, 32 lines per load, the address path bound the
+// kernel: T = 1056, d = 2048 26.6 us for the call, now 19.6; T = 2048, d = 4096 119 and 64).  No packed copy; the norms are the diagonals of the row and column tiles' own products,
+// accumulated beside the block's (one launch less; equal rows give a distance of exactly 0).
+// ------------------------------------------------------------------------------------------
+template <int B, int R>
+__global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__restrict__ h, int T, int d,
+                                                            float *__restrict__ part, int t_pad) {
+    constexpr int U = 4;   // k-steps (16 columns each) per stage
+    constexpr int TILE = 256;   // 16-byte units of a tile's stage: 32 rows x 128 bytes
+    // a stage buffer per wave; the partial products take its place afterwards
+    __shared__ __attribute__((aligned(16))) u32x4_t lds[4][2 * B * TILE];
+    __shared__ float nrm[4][2 * B][32];
+    __shared__ float csum[2][32];
+    static_assert(sizeof(lds[0]) >= sizeof(float) * B * B * 16 * 64, "a wave's partial products fit its stage buffer");
+    // block t of the upper triangle, column by column: IB <= JB
+    const int t = blockIdx.x;
+    int JB = (int)((__builtin_sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+    while ((JB + 1) * (JB + 2) / 2 <= t) ++JB;
+    while (JB * (JB + 1) / 2 > t) --JB;
+    const int IB = t - JB * (JB + 1) / 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane >> 5, c = lane & 31;
+    const int n = (d >> 4) >> 2, k0 = wave * n;   // d is a multiple of 64: equal quarters
+    // global load u of a tile's stage: rows 8u .. 8u+7, eight lanes to a row's 128 bytes
+    const int lr = lane >> 3, lc = lane & 7;
+    const u32x4_t *src[2 * B][U];   // row tiles, then column tiles
+#pragma unroll
+    for (int a = 0; a < 2 * B; ++a)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int row = min((a < B ? IB * B + a : JB * B + a - B) * kTile + 8 * u + lr, T - 1);
+            src[a][u] = reinterpret_cast<const u32x4_t *>(h + (size_t)row * d) + 2 * k0;
+        }
+    u32x4_t *const buf = lds[wave];
+    const int put = lr * 8 + (lc ^ lr);   // + 64 u + TILE a
+    floatx16 acc[B][B], sq[2 * B];
+#pragma unroll
+    for (int a = 0; a < B; ++a)
+#pragma unroll
+        for (int b = 0; b < B; ++b) zero16(acc[a][b]);
+#pragma unroll
+    for (int a = 0; a < 2 * B; ++a) zero16(sq[a]);
+    u32x4_t f[R][2 * B][U];
+#define EF_DISTB_LOAD(f_, kb)                                                                             \
+    {                                                                                                     \
+        const int ch_ = min(2 * (kb) + lc, 2 * n - 1); /* past the quarter's end its last piece again */  \
+        _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
+            _Pragma("unroll") for (int u = 0; u < U; ++u) f_[a][u] = src[a][u][ch_];                      \
+    }
+    // one stage: into the wave's LDS buffer (the wave's LDS operations run in order: no wait before it is reused), the
+    // registers refilled R stages ahead, then operand fragments from LDS
+#define EF_DISTB_STAGE(f_, kb)                                                                            \
+    {                                                                                                     \
+        _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
+            _Pragma("unroll") for (int u = 0; u < U; ++u) buf[a * TILE + 64 * u + put] = f_[a][u];        \
+        EF_DISTB_LOAD(f_, (kb) + R * U)                                                                   \
+        _Pragma("unroll") for (int u = 0; u < U; ++u)                                                     \
+            if ((kb) + u < n) {                                                                           \
+                u32x4_t x[2 * B];                                                                         \
+                _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                         \
+                    x[a] = buf[a * TILE + c * 8 + ((2 * u + g) ^ (c & 7))];                               \
+                _Pragma("unroll") for (int a = 0; a < B; ++a)                                             \
+                    _Pragma("unroll") for (int b = 0; b < B; ++b) acc[a][b] = mfma32v(x[a], x[B + b], acc[a][b]); \
+                _Pragma("unroll") for (int a = 0; a < 2 * B; ++a) sq[a] = mfma32v(x[a], x[a], sq[a]);     \
+            }                                                                                             \
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) EF_DISTB_LOAD(f[r], r * U)
+    for (int kb = 0; kb < n; kb += R * U) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (kb + r * U < n) EF_DISTB_STAGE(f[r], kb + r * U)
+    }
+#undef EF_DISTB_LOAD
+#undef EF_DISTB_STAGE
+    float(*const red)[B * B * 16][64] = reinterpret_cast<float(*)[B * B * 16][64]>(&lds[0][0]);
+    // the partials' stride is a wave's own buffer or less, so every wave has to be done with its stages first
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < B; ++a)
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) red[wave][(a * B + b) * 16 + v][lane] = acc[a][b][v];
+    // accumulator lane l holds column l%32 and rows 8*(v/4) + 4*(l/32) + v%4
+#pragma unroll
+    for (int a = 0; a < 2 * B; ++a)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (8 * (v >> 2) + 4 * g + (v & 3) == c) nrm[wave][a][c] = sq[a][v];
+    __syncthreads();
+    const int a = B == 2 ? wave >> 1 : 0, b = B == 2 ? wave & 1 : 0;   // this wave's tile of the block
+    float sum = 0.f;
+    const int j = (JB * B + b) * kTile + c;
+    if (B == 2 || wave == 0) {
+        const float nj = ((nrm[0][B + b][c] + nrm[1][B + b][c]) + nrm[2][B + b][c]) + nrm[3][B + b][c];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + 4 * g + (v & 3), i = (IB * B + a) * kTile + r;
+            const int q = (a * B + b) * 16 + v;
+            const float ip = ((red[0][q][lane] + red[1][q][lane]) + red[2][q][lane]) + red[3][q][lane];
+            const float ni = ((nrm[0][a][r] + nrm[1][a][r]) + nrm[2][a][r]) + nrm[3][a][r];
+            if (i < j && j < T) {
+                const float dd = ni + nj - 2.f * ip;
+                sum += __builtin_sqrtf(fmaxf(dd, 0.f));
+            }
+        }
+        sum += __shfl_xor(sum, 32);
+    }
+    if (B == 2) {   // one partial per 64 rows: the upper 32 rows' sums come over LDS
+        if (a == 1 && g == 0) csum[b][c] = sum;
+        __syncthreads();
+        if (a == 1) return;
+        sum += csum[b][c];
+    } else if (wave != 0) {
+        return;
+    }
+    if (g == 0 && j < t_pad) part[(size_t)IB * t_pad + j] = sum;
+}
+
+// Per-token sums over the row blocks and their total, for the batches of the two kernels above: one workgroup, since a
+// second launch costs as much as the sums.  Partial row block rb of token j at part[rb * stride + j], row blocks
+// 0 .. j / rows of token j; added in ascending order, the tokens' sums by a fixed tree.
+template <typename P>
+__global__ __launch_bounds__(1024) void dist_sum_kernel(const P *__restrict__ part, int T, int stride, int rows,
+                                                        float *__restrict__ tok_dist, double *__restrict__ dist) {
+    __shared__ double red[1024];
+    double total = 0.0;
+    for (int j = threadIdx.x; j < T; j += 1024) {
+        const int n = j / rows + 1;
+        double s = 0.0;
+        int rb = 0;
+        for (; rb + 8 <= n; rb += 8) {
+            P v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(rb + u) * stride + j];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += (double)v[u];
+        }
+        for (; rb < n; ++rb) s += (double)part[(size_t)rb * stride + j];
+        if (tok_dist) tok_dist[j] = (float)s;
+        total += s;
+    }
+    red[threadIdx.x] = total;
+    __syncthreads();
+    for (int o = 512; o >= 1; o >>= 1) {
+        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *dist = red[0];
 }
 
 constexpr int kDistRowTiles = 4;   // token tiles (32 rows) of operand A per workgroup: 128 rows i
@@ -378,10 +619,15 @@ __global__ __launch_bounds__(64) void dist_final_kernel(const double *__restrict
 }
 
 size_t dist_scratch_floats(int T) {
-    const int t_pad = ((T + kTile - 1) / kTile) * kTile;
+    const int ntl = (T + kTile - 1) / kTile, t_pad = ntl * kTile;
     const int n_rowblk = (T + 63) / 64;
     const int n_wg = (T + 255) / 256;
-    return (size_t)t_pad + (size_t)n_rowblk * t_pad + 2 * (size_t)n_wg + 2;
+    const size_t gram = (size_t)t_pad + (size_t)n_rowblk * t_pad + 2 * (size_t)n_wg + 2;
+    // the forms for fewer tokens keep partials of 16 rows in fp64 or of 32 rows: at most 2 T (T / 16 + 1) floats, less
+    // than the T * 64 floats that every context has for T tokens
+    if (T <= kDistSmallMaxTokens) return gram > 2 * (size_t)T * ((T + 15) / 16) ? gram : 2 * (size_t)T * ((T + 15) / 16);
+    if (!dist_block_wide(T)) return gram > (size_t)t_pad * ntl ? gram : (size_t)t_pad * ntl;
+    return gram;
 }
 
 hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, float *scratch, float *tok_dist,
@@ -391,11 +637,26 @@ hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, fl
     const int t_pad = ntiles * kTile;
     const int n_rowblk = (T + 63) / 64;
     const int n_wg = (T + 255) / 256;
-    if (!dist_needs_packed(T, form)) {
-        // T doubles at the start of the scratch (8-byte aligned: the scratch is), then the usual final sum
-        double *sums = reinterpret_cast<double *>(scratch);
-        hipLaunchKernelGGL(dist_small_kernel, dim3(T), dim3(64 * kDistSmallWaves), 0, s, h, T, d, tok_dist, sums);
+    if (form == 0 && T <= kDistRowMaxTokens) {
+        double *sums = reinterpret_cast<double *>(scratch);   // T doubles (8-byte aligned: the scratch is), then their sum
+        hipLaunchKernelGGL(dist_row_kernel, dim3(T), dim3(64 * kDistRowWaves), 0, s, h, T, d, tok_dist, sums);
         hipLaunchKernelGGL(dist_final_kernel, dim3(1), dim3(64), 0, s, sums, T, dist);
+        return hipGetLastError();
+    }
+    if (form == 0 && T <= kDistSmallMaxTokens) {
+        double *part = reinterpret_cast<double *>(scratch);   // 8-byte aligned: the scratch is
+        const int cols = (T + kDistSmallCols - 1) / kDistSmallCols, rows = (T + kDistSmallRows - 1) / kDistSmallRows;
+        hipLaunchKernelGGL(dist_small_kernel, dim3(rows, cols), dim3(64 * kDistSmallWaves), 0, s, h, T, d, part);
+        // the last row chunk of token j's group is that of its last token: (8 (j / 8) + 7) / 16 = j / 16
+        hipLaunchKernelGGL(dist_sum_kernel<double>, dim3(1), dim3(1024), 0, s, part, T, T, kDistSmallRows, tok_dist, dist);
+        return hipGetLastError();
+    }
+    if (!dist_needs_packed(T, form)) {
+        const bool wide = dist_block_wide(T);
+        const int nb = (T + (wide ? 63 : 31)) / (wide ? 64 : 32), blocks = nb * (nb + 1) / 2;
+        if (wide) hipLaunchKernelGGL((dist_block_kernel<2, 1>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);
+        else hipLaunchKernelGGL((dist_block_kernel<1, 2>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);
+        hipLaunchKernelGGL(dist_sum_kernel<float>, dim3(1), dim3(1024), 0, s, scratch, T, t_pad, wide ? 64 : 32, tok_dist, dist);
         return hipGetLastError();
     }
     float *norms = scratch;

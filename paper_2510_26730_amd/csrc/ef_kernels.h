@@ -137,10 +137,18 @@ hipError_t launch_dequant_q4(const DequantTable &t, int d, hipStream_t s);
 
 // Dist(t): scratch floats launch_token_dist needs for T tokens (norms, partials, workgroup sums)
 size_t dist_scratch_floats(int T);
-// Batches of up to kDistSmallMaxTokens tokens take a kernel that reads the tokens as they are (form 0 only); the Gram
-// forms read the packed copy, which the caller writes first.
+// Form 0 by batch size: up to kDistSmallMaxTokens tokens the squared differences (up to kDistRowMaxTokens one workgroup
+// per token: fewer tokens than that share too little), up to kDistBlockMaxTokens Gram blocks
+// of 32 x 32 or 64 x 64; both read the tokens as they are.  The other Gram forms read the packed copy, which the caller
+// writes first.
+constexpr int kDistRowMaxTokens = 64;
 constexpr int kDistSmallMaxTokens = 256;
-inline bool dist_needs_packed(int T, int form) { return !(form == 0 && T <= kDistSmallMaxTokens); }
+constexpr int kDistBlockMaxTokens = 3584;   // the call at T = 3500: 86 / 144 us (d = 2048 / 4096) against 105 / 155 us
+                                            // through 256 x 256 blocks; at T = 4096 110 / 185 against 111 / 160 us
+inline bool dist_needs_packed(int T, int form) { return !(form == 0 && T <= kDistBlockMaxTokens); }
+// 64 x 64 blocks once there are enough of them for half of the compute units, else 32 x 32 (the call, d = 4096: T = 900
+// 24.6 us with 32 x 32 against 28.3, T = 1056 37 against 29 us)
+inline bool dist_block_wide(int T) { return T > 960; }
 // `form`: 0 = by batch size, 1 = register-fed 128 x 256 Gram blocks, 2 = 256 x 256 blocks through LDS (same bits)
 hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, float *scratch, float *tok_dist,
                              double *dist, int form, hipStream_t s);

@@ -139,6 +139,30 @@ def test_both_gram_forms_give_the_same_bits_and_match_oracle(oracle_mod, T, d):
     assert abs(out[2][1] - ref.sum()) <= 1e-6 * max(ref.sum(), 1.0)
 
 
+@pytest.mark.parametrize("T,d", [(64, 192), (65, 64), (79, 128), (113, 4096), (255, 192), (256, 512), (257, 64), (288, 192),
+                                 (321, 4096), (511, 320), (960, 64), (961, 64), (1025, 192), (1056, 2048), (3584, 64),
+                                 (3585, 64)])
+def test_forms_by_batch_size_match_oracle(oracle_mod, T, d):
+    """Both sides of every batch size at which the form changes, ragged last blocks, d of one k-step per quarter, of an
+    odd number of them and of many.  Every fourth token repeats an earlier one.  Bounds as above: fp32 squared distances
+    (relative error about 1e-6 of the norms), sums in fp64."""
+    say(f"dist by batch size T={T} d={d}")
+    rng = np.random.default_rng(7000 + T + d)
+    v = rng.standard_normal((T, d)).astype(np.float32)
+    v[3::4] = v[np.arange(3, T, 4) // 2]
+    h = synth.f32_to_bf16(v)
+    ctx = make_ctx(d, max(T, 64))
+    try:
+        tok, tot = run_dist(ctx, h, T)
+        tok2, tot2 = run_dist(ctx, h, T)
+    finally:
+        ef.ef_destroy(ctx)
+    ref = oracle_mod.token_dist(h)
+    np.testing.assert_allclose(tok, ref, rtol=1e-5, atol=1e-5 * T)
+    assert abs(tot - ref.sum()) <= 1e-6 * max(ref.sum(), 1.0)
+    assert np.array_equal(tok, tok2) and tot == tot2, "not bit-reproducible"
+
+
 def test_argument_errors():
     ctx = make_ctx(64, 64)
     try:
