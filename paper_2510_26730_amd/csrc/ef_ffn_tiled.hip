@@ -7,28 +7,23 @@
 // the global -> LDS copy is a plain contiguous copy and an LDS operand read is 64 lanes x 16
 // consecutive bytes (no bank conflicts, no swizzle).  The LDS stage buffers (four) are filled by direct
 // global -> LDS loads three stages ahead of the one feeding the matrix cores, one barrier per stage.
-// Workgroups that share a weight panel (same rows, different token panels) have consecutive ids,
-// so the panel is fetched from HBM once and served to the others by L2 / MALL.
+// The workgroups an XCD runs side by side form compact blocks of weight panels x token panels (ef_kernels.h), so that
+// its L2 serves most of their reads.
 #include "ef_device.h"
 #include "ef_kernels.h"
 #include "ef_tiled_pipeline.h"
 
 namespace ef {
 
-// Index of a workgroup within its group -> (weight panel np, token panel mp).  Workgroups with the
-// same index mod 8 land on one XCD; consecutive ones there walk the token panels of
-// kTiledPanelBlock weight panels, so the panels an XCD works on at one time share its L2.
-// Returns false for the padding workgroups past the last weight panel.
-__device__ __forceinline__ bool tiled_panel(int local, int rot, int npanels, int mpanels, int &np, int &mp) {
-    // `rot`: the XCD that takes the group's first panel block.  Groups whose panels do not fill a round of
-    // eight XCDs would otherwise all start on XCD 0 and overfill its 32 compute units while others idle.
-    const int xcd = (local - rot) & 7, j = local >> 3;
-    const int pb = tiled_panel_block(npanels);
-    const int blk = pb * mpanels;
-    const int jb = j / blk, jj = j - jb * blk;
-    np = (jb * 8 + xcd) * pb + jj / mpanels;
-    mp = jj % mpanels;
-    return np < npanels;
+// Index of a workgroup within its group -> its unit.  Workgroups with the same index mod 8 land on one XCD; `rot` is the XCD
+// that takes the first eighth of the group's units (the eighths differ by one unit, so the groups of a launch start on
+// different XCDs).  Returns false for workgroups past the XCD's share.
+__device__ __forceinline__ bool tiled_pick(int local, int rot, int npanels, int mpanels, int slices, TiledUnit &t) {
+    const int part = (local - rot) & 7, n = npanels * mpanels * slices;
+    const int u = tiled_xcd_begin(n, part) + (local >> 3);
+    if (u >= tiled_xcd_begin(n, part + 1)) return false;
+    t = tiled_unit(u, npanels, mpanels);
+    return true;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -48,9 +43,9 @@ __global__ __launch_bounds__(256, 1) void ffn_gate_up_tiled_kernel(GroupTable gt
     const int F = gt.F[grp];
     const int ntiles = gt.n_tiles[grp];
     const int mpanels = (ntiles + 7) >> 3;
-    int np, mp;
-    if (!tiled_panel(local, gt.xcd_rot[grp], F >> 7, mpanels, np, mp)) return;
-    const int rb0 = np * 4, t0 = mp * 8;
+    TiledUnit unit;
+    if (!tiled_pick(local, gt.xcd_rot[grp], F >> 7, mpanels, 1, unit)) return;
+    const int rb0 = unit.np * 4, t0 = unit.mp * 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS DMA targets go through M0
     const int wf = wave & 1, wt = wave >> 1;
@@ -152,14 +147,14 @@ __global__ __launch_bounds__(256, 1) void ffn_down_tiled_kernel(GroupTable gt, c
     const int ntiles = gt.n_tiles[grp];
     const int mpanels = (ntiles + 7) >> 3;
     // K slices across workgroups (one Y plane each, summed by the un-permute) when the tiles alone
-    // would leave most of the chip idle; neighbouring workgroups take the slices of one tile.  One group of the
+    // would leave most of the chip idle.  One group of the
     // launch (the last one) may have a slice count of its own: shorter workgroups that fill the launch's last,
     // partly empty round over the compute units
     const int ksg = grp == split_grp ? split_ksg : ksg_all;
-    const int kslice = local % ksg;
-    int np, mp;
-    if (!tiled_panel(local / ksg, gt.xcd_rot[grp], d >> 8, mpanels, np, mp)) return;
-    const int cb0 = np * 8, t0 = mp * 8;
+    TiledUnit unit;
+    if (!tiled_pick(local, gt.xcd_rot[grp], d >> 8, mpanels, ksg, unit)) return;
+    const int kslice = unit.slice;
+    const int cb0 = unit.np * 8, t0 = unit.mp * 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS DMA targets go through M0
     const int wc = wave & 1, wt = wave >> 1;
@@ -221,7 +216,7 @@ hipError_t launch_ffn_down_tiled(const GroupTable &gt, int total_wgs, int ksg, i
     if (ksg < 1 || (split_grp >= 0 && (split_grp >= gt.n_groups || split_ksg < 1))) return hipErrorInvalidValue;
     for (int i = 0; i < gt.n_groups; ++i) {
         const int ks = i == split_grp ? split_ksg : ksg;
-        if (gt.wg_start[i + 1] - gt.wg_start[i] != ffn_down_tiled_wgs(d, gt.n_tiles[i]) * ks ||
+        if (gt.wg_start[i + 1] - gt.wg_start[i] != ffn_down_tiled_wgs(d, gt.n_tiles[i], ks) ||
             !ffn_tiled_ok(d, gt.F[i], gt.n_tiles[i]) || gt.F[i] / 32 < ks)
             return hipErrorInvalidValue;
     }

@@ -50,7 +50,7 @@ struct GroupTable {
     int F[kMaxGroups];             // FFN hidden dim of the group
     long long act_off[kMaxGroups]; // first 16-byte unit of the group's activation fragments
     const void *blob[kMaxGroups];  // packed weights (cache slot or shared blob)
-    int xcd_rot[kMaxGroups];       // tiled kernels: the group's first weight panel goes to this XCD (0..7)
+    int xcd_rot[kMaxGroups];       // tiled kernels: the XCD (0..7) that takes the first eighth of the group's units
 };
 
 // Optional hand-over of counts and predicted histograms to the host (host-mapped memory): every word is
@@ -168,21 +168,28 @@ constexpr int kTiledMinTiles = 8;
 inline bool ffn_tiled_ok(int d, int F, int n_tiles) {
     return n_tiles >= kTiledMinTiles && F % 128 == 0 && d % 256 == 0;
 }
-// Workgroups are dealt to the 8 XCDs round-robin by index, and each XCD has an L2 of its own.  The
-// tiled kernels therefore number a group's workgroups so that those an XCD runs side by side
-// (indices congruent mod 8, consecutive) form blocks of kTiledPanelBlock weight panels x all token
-// panels: a weight panel is then fetched into one L2 once and read by every token panel there.  The
-// count is padded to whole blocks; workgroups that fall past the last weight panel exit at once.
-constexpr int kTiledPanelBlock = 2;
-// With fewer than 16 weight panels (d = 2048 gives the second half 8) blocks of two would leave half of the
-// XCDs without a panel: such launches deal single panels.
-__host__ __device__ inline int tiled_panel_block(int npanels) { return npanels >= 8 * kTiledPanelBlock ? kTiledPanelBlock : 1; }
-inline int ffn_tiled_wgs(int npanels, int n_tiles) {
-    const int per_round = 8 * tiled_panel_block(npanels);
-    return ((npanels + per_round - 1) / per_round) * per_round * ((n_tiles + 7) / 8);
+// Workgroups are dealt to the 8 XCDs round-robin by index, and each XCD has an L2 of its own and 32 compute units that run
+// one tiled workgroup each.  The units of a group (weight panel x token panel x K slice) are put in one order and every XCD
+// takes an eighth of it, even to one unit, so that the 32 units an XCD runs side by side are neighbours in the order and
+// share panels in its L2: K slices one after the other (units of one slice walk the same columns), strips of up to
+// kTiledStrip token panels, weight panel by weight panel within a strip.  A full strip makes 32 neighbours 4 weight x 8
+// token panels, 12 panels for 32 units; two weight panels x 16 token panels (the order before this one) read 18.
+constexpr int kTiledStrip = 8;
+struct TiledUnit { int np, mp, slice; };
+inline __host__ __device__ int tiled_xcd_begin(int n_units, int xcd) { return (int)((long long)n_units * xcd / 8); }
+inline __host__ __device__ TiledUnit tiled_unit(int u, int npanels, int mpanels) {
+    const int tiles = npanels * mpanels, strips = (mpanels + kTiledStrip - 1) / kTiledStrip;
+    const int w = (mpanels + strips - 1) / strips;
+    const int slice = u / tiles, r = u - slice * tiles;
+    const int strip = r / (w * npanels), rr = r - strip * w * npanels;
+    const int width = mpanels - strip * w < w ? mpanels - strip * w : w;
+    return TiledUnit{rr / width, strip * w + rr % width, slice};
 }
-inline int ffn_gate_up_tiled_wgs(int F, int n_tiles) { return ffn_tiled_wgs(F / 128, n_tiles); }
-inline int ffn_down_tiled_wgs(int d, int n_tiles) { return ffn_tiled_wgs(d / 256, n_tiles); }
+inline int ffn_tiled_units(int npanels, int n_tiles, int slices) { return npanels * ((n_tiles + 7) / 8) * slices; }
+// every XCD gets the same number of workgroups; those past an XCD's share of units exit at once
+inline int ffn_tiled_wgs(int n_units) { return (n_units + 7) / 8 * 8; }
+inline int ffn_gate_up_tiled_wgs(int F, int n_tiles) { return ffn_tiled_wgs(ffn_tiled_units(F / 128, n_tiles, 1)); }
+inline int ffn_down_tiled_wgs(int d, int n_tiles, int slices) { return ffn_tiled_wgs(ffn_tiled_units(d / 256, n_tiles, slices)); }
 
 // workgroups a group needs in the two FFN launches
 inline int ffn_gate_up_wgs(int F, int n_tiles, int tiles_per_pass, int ks) {

@@ -257,32 +257,38 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         ef::GroupTable bdn = big;
         int wg_up = 0, wg_dn = 0;
         // Workgroups go to the XCDs round-robin by index and hold one of an XCD's 32 compute units for their whole
-        // K loop.  A group's panel blocks (block b -> XCD rot + b) are dealt from the start XCD that leaves the
-        // fullest XCD of the first half's launch least full, so groups of a few panels do not pile up on XCD 0.
-        int load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        // K loop.  An XCD takes an eighth of a group's units; the eighths differ by one unit, and each group starts on the
+        // XCD that leaves the fullest XCD of the launch least full.
+        int load_up[8] = {}, load_dn[8] = {};
         const int rot_on = c->tune.tiled_xcd_rotation;
+        auto place = [&](int units, int (&load)[8]) {
+            int best = 0, best_max = 1 << 30;
+            for (int rot = 0; rot < (rot_on ? 8 : 1); ++rot) {
+                int mx = 0;
+                for (int x = 0; x < 8; ++x) {
+                    const int part = (x - rot) & 7;
+                    mx = std::max(mx, load[x] + ef::tiled_xcd_begin(units, part + 1) - ef::tiled_xcd_begin(units, part));
+                }
+                if (mx < best_max) { best_max = mx; best = rot; }
+            }
+            for (int x = 0; x < 8; ++x) {
+                const int part = (x - best) & 7;
+                load[x] += ef::tiled_xcd_begin(units, part + 1) - ef::tiled_xcd_begin(units, part);
+            }
+            return best;
+        };
         for (int i = 0; i < nb; ++i) {
             big.wg_start[i] = wg_up;
             bdn.wg_start[i] = wg_dn;
-            const int pu = big.F[i] / 128, pbu = ef::tiled_panel_block(pu), nblk = (pu + pbu - 1) / pbu;
-            const int mp = (big.n_tiles[i] + 7) / 8;
-            int best = 0, best_max = 1 << 30;
-            for (int rot = 0; rot < (rot_on ? 8 : 1); ++rot) {
-                int trial[8], mx = 0;
-                for (int x = 0; x < 8; ++x) trial[x] = load[x];
-                for (int b = 0; b < nblk; ++b) trial[(rot + b) & 7] += std::min(pbu, pu - b * pbu) * mp;
-                for (int x = 0; x < 8; ++x) mx = std::max(mx, trial[x]);
-                if (mx < best_max) { best_max = mx; best = rot; }
-            }
-            for (int b = 0; b < nblk; ++b) load[(best + b) & 7] += std::min(pbu, pu - b * pbu) * mp;
-            big.xcd_rot[i] = best;
-            bdn.xcd_rot[i] = 0;   // the second half's panels cover every XCD (or K slices interleave them)
+            const int ks = i == split_grp ? split_ksg : ksg_tiled;
+            big.xcd_rot[i] = place(ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1), load_up);
+            bdn.xcd_rot[i] = place(ef::ffn_tiled_units(d / 256, big.n_tiles[i], ks), load_dn);
             wg_up += ef::ffn_gate_up_tiled_wgs(big.F[i], big.n_tiles[i]);
-            wg_dn += ef::ffn_down_tiled_wgs(d, big.n_tiles[i]) * (i == split_grp ? split_ksg : ksg_tiled);
+            wg_dn += ef::ffn_down_tiled_wgs(d, big.n_tiles[i], ks);
         }
         big.wg_start[nb] = wg_up;
-        bdn.wg_start[nb] = wg_dn;
         tiled_up_wgs = wg_up;
+        bdn.wg_start[nb] = wg_dn;
         double b_up = 0.0, b_dn = 0.0, f_up = 0.0, f_dn = 0.0;
         alg_bytes(big, nb, b_up, b_dn);
         for (int i = 0; i < nb; ++i) {
@@ -351,11 +357,11 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     dn.wg_start[n] = wg_dn;
     double b_up = 0.0, b_dn = 0.0;
     alg_bytes(gu, n, b_up, b_dn);
-    // workgroups per CU of the LDS-shared kernels: one (register ring of three stages) unless the phase's tiled first
-    // half runs for well over one round of workgroups over the compute units, in which case two smaller ones (ring of
-    // two stages) share each unit as the tiled launch frees it: Qwen-shaped batch (240-290 tiled workgroups) 217 -> 202 us
-    // per layer with one, DeepSeek-shaped mixed batch (350-580 tiled workgroups) 304 against 309 us with two
-    const int occ = c->tune.lds_shared_occupancy != 0 ? c->tune.lds_shared_occupancy : (tiled_up_wgs > 320 ? 2 : 1);
+    // workgroups per CU of the LDS-shared kernels: two (register ring of two stages each) when the launch has most of the
+    // chip to itself and more workgroups than compute units, else one (ring of three stages): 64 DeepSeek-shaped experts, 300
+    // tokens, 535 us with two against 547 for two layers; beside a tiled launch, whose workgroups hold a unit's LDS, one
+    // is ahead (Qwen-shaped 3000 tokens 1192 against 1280 us, Mixtral-shaped 1000 tokens 2035 against 2105)
+    const int occ = c->tune.lds_shared_occupancy != 0 ? c->tune.lds_shared_occupancy : (tiled_up_wgs < 128 && wg_gu > 256 ? 2 : 1);
     {
         KernelTimer kt(c, s, EF_K_FFN_UP, b_up);
         if (shared) EF_HIP(c, ef::launch_ffn_gate_up_shared(gu, wg_gu, tpp, occ, c->xp, c->act, d, s));
@@ -446,8 +452,8 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         auto add = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             if (!ef::ffn_tiled_ok(d, F, nt) || (routed && nt < c->tune.tiled_min_tiles)) return;
-            wg_up += ef::ffn_gate_up_tiled_wgs(F, nt);
-            wg_dn += ef::ffn_down_tiled_wgs(d, nt);
+            wg_up += ef::ffn_tiled_units(F / 128, nt, 1);
+            wg_dn += ef::ffn_tiled_units(d / 256, nt, 1);
             tiled_rows += cnt;
             tiled_stages_min = std::min(tiled_stages_min, F / 32);
             tiled_stages_max = std::max(tiled_stages_max, F / 32);
@@ -549,7 +555,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 if (!ef::ffn_tiled_ok(d, F, nt) || (routed && nt < c->tune.tiled_min_tiles)) return;
                 const long long work = (long long)nt * F;
                 if (best_work < 0 || work <= best_work) {
-                    best_work = work; split_expert = expert; units = ef::ffn_down_tiled_wgs(d, nt); rows = cnt; F_last = F;
+                    best_work = work; split_expert = expert; units = ef::ffn_tiled_units(d / 256, nt, 1); rows = cnt; F_last = F;
                 }
             };
             if (has_shared) consider(-1, c->cfg.d_ff_shared, T, false);
