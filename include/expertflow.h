@@ -180,9 +180,9 @@ size_t ef_expert_bytes(int d_model, int d_ff);
  * cores in fp16 with fp32 accumulation: tokens are converted from bf16 to fp16 (exact for
  * 2^-14 <= |x| < 65504; larger magnitudes overflow) and the intermediate activations are kept in
  * fp16.  Requires d_model, d_ff and d_ff_shared multiples of 128; with a shared FFN its blob is a
- * 4-bit blob too (ef_pack_expert_q4 with d_ff_shared).  Groups of up to 7 token
- * tiles run through weight-streaming kernels that dequantise on the operand fragment; larger groups
- * (prefill) are first expanded to a 16-bit blob of the same fp16 values (q - 8) * s in a staging
+ * 4-bit blob too (ef_pack_expert_q4 with d_ff_shared).  The kernels dequantise on the operand fragment, in passes of
+ * one, two or four token tiles; the groups of very large launches (prefill of a Mixtral-shaped layer) are
+ * first expanded to a 16-bit blob of the same fp16 values (q - 8) * s in a staging
  * area the context owns (one blob per expert that can reach that size in one call) and then run
  * through the tiled matrix-core kernels in fp16.
  */

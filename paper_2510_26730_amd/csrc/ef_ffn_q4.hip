@@ -1,5 +1,5 @@
 // Grouped SwiGLU expert FFN with 4-bit expert weights (w = (q - 8) * s, one bf16 scale per matrix row
-// and group of 128 inputs), for groups of any size.
+// and group of 128 inputs), for groups of any size (the largest launches expand the weights first: ef_plan.hip).
 //
 // With 4-bit weights a byte of weights meets four times as many token bytes as with bf16, so the
 // re-reads of the token (or activation) fragments, not the weight stream, would bound a kernel in
@@ -59,6 +59,13 @@ __device__ __forceinline__ q4_half2 q4_scale(uint16_t b) {
     return q4_half2{h, h};
 }
 
+// beyond the largest finite fp16 an activation saturates to it, as in the 16-bit kernels; NaN stays NaN
+__device__ __forceinline__ float q4_saturate(float v) {
+    const float lim = 65504.f;
+    v = v > lim ? lim : v;
+    return v < -lim ? -lim : v;
+}
+
 // register ring: stages in flight per wave (four were measured slower than six with two token tiles per pass
 // and one wave per SIMD)
 template <int TT> constexpr int q4_depth() { return 6; }
@@ -96,10 +103,14 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
         const q4_half2 f1_ = q4_scale(sa[slot]), f3_ = q4_scale(sb[slot]);                                \
         u32x4_t xb_[NTL][4];                                                                              \
         _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt)                                                \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j) xb_[tt][j] = xs[(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
+            _Pragma("unroll") for (int j = 0; j < (NTL > 2 ? 1 : 4); ++j) xb_[tt][j] = xs[(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
         u32x4_t a1_ = dequant_q4(qa[slot][0], f1_), a3_ = dequant_q4(qb[slot][0], f3_);                   \
         _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                   \
             u32x4_t n1_ = a1_, n3_ = a3_;                                                                 \
+            if (NTL > 2 && j < 3) { /* wide passes: a k-step ahead, not the whole stage (registers) */   \
+                _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt)                                        \
+                    xb_[tt][j + 1] = xs[(st) & (kQ4Lds - 1)][tt * 4 + j + 1][lane];                       \
+            }                                                                                             \
             if (j < 3) { n1_ = dequant_q4(qa[slot][j + 1], f1_); n3_ = dequant_q4(qb[slot][j + 1], f3_); } \
             _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) {                                           \
                 G[tt] = mfma32h(a1_, xb_[tt][j], G[tt]);                                                  \
@@ -147,6 +158,11 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
 // consecutive 32-row blocks of F), wave = one row block and one of KH halves of the K range.
 //
 // OCC = 2: registers for two workgroups per compute unit (launches with more workgroups than compute units).
+// TT = 4: launches of many workgroups, and groups of 8 token tiles and more.  Bound by the matrix cores (32 instructions
+// of 32 cycles per stage and wave, the dequantisation of about 520 cycles between them); a register ring of three stages
+// and two workgroups per compute unit (ring of two: 3 to 5 % slower, four with one workgroup: 10 to 18 %).  Against passes of two, two
+// layers: Mixtral-shaped 700 tokens 1370 -> 1190 us, DeepSeek-shaped 1000 tokens 564 -> 515; against the expansion to 16
+// bits and 256 x 256 tiles for groups of 8 tiles and more: 1600 -> 1190 and 680 -> 515 us.
 // KH = 2: eight waves, two per SIMD.  A wave issues in order, so with one wave per SIMD its dequantising
 // vector instructions (about 40 % of its cycles), its waits for LDS and barriers (25 %) and its issue stalls
 // add up; a second wave on the SIMD fills them.  A launch rarely has enough row blocks for that (two Mixtral-
@@ -157,7 +173,7 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
 template <int TT, int KH, int OCC>
 __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTable gt, const uint4 *__restrict__ xp,
                                                                        uint4 *__restrict__ act, int d) {
-    constexpr int D = (KH == 2 || OCC == 2) ? 4 : q4_depth<TT>();   // 3 and 6 measured slower with two waves per SIMD
+    constexpr int D = TT == 4 ? 3 : (KH == 2 || OCC == 2) ? 4 : q4_depth<TT>();   // 3 and 6 measured slower with two waves per SIMD
     __shared__ __attribute__((aligned(16))) u32x4_t xs[KH][kQ4Lds][TT * 4][64];
     const int wg = blockIdx.x;
     int grp = 0;
@@ -194,6 +210,8 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
     // In a launch of passes of two most experts have one (eight Mixtral-shaped experts, 64 tokens: 157 -> 131 us; passes
     // of one tile for everybody instead dequantise twice where there are two: 412 against 399 us for two layers).
     if (TT == 1 || ntl == 1) q4_up_stream<TT, 1, D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    else if (TT == 2 || ntl == 2) q4_up_stream<TT, (TT > 1 ? 2 : 1), D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    else if (ntl == 3) q4_up_stream<TT, (TT > 2 ? 3 : TT), D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
     else q4_up_stream<TT, TT, D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
 
     if constexpr (KH == 2) {
@@ -234,7 +252,7 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
                 const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
                 const float v0 = g0 / (1.f + __expf(-g0)) * U[tt][8 * s + 2 * q];
                 const float v1 = g1 / (1.f + __expf(-g1)) * U[tt][8 * s + 2 * q + 1];
-                pk[q] = __builtin_bit_cast(uint32_t, q4_half2{(_Float16)v0, (_Float16)v1});
+                pk[q] = __builtin_bit_cast(uint32_t, q4_half2{(_Float16)q4_saturate(v0), (_Float16)q4_saturate(v1)});
             }
             dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         }
@@ -258,7 +276,8 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     // their waves stall at different times, where the halves of one workgroup meet at the same barriers
     // (seven Mixtral-shaped experts: 127 against 135 us, Qwen-shaped batch 52 against 60 us)
     const bool many = total_wgs > 256;
-    if (tiles_per_pass == 1 && many) hipLaunchKernelGGL((ffn_gate_up_q4_kernel<1, 1, 2>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
+    if (tiles_per_pass == 4) hipLaunchKernelGGL((ffn_gate_up_q4_kernel<4, 1, 2>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
+    else if (tiles_per_pass == 1 && many) hipLaunchKernelGGL((ffn_gate_up_q4_kernel<1, 1, 2>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
     else if (tiles_per_pass == 2 && many) hipLaunchKernelGGL((ffn_gate_up_q4_kernel<2, 1, 2>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
     else if (tiles_per_pass == 1 && halves) hipLaunchKernelGGL((ffn_gate_up_q4_kernel<1, 2, 1>), dim3(total_wgs), dim3(512), 0, s, gt, x, a, d);
     else if (tiles_per_pass == 1) hipLaunchKernelGGL((ffn_gate_up_q4_kernel<1, 1, 1>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
@@ -348,10 +367,10 @@ __device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, si
 // Each K-slice writes its own partial Y plane; the un-permute sums the planes in order.
 // ------------------------------------------------------------------------------------------
 template <int TT>
-__global__ __launch_bounds__(256, 1) void ffn_down_q4_kernel(GroupTable gt, const uint4 *__restrict__ act,
+__global__ __launch_bounds__(256, TT == 4 ? 2 : 1) void ffn_down_q4_kernel(GroupTable gt, const uint4 *__restrict__ act,
                                                              float *__restrict__ Y, int d, int ksg,
                                                              long long y_plane) {
-    constexpr int D = q4_depth<TT>(), CBW = 2;
+    constexpr int D = TT == 4 ? 3 : q4_depth<TT>(), CBW = 2;
     __shared__ __attribute__((aligned(16))) u32x4_t as[kQ4Lds][TT * 4][64];
     const int wg = blockIdx.x;
     int grp = 0;
@@ -387,6 +406,8 @@ __global__ __launch_bounds__(256, 1) void ffn_down_q4_kernel(GroupTable gt, cons
         for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
 
     if (TT == 1 || ntl == 1) q4_down_stream<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+    else if (TT == 2 || ntl == 2) q4_down_stream<TT, (TT > 1 ? 2 : 1), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+    else if (ntl == 3) q4_down_stream<TT, (TT > 2 ? 3 : TT), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
     else q4_down_stream<TT, TT, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
 
     if (!valid) return;
@@ -425,6 +446,8 @@ hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per
         hipLaunchKernelGGL((ffn_down_q4_kernel<1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
     else if (tiles_per_pass == 2)
         hipLaunchKernelGGL((ffn_down_q4_kernel<2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+    else if (tiles_per_pass == 4)
+        hipLaunchKernelGGL((ffn_down_q4_kernel<4>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

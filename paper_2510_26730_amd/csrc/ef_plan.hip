@@ -151,14 +151,26 @@ double tiled_tail_makespan(long long before, long long units, int s) {
     }
 }
 
+// Token tiles per pass over a streamed group's weights, for a launch whose largest group has `max_tiles` and whose first
+// half would have `wgs_of_four` workgroups in passes of four.  16-bit: groups of three or more tiles (too few for the tiled
+// kernels) take passes of four, which halves the re-reads of their weights.  4-bit: passes of four dequantise half as
+// often, but a pass is twice as long; they pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes
+// of two / four: Mixtral-shaped 200 tokens, 1008 workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515;
+// Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-shaped 300 tokens, 671, 289 / 312).
+int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four) {
+    if (max_tiles >= 3 && c->tune.passes_of_four != 0 && (!c->q4 || wgs_of_four >= 896)) return 4;
+    return max_tiles >= 2 ? 2 : 1;
+}
+
 // Build the launch tables of one phase and enqueue both FFN halves.
 int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, const int32_t *counts_host,
                  const std::vector<int> &offs_host, const std::vector<int> &tile_start,
                  const std::vector<long long> &act_off, int shared_tile_start, long long shared_act_off, int T,
                  int ksg_stream, int ksg_tiled, int split_expert, int split_ksg, ef::PlaneTable &planes, long long y_plane,
-                 bool use_tiled, hipStream_t s) {
+                 bool use_tiled, bool expand, hipStream_t s) {
     // split_expert: the tiled group of the layer (expert id, -1 = shared FFN, kNoSplit = none) whose second half takes
-    // split_ksg K slices instead of ksg_tiled; it goes last among the tiled groups of its launch
+    // split_ksg K slices instead of ksg_tiled; it goes last among the tiled groups of its launch.  expand: the tiled groups
+    // of a 4-bit context are expanded to 16 bits first (else they run in passes of four tiles on the 4-bit blobs)
     if (groups.empty()) return EF_OK;
     const int d = c->cfg.d_model, k = c->cfg.top_k;
     // groups with many tokens go to the tiled (matrix-core bound) kernels, the others to the
@@ -198,10 +210,10 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         }
         const int nt = (cnt + ef::kTile - 1) / ef::kTile;
         const bool tiled = allow_tiled && ef::ffn_tiled_ok(d, F, nt) && (pg.expert < 0 || nt >= c->tune.tiled_min_tiles) &&
-                           (!c->q4 || nb < c->q4_stage_slots);
+                           (!c->q4 || !expand || nb < c->q4_stage_slots);
         ef::GroupTable &g = tiled ? big : gu;
         int &i = tiled ? nb : n;
-        if (tiled && c->q4) {   // the tiled kernels read a 16-bit copy written just before them on the same stream
+        if (tiled && c->q4 && expand) {   // the tiled kernels read a 16-bit copy written just before them on the same stream
             void *copy = c->q4_stage + (size_t)nb * c->q4_stage_bytes;
             dq.F[nb] = F; dq.src[nb] = blob; dq.dst[nb] = copy;
             blob = copy;
@@ -280,6 +292,11 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         for (int i = 0; i < nb; ++i) {
             big.wg_start[i] = wg_up;
             bdn.wg_start[i] = wg_dn;
+            if (c->q4 && !expand) {
+                wg_up += ef::ffn_gate_up_q4_wgs(big.F[i], big.n_tiles[i], 4);
+                wg_dn += ef::ffn_down_q4_wgs(d, big.n_tiles[i], 4, ksg_tiled);
+                continue;
+            }
             const int ks = i == split_grp ? split_ksg : ksg_tiled;
             big.xcd_rot[i] = place(ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1), load_up);
             bdn.xcd_rot[i] = place(ef::ffn_tiled_units(d / 256, big.n_tiles[i], ks), load_dn);
@@ -310,23 +327,25 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         }
         {
             KernelTimer kt(c, ts, EF_K_FFN_UP_TILED, b_up, f_up);   // 4-bit: the expansion is timed with the first half
-            if (c->q4) {
+            if (c->q4 && expand) {
                 dq.n = nb;
                 EF_HIP(c, ef::launch_dequant_q4(dq, d, ts));
             }
-            EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, wg_up, c->xp, c->act, d, c->q4, ts));
+            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_gate_up_q4(big, wg_up, 4, c->xp, c->act, d, ts));
+            else EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, wg_up, c->xp, c->act, d, c->q4, ts));
         }
         {
             KernelTimer kt(c, ts, EF_K_FFN_DOWN_TILED, b_dn, f_dn);
-            EF_HIP(c, ef::launch_ffn_down_tiled(bdn, wg_dn, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, ts));
+            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_down_q4(bdn, wg_dn, 4, ksg_tiled, c->act, c->y, y_plane, d, ts));
+            else EF_HIP(c, ef::launch_ffn_down_tiled(bdn, wg_dn, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, ts));
         }
         if (side.forked) EF_HIP(c, side.record());
     }
     if (n == 0) return EF_OK;
     ef::GroupTable dn = gu;
-    // token tiles per pass over a group's weights: groups of three or more tiles (too few for the tiled
-    // kernels) take passes of four, which halves the re-reads of their weights (bf16 kernels only)
-    const int tpp = (max_tiles >= 3 && !c->q4 && c->tune.passes_of_four != 0) ? 4 : max_tiles >= 2 ? 2 : 1;
+    long long wgs_of_four = 0;
+    for (int i = 0; i < n; ++i) wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
+    const int tpp = tiles_per_pass(c, max_tiles, wgs_of_four);
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;
@@ -444,15 +463,25 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     // with a 2048 x 5632 shared expert, 1056 tokens over 64 experts) the tiled kernels were equal to or
     // 8 % faster than streaming the same groups in several passes, even at 150-200 workgroups.
     bool use_tiled = false;
+    // 4-bit contexts: the tiled groups are expanded to 16 bits and go through the 256 x 256 tiles when the groups of 32
+    // tiles and more alone make eight rounds of those over the compute units; below that the expansion (a pass over 2.5
+    // bytes per weight ahead of the first half) and the tiles' fixed costs outweigh them, and the groups run in passes of
+    // four token tiles on the 4-bit blobs, dequantised between the matrix instructions.  Two layers, expanded / direct:
+    // Mixtral-shaped 4000 tokens on two experts 4610 / 5350 us, 2000 tokens on eight 3050 / 3080; DeepSeek-shaped 4000
+    // tokens 1560 / 1459, 2000 tokens on 16 experts 873 / 778; Qwen-shaped 3000 tokens 1120 / 1026.
+    bool q4_expand = false;
+    long long passes_of_four_dn = 0;   // workgroups of a second half of the tiled groups in passes of four
     long long tiled_dn_wgs = 0, tiled_rows = 0;
     int tiled_stages_min = 1 << 30;   // fewest K stages (32 columns each) among the tiled groups
     int tiled_stages_max = 0;         // ... and most
     if (T > 0 && (!c->q4 || c->q4_stage_slots > 0) && c->tune.tiled != 0) {
-        long long wg_up = 0, wg_dn = 0;
+        long long wg_up = 0, wg_dn = 0, wg_up_large = 0;
         auto add = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             if (!ef::ffn_tiled_ok(d, F, nt) || (routed && nt < c->tune.tiled_min_tiles)) return;
             wg_up += ef::ffn_tiled_units(F / 128, nt, 1);
+            if (nt >= 32) wg_up_large += ef::ffn_tiled_units(F / 128, nt, 1);
+            passes_of_four_dn += ef::ffn_down_q4_wgs(d, nt, 4, 1);
             wg_dn += ef::ffn_tiled_units(d / 256, nt, 1);
             tiled_rows += cnt;
             tiled_stages_min = std::min(tiled_stages_min, F / 32);
@@ -461,6 +490,22 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e) add(c->cfg.d_ff, counts_host[e], true);
         if (has_shared) add(c->cfg.d_ff_shared, T, false);
         use_tiled = wg_up >= c->tune.tiled_min_up_wgs && wg_dn >= c->tune.tiled_min_down_wgs;
+        q4_expand = c->q4 && wg_up_large >= 2048;
+        if (c->q4 && use_tiled && !q4_expand && c->tune.passes_of_four != 0) {
+            // Passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
+            // less: one launch per half instead of two on two streams, whose fork and join cost about 10 us (two layers:
+            // Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens 1560 -> 1459)
+            long long four_all = 0, four_tiled = 0;
+            auto count = [&](int F, int cnt, bool routed) {
+                const int nt = (cnt + ef::kTile - 1) / ef::kTile;
+                const long long wgs = (long long)(F / 128) * ((nt + 3) / 4);
+                four_all += wgs;
+                if (ef::ffn_tiled_ok(d, F, nt) && (!routed || nt >= c->tune.tiled_min_tiles)) four_tiled += wgs;
+            };
+            for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
+            if (has_shared) count(c->cfg.d_ff_shared, T, false);
+            if (tiles_per_pass(c, 4, four_all) == 4 || (four_all >= 512 && four_tiled * 4 <= four_all)) use_tiled = false;
+        }
         tiled_dn_wgs = wg_dn;
     }
     // K slices of the second half (one Y plane each, summed by the un-permute): the streamed launch and the tiled
@@ -472,15 +517,20 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         // token tiles per pass of the streamed launch: from the groups that stream (the tiled ones have kernels of
         // their own), with the same rule launch_phase applies to a phase's streamed groups
         int tmax = 1;
+        long long wgs_of_four = 0;
+        auto see = [&](int F, int cnt) {
+            const int nt = (cnt + ef::kTile - 1) / ef::kTile;
+            tmax = std::max(tmax, nt);
+            wgs_of_four += (long long)(F / 128) * ((nt + 3) / 4);
+        };
         auto streams = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             return !(use_tiled && ef::ffn_tiled_ok(d, F, nt) && (!routed || nt >= c->tune.tiled_min_tiles));
         };
         for (int e = 0; e < E; ++e)
-            if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true))
-                tmax = std::max(tmax, (counts_host[e] + ef::kTile - 1) / ef::kTile);
-        if (has_shared && streams(c->cfg.d_ff_shared, T, false)) tmax = std::max(tmax, (T + ef::kTile - 1) / ef::kTile);
-        const int tpp = (tmax >= 3 && !c->q4 && c->tune.passes_of_four != 0) ? 4 : tmax >= 2 ? 2 : 1;
+            if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
+        if (has_shared && streams(c->cfg.d_ff_shared, T, false)) see(c->cfg.d_ff_shared, T);
+        const int tpp = tiles_per_pass(c, tmax, wgs_of_four);
         // workgroups of the streamed launch with one slice (groups that take the tiled kernels do not count)
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0) {
@@ -527,7 +577,18 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             // (any count from 1 to 8: 40 tiles in 6 slices are 240 workgroups, one round over the 256 compute units
             // at a sixth of the length, where 8 slices are 320 workgroups, two rounds at an eighth; a plane more is
             // priced at what it takes to write and read)
-            if (tiled_dn_wgs < 256) {
+            if (c->q4 && !q4_expand) {
+                // passes of four tiles: slices by the same model; two workgroups per compute unit, a stage of 64 columns
+                // about 1 us with both busy
+                const int stages = tiled_stages_max / 2;
+                const double plane_pen = (double)tiled_rows * d * 8.0 / 5e12 / (stages * 1e-6);
+                double best = 0.0;
+                for (int ks = 1; ks <= 8; ++ks) {
+                    if (ks > 1 && (tiled_stages_min / 2 / ks < 6 || y_plane * ks > c->y_floats)) break;
+                    const double t = (double)((passes_of_four_dn * ks + 511) / 512) / ks + (ks - 1) * plane_pen;
+                    if (ks == 1 || t < best - 1e-9) { best = t; ksg_tiled = ks; }
+                }
+            } else if (tiled_dn_wgs < 256) {
                 const int stages_ref = c->tune.down_slices_by_longest_k ? tiled_stages_max : tiled_stages_min;
                 const double plane_pen = (double)tiled_rows * d * 8.0 / 5e12 / (stages_ref * 0.77e-6);
                 double best = 0.0;
@@ -547,7 +608,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         // slices so that its shorter workgroups fill that round: the slice count with the least modelled time,
         // a Y plane more costing what the second half and the un-permute take to write and read it.  The choice
         // depends on the layer's token counts only, never on what is resident.
-        if (use_tiled && ksg_tiled == 1 && forced < 1 && tiled_dn_wgs > 256 && c->tune.tiled_tail_slices != 0) {
+        if (use_tiled && (!c->q4 || q4_expand) && ksg_tiled == 1 && forced < 1 && tiled_dn_wgs > 256 && c->tune.tiled_tail_slices != 0) {
             long long best_work = -1, units = 0, rows = 0;
             int F_last = 0;
             auto consider = [&](int expert, int F, int cnt, bool routed) {
@@ -713,7 +774,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         if (with_shared && has_shared) g.push_back({-1, -1});
         if (!c->fake) {
             int r = launch_phase(c, layer, g, counts_host, offs_host, tile_start, act_off, shared_tile_start,
-                                 shared_act_off, T, ksg, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled, s);
+                                 shared_act_off, T, ksg, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled, q4_expand, s);
             if (r) {   // part of the phase may be enqueued: its slots still get their read marker
                 (void)mark_read(v);
                 v.clear();   // released: the caller's error path has nothing left to unpin

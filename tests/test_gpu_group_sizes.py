@@ -22,6 +22,7 @@ SIZES = {
     "up to four tiles": [97, 128, 65, 96, 33, 1, 0, 127],
     "second passes": [129, 160, 193, 224, 225, 32, 1, 161],
     "tiled beside streamed": [320, 300, 33, 1, 100, 513, 64, 0],
+    "three live tiles last": [350, 449, 257, 480, 0, 97, 289, 1],
 }
 
 
