@@ -485,7 +485,8 @@ int ef_layer_step_fetch(ef_ctx *ctx, int32_t *topk_ids, float *topk_w, int32_t *
  */
 typedef struct ef_tuning {
     int32_t tiled;                   /* 0/1: groups of many token tiles may take the matrix-core tiled kernels (1) */
-    int32_t tiled_min_tiles;         /* 8..4096: routed groups take them from this many 32-token tiles on (10) */
+    int32_t tiled_min_tiles;         /* 8..4096: routed groups take them from this many 32-token tiles on, or one fewer
+                                        when passes of four would leave a single tile (10) */
     int32_t tiled_min_up_wgs;        /* >= 1: ... and only if the tiled first-half launch has this many workgroups (1) */
     int32_t tiled_min_down_wgs;      /* >= 1: ... and the second-half launch this many (1) */
     int32_t tiled_xcd_rotation;      /* 0/1: deal every group's weight-panel blocks from the least loaded XCD (1) */

@@ -151,6 +151,16 @@ double tiled_tail_makespan(long long before, long long units, int s) {
     }
 }
 
+// Whether a group of n_tiles token tiles takes the tiled kernels: every shared FFN that fits them, routed groups from
+// tiled_min_tiles tiles on, and one tile earlier where passes of four would end in a pass of a single tile, a whole read of
+// the weights for it (groups of 9: Mixtral-shaped 1000 tokens 2050 -> 1942 us for two layers, DeepSeek-shaped 1056 tokens
+// 784 -> 776; groups of 8 stay streamed: DeepSeek-shaped 2000 tokens on 16 experts 883 against 905 us).
+bool takes_tiled(const ef_ctx *c, int F, int n_tiles, bool routed) {
+    if (!ef::ffn_tiled_ok(c->cfg.d_model, F, n_tiles)) return false;
+    const int from = c->tune.tiled_min_tiles;
+    return !routed || n_tiles >= from || (n_tiles == from - 1 && n_tiles % 4 == 1);
+}
+
 // Token tiles per pass over a streamed group's weights, for a launch whose largest group has `max_tiles` and whose first
 // half would have `wgs_of_four` workgroups in passes of four.  16-bit: groups of three or more tiles (too few for the tiled
 // kernels) take passes of four, which halves the re-reads of their weights.  4-bit: passes of four dequantise half as
@@ -209,7 +219,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             blob = c->pool + (size_t)pg.slot * c->expert_bytes;
         }
         const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-        const bool tiled = allow_tiled && ef::ffn_tiled_ok(d, F, nt) && (pg.expert < 0 || nt >= c->tune.tiled_min_tiles) &&
+        const bool tiled = allow_tiled && takes_tiled(c, F, nt, pg.expert >= 0) &&
                            (!c->q4 || !expand || nb < c->q4_stage_slots);
         ef::GroupTable &g = tiled ? big : gu;
         int &i = tiled ? nb : n;
@@ -478,7 +488,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         long long wg_up = 0, wg_dn = 0, wg_up_large = 0;
         auto add = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-            if (!ef::ffn_tiled_ok(d, F, nt) || (routed && nt < c->tune.tiled_min_tiles)) return;
+            if (!takes_tiled(c, F, nt, routed)) return;
             wg_up += ef::ffn_tiled_units(F / 128, nt, 1);
             if (nt >= 32) wg_up_large += ef::ffn_tiled_units(F / 128, nt, 1);
             passes_of_four_dn += ef::ffn_down_q4_wgs(d, nt, 4, 1);
@@ -491,20 +501,28 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         if (has_shared) add(c->cfg.d_ff_shared, T, false);
         use_tiled = wg_up >= c->tune.tiled_min_up_wgs && wg_dn >= c->tune.tiled_min_down_wgs;
         q4_expand = c->q4 && wg_up_large >= 2048;
-        if (c->q4 && use_tiled && !q4_expand && c->tune.passes_of_four != 0) {
-            // Passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
-            // less: one launch per half instead of two on two streams, whose fork and join cost about 10 us (two layers:
-            // Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens 1560 -> 1459)
-            long long four_all = 0, four_tiled = 0;
-            auto count = [&](int F, int cnt, bool routed) {
-                const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-                const long long wgs = (long long)(F / 128) * ((nt + 3) / 4);
-                four_all += wgs;
-                if (ef::ffn_tiled_ok(d, F, nt) && (!routed || nt >= c->tune.tiled_min_tiles)) four_tiled += wgs;
-            };
-            for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
-            if (has_shared) count(c->cfg.d_ff_shared, T, false);
+        // Groups that would not use what the tiled kernels offer run with the streamed ones: one launch per half instead of
+        // two on two streams, whose fork and join cost about 10 us.  In passes of four token tiles:
+        long long four_all = 0, four_tiled = 0;
+        auto count = [&](int F, int cnt, bool routed) {
+            const int nt = (cnt + ef::kTile - 1) / ef::kTile;
+            const long long wgs = (long long)(F / 128) * ((nt + 3) / 4);
+            four_all += wgs;
+            if (takes_tiled(c, F, nt, routed)) four_tiled += wgs;
+        };
+        for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
+        if (has_shared) count(c->cfg.d_ff_shared, T, false);
+        if (c->q4 && !q4_expand && c->tune.passes_of_four != 0) {
+            // passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
+            // less (two layers: Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens
+            // 1560 -> 1459)
             if (tiles_per_pass(c, 4, four_all) == 4 || (four_all >= 512 && four_tiled * 4 <= four_all)) use_tiled = false;
+        } else if (!c->q4 && wg_up < 64 && four_all - four_tiled >= 128 && c->tune.passes_of_four != 0 &&
+                   c->tune.lds_shared != 0) {
+            // fewer than 64 of the 256 x 256 tiles beside a streamed launch that covers half of the compute units (two
+            // layers, tiled / all streamed: DeepSeek-shaped 260 tokens, 44 tiles, 526 / 479 us, on 16 experts 361 / 328;
+            // Qwen-shaped 260 tokens on 12 experts, 88 tiles, 290 / 348 us)
+            use_tiled = false;
         }
         tiled_dn_wgs = wg_dn;
     }
@@ -525,7 +543,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         };
         auto streams = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-            return !(use_tiled && ef::ffn_tiled_ok(d, F, nt) && (!routed || nt >= c->tune.tiled_min_tiles));
+            return !(use_tiled && takes_tiled(c, F, nt, routed));
         };
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
@@ -535,12 +553,12 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0) {
                 const int nt = (counts_host[e] + ef::kTile - 1) / ef::kTile;
-                if (use_tiled && ef::ffn_tiled_ok(d, c->cfg.d_ff, nt) && nt >= c->tune.tiled_min_tiles) continue;
+                if (use_tiled && takes_tiled(c, c->cfg.d_ff, nt, true)) continue;
                 streamed_w2_bytes += (0.5 + 2.0 / 128.0) * d * c->cfg.d_ff;
                 base_wgs += c->q4 ? ef::ffn_down_q4_wgs(d, nt, tpp, 1)
                             : tpp == 4 ? ef::ffn_down_shared_wgs(d, nt, tpp, 1) : ef::ffn_down_wgs(d, nt, tpp, 1);
             }
-        if (has_shared && !(use_tiled && ef::ffn_tiled_ok(d, c->cfg.d_ff_shared, (T + ef::kTile - 1) / ef::kTile)))
+        if (has_shared && !(use_tiled && takes_tiled(c, c->cfg.d_ff_shared, (T + ef::kTile - 1) / ef::kTile, false)))
             base_wgs += c->q4 ? ef::ffn_down_q4_wgs(d, (T + ef::kTile - 1) / ef::kTile, tpp, 1)
                         : tpp == 4 ? ef::ffn_down_shared_wgs(d, (T + ef::kTile - 1) / ef::kTile, tpp, 1)
                                    : ef::ffn_down_wgs(d, (T + ef::kTile - 1) / ef::kTile, tpp, 1);
@@ -613,7 +631,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             int F_last = 0;
             auto consider = [&](int expert, int F, int cnt, bool routed) {
                 const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-                if (!ef::ffn_tiled_ok(d, F, nt) || (routed && nt < c->tune.tiled_min_tiles)) return;
+                if (!takes_tiled(c, F, nt, routed)) return;
                 const long long work = (long long)nt * F;
                 if (best_work < 0 || work <= best_work) {
                     best_work = work; split_expert = expert; units = ef::ffn_tiled_units(d / 256, nt, 1); rows = cnt; F_last = F;
