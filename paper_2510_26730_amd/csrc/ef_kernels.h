@@ -11,7 +11,9 @@ constexpr int kMaxGates = 8;   // gate matrices per launch (look-ahead + 1)
 constexpr int kTile = 32;      // tokens per tile (rows of one matrix-core operand fragment)
 constexpr int kMaxGroups = kMaxE + 1;  // routed experts + the dense shared FFN
 constexpr int kDownColBlocks = 2;      // 32-column blocks per wave in the second FFN half
-constexpr int kGroupSmallTiles = 64;   // token tiles the single-workgroup grouping kernel handles
+
+constexpr int kGroupSmallTiles = 4;    // token tiles the single-workgroup grouping kernel handles
+constexpr int kGroupLdsTiles = 64;     // ... and the single-launch one
 
 // Gate / predict launch: G gate matrices applied to the same hidden states.
 struct GateArgs {
@@ -77,6 +79,7 @@ struct PackTable {
 
 hipError_t launch_fill_i32(int32_t *p, int n, int32_t v, hipStream_t s);
 int gate_pick_gpw(int T, int G, int E);
+constexpr size_t kGateSplitFloats = 960 * 1024;   // partial logits of a K-split gate launch (3.75 MiB), in any scratch
 int gate_pick_ksplit(int T, int d, int G, int E, int gpw, size_t part_floats);
 int gate_pick_tsplit(int T, int G, int E, int gpw);
 hipError_t launch_gate(const GateArgs &a, hipStream_t s);

@@ -618,9 +618,13 @@ int gate_pick_ksplit(int T, int d, int G, int E, int gpw, size_t part_floats) {
     const int nb = (std::min(gpw, G) * E + 31) / 32;
     const int kc = nb == 1 ? 256 : 128;
     const int nstage = (d + kc - 1) / kc;
+    // Half a round of workgroups (64 until E = 64 at 1056 and 3000 tokens with one look-ahead layer, 66 and 94 pairs of
+    // tile and gate group, measured 32.4 -> 29.7 and 43.4 -> 38.8 us for the call with two slices; 132 pairs gain nothing).
+    // The split decides the order of the sums: it may not depend on which scratch a call was given, so what the smaller
+    // one, ef_route_static's, holds bounds both.
     int ks = 1;
-    while (ks < kGateMaxSplit && nstage / (ks * 2) >= 4 && ntiles * ngroups * ks < 64 &&
-           (size_t)ntiles * ngroups * (ks * 2) * kTile * nb * 32 <= part_floats)
+    while (ks < kGateMaxSplit && nstage / (ks * 2) >= 4 && ntiles * ngroups * ks < 128 &&
+           (size_t)ntiles * ngroups * (ks * 2) * kTile * nb * 32 <= std::min(part_floats, kGateSplitFloats))
         ks *= 2;
     return ks;
 }
@@ -657,25 +661,7 @@ hipError_t launch_gate(const GateArgs &a, hipStream_t s) {
 // stable grouping by expert: per-tile counts (from the gate kernel) -> scan -> scatter
 // ------------------------------------------------------------------------------------------
 
-// the same scan on counts already in LDS, in place: counts[b*E + e] becomes the exclusive prefix
-__device__ __forceinline__ int scan_expert_inplace(int *cnt, int ntiles, int E, int e, int lane) {
-    int carry = 0;
-    for (int c0 = 0; c0 < ntiles; c0 += 64) {
-        const int b = c0 + lane;
-        const int v = b < ntiles ? cnt[b * E + e] : 0;
-        int incl = v;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off);
-            if (lane >= off) incl += o;
-        }
-        if (b < ntiles) cnt[b * E + e] = carry + incl - v;
-        carry += __shfl(incl, 63);
-    }
-    return carry;
-}
-
-// the same exclusive prefix over the tiles of expert e by one thread, for batches of a few tiles
-constexpr int kGroupSerialTiles = 4;
+// exclusive prefix over the tiles of expert e in place, counts in LDS, by one thread: batches of a few tiles
 __device__ __forceinline__ int scan_expert_serial(int *cnt, int ntiles, int E, int e) {
     int run = 0;
     for (int b = 0; b < ntiles; ++b) {
@@ -738,7 +724,7 @@ __device__ __forceinline__ void export_meta(const GroupExport &ex, const int *to
     for (int x = threadIdx.x; x < ex.n_clear; x += blockDim.x) ex.hist[x] = 0;   // ready for the next layer
 }
 
-// Batches of more than kGroupSmallTiles token tiles: one workgroup per expert forms the exclusive prefix of
+// Larger batches than group_lds_kernel takes: one workgroup per expert forms the exclusive prefix of
 // that expert's per-tile counts over the tiles (16 waves, a contiguous range of tiles each: totals first,
 // then the scan with the bases of the waves before), and leaves the expert's total in counts[e].
 __global__ __launch_bounds__(1024) void group_scan_kernel(const int32_t *__restrict__ bc, int ntiles, int E,
@@ -811,29 +797,22 @@ __global__ __launch_bounds__(64 * kScatterWaves) void group_scatter_kernel(const
     scatter_tile(ids, T, k, b, lane, nxt[wave], perm, inv_perm);
 }
 
-// scan + scatter in one workgroup for up to kGroupSmallTiles token tiles (prefixes stay in LDS)
-__global__ __launch_bounds__(1024) void group_small_kernel(const int32_t *__restrict__ bc, int ntiles,
-                                                           const int32_t *__restrict__ ids, int T, int k, int E,
-                                                           int32_t *__restrict__ counts,
-                                                           int32_t *__restrict__ offsets,
-                                                           int32_t *__restrict__ perm,
-                                                           int32_t *__restrict__ inv_perm, GroupExport ex) {
+// scan + scatter in one workgroup for up to kGroupSmallTiles token tiles (prefixes stay in LDS, one thread per expert)
+__global__ __launch_bounds__(64 * kGroupSmallTiles) void group_small_kernel(const int32_t *__restrict__ bc, int ntiles,
+                                                                            const int32_t *__restrict__ ids, int T, int k, int E,
+                                                                            int32_t *__restrict__ counts,
+                                                                            int32_t *__restrict__ offsets,
+                                                                            int32_t *__restrict__ perm,
+                                                                            int32_t *__restrict__ inv_perm, GroupExport ex) {
     __shared__ int base[kGroupSmallTiles * kMaxE];
     __shared__ int total[kMaxE];
     __shared__ int offs[kMaxE + 1];
-    __shared__ int nxt[16][64];
+    __shared__ int nxt[kGroupSmallTiles][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    // one memory round trip brings the per-tile counts into LDS; the scans then run from there, in place
+    // one memory round trip brings the per-tile counts into LDS; the scan then runs from there, in place
     for (int x = threadIdx.x; x < ntiles * E; x += blockDim.x) base[x] = bc[x];
     __syncthreads();
-    if (ntiles <= kGroupSerialTiles) {   // a few tiles: one thread per expert walks them (no shuffle rounds)
-        if (threadIdx.x < (unsigned)E) total[threadIdx.x] = scan_expert_serial(base, ntiles, E, threadIdx.x);
-    } else {
-        for (int e = wave; e < E; e += 16) {
-            int tot = scan_expert_inplace(base, ntiles, E, e, lane);
-            if (lane == 0) total[e] = tot;
-        }
-    }
+    if (threadIdx.x < (unsigned)E) total[threadIdx.x] = scan_expert_serial(base, ntiles, E, threadIdx.x);
     __syncthreads();
     if (wave == 0) {   // exclusive scan of the E <= 64 totals across the lanes of one wave
         const int t = lane < E ? total[lane] : 0;
@@ -855,11 +834,62 @@ __global__ __launch_bounds__(1024) void group_small_kernel(const int32_t *__rest
     }
     __syncthreads();
     export_meta(ex, total, E);   // the host starts planning while the scatter below still runs
-    for (int b = wave; b < ntiles; b += 16) {
-        nxt[wave][lane] = (lane < E) ? offs[lane] + base[b * E + lane] : 0;
+    if (wave < ntiles) {
+        nxt[wave][lane] = (lane < E) ? offs[lane] + base[wave * E + lane] : 0;
         wave_lds_sync();
-        scatter_tile(ids, T, k, b, lane, nxt[wave], perm, inv_perm);
+        scatter_tile(ids, T, k, wave, lane, nxt[wave], perm, inv_perm);
     }
+}
+
+// Scan and scatter in one launch of several workgroups for up to kGroupLdsTiles token tiles: every workgroup loads all
+// per-tile counts into LDS and forms the totals and the prefixes of its own four tiles itself (a lane per expert walks the
+// tiles), so no workgroup waits for another.  Bound by latency: one load, the walk, one load of the ids.  Against one
+// workgroup that scans and scatters every tile: 64 experts, 33 tiles 12 -> 7 us; beyond 64 tiles the walk costs more than a
+// second launch (125 tiles of 64 experts: 7 us more than scan + scatter).
+__global__ __launch_bounds__(64 * kScatterWaves) void group_lds_kernel(const int32_t *__restrict__ bc, int ntiles,
+                                                                       const int32_t *__restrict__ ids, int T, int k, int E,
+                                                                       int32_t *__restrict__ counts,
+                                                                       int32_t *__restrict__ offsets,
+                                                                       int32_t *__restrict__ perm,
+                                                                       int32_t *__restrict__ inv_perm, GroupExport ex) {
+    __shared__ int cnt[kGroupLdsTiles * kMaxE];
+    __shared__ int total[kMaxE];
+    __shared__ int nxt[kScatterWaves][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int x = threadIdx.x; x < ntiles * E; x += blockDim.x) cnt[x] = bc[x];
+    __syncthreads();
+    const int b = blockIdx.x * kScatterWaves + wave;
+    int tot = 0, before = 0;   // this lane's expert: assignments in all tiles, and in the tiles before b
+    if (lane < E) {
+#pragma unroll 8
+        for (int t = 0; t < ntiles; ++t) {
+            const int v = cnt[t * E + lane];
+            tot += v;
+            before += t < b ? v : 0;
+        }
+    }
+    int incl = tot;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    if (blockIdx.x == 0) {   // uniform over the workgroup
+        if (wave == 0) {
+            if (lane < E) {
+                counts[lane] = tot;
+                offsets[lane] = incl - tot;
+                total[lane] = tot;
+            }
+            if (lane == 63) offsets[E] = incl;
+        }
+        __syncthreads();
+        export_meta(ex, total, E);   // the host starts planning while the scatter below still runs
+    }
+    if (b >= ntiles) return;
+    nxt[wave][lane] = lane < E ? incl - tot + before : 0;
+    wave_lds_sync();
+    scatter_tile(ids, T, k, b, lane, nxt[wave], perm, inv_perm);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1072,8 +1102,13 @@ hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, i
     if (T <= 0) return hipSuccess;
     const int ntiles = (T + kTile - 1) / kTile;
     if (ntiles <= kGroupSmallTiles) {
-        hipLaunchKernelGGL(group_small_kernel, dim3(1), dim3(1024), 0, s, blockcounts, ntiles, ids, T, k, E,
+        hipLaunchKernelGGL(group_small_kernel, dim3(1), dim3(64 * kGroupSmallTiles), 0, s, blockcounts, ntiles, ids, T, k, E,
                            counts, offsets, perm, inv_perm, ex);
+        return hipGetLastError();
+    }
+    if (ntiles <= kGroupLdsTiles) {
+        hipLaunchKernelGGL(group_lds_kernel, dim3((ntiles + kScatterWaves - 1) / kScatterWaves), dim3(64 * kScatterWaves), 0, s,
+                           blockcounts, ntiles, ids, T, k, E, counts, offsets, perm, inv_perm, ex);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(group_scan_kernel, dim3(E), dim3(1024), 0, s, blockcounts, ntiles, E, blockbase, counts);
