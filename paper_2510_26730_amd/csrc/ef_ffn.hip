@@ -399,7 +399,7 @@ __device__ __forceinline__ void down_stream(const uint4 *__restrict__ w2, size_t
 
 // ------------------------------------------------------------------------------------------
 // second half: Y = act W2^T.  A workgroup owns (group, pass of TT token tiles, CBW*32 output
-// columns, one of `ksg` K-slices); its four waves split that slice again and are summed in a fixed
+// columns, one of the group's K-slices); its four waves split that slice again and are summed in a fixed
 // order, (p0 + p2) + (p1 + p3), through LDS.  Each K-slice writes its own partial Y plane; the
 // un-permute sums the planes in order.  The product is formed transposed (W2 fragment first: the operand
 // layouts are mirror images), so a lane ends with one token and groups of four consecutive output columns:
@@ -407,7 +407,7 @@ __device__ __forceinline__ void down_stream(const uint4 *__restrict__ w2, size_t
 // ------------------------------------------------------------------------------------------
 template <int TT>
 __global__ __launch_bounds__(256, 2) void ffn_down_kernel(GroupTable gt, const uint4 *__restrict__ act,
-                                                       float *__restrict__ Y, int d, int ksg,
+                                                       float *__restrict__ Y, int d,
                                                        long long y_plane) {
     constexpr int CBW = kDownColBlocks;
     constexpr int UNR = TT > 2 ? 1 : 2;
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256, 2) void ffn_down_kernel(GroupTable gt, const u
     while (grp + 1 < gt.n_groups && gt.wg_start[grp + 1] <= wg) ++grp;
     const int local = wg - gt.wg_start[grp];
     const int ncbw = (d >> 5) / CBW;
-    const int kslice = local % ksg;
+    const int ksg = gt.ksg[grp], kslice = local % ksg;
     const int cb0 = ((local / ksg) % ncbw) * CBW, pass = (local / ksg) / ncbw;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int F = gt.F[grp];
@@ -483,16 +483,18 @@ __global__ __launch_bounds__(256, 2) void ffn_down_kernel(GroupTable gt, const u
     }
 }
 
-hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pass, int ksg, const void *act,
+hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act,
                            float *y, long long y_plane, int d, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
+    for (int i = 0; i < gt.n_groups; ++i)
+        if (gt.ksg[i] < 1) return hipErrorInvalidValue;
     const uint4 *a = reinterpret_cast<const uint4 *>(act);
     if (tiles_per_pass == 1)
-        hipLaunchKernelGGL((ffn_down_kernel<1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+        hipLaunchKernelGGL((ffn_down_kernel<1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 2)
-        hipLaunchKernelGGL((ffn_down_kernel<2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+        hipLaunchKernelGGL((ffn_down_kernel<2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
-        hipLaunchKernelGGL((ffn_down_kernel<4>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+        hipLaunchKernelGGL((ffn_down_kernel<4>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

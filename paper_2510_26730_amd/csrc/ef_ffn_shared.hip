@@ -220,13 +220,13 @@ __device__ __forceinline__ void shared_down_stream(const uint4 *__restrict__ w2,
 
 // ------------------------------------------------------------------------------------------
 // second half: Y = act W2^T.  Workgroup = (group, pass of TT token tiles, eight consecutive
-// 32-column blocks of d, one of `ksg` K-slices), wave = two column blocks.  Activations (fp16) are operand
+// 32-column blocks of d, one of the group's K-slices), wave = two column blocks.  Activations (fp16) are operand
 // A (rows = tokens), shared through LDS; W2 fragments (fp16) operand B (a lane holds one output column).
 // Each K-slice writes its own partial Y plane; the un-permute sums the planes in order.
 // ------------------------------------------------------------------------------------------
 template <int TT, int D, int OCC>
 __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt, const uint4 *__restrict__ act,
-                                                                 float *__restrict__ Y, int d, int ksg,
+                                                                 float *__restrict__ Y, int d,
                                                                  long long y_plane) {
     constexpr int CBW = 2;
     __shared__ __attribute__((aligned(16))) u32x4_t as[kShLds][TT * 4][64];
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
     while (grp + 1 < gt.n_groups && gt.wg_start[grp + 1] <= wg) ++grp;
     const int local = wg - gt.wg_start[grp];
     const int ncb = d >> 5, ncq = (ncb + 7) >> 3;
-    const int kslice = local % ksg;
+    const int ksg = gt.ksg[grp], kslice = local % ksg;
     const int cq = (local / ksg) % ncq, pass = (local / ksg) / ncq;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int cb0 = cq * 8 + wave * CBW;
@@ -288,22 +288,22 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
     }
 }
 
-hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, int ksg, const void *act,
+hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act,
                                   float *y, long long y_plane, int d, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
-    if (d % 64 != 0 || ksg < 1) return hipErrorInvalidValue;
+    if (d % 64 != 0) return hipErrorInvalidValue;
     for (int i = 0; i < gt.n_groups; ++i)
-        if (gt.F[i] % 128 != 0 || gt.n_tiles[i] <= 0 ||
-            gt.wg_start[i + 1] - gt.wg_start[i] != ffn_down_shared_wgs(d, gt.n_tiles[i], tiles_per_pass, ksg))
+        if (gt.F[i] % 128 != 0 || gt.n_tiles[i] <= 0 || gt.ksg[i] < 1 ||
+            gt.wg_start[i + 1] - gt.wg_start[i] != ffn_down_shared_wgs(d, gt.n_tiles[i], tiles_per_pass, gt.ksg[i]))
             return hipErrorInvalidValue;
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *a = reinterpret_cast<const uint4 *>(act);
     if (tiles_per_pass == 2)
-        hipLaunchKernelGGL((ffn_down_shared_kernel<2, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+        hipLaunchKernelGGL((ffn_down_shared_kernel<2, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4 && occ == 2)
-        hipLaunchKernelGGL((ffn_down_shared_kernel<4, 2, 2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+        hipLaunchKernelGGL((ffn_down_shared_kernel<4, 2, 2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
-        hipLaunchKernelGGL((ffn_down_shared_kernel<4, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, ksg, y_plane);
+        hipLaunchKernelGGL((ffn_down_shared_kernel<4, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

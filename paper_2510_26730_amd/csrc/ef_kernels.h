@@ -52,6 +52,7 @@ struct GroupTable {
     int F[kMaxGroups];             // FFN hidden dim of the group
     long long act_off[kMaxGroups]; // first 16-byte unit of the group's activation fragments
     const void *blob[kMaxGroups];  // packed weights (cache slot or shared blob)
+    uint8_t ksg[kMaxGroups];       // streamed second half: K slices of the group (one Y plane each)
     int xcd_rot[kMaxGroups];       // tiled kernels: the XCD (0..7) that takes the first eighth of the group's units
 };
 
@@ -103,8 +104,8 @@ hipError_t launch_pack_x_dev(const int32_t *counts, const int32_t *offsets, int 
                              bool f16, hipStream_t s);
 hipError_t launch_ffn_gate_up(const GroupTable &gt, int total_wgs, int tiles_per_pass, int ks, const void *xp,
                               void *act, int d, hipStream_t s);
-hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pass, int ksg, const void *act,
-                           float *y, long long y_plane, int d, hipStream_t s);
+hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act, float *y,
+                           long long y_plane, int d, hipStream_t s);
 // K-slice planes of Y each expert's rows (and the shared FFN's) were written to: the streamed and the tiled launch
 // of a layer choose their slice counts separately
 struct PlaneTable {
@@ -125,8 +126,8 @@ inline int ffn_down_q4_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) {
 }
 hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *xp, void *act,
                                  int d, hipStream_t s);
-hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, int ksg, const void *act,
-                              float *y, long long y_plane, int d, hipStream_t s);
+hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act, float *y,
+                              long long y_plane, int d, hipStream_t s);
 // Expands 4-bit expert blobs into 16-bit blobs of the bf16 layout whose elements are the fp16 numbers
 // (q - 8) * s, the same values the 4-bit kernels form on the fly: large groups then run through the
 // tiled matrix-core kernels, which read every weight many times.
@@ -209,8 +210,8 @@ inline int ffn_down_shared_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) 
 }
 hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *xp,
                                      void *act, int d, hipStream_t s);
-hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, int ksg, const void *act,
-                                  float *y, long long y_plane, int d, hipStream_t s);
+hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act, float *y,
+                                  long long y_plane, int d, hipStream_t s);
 inline int ffn_down_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) {
     return (d / 32 / kDownColBlocks) * ((n_tiles + tiles_per_pass - 1) / tiles_per_pass) * ksg;
 }

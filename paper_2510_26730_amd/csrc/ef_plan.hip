@@ -176,7 +176,7 @@ int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four) {
 int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, const int32_t *counts_host,
                  const std::vector<int> &offs_host, const std::vector<int> &tile_start,
                  const std::vector<long long> &act_off, int shared_tile_start, long long shared_act_off, int T,
-                 int ksg_stream, int ksg_tiled, int split_expert, int split_ksg, ef::PlaneTable &planes, long long y_plane,
+                 int ksg_stream, int ksg_shared, int ksg_tiled, int split_expert, int split_ksg, ef::PlaneTable &planes, long long y_plane,
                  bool use_tiled, bool expand, hipStream_t s) {
     // split_expert: the tiled group of the layer (expert id, -1 = shared FFN, kNoSplit = none) whose second half takes
     // split_ksg K slices instead of ksg_tiled; it goes last among the tiled groups of its launch.  expand: the tiled groups
@@ -231,8 +231,9 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         const bool split = tiled && split_expert != kNoSplit && pg.expert == split_expert;
         if (split) split_grp = nb;
         (pg.expert < 0 ? planes.shared : planes.routed[pg.expert]) =
-            (uint8_t)(split ? split_ksg : tiled ? ksg_tiled : ksg_stream);
+            (uint8_t)(split ? split_ksg : tiled ? ksg_tiled : pg.expert < 0 ? ksg_shared : ksg_stream);
         g.tile_start[i] = ts; g.n_tiles[i] = nt; g.row_offset[i] = ro;
+        g.ksg[i] = pg.expert < 0 ? planes.shared : planes.routed[pg.expert];
         g.count[i] = cnt; g.F[i] = F; g.act_off[i] = ao; g.blob[i] = blob;
         if (!tiled) max_tiles = std::max(max_tiles, nt);
         ++i;
@@ -346,7 +347,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         }
         {
             KernelTimer kt(c, ts, EF_K_FFN_DOWN_TILED, b_dn, f_dn);
-            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_down_q4(bdn, wg_dn, 4, ksg_tiled, c->act, c->y, y_plane, d, ts));
+            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_down_q4(bdn, wg_dn, 4, c->act, c->y, y_plane, d, ts));
             else EF_HIP(c, ef::launch_ffn_down_tiled(bdn, wg_dn, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, ts));
         }
         if (side.forked) EF_HIP(c, side.record());
@@ -374,13 +375,13 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         dn.wg_start[i] = wg_dn;
         if (shared) {
             wg_gu += ef::ffn_gate_up_shared_wgs(gu.F[i], gu.n_tiles[i], tpp);
-            wg_dn += ef::ffn_down_shared_wgs(d, gu.n_tiles[i], tpp, ksg_stream);
+            wg_dn += ef::ffn_down_shared_wgs(d, gu.n_tiles[i], tpp, gu.ksg[i]);
             continue;
         }
         wg_gu += c->q4 ? ef::ffn_gate_up_q4_wgs(gu.F[i], gu.n_tiles[i], tpp)
                        : ef::ffn_gate_up_wgs(gu.F[i], gu.n_tiles[i], tpp, ks);
-        wg_dn += c->q4 ? ef::ffn_down_q4_wgs(d, gu.n_tiles[i], tpp, ksg_stream)
-                       : ef::ffn_down_wgs(d, gu.n_tiles[i], tpp, ksg_stream);
+        wg_dn += c->q4 ? ef::ffn_down_q4_wgs(d, gu.n_tiles[i], tpp, gu.ksg[i])
+                       : ef::ffn_down_wgs(d, gu.n_tiles[i], tpp, gu.ksg[i]);
     }
     gu.wg_start[n] = wg_gu;
     dn.wg_start[n] = wg_dn;
@@ -399,9 +400,9 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     }
     {
         KernelTimer kt(c, s, EF_K_FFN_DOWN, b_dn);
-        if (shared) EF_HIP(c, ef::launch_ffn_down_shared(dn, wg_dn, tpp, occ, ksg_stream, c->act, c->y, y_plane, d, s));
-        else if (c->q4) EF_HIP(c, ef::launch_ffn_down_q4(dn, wg_dn, tpp, ksg_stream, c->act, c->y, y_plane, d, s));
-        else EF_HIP(c, ef::launch_ffn_down(dn, wg_dn, tpp, ksg_stream, c->act, c->y, y_plane, d, s));
+        if (shared) EF_HIP(c, ef::launch_ffn_down_shared(dn, wg_dn, tpp, occ, c->act, c->y, y_plane, d, s));
+        else if (c->q4) EF_HIP(c, ef::launch_ffn_down_q4(dn, wg_dn, tpp, c->act, c->y, y_plane, d, s));
+        else EF_HIP(c, ef::launch_ffn_down(dn, wg_dn, tpp, c->act, c->y, y_plane, d, s));
     }
     EF_HIP(c, side.wait());
     return EF_OK;
@@ -481,7 +482,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     // tokens 1560 / 1459, 2000 tokens on 16 experts 873 / 778; Qwen-shaped 3000 tokens 1120 / 1026.
     bool q4_expand = false;
     long long passes_of_four_dn = 0;   // workgroups of a second half of the tiled groups in passes of four
-    long long tiled_dn_wgs = 0, tiled_rows = 0;
+    long long tiled_up_wgs = 0, tiled_dn_wgs = 0, tiled_rows = 0;
     int tiled_stages_min = 1 << 30;   // fewest K stages (32 columns each) among the tiled groups
     int tiled_stages_max = 0;         // ... and most
     if (T > 0 && (!c->q4 || c->q4_stage_slots > 0) && c->tune.tiled != 0) {
@@ -524,11 +525,12 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             // Qwen-shaped 260 tokens on 12 experts, 88 tiles, 290 / 348 us)
             use_tiled = false;
         }
+        tiled_up_wgs = wg_up;
         tiled_dn_wgs = wg_dn;
     }
     // K slices of the second half (one Y plane each, summed by the un-permute): the streamed launch and the tiled
     // launch of the layer choose separately, each for its own workgroup count
-    int ksg = 1, ksg_tiled = 1, split_expert = kNoSplit, split_ksg = 1;
+    int ksg = 1, ksg_shared = 1, ksg_tiled = 1, split_expert = kNoSplit, split_ksg = 1;
     if (T > 0) {
         long long base_wgs = 0;
         double streamed_w2_bytes = 0.0;   // second-half weights of the routed groups that stream (4-bit blobs)
@@ -549,21 +551,28 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
         if (has_shared && streams(c->cfg.d_ff_shared, T, false)) see(c->cfg.d_ff_shared, T);
         const int tpp = tiles_per_pass(c, tmax, wgs_of_four);
+        double stream_work = 0.0;     // workgroups times their k-blocks
+        double stream_bytes = 0.0;    // weights of the streamed groups, as often as their passes read them
+        auto add_base = [&](int F, int nt) {
+            const int wgs = c->q4 ? ef::ffn_down_q4_wgs(d, nt, tpp, 1)
+                                  : tpp == 4 ? ef::ffn_down_shared_wgs(d, nt, tpp, 1) : ef::ffn_down_wgs(d, nt, tpp, 1);
+            base_wgs += wgs;
+            stream_work += (double)wgs * (F / 16);
+            stream_bytes += (c->q4 ? 1.55 : 6.0) * d * F * ((nt + tpp - 1) / tpp);
+        };
         // workgroups of the streamed launch with one slice (groups that take the tiled kernels do not count)
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0) {
                 const int nt = (counts_host[e] + ef::kTile - 1) / ef::kTile;
                 if (use_tiled && takes_tiled(c, c->cfg.d_ff, nt, true)) continue;
                 streamed_w2_bytes += (0.5 + 2.0 / 128.0) * d * c->cfg.d_ff;
-                base_wgs += c->q4 ? ef::ffn_down_q4_wgs(d, nt, tpp, 1)
-                            : tpp == 4 ? ef::ffn_down_shared_wgs(d, nt, tpp, 1) : ef::ffn_down_wgs(d, nt, tpp, 1);
+                add_base(c->cfg.d_ff, nt);
             }
-        if (has_shared && !(use_tiled && takes_tiled(c, c->cfg.d_ff_shared, (T + ef::kTile - 1) / ef::kTile, false)))
-            base_wgs += c->q4 ? ef::ffn_down_q4_wgs(d, (T + ef::kTile - 1) / ef::kTile, tpp, 1)
-                        : tpp == 4 ? ef::ffn_down_shared_wgs(d, (T + ef::kTile - 1) / ef::kTile, tpp, 1)
-                                   : ef::ffn_down_wgs(d, (T + ef::kTile - 1) / ef::kTile, tpp, 1);
-        // the LDS-shared kernels (passes of four tiles) run two workgroups per compute unit
-        const int want = c->tune.down_want_wgs > 0 ? c->tune.down_want_wgs : (tpp == 4 && !c->q4) ? 512 : 256;
+        if (has_shared && streams(c->cfg.d_ff_shared, T, false)) add_base(c->cfg.d_ff_shared, (T + ef::kTile - 1) / ef::kTile);
+        // the LDS-shared kernels (passes of four tiles) run two workgroups per compute unit, beside a tiled launch one (there
+        // twice the workgroups only cost planes: DeepSeek-shaped 1056 tokens 772 -> 750 us for two layers, Mixtral-shaped 700
+        // tokens 1655 -> 1625)
+        const int want = c->tune.down_want_wgs > 0 ? c->tune.down_want_wgs : (tpp == 4 && !c->q4 && !use_tiled) ? 512 : 256;
         const int nkb_min = std::min(c->cfg.d_ff, has_shared ? c->cfg.d_ff_shared : c->cfg.d_ff) / 16;
         // a slice keeps >= 32 fragments per wave (bf16: four waves split it again), >= 6 quads (4-bit), or >= 8
         // stages of four fragments (LDS-shared kernels: a wave walks the whole slice)
@@ -608,18 +617,35 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 }
             } else if (tiled_dn_wgs < 256) {
                 const int stages_ref = c->tune.down_slices_by_longest_k ? tiled_stages_max : tiled_stages_min;
-                const double plane_pen = (double)tiled_rows * d * 8.0 / 5e12 / (stages_ref * 0.77e-6);
+                // Beside a streamed launch the tiled ones are hidden as long as both halves of them end before it does
+                // (5.5 TB/s of weights): then a slice more only costs planes (Mixtral-shaped 400 tokens 1405 -> 1338 us for two layers)
+                const double unit_s = stages_ref * 0.77e-6;
+                const double plane_s = (double)tiled_rows * d * 8.0 / 5e12, stream_s = stream_bytes / 5.5e12;
+                const double up_s = (double)((tiled_up_wgs + 255) / 256) * (d / 32) * 0.6e-6;
                 double best = 0.0;
                 for (int ks = 1; ks <= 8; ++ks) {
                     if (ks > 1 && (stages_ref / ks < 16 || y_plane * ks > c->y_floats)) break;
-                    const double t = (double)((tiled_dn_wgs * ks + 255) / 256) / ks + (ks - 1) * plane_pen;
+                    const double t = std::max(up_s + (double)((tiled_dn_wgs * ks + 255) / 256) / ks * unit_s, stream_s) +
+                                     (ks - 1) * plane_s;
                     if (ks == 1 || t < best - 1e-9) { best = t; ksg_tiled = ks; }
                 }
             }
             if (c->tune.down_split_slice_counts == 0) ksg = ksg_tiled;   // one slice count for both launches
         }
+        // A shared FFN that streams with the routed experts has a K of its own.  It gets more slices, down to about the routed
+        // ones' length, while one of its workgroups runs half as long again as the launch's work spread over two workgroups
+        // per compute unit (Qwen-shaped, K 5632 against 1408, two layers: 100 tokens on 12 experts 253 -> 207 us, 200 tokens
+        // 420 -> 393, one token 150 -> 124); where the other groups fill that time anyway, more planes only cost
+        // (DeepSeek-shaped 32 tokens on 16 experts 183.7 -> 185.8, 4-bit 1000 tokens 508 -> 518).
+        ksg_shared = ksg;
+        if (has_shared && c->tune.down_split_slice_counts != 0) {
+            const int ratio = (c->cfg.d_ff_shared + c->cfg.d_ff / 2) / c->cfg.d_ff;
+            while (ksg_shared < 8 && ksg_shared < ksg * ratio && y_plane * (ksg_shared + 1) <= c->y_floats &&
+                   (double)(c->cfg.d_ff_shared / 16) / ksg_shared > 1.5 * stream_work / 512.0)
+                ++ksg_shared;
+        }
         int forced = c->tune.down_k_slices;
-        if (forced >= 1 && forced <= 8 && y_plane * forced <= c->y_floats) ksg = ksg_tiled = forced;
+        if (forced >= 1 && forced <= 8 && y_plane * forced <= c->y_floats) ksg = ksg_shared = ksg_tiled = forced;
         // A tiled second half of more than one round of workgroups over the compute units ends in a round that is
         // partly empty (1056 workgroups: four rounds and an eighth; every compute unit holds one at a time).  The
         // layer's last tiled group (the one with the least work; the highest expert among equals) is cut into K
@@ -792,7 +818,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         if (with_shared && has_shared) g.push_back({-1, -1});
         if (!c->fake) {
             int r = launch_phase(c, layer, g, counts_host, offs_host, tile_start, act_off, shared_tile_start,
-                                 shared_act_off, T, ksg, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled, q4_expand, s);
+                                 shared_act_off, T, ksg, ksg_shared, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled, q4_expand, s);
             if (r) {   // part of the phase may be enqueued: its slots still get their read marker
                 (void)mark_read(v);
                 v.clear();   // released: the caller's error path has nothing left to unpin
