@@ -82,3 +82,11 @@ def test_streaming_gate_against_oracle(oracle_mod, name, cfg, T, H):
     # the two forms add the K range up in different orders: same ids wherever the oracle sees no near-tie was
     # checked above; weights agree to rounding
     assert np.max(np.abs(results[0]["w"] - results[1]["w"])) < 1e-5
+
+
+@pytest.mark.parametrize("E,H", [(2, 0), (8, 0), (9, 0), (5, 1), (8, 1), (17, 0), (11, 2)],
+                         ids=lambda v: str(v))
+def test_gate_row_blocks_at_their_column_limits(oracle_mod, E, H):
+    """Up to 8, 16 and 32 logit columns a stage holds 4, 8 and 16 blocks of gate rows: both sides of each limit."""
+    cfg = shape("mixtral_prefill", name=f"gs_cols_{E}_{H}", d=768, E=E, k=min(2, E), F=32)
+    test_streaming_gate_against_oracle(oracle_mod, cfg.name, cfg, 6177, H)
