@@ -277,7 +277,9 @@ extern "C" int ef_create(const ef_config *cfg, ef_ctx **out) {
     };
     hipError_t e;
     if ((e = hipMalloc(&c->pool, (size_t)g.slots_total * c->expert_bytes)) != hipSuccess) return bail(e, "slot pool");
-    if ((e = hipMalloc(&c->blockcounts, (size_t)ntile_tok * E * 4)) != hipSuccess) return bail(e, "blockcounts");
+    // per-tile expert counts of the routed layer and of every layer a look-ahead can name
+    const int n_counts = 1 + std::min(EF_MAX_HORIZON, g.n_layers - 1);
+    if ((e = hipMalloc(&c->blockcounts, (size_t)n_counts * ntile_tok * E * 4)) != hipSuccess) return bail(e, "blockcounts");
     if ((e = hipMalloc(&c->blockbase, (size_t)ntile_tok * E * 4)) != hipSuccess) return bail(e, "blockbase");
     if ((e = hipMalloc(&c->xp, xp_bytes)) != hipSuccess) return bail(e, "packed-token scratch");
     // partial logits of K-split gate launches: 8 MiB (64 workgroups x 32 rows x 128 columns x 8 splits), or four
@@ -664,10 +666,11 @@ extern "C" int ef_layer_step_fetch(ef_ctx *c, int32_t *topk_ids, float *topk_w, 
 
 void efi::tuning_defaults(ef_tuning *t) {
     t->tiled = 1;
-    // Routed groups take the tiled kernels from this many token tiles on (the kernels accept 8).  A group of 8 or
-    // 9 tiles is one 256-token panel (plus an almost empty one): its weight panels are read by a single workgroup
-    // each, cold from HBM with three stages in flight, and such workgroups outlast those of a group with several
-    // token panels in the same launch; the streaming kernels serve them better.
+    // Routed groups take the tiled kernels from this many token tiles on, or from one tile less where a streamed pass
+    // of four would start with a single live tile (9 tiles; takes_tiled in the planner).  Below that a group is one
+    // 256-token panel: its weight panels are read by a single workgroup each, cold from HBM with three stages in
+    // flight, and such workgroups outlast those of a group with several token panels in the same launch; the
+    // streaming kernels serve them better.
     t->tiled_min_tiles = 10;
     t->tiled_min_up_wgs = 1;
     t->tiled_min_down_wgs = 1;

@@ -33,6 +33,8 @@ struct GateArgs {
     float routed_scale;
     int32_t *hist[kMaxGates];      // per gate: [E] accumulated with integer atomics, or null
     int32_t *blockcounts;          // [ntiles,E] per-tile counts of gate 0, or null
+    int32_t *hist_tiles;           // null, or [G-1][ntiles][E]: gates 1.. leave per-tile counts here and `hist` alone
+                                   // (one-step launches with gate 0 = the current layer; group_scan_kernel adds them up)
     int gpw;                       // gates per workgroup (gpw * E <= 128 logit columns)
     int ksplit;                    // workgroups that share the K range of one (tile, gate group); >= 1
     int two_step;                  // 1: gate_kernel leaves partial logits, gate_finish_kernel does the per-token part
@@ -93,9 +95,10 @@ constexpr size_t kFusedMaxLds = 48 * 1024;   // dynamic LDS of the fused kernel 
 size_t gate_fused_lds_bytes(int T, int G, int E, int gpw);
 hipError_t launch_gate_fused(const GateArgs &a, int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv_perm,
                              const GroupExport &ex, hipStream_t s);
+// n_hist > 0 (more than kGroupLdsTiles token tiles only): hist[j][E] = sums of the per-tile counts hist_tiles[j], j < n_hist
 hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, int k, int E, int32_t *blockbase,
                         int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv_perm,
-                        const GroupExport &ex, hipStream_t s);
+                        const int32_t *hist_tiles, int n_hist, int32_t *hist, const GroupExport &ex, hipStream_t s);
 // f16: write fp16 instead of bf16 fragments (contexts with 4-bit experts)
 hipError_t launch_pack_x(const PackTable &pt, int total_tiles, const uint16_t *h, int d, int k,
                          const int32_t *perm, void *xp, bool f16, hipStream_t s);

@@ -19,11 +19,10 @@ int run_gates(ef_ctx *c, int layer, const void *hidden, int T, float beta, bool 
               const ef::GroupExport &ex, const EfRouteScratch &rs, hipStream_t s) {
     const int E = c->cfg.n_experts, k = c->cfg.top_k, d = c->cfg.d_model;
     const int ntiles = (T + ef::kTile - 1) / ef::kTile;
-    // the library's own histogram buffer is left zeroed by the hand-over step of the previous layer
-    if (He > 0 && !ex.host_meta) EF_HIP(c, ef::launch_fill_i32(pred_hist, He * E, 0, s));
     const int per_launch = ef::kMaxGates;
     const int total_gates = (do_route ? 1 : 0) + He;
     bool grouped = false;
+    int32_t *hist_tiles = nullptr;
     for (int g0 = 0; g0 < total_gates; g0 += per_launch) {
         ef::GateArgs a{};
         a.h = static_cast<const uint16_t *>(hidden);
@@ -79,6 +78,15 @@ int run_gates(ef_ctx *c, int layer, const void *hidden, int T, float beta, bool 
             if (ts > 1 && need <= rs.gate_part_floats && c->tune.gate_token_split != 0) a.tsplit = ts;
         }
         a.two_step = (a.ksplit > 1 || a.tsplit > 1) ? 1 : 0;
+        // histograms of the look-ahead: the library's own buffer is left zeroed by the hand-over step of the previous
+        // layer; a caller's is written by the scan of the per-tile counts where the call ends in one, and cleared here
+        // for the gates' atomics otherwise (a launch of 4 us)
+        if (He > 0 && !ex.host_meta && g0 == 0) {
+            if (do_route && total_gates <= per_launch && !a.two_step && ntiles > ef::kGroupLdsTiles)
+                hist_tiles = rs.blockcounts + (size_t)ntiles * E;
+            else EF_HIP(c, ef::launch_fill_i32(pred_hist, He * E, 0, s));
+        }
+        a.hist_tiles = hist_tiles;
         const bool has_route = do_route && g0 == 0;
         // decode-sized batches with a K-split gate and few experts: its second step and the grouping run as
         // one workgroup (with more than 16 experts a token takes a whole wave round of the epilogue, and the
@@ -102,7 +110,7 @@ int run_gates(ef_ctx *c, int layer, const void *hidden, int T, float beta, bool 
     if (do_route && !grouped) {
         KernelTimer kt(c, s, EF_K_GROUP, (double)ntiles * E * 8 + (double)(2 * E + 1) * 4 + (double)T * k * 12);
         EF_HIP(c, ef::launch_group(rs.blockcounts, topk_ids, T, k, E, rs.blockbase, counts, offsets, perm,
-                                   inv_perm, ex, s));
+                                   inv_perm, hist_tiles, hist_tiles ? He : 0, pred_hist, ex, s));
     }
     return EF_OK;
 }

@@ -332,7 +332,8 @@ __device__ __forceinline__ void gate_epilogue(const GateArgs &a, float (*logits)
     for (int x = tid; x < N; x += NT) {
         const int gi = g0 + x / a.E, ee = x % a.E;
         int32_t *hp = pick(a.hist, gi);
-        if (hp && cnt[x] > 0) atomicAdd(&hp[ee], cnt[x]);
+        if (hp && a.hist_tiles) a.hist_tiles[((size_t)(gi - 1) * ((a.T + kTile - 1) / kTile) + tile) * a.E + ee] = cnt[x];
+        else if (hp && cnt[x] > 0) atomicAdd(&hp[ee], cnt[x]);
         if (a.blockcounts && gi == 0) {
             if (!shared_tile) a.blockcounts[(size_t)tile * a.E + ee] = cnt[x];
             else if (cnt[x] > 0) atomicAdd(&a.blockcounts[(size_t)tile * a.E + ee], cnt[x]);
@@ -732,12 +733,17 @@ __device__ __forceinline__ void export_meta(const GroupExport &ex, const int *to
 
 // Larger batches than group_lds_kernel takes: one workgroup per expert forms the exclusive prefix of
 // that expert's per-tile counts over the tiles (16 waves, a contiguous range of tiles each: totals first,
-// then the scan with the bases of the waves before), and leaves the expert's total in counts[e].
+// then the scan with the bases of the waves before), and leaves the expert's total in counts[e].  Further blocks of E
+// workgroups add up the per-tile counts of the look-ahead gates: their histograms need no fill before the gate launch
+// and no atomics in it (32768 tokens, one layer predicted, the call: 61.3 -> 57.6 us).
 __global__ __launch_bounds__(1024) void group_scan_kernel(const int32_t *__restrict__ bc, int ntiles, int E,
                                                           int32_t *__restrict__ blockbase,
-                                                          int32_t *__restrict__ counts) {
+                                                          int32_t *__restrict__ counts,
+                                                          const int32_t *__restrict__ hist_tiles,
+                                                          int32_t *__restrict__ hist) {
     __shared__ int wtot[16];
-    const int e = blockIdx.x;
+    const int e = blockIdx.x, g = blockIdx.y;
+    if (g > 0) bc = hist_tiles + (size_t)(g - 1) * ntiles * E;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int per = (((ntiles + 15) / 16 + 63) / 64) * 64;     // tiles per wave, whole chunks of 64
     const int lo = min(ntiles, wave * per), hi = min(ntiles, lo + per);
@@ -750,6 +756,10 @@ __global__ __launch_bounds__(1024) void group_scan_kernel(const int32_t *__restr
     for (int w = 0; w < 16; ++w) {
         if (w < wave) carry += wtot[w];
         all += wtot[w];
+    }
+    if (g > 0) {
+        if (threadIdx.x == 0) hist[(g - 1) * E + e] = all;
+        return;
     }
     for (int c0 = lo; c0 < hi; c0 += 64) {
         const int b = c0 + lane;
@@ -1104,9 +1114,10 @@ hipError_t launch_gate_fused(const GateArgs &a, int32_t *counts, int32_t *offset
 
 hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, int k, int E, int32_t *blockbase,
                         int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv_perm,
-                        const GroupExport &ex, hipStream_t s) {
+                        const int32_t *hist_tiles, int n_hist, int32_t *hist, const GroupExport &ex, hipStream_t s) {
     if (T <= 0) return hipSuccess;
     const int ntiles = (T + kTile - 1) / kTile;
+    if (n_hist > 0 && (ntiles <= kGroupLdsTiles || n_hist >= kMaxGates || !hist_tiles || !hist)) return hipErrorInvalidValue;
     if (ntiles <= kGroupSmallTiles) {
         hipLaunchKernelGGL(group_small_kernel, dim3(1), dim3(64 * kGroupSmallTiles), 0, s, blockcounts, ntiles, ids, T, k, E,
                            counts, offsets, perm, inv_perm, ex);
@@ -1117,7 +1128,8 @@ hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, i
                            blockcounts, ntiles, ids, T, k, E, counts, offsets, perm, inv_perm, ex);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(group_scan_kernel, dim3(E), dim3(1024), 0, s, blockcounts, ntiles, E, blockbase, counts);
+    hipLaunchKernelGGL(group_scan_kernel, dim3(E, 1 + std::max(0, n_hist)), dim3(1024), 0, s, blockcounts, ntiles, E,
+                       blockbase, counts, hist_tiles, hist);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(group_scatter_kernel, dim3((ntiles + kScatterWaves - 1) / kScatterWaves), dim3(64 * kScatterWaves),

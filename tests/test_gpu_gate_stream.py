@@ -90,3 +90,11 @@ def test_gate_row_blocks_at_their_column_limits(oracle_mod, E, H):
     """Up to 8, 16 and 32 logit columns a stage holds 4, 8 and 16 blocks of gate rows: both sides of each limit."""
     cfg = shape("mixtral_prefill", name=f"gs_cols_{E}_{H}", d=768, E=E, k=min(2, E), F=32)
     test_streaming_gate_against_oracle(oracle_mod, cfg.name, cfg, 6177, H)
+
+
+@pytest.mark.parametrize("T,H", [(2049, 2), (2080, 7), (6145, 1), (32800, 2)], ids=lambda v: str(v))
+def test_histograms_from_per_tile_counts_at_their_limits(oracle_mod, T, H):
+    """From 65 token tiles on the grouping adds the look-ahead histograms up from per-tile counts: first such batch,
+    an odd last tile, the widest look-ahead, more than one chunk of 64 tiles per wave (over 1024 tiles)."""
+    cfg = shape("mixtral_prefill", name=f"gs_hist_{T}_{H}", d=256, F=32)
+    test_streaming_gate_against_oracle(oracle_mod, cfg.name, cfg, T, H)
