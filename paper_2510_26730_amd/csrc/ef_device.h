@@ -63,4 +63,11 @@ __device__ __forceinline__ void zero16(floatx16 &a) {
     for (int v = 0; v < 16; ++v) a[v] = 0.f;
 }
 
+// Orders a wave's LDS accesses before its later ones where lanes meet each other's data.  The hardware runs a wave's LDS
+// operations in order; the compiler, which sees one lane's addresses, has to be told.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace ef

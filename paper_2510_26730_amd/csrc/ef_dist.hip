@@ -237,12 +237,14 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
         _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
             _Pragma("unroll") for (int u = 0; u < U; ++u) f_[a][u] = src[a][u][ch_];                      \
     }
-    // one stage: into the wave's LDS buffer (the wave's LDS operations run in order: no wait before it is reused), the
-    // registers refilled R stages ahead, then operand fragments from LDS
+    // one stage: into the wave's LDS buffer, the registers refilled R stages ahead, then operand fragments from LDS.  A
+    // lane reads what other lanes of its wave wrote and the next stage overwrites it: both ways the order is stated to the
+    // compiler (no wait and no instruction: the hardware keeps a wave's LDS operations in order)
 #define EF_DISTB_STAGE(f_, kb)                                                                            \
     {                                                                                                     \
         _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
             _Pragma("unroll") for (int u = 0; u < U; ++u) buf[a * TILE + 64 * u + put] = f_[a][u];        \
+        wave_lds_sync();                                                                                  \
         EF_DISTB_LOAD(f_, (kb) + R * U)                                                                   \
         _Pragma("unroll") for (int u = 0; u < U; ++u)                                                     \
             if ((kb) + u < n) {                                                                           \
@@ -253,6 +255,7 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
                     _Pragma("unroll") for (int b = 0; b < B; ++b) acc[a][b] = mfma32v(x[a], x[B + b], acc[a][b]); \
                 _Pragma("unroll") for (int a = 0; a < 2 * B; ++a) sq[a] = mfma32v(x[a], x[a], sq[a]);     \
             }                                                                                             \
+        wave_lds_sync();                                                                                  \
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) EF_DISTB_LOAD(f[r], r * U)

@@ -36,12 +36,6 @@ hipError_t launch_fill_i32(int32_t *p, int n, int32_t v, hipStream_t s) {
 constexpr int kGateWaves = 8;
 constexpr int kGateMaxSplit = 16;   // K splits of one (tile, gate group) across workgroups
 
-// orders the LDS writes of a wave before its later LDS reads (other lanes' data of the same wave)
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // arr[idx] of a by-value kernel-argument array without forcing the struct into scratch memory
 template <class T>
 __device__ __forceinline__ T pick(const T (&arr)[kMaxGates], int idx) {
