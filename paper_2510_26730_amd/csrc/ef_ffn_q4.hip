@@ -259,8 +259,8 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
     }
 }
 
-hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *xp, void *act,
-                                 int d, hipStream_t s) {
+hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, bool k_halves, const void *xp,
+                                 void *act, int d, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
     if (d % 128 != 0) return hipErrorInvalidValue;
     for (int i = 0; i < gt.n_groups; ++i)
@@ -271,7 +271,7 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     const uint4 *x = reinterpret_cast<const uint4 *>(xp);
     uint4 *a = reinterpret_cast<uint4 *>(act);
     // two K halves per workgroup when each half keeps a few stages (d / 64 stages in all, an even number)
-    const bool halves = (d >> 6) % 2 == 0 && (d >> 6) >= 8;
+    const bool halves = k_halves && (d >> 6) % 2 == 0 && (d >> 6) >= 8;
     // more workgroups than compute units: two of them per unit instead (whole K range each, the short register ring);
     // their waves stall at different times, where the halves of one workgroup meet at the same barriers
     // (seven Mixtral-shaped experts: 127 against 135 us, Qwen-shaped batch 52 against 60 us)

@@ -127,8 +127,9 @@ inline int ffn_gate_up_q4_wgs(int F, int n_tiles, int tiles_per_pass) {
 inline int ffn_down_q4_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) {
     return ((d / 32 + 7) / 8) * ((n_tiles + tiles_per_pass - 1) / tiles_per_pass) * ksg;
 }
-hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *xp, void *act,
-                                 int d, hipStream_t s);
+// k_halves: a launch of few workgroups may split K over two halves of a workgroup (a different order of the sums)
+hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, bool k_halves, const void *xp,
+                                 void *act, int d, hipStream_t s);
 hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act, float *y,
                               long long y_plane, int d, hipStream_t s);
 // Expands 4-bit expert blobs into 16-bit blobs of the bf16 layout whose elements are the fp16 numbers

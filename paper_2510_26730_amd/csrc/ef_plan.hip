@@ -184,8 +184,9 @@ int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four) {
 int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, const int32_t *counts_host,
                  const std::vector<int> &offs_host, const std::vector<int> &tile_start,
                  const std::vector<long long> &act_off, int shared_tile_start, long long shared_act_off, int T,
-                 int ksg_stream, int ksg_shared, int ksg_tiled, int split_expert, int split_ksg, ef::PlaneTable &planes, long long y_plane,
-                 bool use_tiled, bool expand, hipStream_t s) {
+                 int tpp_layer, int ksg_stream, int ksg_shared, int ksg_tiled, int split_expert, int split_ksg,
+                 ef::PlaneTable &planes, long long y_plane, bool use_tiled, bool expand, hipStream_t s) {
+    // tpp_layer: token tiles per pass that the layer's streamed groups would take in one launch.
     // split_expert: the tiled group of the layer (expert id, -1 = shared FFN, kNoSplit = none) whose second half takes
     // split_ksg K slices instead of ksg_tiled; it goes last among the tiled groups of its launch.  expand: the tiled groups
     // of a 4-bit context are expanded to 16 bits first (else they run in passes of four tiles on the 4-bit blobs)
@@ -196,6 +197,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     ef::GroupTable gu{}, big{};
     ef::DequantTable dq{};
     int n = 0, nb = 0, max_tiles = 1;
+    bool large = false;   // 4-bit: a streamed group has a tiled one's size
     const bool allow_tiled = use_tiled;
     // Workgroups start in index order; groups with the most work go first so that the launch's last round holds
     // the short ones (the groups are independent: the order changes no result)
@@ -243,7 +245,10 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         g.tile_start[i] = ts; g.n_tiles[i] = nt; g.row_offset[i] = ro;
         g.ksg[i] = pg.expert < 0 ? planes.shared : planes.routed[pg.expert];
         g.count[i] = cnt; g.F[i] = F; g.act_off[i] = ao; g.blob[i] = blob;
-        if (!tiled) max_tiles = std::max(max_tiles, nt);
+        if (!tiled) {
+            max_tiles = std::max(max_tiles, nt);
+            large = large || (c->q4 && c->tune.tiled != 0 && takes_tiled(c, F, nt, pg.expert >= 0));
+        }
         ++i;
     }
     gu.n_groups = n;
@@ -350,7 +355,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
                 dq.n = nb;
                 EF_HIP(c, ef::launch_dequant_q4(dq, d, ts));
             }
-            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_gate_up_q4(big, wg_up, 4, c->xp, c->act, d, ts));
+            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_gate_up_q4(big, wg_up, 4, false, c->xp, c->act, d, ts));
             else EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, wg_up, c->xp, c->act, d, c->q4, ts));
         }
         {
@@ -364,7 +369,10 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     ef::GroupTable dn = gu;
     long long wgs_of_four = 0;
     for (int i = 0; i < n; ++i) wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
-    const int tpp = tiles_per_pass(c, max_tiles, wgs_of_four);
+    // 4-bit groups of a tiled one's size stream because of what the whole layer holds; a phase that has one keeps to the
+    // layer's pass width (for which the K slices of the second half were chosen) and does not cut the first half's K range
+    // in two, whatever else is resident: such a group's sums do not depend on the phase it runs in
+    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four);
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;
@@ -403,7 +411,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     {
         KernelTimer kt(c, s, EF_K_FFN_UP, b_up);
         if (shared) EF_HIP(c, ef::launch_ffn_gate_up_shared(gu, wg_gu, tpp, occ, c->xp, c->act, d, s));
-        else if (c->q4) EF_HIP(c, ef::launch_ffn_gate_up_q4(gu, wg_gu, tpp, c->xp, c->act, d, s));
+        else if (c->q4) EF_HIP(c, ef::launch_ffn_gate_up_q4(gu, wg_gu, tpp, !large, c->xp, c->act, d, s));
         else EF_HIP(c, ef::launch_ffn_gate_up(gu, wg_gu, tpp, ks, c->xp, c->act, d, s));
     }
     {
@@ -539,6 +547,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     // K slices of the second half (one Y plane each, summed by the un-permute): the streamed launch and the tiled
     // launch of the layer choose separately, each for its own workgroup count
     int ksg = 1, ksg_shared = 1, ksg_tiled = 1, split_expert = kNoSplit, split_ksg = 1;
+    int tpp = 1;
     if (T > 0) {
         long long base_wgs = 0;
         double streamed_w2_bytes = 0.0;   // second-half weights of the routed groups that stream (4-bit blobs)
@@ -558,7 +567,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
         if (has_shared && streams(c->cfg.d_ff_shared, T, false)) see(c->cfg.d_ff_shared, T);
-        const int tpp = tiles_per_pass(c, tmax, wgs_of_four);
+        tpp = tiles_per_pass(c, tmax, wgs_of_four);
         double stream_work = 0.0;     // workgroups times their k-blocks
         double stream_bytes = 0.0;    // weights of the streamed groups, as often as their passes read them
         auto add_base = [&](int F, int nt) {
@@ -826,7 +835,8 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         if (with_shared && has_shared) g.push_back({-1, -1});
         if (!c->fake) {
             int r = launch_phase(c, layer, g, counts_host, offs_host, tile_start, act_off, shared_tile_start,
-                                 shared_act_off, T, ksg, ksg_shared, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled, q4_expand, s);
+                                 shared_act_off, T, tpp, ksg, ksg_shared, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled,
+                                 q4_expand, s);
             if (r) {   // part of the phase may be enqueued: its slots still get their read marker
                 (void)mark_read(v);
                 v.clear();   // released: the caller's error path has nothing left to unpin

@@ -26,13 +26,14 @@ SIZES = {
 }
 
 
-def run_groups(oracle_mod, cfg, sizes, q4, tune):
+def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None):
+    """Output of the layer; compared with the oracle if one is given.  slots: fewer cache slots than experts, all empty."""
     T, E = sum(sizes), cfg.E
-    st = LayerStack(cfg, 1, slots_total=E, max_tokens=T, q4=q4)
+    st = LayerStack(cfg, 1, slots_total=slots or E, max_tokens=T, q4=q4)
     try:
         if tune:
             ef.ef_set_tuning(st.ctx, **tune)
-        for e in range(E):
+        for e in range(E if slots is None else 0):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
         rng = np.random.default_rng(sum(sizes) + 1)
         ids = np.repeat(np.arange(E, dtype=np.int32), sizes)
@@ -49,6 +50,8 @@ def run_groups(oracle_mod, cfg, sizes, q4, tune):
         hd, d_ids, d_w, d_off, d_perm, d_inv = dev_u16(h), dev(ids), dev(w), dev(offsets), dev(perm), dev(inv)
         ef.ef_moe_ffn(st.ctx, 0, hd, T, d_ids, d_w, counts, d_off, d_perm, d_inv, out, torch.cuda.current_stream())
         torch.cuda.synchronize()
+        if oracle_mod is None:
+            return out.cpu().numpy()
         ffn = oracle_mod.expert_ffn_q4 if q4 else oracle_mod.expert_ffn
         y = ffn(h, st.experts[0], ids.reshape(T, 1), perm)
         shared = None
@@ -75,3 +78,18 @@ def test_group_sizes(oracle_mod, sizes, d, F, F_shared, q4):
 def test_group_sizes_of_the_shared_forms(oracle_mod, tune):
     cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups", d=512, F=640, k=1)
     run_groups(oracle_mod, cfg, SIZES["second passes"], False, tune)
+
+
+@pytest.mark.parametrize("sizes,F", [([257, 300, 288, 320, 352, 290, 383, 289], 4864),   # 912 workgroups in passes of four
+                                     ([140, 320, 160, 150, 3, 97, 33, 129], 4736)])      # 518, one group of ten tiles
+def test_q4_large_groups_do_not_depend_on_phases(sizes, F):
+    """4-bit groups of nine tiles and more that stream because of the whole layer's size: the same bits with every expert
+    resident (one phase) and through a single cache slot (one expert per phase)."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_phases", d=512, F=F, F_shared=0, k=1)
+    a = run_groups(None, cfg, sizes, True, {})
+    b = run_groups(None, cfg, sizes, True, {}, slots=1)
+    rng = np.random.default_rng(sum(sizes) + 1)
+    ids = np.repeat(np.arange(cfg.E), sizes)
+    rng.shuffle(ids)
+    large = np.asarray(sizes)[ids] > 8 * 32
+    assert np.all(np.isfinite(a)) and np.array_equal(a[large], b[large])
