@@ -518,6 +518,9 @@ typedef struct ef_tuning {
     int32_t dist_form;               /* ef_token_dist: 0 = by batch size (up to 256 tokens: differences summed directly,
                                         no Gram matrix; up to 3584: Gram blocks of 32 x 32 or 64 x 64), 1 = Gram blocks of 128 x 256 fed from registers, 2 = Gram blocks
                                         of 256 x 256 staged through LDS; 1 and 2 give the same bits (0) */
+    int32_t q4_expand_min_units;     /* >= 0: 4-bit groups of a tiled one's size are expanded to 16 bits and take the tiled
+                                        kernels when those of 32 token tiles and more make this many of their workgroups
+                                        (2048); 0 = always */
 } ef_tuning;
 int ef_get_tuning(ef_ctx *ctx, ef_tuning *out);
 int ef_set_tuning(ef_ctx *ctx, const ef_tuning *t);

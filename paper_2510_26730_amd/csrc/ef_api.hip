@@ -696,6 +696,7 @@ void efi::tuning_defaults(ef_tuning *t) {
     t->early_pack = 1;
     t->copy_chunk_mib = 32;
     t->copy_depth = 2;
+    t->q4_expand_min_units = 2048;
 }
 
 extern "C" int ef_get_tuning(ef_ctx *c, ef_tuning *out) {
@@ -735,6 +736,7 @@ extern "C" int ef_set_tuning(ef_ctx *c, const ef_tuning *t) {
     else if (!flag(t->early_pack)) bad = "early_pack";
     else if (t->copy_chunk_mib < 1 || t->copy_chunk_mib > 1024) bad = "copy_chunk_mib";
     else if (t->copy_depth < 1 || t->copy_depth > 8) bad = "copy_depth";
+    else if (t->q4_expand_min_units < 0) bad = "q4_expand_min_units";
     if (bad) return fail(c, EF_EINVAL, "ef_set_tuning: %s out of range", bad);
     c->tune = *t;
     {

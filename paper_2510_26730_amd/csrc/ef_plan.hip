@@ -517,7 +517,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e) add(c->cfg.d_ff, counts_host[e], true);
         if (has_shared) add(c->cfg.d_ff_shared, T, false);
         use_tiled = wg_up >= c->tune.tiled_min_up_wgs && wg_dn >= c->tune.tiled_min_down_wgs;
-        q4_expand = c->q4 && wg_up_large >= 2048;
+        q4_expand = c->q4 && wg_up_large >= c->tune.q4_expand_min_units;
         // Groups that would not use what the tiled kernels offer run with the streamed ones: one launch per half instead of
         // two on two streams, whose fork and join cost about 10 us.  In passes of four token tiles:
         long long four_all = 0, four_tiled = 0;

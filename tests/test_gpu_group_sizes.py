@@ -74,6 +74,15 @@ def test_group_sizes(oracle_mod, sizes, d, F, F_shared, q4):
     run_groups(oracle_mod, cfg, SIZES[sizes], q4, {})
 
 
+@pytest.mark.parametrize("F_shared", [256, 1024])
+@pytest.mark.parametrize("sizes", ["tiled beside streamed", "three live tiles last"], ids=lambda s: s.replace(" ", "_"))
+def test_expanded_groups_of_two_widths(oracle_mod, sizes, F_shared):
+    """4-bit routed groups and the shared FFN expanded side by side (hidden sizes on both sides of each other in one staging
+    area, ragged token panels), beside streamed groups."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups", d=512, F=640, F_shared=F_shared, k=1)
+    run_groups(oracle_mod, cfg, SIZES[sizes], True, dict(q4_expand_min_units=0))
+
+
 @pytest.mark.parametrize("tune", [dict(lds_shared_occupancy=2), dict(lds_shared_occupancy=1, down_k_slices=3)], ids=str)
 def test_group_sizes_of_the_shared_forms(oracle_mod, tune):
     cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups", d=512, F=640, k=1)

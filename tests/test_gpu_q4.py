@@ -108,21 +108,25 @@ def test_q4_full_size_mixtral_decode(oracle_mod):
         st.close()
 
 
+@pytest.mark.parametrize("expand", [True, False])
 @pytest.mark.parametrize("kw,T,tiled", [
     (dict(d=256, F=128), 1500, True),            # every expert above 8 tiles, smallest shape the tiled kernels take
     (dict(d=512, F=384), 900, True),             # popularity skew: some experts tiled, the others streamed in passes
     (dict(d=512, F=384), 900, False),            # the same batch with the tiled kernels switched off
     (dict(d=384, F=256), 1500, True),            # d not a multiple of 256: stays on the streaming kernels
 ])
-def test_q4_large_groups_through_tiled_kernels(oracle_mod, kw, T, tiled):
-    """Groups of 8 token tiles or more: the 4-bit blobs are expanded to fp16 blobs and go through the
-    matrix-core tiled kernels; smaller groups of the same layer keep the streaming kernels."""
+def test_q4_large_groups_through_tiled_kernels(oracle_mod, kw, T, tiled, expand):
+    """Groups of 8 token tiles or more, with the threshold of the expansion at its lowest: the 4-bit blobs are expanded to
+    fp16 blobs and go through the matrix-core tiled kernels; smaller groups of the same layer keep the streaming kernels.
+    With the default threshold such small layers run in passes of four tiles on the 4-bit blobs."""
     cfg = q4_shape("tiny", name="tiny_q4_prefill", **kw)
     say(f"q4 large groups d={cfg.d} F={cfg.F} E={cfg.E} k={cfg.k} T={T} tiled={tiled}")
     st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=T, q4=True, flags=ef.EF_FLAG_PROFILE)
     try:
         if not tiled:
             ef.ef_set_tuning(st.ctx, tiled=0)
+        if expand:
+            ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
@@ -155,14 +159,18 @@ def test_q4_full_size_mixtral_prefill(oracle_mod):
         st.close()
 
 
+@pytest.mark.parametrize("expand", [True, False])
 @pytest.mark.parametrize("T,tiled_shared", [(130, False), (1, False), (300, True), (515, True)])
-def test_q4_shared_ffn(oracle_mod, T, tiled_shared):
+def test_q4_shared_ffn(oracle_mod, T, tiled_shared, expand):
     """DeepSeek-like layer whose routed experts and dense shared FFN are all 4-bit: the shared group streams
-    with the routed ones while it has fewer than 8 token tiles and takes the expansion + tiled kernels above."""
+    with the routed ones while it has fewer than 8 token tiles; above it takes the expansion + tiled kernels (threshold at
+    its lowest) or passes of four tiles in launches of its own (default threshold)."""
     cfg = dataclasses.replace(synth.CONFIGS["deepseek_v2_lite"], name="deepseek_q4_shared", d=256, F=128, F_shared=384)
     say(f"q4 shared FFN d={cfg.d} F={cfg.F} Fs={cfg.F_shared} E={cfg.E} k={cfg.k} T={T}")
     st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=max(T, 64), q4=True, flags=ef.EF_FLAG_PROFILE)
     try:
+        if expand:
+            ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
@@ -173,14 +181,18 @@ def test_q4_shared_ffn(oracle_mod, T, tiled_shared):
         st.close()
 
 
-def test_q4_full_size_qwen_mixed_batch(oracle_mod):
-    """Qwen1.5-MoE-shaped layer, T = 640, 60 routed experts and the 5632-wide shared FFN all 4-bit
-    (`bench.py --workload qwen15_moe --int4`): shared FFN expanded and tiled, routed experts streamed; sampled tokens."""
+@pytest.mark.parametrize("expand", [True, False])
+def test_q4_full_size_qwen_mixed_batch(oracle_mod, expand):
+    """Qwen1.5-MoE-shaped layer, T = 640, 60 routed experts and the 5632-wide shared FFN all 4-bit: routed experts streamed,
+    shared FFN expanded and tiled (threshold at its lowest) or in passes of four tiles on its 4-bit blob (the default:
+    `bench.py --workload qwen_mixed --int4`); sampled tokens."""
     cfg = dataclasses.replace(synth.CONFIGS["qwen15_moe"], name="qwen15_moe_q4")
     T = 640
     say(f"q4 full size: Qwen-shaped layer, T={T}, shared FFN {cfg.F_shared}")
     st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=T, q4=True, flags=ef.EF_FLAG_PROFILE)
     try:
+        if expand:
+            ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
@@ -192,14 +204,18 @@ def test_q4_full_size_qwen_mixed_batch(oracle_mod):
         st.close()
 
 
-def test_q4_large_groups_in_phases(oracle_mod):
-    """More active experts (of 8+ token tiles each) than the three cache slots: the call works in phases that
-    reuse the slots and the fp16 staging copies; every phase expands its own experts before its tiled launches."""
+@pytest.mark.parametrize("expand", [True, False])
+def test_q4_large_groups_in_phases(oracle_mod, expand):
+    """More active experts (of 8+ token tiles each) than the three cache slots: the call works in phases that reuse the
+    slots and (threshold of the expansion at its lowest) the fp16 staging copies; every phase expands its own experts
+    before its tiled launches."""
     cfg = q4_shape("tiny", name="tiny_q4_phases", d=256, F=256)
     T = 1500
     say(f"q4 large groups in phases d={cfg.d} F={cfg.F} E={cfg.E} k={cfg.k} T={T}, 3 slots")
     st = LayerStack(cfg, 1, slots_total=3, max_tokens=T, q4=True, flags=ef.EF_FLAG_PROFILE)
     try:
+        if expand:
+            ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
         assert res.sum() == 0
         layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, res)
