@@ -86,8 +86,9 @@ enum {
     EF_K_GROUP = 2,    /* per-expert prefix over the tiles + stable scatter: counts, offsets, perm, inv_perm */
     EF_K_FFN_UP_TILED = 3,   /* first FFN half, groups with many tokens (matrix-core bound tiles) */
     EF_K_PACK = 4,     /* token permutation into per-expert operand tiles */
-    EF_K_FFN_UP = 5,   /* grouped act = silu(X W1^T) * (X W3^T) */
-    EF_K_FFN_DOWN = 6, /* grouped Y = act W2^T */
+    EF_K_FFN_UP = 5,   /* grouped act = silu(X W1^T) * (X W3^T), weights streamed; large 4-bit groups that are not expanded
+                          may take a launch of their own beside the others' */
+    EF_K_FFN_DOWN = 6, /* grouped Y = act W2^T, likewise */
     EF_K_COMBINE = 7,  /* weighted un-permute */
     EF_K_FFN_DOWN_TILED = 8, /* second FFN half, groups with many tokens */
     EF_K_DIST = 9,     /* intra-batch diversity Dist(t): norms, Gram tiles, reductions (one bracket) */

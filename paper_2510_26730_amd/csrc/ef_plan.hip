@@ -349,19 +349,24 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             ts = c->side_stream;
             side.forked = true;
         }
-        {
-            KernelTimer kt(c, ts, EF_K_FFN_UP_TILED, b_up, f_up);   // 4-bit: the expansion is timed with the first half
-            if (c->q4 && expand) {
-                dq.n = nb;
-                EF_HIP(c, ef::launch_dequant_q4(dq, d, ts));
+        if (c->q4 && !expand) {   // passes of four on the 4-bit blobs: counted with the streamed launches
+            {
+                KernelTimer kt(c, ts, EF_K_FFN_UP, b_up);
+                EF_HIP(c, ef::launch_ffn_gate_up_q4(big, wg_up, 4, false, c->xp, c->act, d, ts));
             }
-            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_gate_up_q4(big, wg_up, 4, false, c->xp, c->act, d, ts));
-            else EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, wg_up, c->xp, c->act, d, c->q4, ts));
-        }
-        {
+            KernelTimer kt(c, ts, EF_K_FFN_DOWN, b_dn);
+            EF_HIP(c, ef::launch_ffn_down_q4(bdn, wg_dn, 4, c->act, c->y, y_plane, d, ts));
+        } else {
+            {
+                KernelTimer kt(c, ts, EF_K_FFN_UP_TILED, b_up, f_up);   // 4-bit: the expansion is timed with the first half
+                if (c->q4) {
+                    dq.n = nb;
+                    EF_HIP(c, ef::launch_dequant_q4(dq, d, ts));
+                }
+                EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, wg_up, c->xp, c->act, d, c->q4, ts));
+            }
             KernelTimer kt(c, ts, EF_K_FFN_DOWN_TILED, b_dn, f_dn);
-            if (c->q4 && !expand) EF_HIP(c, ef::launch_ffn_down_q4(bdn, wg_dn, 4, c->act, c->y, y_plane, d, ts));
-            else EF_HIP(c, ef::launch_ffn_down_tiled(bdn, wg_dn, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, ts));
+            EF_HIP(c, ef::launch_ffn_down_tiled(bdn, wg_dn, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, ts));
         }
         if (side.forked) EF_HIP(c, side.record());
     }
