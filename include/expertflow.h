@@ -184,8 +184,8 @@ size_t ef_expert_bytes(int d_model, int d_ff);
  * 4-bit blob too (ef_pack_expert_q4 with d_ff_shared).  The kernels dequantise on the operand fragment, in passes of
  * one, two or four token tiles; the groups of very large launches (prefill of a Mixtral-shaped layer) are
  * first expanded to a 16-bit blob of the same fp16 values (q - 8) * s in a staging
- * area the context owns (one blob per expert that can reach that size in one call) and then run
- * through the tiled matrix-core kernels in fp16.
+ * area the context owns (one blob per expert that can take the tiled kernels in one call; only in contexts
+ * whose max_tokens admits such a launch) and then run through the tiled matrix-core kernels in fp16.
  */
 size_t ef_expert_bytes_q4(int d_model, int d_ff);   /* 0 if d_model % 128 or d_ff % 128 is non-zero */
 
@@ -521,7 +521,8 @@ typedef struct ef_tuning {
                                         of 256 x 256 staged through LDS; 1 and 2 give the same bits (0) */
     int32_t q4_expand_min_units;     /* >= 0: 4-bit groups of a tiled one's size are expanded to 16 bits and take the tiled
                                         kernels when those of 32 token tiles and more make this many of their workgroups
-                                        (2048); 0 = always */
+                                        (2048); 0 = always.  ef_set_tuning allocates the staging area for the expansion
+                                        when a lower value first admits it (EF_ENOMEM if it does not fit) */
 } ef_tuning;
 int ef_get_tuning(ef_ctx *ctx, ef_tuning *out);
 int ef_set_tuning(ef_ctx *ctx, const ef_tuning *t);

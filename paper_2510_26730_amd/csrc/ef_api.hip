@@ -201,6 +201,34 @@ extern "C" int ef_destroy(ef_ctx *c) {
     return EF_OK;
 }
 
+// The 16-bit staging area of a 4-bit context, once a call of max_tokens tokens could be expanded with this threshold (a
+// Qwen-shaped context of 640 tokens cannot: 0.83 GB less).  In such a call every group of more than (kTiledMinTiles - 1)
+// tiles is expanded: as many routed experts as that many tokens fill, plus the shared FFN (every token).
+static hipError_t q4_stage_reserve(ef_ctx *c, int min_units) {
+    if (!c->q4 || c->fake || c->q4_stage) return hipSuccess;
+    const ef_config &g = c->cfg;
+    const int d = g.d_model;
+    const long long Tm = g.max_tokens, rows = Tm * g.top_k;
+    const bool routed = ef::ffn_tiled_ok(d, g.d_ff, ef::kTiledMinTiles);
+    const bool shared = g.d_ff_shared > 0 && ef::ffn_tiled_ok(d, g.d_ff_shared, ef::kTiledMinTiles);
+    // most first-half workgroups that groups of kQ4ExpandTiles tiles and more can make: n of them hold at most `rows`
+    // tokens in panels of 256, one of them at most Tm
+    const long long large = (ef::kQ4ExpandTiles - 1) * ef::kTile + 1;
+    const long long n = Tm >= large ? std::min<long long>(g.n_experts, rows / large) : 0;
+    long long units = 0;
+    if (routed) units += (g.d_ff / 128) * std::min(rows / 256 + n, n * ((Tm + 255) / 256));
+    if (shared && Tm >= large) units += (g.d_ff_shared / 128) * ((Tm + 255) / 256);
+    if (units < min_units) return hipSuccess;
+    const long long need = (ef::kTiledMinTiles - 1) * ef::kTile + 1;
+    const int slots = (routed ? (int)std::min<long long>(g.n_experts, rows / need) : 0) + (shared && Tm >= need ? 1 : 0);
+    if (slots == 0) return hipSuccess;
+    c->q4_stage_bytes = ef_expert_bytes(d, std::max(g.d_ff, g.d_ff_shared));
+    const hipError_t e = hipMalloc(&c->q4_stage, (size_t)slots * c->q4_stage_bytes);
+    if (e == hipSuccess) c->q4_stage_slots = slots;
+    else c->q4_stage = nullptr;
+    return e;
+}
+
 extern "C" int ef_create(const ef_config *cfg, ef_ctx **out) {
     if (!cfg || !out) return fail(nullptr, EF_EINVAL, "ef_create: null argument");
     *out = nullptr;
@@ -288,19 +316,7 @@ extern "C" int ef_create(const ef_config *cfg, ef_ctx **out) {
     if ((e = hipMalloc(&c->gate_part, c->gate_part_floats * 4)) != hipSuccess) return bail(e, "gate partials");
     if ((e = hipMalloc(&c->act, act_bytes)) != hipSuccess) return bail(e, "activation scratch");
     if ((e = hipMalloc(&c->y, y_bytes)) != hipSuccess) return bail(e, "expert-output scratch");
-    if (c->q4) {
-        // 4-bit groups with enough tokens for the tiled kernels are expanded to 16 bits first.  A group needs more
-        // than (kTiledMinTiles - 1) tiles of tokens, so at most `can` routed experts of one call qualify, plus the
-        // shared FFN (every token).
-        const long long need = (ef::kTiledMinTiles - 1) * ef::kTile + 1;
-        if (ef::ffn_tiled_ok(d, g.d_ff, ef::kTiledMinTiles)) c->q4_stage_slots = (int)std::min<long long>(E, Tm * k / need);
-        if (g.d_ff_shared > 0 && ef::ffn_tiled_ok(d, g.d_ff_shared, ef::kTiledMinTiles) && Tm >= need)
-            c->q4_stage_slots += 1;
-        c->q4_stage_bytes = ef_expert_bytes(d, std::max(g.d_ff, g.d_ff_shared));
-        if (c->q4_stage_slots > 0 &&
-            (e = hipMalloc(&c->q4_stage, (size_t)c->q4_stage_slots * c->q4_stage_bytes)) != hipSuccess)
-            return bail(e, "16-bit staging of 4-bit experts");
-    }
+    if ((e = q4_stage_reserve(c, c->tune.q4_expand_min_units)) != hipSuccess) return bail(e, "16-bit staging of 4-bit experts");
 
     {
         const size_t n = (size_t)Tm * k;
@@ -738,6 +754,9 @@ extern "C" int ef_set_tuning(ef_ctx *c, const ef_tuning *t) {
     else if (t->copy_depth < 1 || t->copy_depth > 8) bad = "copy_depth";
     else if (t->q4_expand_min_units < 0) bad = "q4_expand_min_units";
     if (bad) return fail(c, EF_EINVAL, "ef_set_tuning: %s out of range", bad);
+    if (hipError_t e = q4_stage_reserve(c, t->q4_expand_min_units); e != hipSuccess)
+        return fail(c, e == hipErrorOutOfMemory ? EF_ENOMEM : EF_EHIP, "ef_set_tuning: 16-bit staging of 4-bit experts: %s",
+                    hipGetErrorString(e));
     c->tune = *t;
     {
         std::lock_guard<std::mutex> lock(c->eng.mu);     // the copy worker reads these

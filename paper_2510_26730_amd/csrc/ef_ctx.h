@@ -112,7 +112,8 @@ struct ef_ctx {
     void *xp = nullptr, *act = nullptr;
     float *gate_part = nullptr;      // partial logits of K-split gate launches (small batches)
     bool q4 = false;                 // routed experts are 4-bit blobs
-    char *q4_stage = nullptr;        // 16-bit copies of the 4-bit experts that go through the tiled kernels in a phase
+    char *q4_stage = nullptr;        // 16-bit copies of the 4-bit experts that go through the tiled kernels in a phase, or
+                                     // null while no call of max_tokens tokens can be expanded
     int q4_stage_slots = 0;          // how many such copies fit (as many groups as can reach the tiled size at once)
     size_t q4_stage_bytes = 0;       // bytes of one copy (the larger of routed and shared FFN)
     bool prepacked = false;          // ef_layer_step already enqueued the token packing of the coming ef_moe_ffn

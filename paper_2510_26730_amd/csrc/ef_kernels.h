@@ -141,6 +141,9 @@ struct DequantTable {
     const void *src[kMaxGroups];   // 4-bit blob (cache slot)
     void *dst[kMaxGroups];         // 3*d*F*2 bytes each
 };
+// A launch of large groups is expanded when those of this many token tiles and more make ef_tuning.q4_expand_min_units of
+// the tiled first half's workgroups.
+constexpr int kQ4ExpandTiles = 32;
 hipError_t launch_dequant_q4(const DequantTable &t, int d, hipStream_t s);
 
 // Dist(t): scratch floats launch_token_dist needs for T tokens (norms, partials, workgroup sums)

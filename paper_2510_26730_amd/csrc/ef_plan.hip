@@ -506,13 +506,13 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     long long tiled_up_wgs = 0, tiled_dn_wgs = 0, tiled_rows = 0;
     int tiled_stages_min = 1 << 30;   // fewest K stages (32 columns each) among the tiled groups
     int tiled_stages_max = 0;         // ... and most
-    if (T > 0 && (!c->q4 || c->q4_stage_slots > 0) && c->tune.tiled != 0) {
+    if (T > 0 && c->tune.tiled != 0) {
         long long wg_up = 0, wg_dn = 0, wg_up_large = 0;
         auto add = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             if (!takes_tiled(c, F, nt, routed)) return;
             wg_up += ef::ffn_tiled_units(F / 128, nt, 1);
-            if (nt >= 32) wg_up_large += ef::ffn_tiled_units(F / 128, nt, 1);
+            if (nt >= ef::kQ4ExpandTiles) wg_up_large += ef::ffn_tiled_units(F / 128, nt, 1);
             passes_of_four_dn += ef::ffn_down_q4_wgs(d, nt, 4, 1);
             wg_dn += ef::ffn_tiled_units(d / 256, nt, 1);
             tiled_rows += cnt;
@@ -522,7 +522,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e) add(c->cfg.d_ff, counts_host[e], true);
         if (has_shared) add(c->cfg.d_ff_shared, T, false);
         use_tiled = wg_up >= c->tune.tiled_min_up_wgs && wg_dn >= c->tune.tiled_min_down_wgs;
-        q4_expand = c->q4 && wg_up_large >= c->tune.q4_expand_min_units;
+        q4_expand = c->q4_stage && wg_up_large >= c->tune.q4_expand_min_units;
         // Groups that would not use what the tiled kernels offer run with the streamed ones: one launch per half instead of
         // two on two streams, whose fork and join cost about 10 us.  In passes of four token tiles:
         long long four_all = 0, four_tiled = 0;

@@ -240,3 +240,24 @@ def test_q4_create_rejects_bad_shapes():
         args.update(kw)
         with pytest.raises(ef.EfError):
             ef.ef_create(**args)
+
+
+def test_q4_staging_only_where_a_call_can_be_expanded():
+    """Qwen-shaped 4-bit context of 640 tokens: no batch it takes reaches the expansion, so its staging area (12 blobs of
+    69 MB) is not there until the threshold is lowered to "always": no group reaches 32 tiles, at any other it stays out."""
+    cfg = synth.CONFIGS["qwen15_moe"]
+    area = 12 * ef.ef_expert_bytes(cfg.d, cfg.F_shared)
+    free = [torch.cuda.mem_get_info()[0]]
+    ctx = ef.ef_create(n_layers=1, d_model=cfg.d, n_experts=cfg.E, top_k=cfg.k, d_ff=cfg.F, d_ff_shared=cfg.F_shared,
+                       slots_total=1, max_tokens=640, weight_bits=4)
+    try:
+        for units in (None, 1, 0):
+            if units is not None:
+                ef.ef_set_tuning(ctx, q4_expand_min_units=units)
+            free.append(torch.cuda.mem_get_info()[0])
+    finally:
+        ef.ef_destroy(ctx)
+    used = [free[0] - f for f in free]
+    say(f"staging {area}, used {used}")
+    assert used[2] <= used[1] + area // 16 and used[1] < area      # everything else: 0.43 GB
+    assert used[3] >= used[1] + area
