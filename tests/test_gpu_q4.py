@@ -129,6 +129,7 @@ def test_q4_large_groups_through_tiled_kernels(oracle_mod, kw, T, tiled, expand)
             ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        ef.ef_get_stats(st.ctx)     # waits for the copies: one phase
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
         layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, res)
         launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
@@ -150,6 +151,7 @@ def test_q4_full_size_mixtral_prefill(oracle_mod):
     try:
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        ef.ef_get_stats(st.ctx)     # waits for the copies: one phase
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
         toks = np.sort(np.random.default_rng(T).permutation(T)[:4])
         layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, res, toks)
@@ -173,6 +175,7 @@ def test_q4_shared_ffn(oracle_mod, T, tiled_shared, expand):
             ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        ef.ef_get_stats(st.ctx)     # waits for the copies: one phase
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
         layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, res)
         launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
@@ -198,6 +201,7 @@ def test_q4_full_size_qwen_mixed_batch(oracle_mod, expand):
             ef.ef_set_tuning(st.ctx, q4_expand_min_units=0)
         for e in range(cfg.E):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        ef.ef_get_stats(st.ctx)     # waits for the copies: one phase
         res = ef.ef_cache_query(st.ctx, 0, cfg.E)
         toks = np.sort(np.random.default_rng(T).permutation(T)[:6])
         layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, res, toks)
