@@ -534,11 +534,13 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         };
         for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
         if (has_shared) count(c->cfg.d_ff_shared, T, false);
-        if (c->q4 && !q4_expand && c->tune.passes_of_four != 0) {
+        if (c->q4 && !q4_expand) {
             // passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
             // less (two layers: Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens
-            // 1560 -> 1459)
-            if (tiles_per_pass(c, 4, four_all) == 4 || (four_all >= 512 && four_tiled * 4 <= four_all)) use_tiled = false;
+            // 1560 -> 1459); a launch of their own is passes of four too
+            if (c->tune.passes_of_four == 0 || tiles_per_pass(c, 4, four_all) == 4 ||
+                (four_all >= 512 && four_tiled * 4 <= four_all))
+                use_tiled = false;
         } else if (!c->q4 && wg_up < 64 && four_all - four_tiled >= 128 && c->tune.passes_of_four != 0 &&
                    c->tune.lds_shared != 0) {
             // fewer than 64 of the 256 x 256 tiles beside a streamed launch that covers half of the compute units (two

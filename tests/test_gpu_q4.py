@@ -140,6 +140,24 @@ def test_q4_large_groups_through_tiled_kernels(oracle_mod, kw, T, tiled, expand)
         st.close()
 
 
+def test_q4_without_passes_of_four(oracle_mod):
+    """passes_of_four = 0: large and small groups alike in passes of two, one streamed launch per half."""
+    cfg = q4_shape("tiny", name="tiny_q4_passes", d=512, F=384)
+    T = 900
+    say(f"q4 passes of two d={cfg.d} F={cfg.F} E={cfg.E} k={cfg.k} T={T}")
+    st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=T, q4=True, flags=ef.EF_FLAG_PROFILE)
+    try:
+        ef.ef_set_tuning(st.ctx, passes_of_four=0)
+        for e in range(cfg.E):
+            ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        ef.ef_get_stats(st.ctx)     # waits for the copies: one phase
+        layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, ef.ef_cache_query(st.ctx, 0, cfg.E))
+        launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
+        assert launches["ffn_up"] == launches["ffn_down"] == 1 and launches["ffn_up_tiled"] == launches["ffn_down_tiled"] == 0
+    finally:
+        st.close()
+
+
 def test_q4_full_size_mixtral_prefill(oracle_mod):
     """The prefill shape with 4-bit experts (T = 8192, every expert far above 8 tiles: expansion to fp16 and
     the tiled kernels, the configuration `bench.py --workload mixtral_prefill --int4 --all-resident` times);
