@@ -13,6 +13,8 @@ constexpr size_t kCountsBytes = (size_t)(EF_ROUTE_STATIC_MAX_TOKENS / ef::kTile)
 constexpr size_t kPartOffset = 2 * kCountsBytes;
 constexpr size_t kScratchBytes = EF_ROUTE_STATIC_SCRATCH_BYTES;
 static_assert(kPartOffset < kScratchBytes && kPartOffset % 256 == 0, "scratch layout");
+static_assert((kScratchBytes - kPartOffset) / sizeof(float) >= ef::kGateSplitFloats,
+              "a gate's K split may use kGateSplitFloats in either scratch: less here and ef_route would split, and round, differently");
 
 // Every GPU the library runs on holds its own copy of this array, at its own address, until the process ends.
 // In host code the name is only a handle for hipGetSymbolAddress: kernels get the resolved address.
