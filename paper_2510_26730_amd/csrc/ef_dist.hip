@@ -7,9 +7,9 @@
 // contraction over d that runs on the matrix cores from the packed (operand-fragment) copy of the
 // tokens; only tiles that hold a pair i < j are computed.  Three steps on one stream:
 //   1. squared norms n_i in fp32 (bf16 products are exact in fp32), one wave per token;
-//   2. Gram tiles: a workgroup owns 128 rows i x 256 columns j, a wave 64 x 128 (2 x 4 MFMA
-//      32x32x16 accumulators); the epilogue turns inner products into distances, masks i >= j and
-//      columns past T, and adds the 64 rows of the wave per column: one partial per (64-row block,
+//   2. Gram tiles: a workgroup owns 256 rows i x 256 columns j whose operands pass through LDS (dist_form 1: 128 x 256,
+//      operands straight into registers); the epilogue turns inner products into distances, masks i >= j and
+//      columns past T, and adds 64 rows per column: one partial per (64-row block,
 //      token j), no atomics;
 //   3. per token the partials of its row blocks are added in ascending order, and the per-token
 //      values are added in fixed order (workgroup tree, then one workgroup over the workgroup
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(64 * kDistSmallWaves) void dist_small_kernel(const 
 }
 
 // ------------------------------------------------------------------------------------------
-// Gram blocks of batches between the two sizes above and below (a few hundred to about two thousand tokens): too few
+// Gram blocks of batches between the two sizes above and below (kDistSmallMaxTokens to kDistBlockMaxTokens): too few
 // 256 x 256 (or 128 x 256) blocks to fill the chip, each walking all of d alone: 25 workgroups and 49 us at T = 1056,
 // d = 2048.  Here a workgroup owns a block of 32B x 32B pairs (B = 1 or 2) and its four waves a quarter of d each: their
 // partial products meet in LDS in a fixed order.  Rows are read as they are, whole 128-byte lines by eight lanes each,
@@ -447,7 +447,6 @@ __host__ __device__ inline long long gram_blocks_before(int R, int nB) {
     return r * nB - r * (r - 1) / 2;                           // row IB holds nB - IB blocks
 }
 inline long long gram_blocks(int nB) { return (long long)nB * (nB + 1) / 2; }
-constexpr long long kDistTiledMinBlocks = 64;
 
 __global__ __launch_bounds__(256, 1) void dist_gram_tiled_kernel(const uint4 *__restrict__ xp,
                                                                   const float *__restrict__ norms, int T, int d,
@@ -669,11 +668,9 @@ hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, fl
     off += off & 1;
     double *wg_sums = reinterpret_cast<double *>(scratch + off);
     hipLaunchKernelGGL(dist_norm_kernel, dim3((t_pad + 3) / 4), dim3(256), 0, s, h, T, d, norms, t_pad);
-    // 256 x 256 blocks through LDS once they fill a quarter of the compute units; below that the
-    // 128 x 256 blocks of the register-fed kernel, two to a compute unit, spread the batch wider
     const int nB = (ntiles + 7) / 8;
     const long long total = gram_blocks(nB);
-    if (form == 2 || (form == 0 && total >= kDistTiledMinBlocks)) {
+    if (form != 1) {
         // One block per compute unit at a time: the blocks left over after the last full round of 256 would be a
         // round of their own.  Up to 64 of them run as quarters instead (at most 256 workgroups, each with a
         // quarter of the matrix-core work per stage).

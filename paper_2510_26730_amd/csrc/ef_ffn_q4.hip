@@ -68,7 +68,7 @@ __device__ __forceinline__ float q4_saturate(float v) {
 
 // register ring: stages in flight per wave (four were measured slower than six with two token tiles per pass
 // and one wave per SIMD)
-template <int TT> constexpr int q4_depth() { return 6; }
+constexpr int kQ4Depth = 6;
 constexpr int kQ4Lds = 4;     // LDS ring of shared token / activation fragments (stages)
 
 // K loop of the first half for NTL live token tiles of a pass of TT: stages [k0, k0 + nloc) of 64 inputs each, `xs` the
@@ -173,7 +173,7 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
 template <int TT, int KH, int OCC>
 __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTable gt, const uint4 *__restrict__ xp,
                                                                        uint4 *__restrict__ act, int d) {
-    constexpr int D = TT == 4 ? 3 : (KH == 2 || OCC == 2) ? 4 : q4_depth<TT>();   // 3 and 6 measured slower with two waves per SIMD
+    constexpr int D = TT == 4 ? 3 : (KH == 2 || OCC == 2) ? 4 : kQ4Depth;   // 3 and 6 measured slower with two waves per SIMD
     __shared__ __attribute__((aligned(16))) u32x4_t xs[KH][kQ4Lds][TT * 4][64];
     const int wg = blockIdx.x;
     int grp = 0;
@@ -370,7 +370,7 @@ template <int TT>
 __global__ __launch_bounds__(256, TT == 4 ? 2 : 1) void ffn_down_q4_kernel(GroupTable gt, const uint4 *__restrict__ act,
                                                              float *__restrict__ Y, int d,
                                                              long long y_plane) {
-    constexpr int D = TT == 4 ? 3 : q4_depth<TT>(), CBW = 2;
+    constexpr int D = TT == 4 ? 3 : kQ4Depth, CBW = 2;
     __shared__ __attribute__((aligned(16))) u32x4_t as[kQ4Lds][TT * 4][64];
     const int wg = blockIdx.x;
     int grp = 0;
