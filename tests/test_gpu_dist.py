@@ -163,6 +163,23 @@ def test_forms_by_batch_size_match_oracle(oracle_mod, T, d):
     assert np.array_equal(tok, tok2) and tot == tot2, "not bit-reproducible"
 
 
+@pytest.mark.parametrize("T,d", [(64, 4096), (100, 4096), (256, 2048)])
+def test_distances_do_not_drift(oracle_mod, T, d):
+    """The mean relative error of the distances stays below a quarter of one fp32 rounding (2^-26 = 1.5e-8): rounding to
+    nearest has no sign of its own while the sums it is applied to stay short.  One chain of all of a lane's
+    products drifts: 2e-8 to 5e-8 here."""
+    say(f"dist drift T={T} d={d}")
+    h = synth.f32_to_bf16(np.random.default_rng(T).standard_normal((T, d)).astype(np.float32))
+    ctx = make_ctx(d, max(T, 64))
+    try:
+        tok, tot = run_dist(ctx, h, T)
+    finally:
+        ef.ef_destroy(ctx)
+    ref = oracle_mod.token_dist(h).sum()
+    say(f"  relative error of the total {(tot - ref) / ref:.1e}")
+    assert abs(tot - ref) <= 2.0 ** -26 * ref
+
+
 def test_argument_errors():
     ctx = make_ctx(64, 64)
     try:
