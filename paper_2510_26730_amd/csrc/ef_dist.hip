@@ -194,9 +194,18 @@ __global__ __launch_bounds__(64 * kDistSmallWaves) void dist_small_kernel(const 
 // partial products meet in LDS in a fixed order.  Rows are read as they are, whole 128-byte lines by eight lanes each,
 // and turned into operand fragments through a wave's own LDS buffer, pieces of a row rotated by an exclusive or so that
 // neither side meets bank conflicts (read straight into operand registers, 32 lines per load, the address path bound the
-// kernel: T = 1056, d = 2048 26.6 us for the call, now 19.6; T = 2048, d = 4096 119 and 64).  No packed copy; the norms are the diagonals of the row and column tiles' own products,
-// accumulated beside the block's (one launch less; equal rows give a distance of exactly 0).
+// kernel: T = 1056, d = 2048 26.6 against 18.8 us for the call; T = 2048, d = 4096 119 and 66).  No packed copy; the norms
+// are the diagonals of the row and column tiles' own products, formed beside the block's in the same order (one launch
+// less; equal rows give a distance of exactly 0).  Products are summed stage by stage (below), which takes those two sizes
+// to 19.6 and 71 us.
 // ------------------------------------------------------------------------------------------
+// element dv of an accumulator, dv different from lane to lane
+__device__ __forceinline__ float diag_of(const floatx16 &m, int dv) {
+    float r = m[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) r = dv == v ? m[v] : r;
+    return r;
+}
 template <int B, int R>
 __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__restrict__ h, int T, int d,
                                                             float *__restrict__ part, int t_pad) {
@@ -218,48 +227,69 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
     const int n = (d >> 4) >> 2, k0 = wave * n;   // d is a multiple of 64: equal quarters
     // global load u of a tile's stage: rows 8u .. 8u+7, eight lanes to a row's 128 bytes
     const int lr = lane >> 3, lc = lane & 7;
-    const u32x4_t *src[2 * B][U];   // row tiles, then column tiles
-#pragma unroll
-    for (int a = 0; a < 2 * B; ++a)
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int row = min((a < B ? IB * B + a : JB * B + a - B) * kTile + 8 * u + lr, T - 1);
-            src[a][u] = reinterpret_cast<const u32x4_t *>(h + (size_t)row * d) + 2 * k0;
-        }
+    // of row tiles, then column tiles; rows past the last token read the last one (16-byte units: T d / 8 fits 32 bits)
+    const u32x4_t *const h4 = reinterpret_cast<const u32x4_t *>(h) + 2 * k0;
+    const unsigned stride = d >> 3, last = (unsigned)(T - 1) * stride;
+    const unsigned row0 = (unsigned)(IB * B * kTile + lr) * stride, col0 = (unsigned)(JB * B * kTile + lr) * stride;
     u32x4_t *const buf = lds[wave];
     const int put = lr * 8 + (lc ^ lr);   // + 64 u + TILE a
-    floatx16 acc[B][B], sq[2 * B];
+    // The matrix instruction's sums of like sign drift upwards as the accumulator grows (a norm from one chain of 32: 4e-8
+    // of it on average, from chains of 4: 5e-9), and the norm of a token enters all of its distances.  So a stage's
+    // products form a chain of their own, which is then added to the total (for the norms to the lane's diagonal element).
+    floatx16 acc[B][B];
+    float diag[2 * B];   // of the lanes that hold a diagonal element: row c of tile a, in the lanes with g = c / 4 % 2
 #pragma unroll
     for (int a = 0; a < B; ++a)
 #pragma unroll
         for (int b = 0; b < B; ++b) zero16(acc[a][b]);
 #pragma unroll
-    for (int a = 0; a < 2 * B; ++a) zero16(sq[a]);
+    for (int a = 0; a < 2 * B; ++a) diag[a] = 0.f;
+    const int dv = 4 * (c >> 3) + (c & 3);   // accumulator element of that row
     u32x4_t f[R][2 * B][U];
 #define EF_DISTB_LOAD(f_, kb)                                                                             \
     {                                                                                                     \
-        const int ch_ = min(2 * (kb) + lc, 2 * n - 1); /* past the quarter's end its last piece again */  \
+        const unsigned ch_ = min(2 * (kb) + lc, 2 * n - 1); /* past the quarter's end its last piece again */  \
         _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
-            _Pragma("unroll") for (int u = 0; u < U; ++u) f_[a][u] = src[a][u][ch_];                      \
+            _Pragma("unroll") for (int u = 0; u < U; ++u)                                                 \
+                f_[a][u] = h4[min((a < B ? row0 : col0) + (unsigned)((a % B) * kTile + 8 * u) * stride, last) + ch_]; \
+    }
+    // products of the stage in LDS: row tile `a` with the column tiles, its norm and that of column tile `a`
+#define EF_DISTB_PRODUCTS                                                                                 \
+    _Pragma("unroll") for (int a = 0; a < B; ++a) {                                                       \
+        floatx16 p_[B], qr_, qc_;                                                                         \
+        _Pragma("unroll") for (int b = 0; b < B; ++b) zero16(p_[b]);                                      \
+        zero16(qr_);                                                                                      \
+        zero16(qc_);                                                                                      \
+        _Pragma("unroll") for (int u = 0; u < U; ++u) {                                                   \
+            const int at_ = c * 8 + ((2 * u + g) ^ (c & 7));                                              \
+            const u32x4_t x_ = buf[a * TILE + at_];                                                       \
+            u32x4_t y_[B];                                                                                \
+            _Pragma("unroll") for (int b = 0; b < B; ++b) y_[b] = buf[(B + b) * TILE + at_];              \
+            _Pragma("unroll") for (int b = 0; b < B; ++b) p_[b] = mfma32v(x_, y_[b], p_[b]);              \
+            qr_ = mfma32v(x_, x_, qr_);                                                                   \
+            qc_ = mfma32v(y_[a], y_[a], qc_);                                                             \
+        }                                                                                                 \
+        _Pragma("unroll") for (int b = 0; b < B; ++b)                                                     \
+            _Pragma("unroll") for (int v = 0; v < 16; ++v) acc[a][b][v] += p_[b][v];                      \
+        diag[a] += diag_of(qr_, dv);                                                                      \
+        diag[B + a] += diag_of(qc_, dv);                                                                  \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
     }
     // one stage: into the wave's LDS buffer, the registers refilled R stages ahead, then operand fragments from LDS.  A
     // lane reads what other lanes of its wave wrote and the next stage overwrites it: both ways the order is stated to the
     // compiler (no wait and no instruction: the hardware keeps a wave's LDS operations in order)
 #define EF_DISTB_STAGE(f_, kb)                                                                            \
     {                                                                                                     \
+        if ((kb) + U > n) { /* the quarter ends inside the stage: zeros past its end */                   \
+            const bool past_ = 2 * (kb) + lc >= 2 * n;                                                    \
+            _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                             \
+                _Pragma("unroll") for (int u = 0; u < U; ++u) f_[a][u] = past_ ? u32x4_t{0, 0, 0, 0} : f_[a][u]; \
+        }                                                                                                 \
         _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
             _Pragma("unroll") for (int u = 0; u < U; ++u) buf[a * TILE + 64 * u + put] = f_[a][u];        \
         wave_lds_sync();                                                                                  \
         EF_DISTB_LOAD(f_, (kb) + R * U)                                                                   \
-        _Pragma("unroll") for (int u = 0; u < U; ++u)                                                     \
-            if ((kb) + u < n) {                                                                           \
-                u32x4_t x[2 * B];                                                                         \
-                _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                         \
-                    x[a] = buf[a * TILE + c * 8 + ((2 * u + g) ^ (c & 7))];                               \
-                _Pragma("unroll") for (int a = 0; a < B; ++a)                                             \
-                    _Pragma("unroll") for (int b = 0; b < B; ++b) acc[a][b] = mfma32v(x[a], x[B + b], acc[a][b]); \
-                _Pragma("unroll") for (int a = 0; a < 2 * B; ++a) sq[a] = mfma32v(x[a], x[a], sq[a]);     \
-            }                                                                                             \
+        EF_DISTB_PRODUCTS                                                                                 \
         wave_lds_sync();                                                                                  \
     }
 #pragma unroll
@@ -270,6 +300,7 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
             if (kb + r * U < n) EF_DISTB_STAGE(f[r], kb + r * U)
     }
 #undef EF_DISTB_LOAD
+#undef EF_DISTB_PRODUCTS
 #undef EF_DISTB_STAGE
     float(*const red)[B * B * 16][64] = reinterpret_cast<float(*)[B * B * 16][64]>(&lds[0][0]);
     // the partials' stride is a wave's own buffer or less, so every wave has to be done with its stages first
@@ -281,11 +312,10 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
 #pragma unroll
             for (int v = 0; v < 16; ++v) red[wave][(a * B + b) * 16 + v][lane] = acc[a][b][v];
     // accumulator lane l holds column l%32 and rows 8*(v/4) + 4*(l/32) + v%4
+    if (g == ((c >> 2) & 1)) {
 #pragma unroll
-    for (int a = 0; a < 2 * B; ++a)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            if (8 * (v >> 2) + 4 * g + (v & 3) == c) nrm[wave][a][c] = sq[a][v];
+        for (int a = 0; a < 2 * B; ++a) nrm[wave][a][c] = diag[a];
+    }
     __syncthreads();
     const int a = B == 2 ? wave >> 1 : 0, b = B == 2 ? wave & 1 : 0;   // this wave's tile of the block
     float sum = 0.f;

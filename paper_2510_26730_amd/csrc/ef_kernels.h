@@ -154,11 +154,11 @@ size_t dist_scratch_floats(int T);
 // writes first.
 constexpr int kDistRowMaxTokens = 64;
 constexpr int kDistSmallMaxTokens = 256;
-constexpr int kDistBlockMaxTokens = 3584;   // the call at T = 3500: 86 / 144 us (d = 2048 / 4096) against 105 / 155 us
-                                            // through 256 x 256 blocks; at T = 4096 110 / 185 against 111 / 160 us
+constexpr int kDistBlockMaxTokens = 3584;   // the call at T = 3500: 87 / 148 us (d = 2048 / 4096) against 106 / 156 us
+                                            // through 256 x 256 blocks; from T = 4096 on those are level or ahead
 inline bool dist_needs_packed(int T, int form) { return !(form == 0 && T <= kDistBlockMaxTokens); }
-// 64 x 64 blocks once there are enough of them for half of the compute units, else 32 x 32 (the call, d = 4096: T = 900
-// 24.6 us with 32 x 32 against 28.3, T = 1056 37 against 29 us)
+// 64 x 64 blocks once there are enough of them for half of the compute units, else 32 x 32 (the call, d = 2048 /
+// 4096: T = 900 16.0 / 23.6 us with 32 x 32 against 19.5 / 30.2, T = 1200 22.7 / 33.2 against 20.4 / 30.5)
 inline bool dist_block_wide(int T) { return T > 960; }
 // `form`: 0 = by batch size, 1 = register-fed 128 x 256 Gram blocks, 2 = 256 x 256 blocks through LDS (same bits)
 hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, float *scratch, float *tok_dist,

@@ -163,11 +163,11 @@ def test_forms_by_batch_size_match_oracle(oracle_mod, T, d):
     assert np.array_equal(tok, tok2) and tot == tot2, "not bit-reproducible"
 
 
-@pytest.mark.parametrize("T,d", [(64, 4096), (100, 4096), (256, 2048)])
+@pytest.mark.parametrize("T,d", [(64, 4096), (100, 4096), (256, 2048), (500, 4096), (960, 2048), (1056, 2048), (1500, 4096)])
 def test_distances_do_not_drift(oracle_mod, T, d):
     """The mean relative error of the distances stays below a quarter of one fp32 rounding (2^-26 = 1.5e-8): rounding to
-    nearest has no sign of its own while the sums it is applied to stay short.  One chain of all of a lane's
-    products drifts: 2e-8 to 5e-8 here."""
+    nearest has no sign of its own while the sums it is applied to stay short.  One chain of all of a lane's or a matrix
+    accumulator's products drifts: 2e-8 to 5e-8 here."""
     say(f"dist drift T={T} d={d}")
     h = synth.f32_to_bf16(np.random.default_rng(T).standard_normal((T, d)).astype(np.float32))
     ctx = make_ctx(d, max(T, 64))
@@ -178,6 +178,19 @@ def test_distances_do_not_drift(oracle_mod, T, d):
     ref = oracle_mod.token_dist(h).sum()
     say(f"  relative error of the total {(tot - ref) / ref:.1e}")
     assert abs(tot - ref) <= 2.0 ** -26 * ref
+
+
+@pytest.mark.parametrize("T,d", [(40, 64), (200, 320), (300, 192), (1056, 2048)])
+def test_equal_tokens_have_no_distance(T, d):
+    """Norms and inner products are formed in the same order: equal rows give exactly 0, not the root of a rounding."""
+    say(f"dist equal tokens T={T} d={d}")
+    h = np.tile(synth.f32_to_bf16(np.random.default_rng(d).standard_normal((1, d)).astype(np.float32)), (T, 1))
+    ctx = make_ctx(d, max(T, 64))
+    try:
+        tok, tot = run_dist(ctx, h, T)
+    finally:
+        ef.ef_destroy(ctx)
+    assert tot == 0.0 and not tok.any()
 
 
 def test_argument_errors():
