@@ -10,7 +10,8 @@ layer per second), inputs resident in HBM, expert store in pinned host memory, c
 the warm-up steps.  Prints ONE JSON line: the top-level fields are the headline workload
 (BASELINE configuration 2, the one the metric is quoted on); `workloads` carries the same
 measurement for every BASELINE configuration (1-5, configuration 4 at both of its batch shapes)
-plus operating points with misses and prefetches.  With --workload NAME only that one is run.
+plus operating points with misses and prefetches, each in a few figures so that the whole line stays under 6000
+characters; --full puts every measured object into the line.  With --workload NAME only that one is run.
 """
 from __future__ import annotations
 
@@ -432,6 +433,49 @@ def route_sweep(args):
                       "hbm_peak_GBps": HBM_PEAK_GBPS, "route_sweep": rows}))
 
 
+# what the line carries of the headline beside the fields every line has, of its objects, and of each workload
+HEAD_KEYS = ("config", "us_per_layer", "ms_per_step_p10_p50_p90", "stall_frac", "hit_rate", "beta_changed_token_frac", "roofline",
+             "cpu_baseline")
+FULL_KEYS = HEAD_KEYS[:6] + ("link_bound_bytes_per_layer", "expert_bytes", "cache", "kernels", "token_dist") + HEAD_KEYS[6:]
+ROOF_KEYS = ("bound", "kernel", "achieved", "unit", "frac", "frac_of_measured_peak", "avg_launch_us")
+WORKLOAD_KEYS = ("name", "value", "us_per_layer", "stall_frac", "hit_rate")
+
+
+def rounded(x, digits=5):
+    """The same object with its floats at `digits` significant digits."""
+    if isinstance(x, float):
+        return float(f"{x:.{digits}g}")
+    if isinstance(x, dict):
+        return {k: rounded(v, digits) for k, v in x.items()}
+    return [rounded(v, digits) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def line_of(results, peaks, full, many):
+    """The benchmark's line: results[0] is the headline; many: a default run, whose other workloads go along."""
+    head = results[0]
+    line = {"metric": "MoE-layer tokens/s (route+predict+FFN) at 1 GPU", "value": head["value"], "unit": "tokens/s",
+            "n_gpus": 1, "steps": head["steps"], "warmup": head["warmup"], "ms_per_step": head["ms_per_step"],
+            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic"}
+    if full:
+        line.update((key, head[key]) for key in FULL_KEYS if key in head)
+        if peaks:
+            line["measured_peaks"] = peaks
+        if many:
+            line["workloads"] = results
+        return line
+    line.update((key, rounded(head[key])) for key in HEAD_KEYS if key in head)
+    if peaks:
+        line["measured_peaks"] = {k: rounded(v) for k, v in peaks.items() if isinstance(v, float)}
+    if many:
+        line["workloads"] = []
+        for r in results:
+            w = {k: rounded(r[k]) for k in WORKLOAD_KEYS}
+            if r.get("roofline"):
+                w["roofline"] = {k: rounded(r["roofline"].get(k)) for k in ROOF_KEYS}
+            line["workloads"].append(w)
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -468,6 +512,8 @@ def main():
                     help="measure routing + grouping alone at these batch sizes (Mixtral-shaped gate, tiny experts), "
                          "e.g. 8192,32768,131072, with both forms of the gate kernel, instead of the workloads")
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--full", action="store_true",
+                    help="every measured object (kernels, cache and copy statistics of every workload) in the line")
     ap.add_argument("--cpu-seconds", type=float, default=10.0, help="target CPU time of the headline's oracle baseline")
     ap.add_argument("--calib-copy", type=int, default=0,
                     help="MiB of a plain device-to-device copy done 4 times before the run (a kernel of known "
@@ -547,19 +593,7 @@ def main():
             m = peaks["mfma_16bit_TFLOPps"] if roof["bound"] == "mfma" else peaks["hbm_read_GBps"]
             roof["measured_peak"] = m
             roof["frac_of_measured_peak"] = roof["achieved"] / m if m else None
-    head = results[0]
-    line = {"metric": "MoE-layer tokens/s (route+predict+FFN) at 1 GPU", "value": head["value"], "unit": "tokens/s",
-            "n_gpus": 1, "steps": head["steps"], "warmup": head["warmup"], "ms_per_step": head["ms_per_step"],
-            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic"}
-    for key in ("config", "us_per_layer", "ms_per_step_p10_p50_p90", "stall_frac", "hit_rate", "beta_changed_token_frac",
-                "link_bound_bytes_per_layer", "expert_bytes", "cache", "kernels", "token_dist", "roofline", "cpu_baseline"):
-        if key in head:
-            line[key] = head[key]
-    if peaks:
-        line["measured_peaks"] = peaks
-    if not single:
-        line["workloads"] = results
-    print(json.dumps(line))
+    print(json.dumps(line_of(results, peaks, args.full, not single)))
 
 
 if __name__ == "__main__":
