@@ -26,15 +26,17 @@ SIZES = {
 }
 
 
-def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None):
-    """Output of the layer; compared with the oracle if one is given.  slots: fewer cache slots than experts, all empty."""
+def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None):
+    """Output of the layer; compared with the oracle if one is given.  slots: fewer cache slots than experts, all empty.
+    expect: launches of kernel kinds."""
     T, E = sum(sizes), cfg.E
-    st = LayerStack(cfg, 1, slots_total=slots or E, max_tokens=T, q4=q4)
+    st = LayerStack(cfg, 1, slots_total=slots or E, max_tokens=T, q4=q4, flags=ef.EF_FLAG_PROFILE if expect else 0)
     try:
         if tune:
             ef.ef_set_tuning(st.ctx, **tune)
         for e in range(E if slots is None else 0):
             ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        ef.ef_get_stats(st.ctx)     # waits for the copies: one phase
         rng = np.random.default_rng(sum(sizes) + 1)
         ids = np.repeat(np.arange(E, dtype=np.int32), sizes)
         rng.shuffle(ids)
@@ -50,6 +52,9 @@ def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None):
         hd, d_ids, d_w, d_off, d_perm, d_inv = dev_u16(h), dev(ids), dev(w), dev(offsets), dev(perm), dev(inv)
         ef.ef_moe_ffn(st.ctx, 0, hd, T, d_ids, d_w, counts, d_off, d_perm, d_inv, out, torch.cuda.current_stream())
         torch.cuda.synchronize()
+        if expect:
+            launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
+            assert {k: launches[k] for k in expect} == expect
         if oracle_mod is None:
             return out.cpu().numpy()
         ffn = oracle_mod.expert_ffn_q4 if q4 else oracle_mod.expert_ffn
@@ -62,6 +67,7 @@ def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None):
                 shared = oracle_mod.dense_ffn(h, *st.shared[0])
         ref = oracle_mod.combine(y, w.astype(np.float64), inv, shared)
         print(sizes, tune, float_close(out.cpu().numpy(), ref), flush=True)
+        return out.cpu().numpy()
     finally:
         st.close()
 
@@ -102,3 +108,31 @@ def test_q4_large_groups_do_not_depend_on_phases(sizes, F):
     rng.shuffle(ids)
     large = np.asarray(sizes)[ids] > 8 * 32
     assert np.all(np.isfinite(a)) and np.array_equal(a[large], b[large])
+
+
+MANY = [320] + [1 + 5 * i % 40 for i in range(63)]     # one group of ten tiles, 63 of one or two
+
+
+@pytest.mark.parametrize("F,q4,expect", [
+    (384, False, dict(ffn_up=1, ffn_up_tiled=0)),      # 6 tiled units beside 189 streamed workgroups: all streamed
+    (256, False, dict(ffn_up=1, ffn_up_tiled=1)),      # 4 beside 126: fewer than half of the compute units
+    (1792, True, dict(ffn_up=1, ffn_up_tiled=0)),      # 924 workgroups in passes of four: every group takes them
+    (1024, True, dict(ffn_up=1, ffn_up_tiled=0)),      # 528, the large group a 22nd of them: one launch, passes of two
+    (256, True, dict(ffn_up=2, ffn_up_tiled=0)),       # 132: the large group in passes of four of its own
+])
+def test_one_large_group_among_many_small(oracle_mod, F, q4, expect):
+    """Where a group of a tiled one's size runs, by what runs beside it: each rule of the plan, by the launches it makes."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_many", d=256, E=64, F=F, F_shared=0, k=1)
+    run_groups(oracle_mod, cfg, MANY, q4, {}, expect=expect)
+
+
+@pytest.mark.parametrize("q4", [False, True], ids=["bf16", "int4"])
+@pytest.mark.parametrize("sizes", ["one tile", "up to four tiles"], ids=lambda s: s.replace(" ", "_"))
+def test_wide_shared_ffn_takes_slices_of_its_own(oracle_mod, sizes, q4):
+    """A streamed shared FFN eleven times as wide as the experts: more K slices than theirs (the sums round differently from
+    one slice count for all), in the kernels of one and two tiles per pass and of four."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_wide", d=512, F=128, F_shared=1408, k=1)
+    small = [n // 4 for n in SIZES[sizes]]             # the shared FFN sees every token: seven tiles at most
+    out = run_groups(oracle_mod, cfg, small, q4, {}, expect=dict(ffn_up=1, ffn_up_tiled=0))
+    same = run_groups(None, cfg, small, q4, dict(down_split_slice_counts=0))
+    assert not np.array_equal(out, same)
