@@ -532,8 +532,10 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             four_all += wgs;
             if (takes_tiled(c, F, nt, routed)) four_tiled += wgs;
         };
-        for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
-        if (has_shared) count(c->cfg.d_ff_shared, T, false);
+        if (use_tiled) {   // a decode batch has none: nothing to look at (0.1 us of the host with 64 experts)
+            for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
+            if (has_shared) count(c->cfg.d_ff_shared, T, false);
+        }
         if (c->q4 && !q4_expand) {
             // passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
             // less (two layers: Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens
