@@ -162,11 +162,34 @@ double tiled_tail_makespan(long long before, long long units, int s) {
 // Whether a group of n_tiles token tiles takes the tiled kernels: every shared FFN that fits them, routed groups from
 // tiled_min_tiles tiles on, and one tile earlier where passes of four would end in a pass of a single tile, a whole read of
 // the weights for it (groups of 9: Mixtral-shaped 1000 tokens 2050 -> 1942 us for two layers, DeepSeek-shaped 1056 tokens
-// 784 -> 776; groups of 8 stay streamed: DeepSeek-shaped 2000 tokens on 16 experts 883 against 905 us).
-bool takes_tiled(const ef_ctx *c, int F, int n_tiles, bool routed) {
+// 784 -> 776; groups of 8 stay streamed: DeepSeek-shaped 2000 tokens on 16 experts 883 against 905 us).  `early`: whether the
+// layer's groups take them one tile earlier (early_tiled).
+bool ends_in_one_tile(const ef_ctx *c, int n_tiles) { return n_tiles == c->tune.tiled_min_tiles - 1 && n_tiles % 4 == 1; }
+bool takes_tiled(const ef_ctx *c, int F, int n_tiles, bool routed, bool early) {
     if (!ef::ffn_tiled_ok(c->cfg.d_model, F, n_tiles)) return false;
-    const int from = c->tune.tiled_min_tiles;
-    return !routed || n_tiles >= from || (n_tiles == from - 1 && n_tiles % 4 == 1);
+    return !routed || n_tiles >= c->tune.tiled_min_tiles || (early && ends_in_one_tile(c, n_tiles));
+}
+
+// The earlier line costs more than it saves where it takes the last free compute units: the streamed launch has fewer
+// workgroups than there are units, and the groups it adds bring the tiled first half from less than a round to (nearly) all
+// of one, so that the streamed workgroups wait for the tiled ones (DeepSeek-shaped on 16 experts, 660 / 680 tokens, 206 and 209
+// units without them: 452 -> 426 / 468 -> 446 us for two layers; Qwen-shaped on 12 experts, 680 tokens 422 -> 413; with 198
+// units in all, 580 tokens, the earlier line saves 2 %, and from 270 on 1 to 2 %).
+bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, int T) {
+    if (c->q4) return true;
+    bool any = false;
+    for (int e = 0; e < c->cfg.n_experts; ++e) any = any || ends_in_one_tile(c, (counts_host[e] + ef::kTile - 1) / ef::kTile);
+    if (!any) return true;
+    long long with = 0, without = 0, streamed = 0;   // tiled units with and without those groups, streamed workgroups without
+    auto add = [&](int F, int cnt, bool routed) {
+        const int nt = (cnt + ef::kTile - 1) / ef::kTile, units = ef::ffn_tiled_units(F / 128, nt, 1);
+        if (takes_tiled(c, F, nt, routed, true)) with += units;
+        if (takes_tiled(c, F, nt, routed, false)) without += units;
+        else streamed += (long long)(F / 128) * ((nt + 3) / 4);
+    };
+    for (int e = 0; e < c->cfg.n_experts; ++e) add(c->cfg.d_ff, counts_host[e], true);
+    if (has_shared) add(c->cfg.d_ff_shared, T, false);
+    return streamed > 256 || with <= 224 || without >= 240;
 }
 
 // Token tiles per pass over a streamed group's weights, for a launch whose largest group has `max_tiles` and whose first
@@ -185,7 +208,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
                  const std::vector<int> &offs_host, const std::vector<int> &tile_start,
                  const std::vector<long long> &act_off, int shared_tile_start, long long shared_act_off, int T,
                  int tpp_layer, int ksg_stream, int ksg_shared, int ksg_tiled, int split_expert, int split_ksg,
-                 ef::PlaneTable &planes, long long y_plane, bool use_tiled, bool expand, hipStream_t s) {
+                 ef::PlaneTable &planes, long long y_plane, bool use_tiled, bool early, bool expand, hipStream_t s) {
     // tpp_layer: token tiles per pass that the layer's streamed groups would take in one launch.
     // split_expert: the tiled group of the layer (expert id, -1 = shared FFN, kNoSplit = none) whose second half takes
     // split_ksg K slices instead of ksg_tiled; it goes last among the tiled groups of its launch.  expand: the tiled groups
@@ -229,7 +252,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             blob = c->pool + (size_t)pg.slot * c->expert_bytes;
         }
         const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-        const bool tiled = allow_tiled && takes_tiled(c, F, nt, pg.expert >= 0) &&
+        const bool tiled = allow_tiled && takes_tiled(c, F, nt, pg.expert >= 0, early) &&
                            (!c->q4 || !expand || nb < c->q4_stage_slots);
         ef::GroupTable &g = tiled ? big : gu;
         int &i = tiled ? nb : n;
@@ -247,7 +270,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         g.count[i] = cnt; g.F[i] = F; g.act_off[i] = ao; g.blob[i] = blob;
         if (!tiled) {
             max_tiles = std::max(max_tiles, nt);
-            large = large || (c->q4 && c->tune.tiled != 0 && takes_tiled(c, F, nt, pg.expert >= 0));
+            large = large || (c->q4 && c->tune.tiled != 0 && takes_tiled(c, F, nt, pg.expert >= 0, early));
         }
         ++i;
     }
@@ -501,6 +524,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     // with a 2048 x 5632 shared expert, 1056 tokens over 64 experts) the tiled kernels were equal to or
     // 8 % faster than streaming the same groups in several passes, even at 150-200 workgroups.
     bool use_tiled = false;
+    const bool early = early_tiled(c, counts_host, has_shared, T);
     // 4-bit contexts: the tiled groups are expanded to 16 bits and go through the 256 x 256 tiles when the groups of 32
     // tiles and more alone make eight rounds of those over the compute units; below that the expansion (a pass over 2.5
     // bytes per weight ahead of the first half) and the tiles' fixed costs outweigh them, and the groups run in passes of
@@ -516,7 +540,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         long long wg_up = 0, wg_dn = 0, wg_up_large = 0;
         auto add = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-            if (!takes_tiled(c, F, nt, routed)) return;
+            if (!takes_tiled(c, F, nt, routed, early)) return;
             wg_up += ef::ffn_tiled_units(F / 128, nt, 1);
             if (nt >= ef::kQ4ExpandTiles) wg_up_large += ef::ffn_tiled_units(F / 128, nt, 1);
             passes_of_four_dn += ef::ffn_down_q4_wgs(d, nt, 4, 1);
@@ -536,7 +560,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             const long long wgs = (long long)(F / 128) * ((nt + 3) / 4);
             four_all += wgs;
-            if (takes_tiled(c, F, nt, routed)) four_tiled += wgs;
+            if (takes_tiled(c, F, nt, routed, early)) four_tiled += wgs;
         };
         if (use_tiled) {   // a decode batch has none: nothing to look at (0.1 us of the host with 64 experts)
             for (int e = 0; e < E; ++e) count(c->cfg.d_ff, counts_host[e], true);
@@ -577,7 +601,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         };
         auto streams = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-            return !(use_tiled && takes_tiled(c, F, nt, routed));
+            return !(use_tiled && takes_tiled(c, F, nt, routed, early));
         };
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
@@ -596,7 +620,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0) {
                 const int nt = (counts_host[e] + ef::kTile - 1) / ef::kTile;
-                if (use_tiled && takes_tiled(c, c->cfg.d_ff, nt, true)) continue;
+                if (use_tiled && takes_tiled(c, c->cfg.d_ff, nt, true, early)) continue;
                 streamed_w2_bytes += (0.5 + 2.0 / 128.0) * d * c->cfg.d_ff;
                 add_base(c->cfg.d_ff, nt);
             }
@@ -689,7 +713,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             int F_last = 0;
             auto consider = [&](int expert, int F, int cnt, bool routed) {
                 const int nt = (cnt + ef::kTile - 1) / ef::kTile;
-                if (!takes_tiled(c, F, nt, routed)) return;
+                if (!takes_tiled(c, F, nt, routed, early)) return;
                 const long long work = (long long)nt * F;
                 if (best_work < 0 || work <= best_work) {
                     best_work = work; split_expert = expert; units = ef::ffn_tiled_units(d / 256, nt, 1); rows = cnt; F_last = F;
@@ -851,7 +875,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         if (!c->fake) {
             int r = launch_phase(c, layer, g, counts_host, offs_host, tile_start, act_off, shared_tile_start,
                                  shared_act_off, T, tpp, ksg, ksg_shared, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled,
-                                 q4_expand, s);
+                                 early, q4_expand, s);
             if (r) {   // part of the phase may be enqueued: its slots still get their read marker
                 (void)mark_read(v);
                 v.clear();   // released: the caller's error path has nothing left to unpin

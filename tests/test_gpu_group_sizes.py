@@ -26,9 +26,9 @@ SIZES = {
 }
 
 
-def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None):
+def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=None):
     """Output of the layer; compared with the oracle if one is given.  slots: fewer cache slots than experts, all empty.
-    expect: launches of kernel kinds."""
+    expect: launches of kernel kinds; flops: their algorithmic flops."""
     T, E = sum(sizes), cfg.E
     st = LayerStack(cfg, 1, slots_total=slots or E, max_tokens=T, q4=q4, flags=ef.EF_FLAG_PROFILE if expect else 0)
     try:
@@ -55,6 +55,9 @@ def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None):
         if expect:
             launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
             assert {k: launches[k] for k in expect} == expect
+        if flops:
+            done = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_flops"]))
+            assert {k: done[k] for k in flops} == flops
         if oracle_mod is None:
             return out.cpu().numpy()
         ffn = oracle_mod.expert_ffn_q4 if q4 else oracle_mod.expert_ffn
@@ -136,3 +139,15 @@ def test_wide_shared_ffn_takes_slices_of_its_own(oracle_mod, sizes, q4):
     out = run_groups(oracle_mod, cfg, small, q4, {}, expect=dict(ffn_up=1, ffn_up_tiled=0))
     same = run_groups(None, cfg, small, q4, dict(down_split_slice_counts=0))
     assert not np.array_equal(out, same)
+
+
+@pytest.mark.parametrize("tens,early", [(4, True), (5, False), (6, True)])
+def test_nine_tiles_join_the_tiled_launch_unless_they_fill_the_chip(oracle_mod, tens, early):
+    """A group of nine tiles (44 units of a first half) beside `tens` groups of ten in the tiled launch: 220 units in all, from
+    220 to 264 over the 256 compute units, and from 264 to 308.  The tiled launches' flops say which groups they held."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_nine", d=256, F=2816, F_shared=0, k=1)
+    sizes = ([288] + [320] * tens + [40, 0, 7])[:8]
+    sizes += [0] * (8 - len(sizes))
+    want = 4.0 * cfg.d * cfg.F * (320 * tens + (288 if early else 0))
+    run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=int(not early or sum(sizes) > 288 + 320 * tens), ffn_up_tiled=1),
+               flops=dict(ffn_up_tiled=want))
