@@ -54,7 +54,9 @@ struct GroupTable {
     int F[kMaxGroups];             // FFN hidden dim of the group
     long long act_off[kMaxGroups]; // first 16-byte unit of the group's activation fragments
     const void *blob[kMaxGroups];  // packed weights (cache slot or shared blob)
-    uint8_t ksg[kMaxGroups];       // streamed second half: K slices of the group (one Y plane each)
+    int ksg[kMaxGroups];           // streamed second half: K slices of the group (one Y plane each); a whole word comes with
+                                   // the scalar loads of the other fields, a byte is a vector load of its own ahead of
+                                   // everything else (4-bit Mixtral-shaped decode of one token 149.6 against 148.6 us)
     int xcd_rot[kMaxGroups];       // tiled kernels: the XCD (0..7) that takes the first eighth of the group's units
 };
 
