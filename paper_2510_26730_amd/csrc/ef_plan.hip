@@ -638,8 +638,9 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         // 4-bit: two workgroups per compute unit (their waves stall at different times) while the planes this adds
         // cost little beside the weights, at most a quarter of their bytes written and read: eight Mixtral-shaped
         // experts 64 tokens 416 -> 390 us per two layers, 64 DeepSeek-shaped 100 tokens 210 -> 204 us; past that
-        // the planes cost more than they gain (300 tokens, 0.4 of the weights' bytes: 385 -> 394 us)
-        if (c->q4 && c->tune.down_want_wgs == 0)
+        // the planes cost more than they gain (300 tokens, 0.4 of the weights' bytes: 385 -> 394 us).  Groups of one tile
+        // each gain nothing (8 tokens 314.7 -> 318.0 us, 16 tokens 341.5 -> 349.7, 4 and 30 the same)
+        if (c->q4 && tpp > 1 && c->tune.down_want_wgs == 0)
             while (ksg < 8 && base_wgs * ksg < 512 && units / (ksg * 2) >= 1 && y_plane * (ksg * 2) <= c->y_floats &&
                    8.0 * y_plane * ksg <= 0.25 * streamed_w2_bytes)
                 ksg *= 2;
