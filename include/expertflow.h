@@ -522,7 +522,7 @@ typedef struct ef_tuning {
                                         of 256 x 256 staged through LDS; 1 and 2 give the same bits (0) */
     int32_t q4_expand_min_units;     /* >= 0: 4-bit groups of a tiled one's size are expanded to 16 bits and take the tiled
                                         kernels when those of 32 token tiles and more make this many of their workgroups
-                                        (2048); 0 = always.  ef_set_tuning allocates the staging area for the expansion
+                                        (2048; five sixths of it where no smaller group is tiled); 0 = always.  ef_set_tuning allocates the staging area for the expansion
                                         when a lower value first admits it (EF_ENOMEM if it does not fit) */
 } ef_tuning;
 int ef_get_tuning(ef_ctx *ctx, ef_tuning *out);

@@ -218,7 +218,7 @@ static hipError_t q4_stage_reserve(ef_ctx *c, int min_units) {
     long long units = 0;
     if (routed) units += (g.d_ff / 128) * std::min(rows / 256 + n, n * ((Tm + 255) / 256));
     if (shared && Tm >= large) units += (g.d_ff_shared / 128) * ((Tm + 255) / 256);
-    if (units < min_units) return hipSuccess;
+    if (units < ef::q4_expand_units(min_units, true)) return hipSuccess;
     const long long need = (ef::kTiledMinTiles - 1) * ef::kTile + 1;
     const int slots = (routed ? (int)std::min<long long>(g.n_experts, rows / need) : 0) + (shared && Tm >= need ? 1 : 0);
     if (slots == 0) return hipSuccess;

@@ -144,8 +144,9 @@ struct DequantTable {
     void *dst[kMaxGroups];         // 3*d*F*2 bytes each
 };
 // A launch of large groups is expanded when those of this many token tiles and more make ef_tuning.q4_expand_min_units of
-// the tiled first half's workgroups.
+// the tiled first half's workgroups, or five sixths of that if no smaller group is tiled.
 constexpr int kQ4ExpandTiles = 32;
+inline int q4_expand_units(int min_units, bool only_large) { return only_large ? min_units - min_units / 6 : min_units; }
 hipError_t launch_dequant_q4(const DequantTable &t, int d, hipStream_t s);
 
 // Dist(t): scratch floats launch_token_dist needs for T tokens (norms, partials, workgroup sums)

@@ -552,7 +552,10 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e) add(c->cfg.d_ff, counts_host[e], true);
         if (has_shared) add(c->cfg.d_ff_shared, T, false);
         use_tiled = wg_up >= c->tune.tiled_min_up_wgs && wg_dn >= c->tune.tiled_min_down_wgs;
-        q4_expand = c->q4_stage && wg_up_large >= c->tune.q4_expand_min_units;
+        // Where every tiled group is that large, seven rounds do (Mixtral-shaped on two experts, 1700 / 2000 / 2300 tokens, 1568,
+        // 1792 and 2016 units: direct 2360 / 2670 / 3210 us, expanded 2360 / 2540 / 2950; eight experts, 3300 tokens, smaller
+        // groups beside: 4635 / 5215).
+        q4_expand = c->q4_stage && wg_up_large >= ef::q4_expand_units(c->tune.q4_expand_min_units, wg_up_large == wg_up);
         // Groups that would not use what the tiled kernels offer run with the streamed ones: one launch per half instead of
         // two on two streams, whose fork and join cost about 10 us.  In passes of four token tiles:
         long long four_all = 0, four_tiled = 0;

@@ -151,3 +151,16 @@ def test_nine_tiles_join_the_tiled_launch_unless_they_fill_the_chip(oracle_mod, 
     want = 4.0 * cfg.d * cfg.F * (320 * tens + (288 if early else 0))
     run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=int(not early or sum(sizes) > 288 + 320 * tens), ffn_up_tiled=1),
                flops=dict(ffn_up_tiled=want))
+
+
+@pytest.mark.parametrize("sizes,expanded", [([1800, 1793], True),            # 1792 units, all in groups of 57 tiles
+                                            ([1800, 1792, 300], False),      # 1680, and a group of ten tiles
+                                            ([1792, 1792], False)])          # 1568
+def test_q4_two_large_groups_are_expanded(sizes, expanded):
+    """Seven rounds of tiled workgroups are enough where every tiled group has 32 tiles and more: the launches say which
+    kernels ran, and both forms agree to the rounding of the intermediate activation."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_two", d=256, E=3, F=14336, F_shared=0, k=1)
+    sizes = sizes + [0] * (3 - len(sizes))
+    out = run_groups(None, cfg, sizes, True, {}, expect=dict(ffn_up=int(not expanded), ffn_up_tiled=int(expanded)))
+    other = run_groups(None, cfg, sizes, True, dict(q4_expand_min_units=1 << 20 if expanded else 0))
+    assert np.linalg.norm(out - other) <= 1e-3 * np.linalg.norm(other)
