@@ -432,15 +432,17 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     double b_up = 0.0, b_dn = 0.0;
     alg_bytes(gu, n, b_up, b_dn);
     // Workgroups per compute unit of the LDS-shared kernels: two (register ring of two stages each) or one (ring of three).
-    // A tiled workgroup holds its unit's LDS.  Two for a launch of more workgroups than units that has most of the chip to
-    // itself (64 DeepSeek-shaped experts, 300 tokens, 535 us with two against 547 for two layers), and for one of at most a
+    // A tiled workgroup holds its unit's LDS.  Two for a launch that has most of the chip to itself and more workgroups than
+    // units (64 DeepSeek-shaped experts, 200 tokens, 440 us with two against 452 for two layers, Qwen-shaped 250 tokens 418 /
+    // 424), with the long streams of a large model dimension more than two per unit (eight Mixtral-shaped experts, 130 tokens
+    // 1026 / 1050; two experts, 448 workgroups, 200 tokens 560 / 520), and for one of at most a
     // workgroup per unit beside a tiled launch of more than one round: its workgroups start where a tiled one has ended and
     // are done sooner in pairs (DeepSeek-shaped on 16 experts, 700 / 1056 / 1700 tokens 472 -> 460 / 592 -> 541 / 755 -> 703
     // us, Qwen-shaped on 12, 1056 tokens 587 -> 565; 850 tokens 495 -> 500).  One otherwise: beside less than a round of
     // tiled ones there are units without any (DeepSeek-shaped 600 tokens on 16 experts 397 against 425, Qwen-shaped 640 on
     // 12 389 / 418), and a long streamed launch beside a long tiled one is better off with the deeper ring (64 experts, 1300
     // tokens 797 / 865, Qwen-shaped 3000 tokens 1192 / 1280, Mixtral-shaped 1000 tokens 2035 / 2105).
-    const bool pairs = tiled_up_wgs < 128 ? wg_gu > 256 : tiled_up_wgs > 256 && wg_gu <= 256;
+    const bool pairs = tiled_up_wgs < 128 ? wg_gu > (d > 2048 ? 512 : 256) : tiled_up_wgs > 256 && wg_gu <= 256;
     const int occ = c->tune.lds_shared_occupancy != 0 ? c->tune.lds_shared_occupancy : pairs ? 2 : 1;
     {
         KernelTimer kt(c, s, EF_K_FFN_UP, b_up);
