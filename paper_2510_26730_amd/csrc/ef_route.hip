@@ -621,9 +621,13 @@ int gate_pick_ksplit(int T, int d, int G, int E, int gpw, size_t part_floats) {
     const int nstage = (d + kc - 1) / kc;
     // Half a round of workgroups (64 until E = 64 at 1056 and 3000 tokens with one look-ahead layer, 66 and 94 pairs of
     // tile and gate group, measured 32.4 -> 29.7 and 43.4 -> 38.8 us for the call with two slices; 132 pairs gain nothing).
+    // With one 32-column block the per-token part is short and the one-kernel form wins from 65 pairs on (8 experts, 2100 /
+    // 3000 / 4000 tokens 20.8 / 20.7 / 20.9 us against 20.9 / 22.3 / 23.1 with two slices, one look-ahead layer 20.5 / 20.6 /
+    // 20.8 against 23.0 / 24.4 / 25.9; at 64 pairs 20.1 against 19.5).
     // The split decides the order of the sums: it may not depend on which scratch a call was given, so what the smaller
     // one, ef_route_static's, holds bounds both.
     int ks = 1;
+    if (nb == 1 && ntiles * ngroups > 64) return ks;
     while (ks < kGateMaxSplit && nstage / (ks * 2) >= 4 && ntiles * ngroups * ks < 128 &&
            (size_t)ntiles * ngroups * (ks * 2) * kTile * nb * 32 <= std::min(part_floats, kGateSplitFloats))
         ks *= 2;
