@@ -292,6 +292,8 @@ def run_workload(name, spec, args, cpu_seconds):
     roof = None
     if dom:
         bound, kname = KIND_BOUND[dom_name]
+        if int4 and dom_name in ("ffn_up", "ffn_down"):
+            kname = kname.replace("_kernel", "_q4_kernel")
         if bound == "mfma":
             a = dom["TFLOPps"]
             traffic, src = (None, None)

@@ -10,6 +10,9 @@
  * library owns the context, its HBM expert-slot pool, its copy stream, its
  * events and its scratch buffers.
  *
+ * Scratch: the device calls of a context share its scratch (per-tile counts, partial logits, packed tokens, expert
+ * outputs), so calls that may overlap in time on different streams have to be ordered by events.
+ *
  * Asynchrony: ef_predict / ef_route / ef_moe_ffn only enqueue work on `stream`
  * (ef_moe_ffn may run part of a layer's kernels on a side stream of its own,
  * forked from and joined back into `stream` by events inside the call);
@@ -480,17 +483,18 @@ int ef_layer_step_fetch(ef_ctx *ctx, int32_t *topk_ids, float *topk_w, int32_t *
 /*
  * Launch-shape tuning: which kernel form a group takes and how launches are split.  For sweeps and for tests
  * that force one kernel form; cites no passage of the paper.  No setting changes what is computed, only the
- * order in which partial sums over K slices are added.  ef_create installs the defaults (the measured best);
+ * order in which partial sums are added.  ef_create installs the defaults (the measured best);
  * ef_set_tuning rejects values outside the ranges below with EF_EINVAL and changes nothing then.  "0 = auto"
  * fields let the library choose per launch.  Nothing in the library reads environment variables.
  */
 typedef struct ef_tuning {
     int32_t tiled;                   /* 0/1: groups of many token tiles may take the matrix-core tiled kernels (1) */
     int32_t tiled_min_tiles;         /* 8..4096: routed groups take them from this many 32-token tiles on, or one fewer
-                                        when passes of four would leave a single tile (10) */
+                                        when passes of four would leave a single tile and units stay free beside them (10) */
     int32_t tiled_min_up_wgs;        /* >= 1: ... and only if the tiled first-half launch has this many workgroups (1) */
     int32_t tiled_min_down_wgs;      /* >= 1: ... and the second-half launch this many (1) */
-    int32_t tiled_xcd_rotation;      /* 0/1: deal every group's weight-panel blocks from the least loaded XCD (1) */
+    int32_t tiled_xcd_rotation;      /* 0/1: each tiled group's units, an eighth per XCD, start on the XCD that leaves the
+                                        fullest one least full (1); 0: all groups start on XCD 0 */
     int32_t overlap_tiled;           /* 0/1: a phase's tiled launches run on a side stream beside its streamed ones (1) */
     int32_t sort_groups;             /* 0/1: groups with the most work first in a launch (1) */
     int32_t passes_of_four;          /* 0/1: streamed groups of >= 3 token tiles take passes of four tiles (1) */
@@ -503,7 +507,8 @@ typedef struct ef_tuning {
     int32_t down_want_wgs;           /* 0 = auto (256; 512 for the LDS-shared kernels), else >= 1: target of the K-slice split */
     int32_t down_k_slices;           /* 0 = auto, else 1..8: K-slice planes of the second half (both launches) */
     int32_t down_slices_by_longest_k; /* 0/1: the tiled second half sizes its slices by the group with the longest K (1) */
-    int32_t down_split_slice_counts; /* 0/1: the streamed and the tiled launch of a layer choose their slice counts separately (1) */
+    int32_t down_split_slice_counts; /* 0/1: the streamed and the tiled launch of a layer choose their slice counts
+                                        separately, and a streamed shared FFN its own (1) */
     int32_t gate_k_split;            /* 0 = auto, else 1..16: workgroups sharing the K range of one (tile, gate group) */
     int32_t gate_token_split;        /* 0/1: the gate's second step may split a tile's tokens over workgroups (1) */
     int32_t gate_fused_finish;       /* 0/1: decode-sized batches fuse the gate's second step with the grouping (1) */
@@ -518,8 +523,9 @@ typedef struct ef_tuning {
                                         that fill the launch's last, partly empty round: 0 = never, 1 = as many as a
                                         model of the launch finds best, 2 / 4 / 8 = that many (1) */
     int32_t dist_form;               /* ef_token_dist: 0 = by batch size (up to 256 tokens: differences summed directly,
-                                        no Gram matrix; up to 3584: Gram blocks of 32 x 32 or 64 x 64), 1 = Gram blocks of 128 x 256 fed from registers, 2 = Gram blocks
-                                        of 256 x 256 staged through LDS; 1 and 2 give the same bits (0) */
+                                        no Gram matrix; up to 3584: Gram blocks of 32 x 32 or 64 x 64; beyond: as 2),
+                                        1 = Gram blocks of 128 x 256 fed from registers, 2 = Gram blocks of 256 x 256
+                                        staged through LDS; 1 and 2 give the same bits (0) */
     int32_t q4_expand_min_units;     /* >= 0: 4-bit groups of a tiled one's size are expanded to 16 bits and take the tiled
                                         kernels when those of 32 token tiles and more make this many of their workgroups
                                         (2048; five sixths of it where no smaller group is tiled); 0 = always.  ef_set_tuning allocates the staging area for the expansion

@@ -1,5 +1,6 @@
-// Grouped SwiGLU expert FFN for groups of a few token tiles (3 to 7: too many for one pass of the plain
-// weight-streaming kernels, too few for the matrix-core tiled ones).
+// Grouped SwiGLU expert FFN for launches whose largest group has a few token tiles (three or more, too many for one pass
+// of the plain weight-streaming kernels; routed groups up to 9, beyond that the matrix-core tiled kernels, unless few tiled
+// workgroups would run beside many streamed ones: ef_plan.hip).
 //
 // The plain streaming kernels give every wave its own copy of the token (or activation) fragments: with
 // TT token tiles per pass a wave fetches TT KiB of them from L2 for every 2 KiB of weights, and at four

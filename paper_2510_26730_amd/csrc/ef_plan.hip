@@ -521,10 +521,10 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     // split while the layer's launch would have too few workgroups, a slice keeps >= 32 fragments per
     // wave and the planes fit the scratch.  One value per call: every phase shares the planes.
     const long long y_plane = ((long long)T * k + (has_shared ? T : 0)) * d;
-    // Groups of at least 8 token tiles go to the matrix-core tiled kernels.  The two thresholds (total
-    // workgroups of the tiled launches) exist for tuning only: on the mixed batches measured (640 tokens
-    // with a 2048 x 5632 shared expert, 1056 tokens over 64 experts) the tiled kernels were equal to or
-    // 8 % faster than streaming the same groups in several passes, even at 150-200 workgroups.
+    // Groups of many token tiles (takes_tiled) go to the matrix-core tiled kernels, unless the rules below say otherwise.
+    // The two thresholds (total workgroups of the tiled launches) exist for tuning only: on the mixed batches measured (640
+    // tokens with a 2048 x 5632 shared expert, 1056 tokens over 64 experts) the tiled kernels were equal to or 8 % faster
+    // than streaming the same groups in several passes, even at 150-200 workgroups.
     bool use_tiled = false;
     const bool early = early_tiled(c, counts_host, has_shared, T);
     // 4-bit contexts: the tiled groups are expanded to 16 bits and go through the 256 x 256 tiles when the groups of 32
@@ -679,8 +679,10 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 }
             } else if (tiled_dn_wgs < 256) {
                 const int stages_ref = c->tune.down_slices_by_longest_k ? tiled_stages_max : tiled_stages_min;
-                // Beside a streamed launch the tiled ones are hidden as long as both halves of them end before it does
-                // (5.5 TB/s of weights): then a slice more only costs planes (Mixtral-shaped 400 tokens 1405 -> 1338 us for two layers)
+                // Beside a streamed launch the tiled ones are hidden as long as both halves of them end before it does: then
+                // a slice more only costs planes (Mixtral-shaped 400 tokens 1405 -> 1338 us for two layers).  The streamed
+                // launches are taken at 5.5 TB/s of weights, which long ones reach; 110 workgroups of Qwen-shaped experts take
+                // 92 us where this says 35, so short ones count as hiding less than they do
                 const double unit_s = stages_ref * 0.77e-6;
                 const double plane_s = (double)tiled_rows * d * 8.0 / 5e12, stream_s = stream_bytes / 5.5e12;
                 const double up_s = (double)((tiled_up_wgs + 255) / 256) * (d / 32) * 0.6e-6;
@@ -697,7 +699,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         // A shared FFN that streams with the routed experts has a K of its own.  It gets more slices, down to about the routed
         // ones' length, while one of its workgroups runs half as long again as the launch's work spread over two workgroups
         // per compute unit (Qwen-shaped, K 5632 against 1408, two layers: 100 tokens on 12 experts 253 -> 207 us, 200 tokens
-        // 420 -> 393, one token 150 -> 124); where the other groups fill that time anyway, more planes only cost
+        // 420 -> 393, one token 150 -> 124).  The routed ones' length is what keeps its slices from getting too short; where the other groups fill that time anyway, more planes only cost
         // (DeepSeek-shaped 32 tokens on 16 experts 183.7 -> 185.8, 4-bit 1000 tokens 508 -> 518).
         ksg_shared = ksg;
         if (has_shared && c->tune.down_split_slice_counts != 0) {
