@@ -33,14 +33,14 @@ struct GateArgs {
     float routed_scale;
     int32_t *hist[kMaxGates];      // per gate: [E] accumulated with integer atomics, or null
     int32_t *blockcounts;          // [ntiles,E] per-tile counts of gate 0, or null
-    int32_t *hist_tiles;           // null, or [G-1][ntiles][E]: gates 1.. leave per-tile counts here and `hist` alone
-                                   // (one-step launches with gate 0 = the current layer; group_scan_kernel adds them up)
     int gpw;                       // gates per workgroup (gpw * E <= 128 logit columns)
     int ksplit;                    // workgroups that share the K range of one (tile, gate group); >= 1
     int two_step;                  // 1: gate_kernel leaves partial logits, gate_finish_kernel does the per-token part
     int tsplit;                    // two_step: workgroups that share the 32 tokens of a tile in the finish (1, 2, 4)
     float *part;                   // two_step: [tiles][groups][ksplit][32][32 * column blocks] partial logits
     int stream;                    // 1: launches that qualify (gate_stream_ok) take the streaming form of the kernel
+    int32_t *hist_tiles;           // null, or [G-1][ntiles][E]: gates 1.. leave per-tile counts here and `hist` alone
+                                   // (one-step launches with gate 0 = the current layer; group_scan_kernel adds them up)
 };
 
 // Grouped FFN launch: one group per active expert (+ one for the dense shared FFN).

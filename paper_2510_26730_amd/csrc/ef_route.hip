@@ -46,7 +46,7 @@ __device__ __forceinline__ T pick(const T (&arr)[kMaxGates], int idx) {
     return v;
 }
 
-template <int NB, int NW = kGateWaves>
+template <int NB, int NW = kGateWaves, bool TILE_HISTS = true>
 __device__ __forceinline__ void gate_epilogue(const GateArgs &a, float (*logits)[NB * 32 + 1], int *cnt,
                                               const float *sbias, float (*s_sc)[64],
                                               int tile, int g0, int Gl, int tok_lo, int tok_n, bool shared_tile);
@@ -241,8 +241,9 @@ __global__ __launch_bounds__(64 * kGateWaves) void gate_kernel(GateArgs a) {
 }
 
 // per-token part of the gate kernels: selection scores, biased top-k, combine weights, counts.
-// `logits` holds the tile's router logits without the gate bias (sbias), `cnt` is zeroed.
-template <int NB, int NW>
+// `logits` holds the tile's router logits without the gate bias (sbias), `cnt` is zeroed.  TILE_HISTS: the launch may ask
+// for per-tile counts of the look-ahead gates (a second gate step never does).
+template <int NB, int NW, bool TILE_HISTS>
 __device__ __forceinline__ void gate_epilogue(const GateArgs &a, float (*logits)[NB * 32 + 1], int *cnt,
                                               const float *sbias, float (*s_sc)[64],
                                               int tile, int g0, int Gl, int tok_lo, int tok_n, bool shared_tile) {
@@ -326,7 +327,7 @@ __device__ __forceinline__ void gate_epilogue(const GateArgs &a, float (*logits)
     for (int x = tid; x < N; x += NT) {
         const int gi = g0 + x / a.E, ee = x % a.E;
         int32_t *hp = pick(a.hist, gi);
-        if (hp && a.hist_tiles) a.hist_tiles[((size_t)(gi - 1) * ((a.T + kTile - 1) / kTile) + tile) * a.E + ee] = cnt[x];
+        if (TILE_HISTS && hp && a.hist_tiles) a.hist_tiles[((size_t)(gi - 1) * ((a.T + kTile - 1) / kTile) + tile) * a.E + ee] = cnt[x];
         else if (hp && cnt[x] > 0) atomicAdd(&hp[ee], cnt[x]);
         if (a.blockcounts && gi == 0) {
             if (!shared_tile) a.blockcounts[(size_t)tile * a.E + ee] = cnt[x];
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(64 * kGateWaves) void gate_finish_kernel(GateArgs a
         logits[x / (NB * 32)][x % (NB * 32)] = v;
     }
     __syncthreads();
-    gate_epilogue<NB>(a, logits, cnt, sbias, s_sc, tile, g0, Gl, blockIdx.z * tok_n, tok_n, a.tsplit > 1);
+    gate_epilogue<NB, kGateWaves, false>(a, logits, cnt, sbias, s_sc, tile, g0, Gl, blockIdx.z * tok_n, tok_n, a.tsplit > 1);
 }
 
 template <int NB>
