@@ -130,8 +130,10 @@ struct ef_ctx {
     // what the last ef_layer_step saw (ef_layer_step_fetch)
     int last_T = 0, last_He = 0;
     int32_t last_hist[EF_MAX_HORIZON * EF_MAX_EXPERTS] = {};
-    // side stream on which a phase's tiled launches run beside its streamed launches, and the fork / join events
+    // side stream on which a phase's streamed launches run beside its tiled launches, and the fork / join events
     hipStream_t side_stream = nullptr;
+    bool forks = false;              // the last layer's first phase took both streams: the next one is likely to
+    bool side_waits = false;         // ef_layer_step already made the side stream wait for the coming ef_moe_ffn's tokens
     std::vector<hipEvent_t> fork_ring;
     size_t fork_next = 0;
     // event rings
@@ -202,6 +204,12 @@ int copy_engine_drain(ef_ctx *c);        // until the queue is empty (statistics
 // fake-copy contexts: run the queue up to the fake clock / until the copies into these slots are complete
 void fake_copy_advance(ef_ctx *c, double now);
 double fake_copy_wait(ef_ctx *c, const int *slots, int n);
+
+inline hipEvent_t next_fork_event(ef_ctx *c) {
+    hipEvent_t ev = c->fork_ring[c->fork_next];
+    c->fork_next = (c->fork_next + 1) % c->fork_ring.size();
+    return ev;
+}
 
 // Brackets one kernel launch with events on the launch stream when profiling is on.
 struct KernelTimer {

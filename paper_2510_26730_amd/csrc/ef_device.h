@@ -6,6 +6,7 @@
 // An operand fragment is therefore 64 lanes x 16 bytes = one contiguous 1 KiB read when the data
 // is stored in fragment order (expert weights, packed tokens, activations).
 #pragma once
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
@@ -61,6 +62,14 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
 __device__ __forceinline__ void zero16(floatx16 &a) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) a[v] = 0.f;
+}
+
+// a launch whose completion is the event `done`, if that is not null (a record behind it would be a packet of its own)
+template <class Kernel, class... Args>
+inline hipError_t launch_done(Kernel kernel, dim3 grid, dim3 block, hipEvent_t done, hipStream_t s, Args... args) {
+    if (done) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, nullptr, done, 0, args...);
+    else hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
+    return hipGetLastError();
 }
 
 // Orders a wave's LDS accesses before its later ones where lanes meet each other's data.  The hardware runs a wave's LDS

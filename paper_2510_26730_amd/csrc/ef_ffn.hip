@@ -5,8 +5,6 @@
 // sees few tokens (decode); every weight fragment is then used exactly once.  The kernels are
 // therefore built around long, contiguous, software-pipelined 1 KiB fragment streams per wave and
 // enough waves in flight; the matrix cores only have to keep up.
-#include <hip/hip_ext.h>
-
 #include "ef_device.h"
 #include "ef_kernels.h"
 
@@ -128,15 +126,14 @@ __global__ __launch_bounds__(256) void pack_x_dev_kernel(const int32_t *__restri
 
 hipError_t launch_pack_x_dev(const int32_t *counts, const int32_t *offsets, int E, bool has_shared, int T,
                              int max_tiles, const uint16_t *h, int d, int k, const int32_t *perm, void *xp,
-                             bool f16, hipStream_t s) {
+                             bool f16, hipEvent_t done, hipStream_t s) {
     if (max_tiles <= 0) return hipSuccess;
     const int nkb = d >> 4;
     int chunks = 1;
     while (max_tiles * chunks < 1024 && nkb / (chunks * 2) >= 8) chunks *= 2;
     const int kb_per_wg = (nkb + chunks - 1) / chunks;
-    hipLaunchKernelGGL(pack_x_dev_kernel, dim3(max_tiles, chunks), dim3(256), 0, s, counts, offsets, E,
+    return launch_done(pack_x_dev_kernel, dim3(max_tiles, chunks), dim3(256), done, s, counts, offsets, E,
                        has_shared ? 1 : 0, T, h, d, k, perm, reinterpret_cast<uint4 *>(xp), kb_per_wg, f16 ? 1 : 0);
-    return hipGetLastError();
 }
 
 // K loop of the first FFN half for NTL live token tiles: three register stages of UNR fragments per
@@ -484,19 +481,18 @@ __global__ __launch_bounds__(256, 2) void ffn_down_kernel(GroupTable gt, const u
 }
 
 hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act,
-                           float *y, long long y_plane, int d, hipStream_t s) {
+                           float *y, long long y_plane, int d, hipEvent_t done, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
     for (int i = 0; i < gt.n_groups; ++i)
         if (gt.ksg[i] < 1) return hipErrorInvalidValue;
     const uint4 *a = reinterpret_cast<const uint4 *>(act);
     if (tiles_per_pass == 1)
-        hipLaunchKernelGGL((ffn_down_kernel<1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
+        return launch_done(ffn_down_kernel<1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 2)
-        hipLaunchKernelGGL((ffn_down_kernel<2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
+        return launch_done(ffn_down_kernel<2>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
-        hipLaunchKernelGGL((ffn_down_kernel<4>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+        return launch_done(ffn_down_kernel<4>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
+    return hipErrorInvalidValue;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -541,13 +537,8 @@ hipError_t launch_combine(const float *y, const PlaneTable &planes, long long y_
                           const int32_t *ids, const int32_t *inv_perm, int T, int k, int d, long long shared_row0,
                           float *out, hipEvent_t done, hipStream_t s) {
     if (T <= 0) return hipSuccess;
-    if (done)
-        hipExtLaunchKernelGGL(combine_kernel, dim3(T, (d + 1023) / 1024), dim3(256), 0, s, nullptr, done, 0, y, planes,
-                              y_plane, w, ids, inv_perm, T, k, d, shared_row0, out);
-    else
-        hipLaunchKernelGGL(combine_kernel, dim3(T, (d + 1023) / 1024), dim3(256), 0, s, y, planes, y_plane, w, ids,
-                           inv_perm, T, k, d, shared_row0, out);
-    return hipGetLastError();
+    return launch_done(combine_kernel, dim3(T, (d + 1023) / 1024), dim3(256), done, s, y, planes, y_plane, w, ids, inv_perm, T,
+                       k, d, shared_row0, out);
 }
 
 }  // namespace ef

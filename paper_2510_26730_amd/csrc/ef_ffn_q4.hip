@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256, TT == 4 ? 2 : 1) void ffn_down_q4_kernel(Group
 }
 
 hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act,
-                              float *y, long long y_plane, int d, hipStream_t s) {
+                              float *y, long long y_plane, int d, hipEvent_t done, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
     if (d % 128 != 0) return hipErrorInvalidValue;
     for (int i = 0; i < gt.n_groups; ++i)
@@ -443,13 +443,12 @@ hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *a = reinterpret_cast<const uint4 *>(act);
     if (tiles_per_pass == 1)
-        hipLaunchKernelGGL((ffn_down_q4_kernel<1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
+        return launch_done(ffn_down_q4_kernel<1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 2)
-        hipLaunchKernelGGL((ffn_down_q4_kernel<2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
+        return launch_done(ffn_down_q4_kernel<2>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
-        hipLaunchKernelGGL((ffn_down_q4_kernel<4>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+        return launch_done(ffn_down_q4_kernel<4>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
+    return hipErrorInvalidValue;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
 }
 
 hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act,
-                                  float *y, long long y_plane, int d, hipStream_t s) {
+                                  float *y, long long y_plane, int d, hipEvent_t done, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
     if (d % 64 != 0) return hipErrorInvalidValue;
     for (int i = 0; i < gt.n_groups; ++i)
@@ -300,13 +300,12 @@ hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *a = reinterpret_cast<const uint4 *>(act);
     if (tiles_per_pass == 2)
-        hipLaunchKernelGGL((ffn_down_shared_kernel<2, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
+        return launch_done(ffn_down_shared_kernel<2, kShDepth, 1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4 && occ == 2)
-        hipLaunchKernelGGL((ffn_down_shared_kernel<4, 2, 2>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
+        return launch_done(ffn_down_shared_kernel<4, 2, 2>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
-        hipLaunchKernelGGL((ffn_down_shared_kernel<4, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, a, y, d, y_plane);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+        return launch_done(ffn_down_shared_kernel<4, kShDepth, 1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace ef

@@ -101,16 +101,17 @@ hipError_t launch_gate_fused(const GateArgs &a, int32_t *counts, int32_t *offset
 hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, int k, int E, int32_t *blockbase,
                         int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv_perm,
                         const int32_t *hist_tiles, int n_hist, int32_t *hist, const GroupExport &ex, hipStream_t s);
-// f16: write fp16 instead of bf16 fragments (contexts with 4-bit experts)
+// f16: write fp16 instead of bf16 fragments (contexts with 4-bit experts).  `done` (here and below): null, or an event that
+// is recorded as the launch's own completion
 hipError_t launch_pack_x(const PackTable &pt, int total_tiles, const uint16_t *h, int d, int k,
                          const int32_t *perm, void *xp, bool f16, hipStream_t s);
 hipError_t launch_pack_x_dev(const int32_t *counts, const int32_t *offsets, int E, bool has_shared, int T,
                              int max_tiles, const uint16_t *h, int d, int k, const int32_t *perm, void *xp,
-                             bool f16, hipStream_t s);
+                             bool f16, hipEvent_t done, hipStream_t s);
 hipError_t launch_ffn_gate_up(const GroupTable &gt, int total_wgs, int tiles_per_pass, int ks, const void *xp,
                               void *act, int d, hipStream_t s);
 hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act, float *y,
-                           long long y_plane, int d, hipStream_t s);
+                           long long y_plane, int d, hipEvent_t done, hipStream_t s);
 // K-slice planes of Y each expert's rows (and the shared FFN's) were written to: the streamed and the tiled launch
 // of a layer choose their slice counts separately
 struct PlaneTable {
@@ -133,7 +134,7 @@ inline int ffn_down_q4_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) {
 hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, bool k_halves, const void *xp,
                                  void *act, int d, hipStream_t s);
 hipError_t launch_ffn_down_q4(const GroupTable &gt, int total_wgs, int tiles_per_pass, const void *act, float *y,
-                              long long y_plane, int d, hipStream_t s);
+                              long long y_plane, int d, hipEvent_t done, hipStream_t s);
 // Expands 4-bit expert blobs into 16-bit blobs of the bf16 layout whose elements are the fp16 numbers
 // (q - 8) * s, the same values the 4-bit kernels form on the fly: large groups then run through the
 // tiled matrix-core kernels, which read every weight many times.
@@ -221,7 +222,7 @@ inline int ffn_down_shared_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) 
 hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *xp,
                                      void *act, int d, hipStream_t s);
 hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act, float *y,
-                                  long long y_plane, int d, hipStream_t s);
+                                  long long y_plane, int d, hipEvent_t done, hipStream_t s);
 inline int ffn_down_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) {
     return (d / 32 / kDownColBlocks) * ((n_tiles + tiles_per_pass - 1) / tiles_per_pass) * ksg;
 }

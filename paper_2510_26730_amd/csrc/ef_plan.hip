@@ -208,11 +208,13 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
                  const std::vector<int> &offs_host, const std::vector<int> &tile_start,
                  const std::vector<long long> &act_off, int shared_tile_start, long long shared_act_off, int T,
                  int tpp_layer, int ksg_stream, int ksg_shared, int ksg_tiled, int split_expert, int split_ksg,
-                 ef::PlaneTable &planes, long long y_plane, bool use_tiled, bool early, bool expand, hipStream_t s) {
+                 ef::PlaneTable &planes, long long y_plane, bool use_tiled, bool early, bool expand, bool side_waits,
+                 bool *forked, hipStream_t s) {
     // tpp_layer: token tiles per pass that the layer's streamed groups would take in one launch.
     // split_expert: the tiled group of the layer (expert id, -1 = shared FFN, kNoSplit = none) whose second half takes
     // split_ksg K slices instead of ksg_tiled; it goes last among the tiled groups of its launch.  expand: the tiled groups
-    // of a 4-bit context are expanded to 16 bits first (else they run in passes of four tiles on the 4-bit blobs)
+    // of a 4-bit context are expanded to 16 bits first (else they run in passes of four tiles on the 4-bit blobs).
+    // side_waits: the side stream already waits for what this phase needs.  *forked: whether the phase took both streams
     if (groups.empty()) return EF_OK;
     const int d = c->cfg.d_model, k = c->cfg.top_k;
     // groups with many tokens go to the tiled (matrix-core bound) kernels, the others to the
@@ -284,36 +286,48 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             b_dn += wb * d * g.F[i] + 2.0 * g.count[i] * g.F[i] + 4.0 * g.count[i] * d;
         }
     };
-    // Set once this phase's tiled launches have been forked to the side stream.  Whatever path leaves this
-    // function afterwards (an error included), the caller's stream is made to wait for the side stream: the
-    // caller releases the phase's cache slots behind its own stream, and kernels still running on the side
+    // A phase with both kinds of groups runs its streamed launches on the side stream, beside the tiled ones: the two touch
+    // different groups (tiles of the packed tokens, activations, rows of Y), small tiled launches leave half of the compute
+    // units idle, and the streamed kernels are bound by HBM, not by compute units.  Fork: the side stream waits for
+    // everything enqueued so far (the token packing, the previous layer's un-permute); ef_layer_step has made it wait behind
+    // the packing while the routing ran where the previous layer forked too (13-16 us of host time that the compute units
+    // would otherwise idle through), else it waits for an event here.  Join: the caller's stream waits behind the last
+    // side-stream launch before anything after this phase.  Both events are completion events of the launches themselves: a
+    // separate record is a packet of its own (other stream 8.5 us after the forking kernel instead of 11.6, its own stream
+    // 2.6 instead of 5.7, join 7 instead of 11).
+    // Once `forked`, whatever path leaves this function (an error included) makes the caller's stream wait for the side
+    // stream: the caller releases the phase's cache slots behind its own stream, and kernels still running on the side
     // stream read those slots.
     struct SideJoin {
         ef_ctx *c;
         hipStream_t s;
         bool forked = false;
-        hipEvent_t join = nullptr;
-        hipEvent_t next_event() {
-            hipEvent_t ev = c->fork_ring[c->fork_next];
-            c->fork_next = (c->fork_next + 1) % c->fork_ring.size();
-            return ev;
-        }
-        hipError_t record() {   // behind the last launch on the side stream
-            join = next_event();
-            return hipEventRecord(join, c->side_stream);
-        }
+        hipEvent_t join = nullptr;   // completion of the last side-stream launch, once that has been enqueued
         hipError_t wait() {
             if (!forked) return hipSuccess;
-            hipError_t e = join ? hipSuccess : record();
+            hipError_t e = hipSuccess;
+            if (!join) {
+                join = next_fork_event(c);
+                e = hipEventRecord(join, c->side_stream);
+            }
             if (e == hipSuccess) e = hipStreamWaitEvent(s, join, 0);
             forked = false;
             return e;
         }
         ~SideJoin() { (void)wait(); }
     } side{c, s};
-    int tiled_up_wgs = 0;
+    const bool forks = n > 0 && nb > 0 && c->side_stream && c->tune.overlap_tiled != 0;
+    if (forks && !side_waits) {
+        hipEvent_t fork = next_fork_event(c);
+        EF_HIP(c, hipEventRecord(fork, s));
+        EF_HIP(c, hipStreamWaitEvent(c->side_stream, fork, 0));
+    }
+    side.forked = *forked = forks;
+    hipStream_t gs = forks ? c->side_stream : s;   // of the streamed launches
+    int tiled_up_wgs = 0, tiled_dn_wgs = 0;
+    double tb_up = 0.0, tb_dn = 0.0, tf_up = 0.0, tf_dn = 0.0;
+    ef::GroupTable bdn = big;
     if (nb > 0) {
-        ef::GroupTable bdn = big;
         int wg_up = 0, wg_dn = 0;
         // Workgroups go to the XCDs round-robin by index and hold one of an XCD's 32 compute units for their whole
         // K loop.  An XCD takes an eighth of a group's units; the eighths differ by one unit, and each group starts on the
@@ -353,47 +367,41 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         big.wg_start[nb] = wg_up;
         tiled_up_wgs = wg_up;
         bdn.wg_start[nb] = wg_dn;
-        double b_up = 0.0, b_dn = 0.0, f_up = 0.0, f_dn = 0.0;
-        alg_bytes(big, nb, b_up, b_dn);
+        tiled_dn_wgs = wg_dn;
+        alg_bytes(big, nb, tb_up, tb_dn);
         for (int i = 0; i < nb; ++i) {
-            f_up += 4.0 * big.count[i] * d * big.F[i];   // two d x F products, 2 flops per multiply-add
-            f_dn += 2.0 * big.count[i] * d * big.F[i];
+            tf_up += 4.0 * big.count[i] * d * big.F[i];   // two d x F products, 2 flops per multiply-add
+            tf_dn += 2.0 * big.count[i] * d * big.F[i];
         }
-        // A phase with both kinds of groups runs its tiled launches on the side stream, beside the streamed ones:
-        // the two touch different groups (tiles of the packed tokens, activations, rows of Y), small tiled launches
-        // leave half of the compute units idle, and the streamed kernels are bound by HBM, not by compute units.
-        // Fork: the side stream waits for everything enqueued so far (the token packing, the previous layer's
-        // un-permute).  Join: the caller's stream waits for the side stream before anything after this phase.
-        hipStream_t ts = s;
-        if (n > 0 && c->side_stream && c->tune.overlap_tiled != 0) {
-            hipEvent_t fork = side.next_event();
-            EF_HIP(c, hipEventRecord(fork, s));
-            EF_HIP(c, hipStreamWaitEvent(c->side_stream, fork, 0));
-            ts = c->side_stream;
-            side.forked = true;
-        }
-        if (c->q4 && !expand) {   // passes of four on the 4-bit blobs: counted with the streamed launches
-            {
-                KernelTimer kt(c, ts, EF_K_FFN_UP, b_up);
-                EF_HIP(c, ef::launch_ffn_gate_up_q4(big, wg_up, 4, false, c->xp, c->act, d, ts));
-            }
-            KernelTimer kt(c, ts, EF_K_FFN_DOWN, b_dn);
-            EF_HIP(c, ef::launch_ffn_down_q4(bdn, wg_dn, 4, c->act, c->y, y_plane, d, ts));
-        } else {
-            {
-                KernelTimer kt(c, ts, EF_K_FFN_UP_TILED, b_up, f_up);   // 4-bit: the expansion is timed with the first half
-                if (c->q4) {
-                    dq.n = nb;
-                    EF_HIP(c, ef::launch_dequant_q4(dq, d, ts));
-                }
-                EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, wg_up, c->xp, c->act, d, c->q4, ts));
-            }
-            KernelTimer kt(c, ts, EF_K_FFN_DOWN_TILED, b_dn, f_dn);
-            EF_HIP(c, ef::launch_ffn_down_tiled(bdn, wg_dn, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, ts));
-        }
-        if (side.forked) EF_HIP(c, side.record());
     }
-    if (n == 0) return EF_OK;
+    auto tiled_up = [&]() -> int {
+        if (c->q4 && !expand) {   // passes of four on the 4-bit blobs: counted with the streamed launches
+            KernelTimer kt(c, s, EF_K_FFN_UP, tb_up);
+            EF_HIP(c, ef::launch_ffn_gate_up_q4(big, tiled_up_wgs, 4, false, c->xp, c->act, d, s));
+            return EF_OK;
+        }
+        KernelTimer kt(c, s, EF_K_FFN_UP_TILED, tb_up, tf_up);   // 4-bit: the expansion is timed with the first half
+        if (c->q4) {
+            dq.n = nb;
+            EF_HIP(c, ef::launch_dequant_q4(dq, d, s));
+        }
+        EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, tiled_up_wgs, c->xp, c->act, d, c->q4, s));
+        return EF_OK;
+    };
+    auto tiled_down = [&]() -> int {
+        if (c->q4 && !expand) {
+            KernelTimer kt(c, s, EF_K_FFN_DOWN, tb_dn);
+            EF_HIP(c, ef::launch_ffn_down_q4(bdn, tiled_dn_wgs, 4, c->act, c->y, y_plane, d, nullptr, s));
+            return EF_OK;
+        }
+        KernelTimer kt(c, s, EF_K_FFN_DOWN_TILED, tb_dn, tf_dn);
+        EF_HIP(c, ef::launch_ffn_down_tiled(bdn, tiled_dn_wgs, ksg_tiled, split_grp, split_ksg, c->act, c->y, y_plane, d, s));
+        return EF_OK;
+    };
+    // both first halves before the second ones: the stream that is served last waits for one launch call, not for two
+    int rc = nb > 0 ? tiled_up() : EF_OK;
+    if (rc) return rc;
+    if (n == 0) return tiled_down();
     ef::GroupTable dn = gu;
     long long wgs_of_four = 0;
     for (int i = 0; i < n; ++i) wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
@@ -447,16 +455,19 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     const bool pairs = tiled_up_wgs < 128 ? wg_gu > (d > 2048 ? 512 : 256) || (wg_gu <= 128 && d <= 1024) : tiled_up_wgs > 256 && wg_gu <= 256;
     const int occ = c->tune.lds_shared_occupancy != 0 ? c->tune.lds_shared_occupancy : pairs ? 2 : 1;
     {
-        KernelTimer kt(c, s, EF_K_FFN_UP, b_up);
-        if (shared) EF_HIP(c, ef::launch_ffn_gate_up_shared(gu, wg_gu, tpp, occ, c->xp, c->act, d, s));
-        else if (c->q4) EF_HIP(c, ef::launch_ffn_gate_up_q4(gu, wg_gu, tpp, !large, c->xp, c->act, d, s));
-        else EF_HIP(c, ef::launch_ffn_gate_up(gu, wg_gu, tpp, ks, c->xp, c->act, d, s));
+        KernelTimer kt(c, gs, EF_K_FFN_UP, b_up);
+        if (shared) EF_HIP(c, ef::launch_ffn_gate_up_shared(gu, wg_gu, tpp, occ, c->xp, c->act, d, gs));
+        else if (c->q4) EF_HIP(c, ef::launch_ffn_gate_up_q4(gu, wg_gu, tpp, !large, c->xp, c->act, d, gs));
+        else EF_HIP(c, ef::launch_ffn_gate_up(gu, wg_gu, tpp, ks, c->xp, c->act, d, gs));
     }
+    if (nb > 0 && (rc = tiled_down())) return rc;
     {
-        KernelTimer kt(c, s, EF_K_FFN_DOWN, b_dn);
-        if (shared) EF_HIP(c, ef::launch_ffn_down_shared(dn, wg_dn, tpp, occ, c->act, c->y, y_plane, d, s));
-        else if (c->q4) EF_HIP(c, ef::launch_ffn_down_q4(dn, wg_dn, tpp, c->act, c->y, y_plane, d, s));
-        else EF_HIP(c, ef::launch_ffn_down(dn, wg_dn, tpp, c->act, c->y, y_plane, d, s));
+        KernelTimer kt(c, gs, EF_K_FFN_DOWN, b_dn);
+        hipEvent_t done = forks ? next_fork_event(c) : nullptr;
+        if (shared) EF_HIP(c, ef::launch_ffn_down_shared(dn, wg_dn, tpp, occ, c->act, c->y, y_plane, d, done, gs));
+        else if (c->q4) EF_HIP(c, ef::launch_ffn_down_q4(dn, wg_dn, tpp, c->act, c->y, y_plane, d, done, gs));
+        else EF_HIP(c, ef::launch_ffn_down(dn, wg_dn, tpp, c->act, c->y, y_plane, d, done, gs));
+        side.join = done;
     }
     EF_HIP(c, side.wait());
     return EF_OK;
@@ -467,9 +478,9 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
 extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const int32_t *topk_ids,
                           const float *topk_w, const int32_t *counts_host, const int32_t *offsets,
                           const int32_t *perm, const int32_t *inv_perm, float *out, void *stream) {
-    // set by ef_layer_step for the call it makes right afterwards; never survives this call
-    const bool prepacked = c && c->prepacked;
-    if (c) c->prepacked = false;
+    // set by ef_layer_step for the call it makes right afterwards; never survive this call
+    const bool prepacked = c && c->prepacked, side_waits = prepacked && c->side_waits;
+    if (c) c->prepacked = c->side_waits = false;
     int rc = check_ctx_layer(c, layer);
     if (rc) return rc;
     if (T < 0 || T > c->cfg.max_tokens) return fail(c, EF_EINVAL, "ef_moe_ffn: T=%d outside 0..max_tokens", T);
@@ -883,9 +894,11 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         std::vector<PhaseGroup> g = v;
         if (with_shared && has_shared) g.push_back({-1, -1});
         if (!c->fake) {
+            bool forked = false;
             int r = launch_phase(c, layer, g, counts_host, offs_host, tile_start, act_off, shared_tile_start,
                                  shared_act_off, T, tpp, ksg, ksg_shared, ksg_tiled, split_expert, split_ksg, planes, y_plane, use_tiled,
-                                 early, q4_expand, s);
+                                 early, q4_expand, with_shared && side_waits, &forked, s);
+            if (with_shared) c->forks = forked;
             if (r) {   // part of the phase may be enqueued: its slots still get their read marker
                 (void)mark_read(v);
                 v.clear();   // released: the caller's error path has nothing left to unpin
