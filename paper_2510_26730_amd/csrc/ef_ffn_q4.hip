@@ -66,19 +66,33 @@ __device__ __forceinline__ float q4_saturate(float v) {
     return v < -lim ? -lim : v;
 }
 
+// 16 rows of matrix A (weights) x 16 tokens, 32 inputs: lane l carries 8 inputs (group l / 16) of row, and of token, l % 16;
+// the accumulator lane l holds token l % 16 and rows 4 (l / 16) .. + 3.
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ floatx4_t mfma16h(u32x4_t a, u32x4_t b, floatx4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a), __builtin_bit_cast(half8_t, b), c, 0, 0, 0);
+}
+// x, y: a dword per lane of two fragments (32 rows, lanes 32 g + i) -> lo: of rows 0..15, hi: of rows 16..31, lane l row
+// l % 16, with the inputs of its quarter l / 16 = 2 g + f from half g of fragment f (0: x, 1: y).  For x = y: a value per row
+// in the lanes of that row.
+__device__ __forceinline__ void split_rows(uint32_t x, uint32_t y, uint32_t &lo, uint32_t &hi) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    lo = r[0];
+    hi = r[1];
+}
+
 // register ring: stages in flight per wave (four were measured slower than six with two token tiles per pass
 // and one wave per SIMD)
 constexpr int kQ4Depth = 6;
 constexpr int kQ4Lds = 4;     // LDS ring of shared token / activation fragments (stages)
 
-// K loop of the first half for NTL live token tiles of a pass of TT: stages [k0, k0 + nloc) of 64 inputs each, `xs` the
-// LDS ring of the four waves that share these stages.  The number of live tiles is the same for a whole workgroup.
-template <int TT, int NTL, int D>
-__device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, const uint16_t *__restrict__ sA,
-                                             const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int k0, int nloc,
-                                             int wave, int lane, floatx16 (&G)[TT], floatx16 (&U)[TT]) {
-    u32x4_t qa[D], qb[D], xr[D][NTL];
-    uint16_t sa[D], sb[D];
+// The K loops of the first half share everything but a stage's arithmetic (COMPUTE).  A stage: hand the next stage's token
+// fragments to the workgroup, compute this one, refill the register slot just used, barrier (the next stage's fragments are
+// visible; this stage's LDS buffer is overwritten three stages from now).  Loads are unconditional: past the end the last
+// stage is read again.
+// a scale holds for two stages: where the loop starts at an even one (PAIRS) and the ring has an even length, the even slots
+// hold the even stages and only those load it
+#define EF_Q4U_SCALES(slot) (!PAIRS || D % 2 != 0 || (slot) % 2 == 0)
 #define EF_Q4U_LOAD(slot, kq)                                                                             \
     {                                                                                                     \
         const int kc_ = k0 + min((kq), nloc - 1);                                                         \
@@ -87,20 +101,51 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
         __builtin_amdgcn_sched_barrier(0);                                                                \
         qa[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w13 + (size_t)kc_ * 128));       \
         qb[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w13 + (size_t)kc_ * 128 + 64));  \
-        sa[slot] = sA[(size_t)(kc_ >> 1) * 64];                                                           \
-        sb[slot] = sA[(size_t)(kc_ >> 1) * 64 + 32];                                                      \
+        if (EF_Q4U_SCALES(slot)) {                                                                        \
+            sa[slot] = sA[(size_t)(kc_ >> 1) * 64];                                                       \
+            sb[slot] = sA[(size_t)(kc_ >> 1) * 64 + 32];                                                  \
+        }                                                                                                 \
     }
 #define EF_Q4U_SHARE(slot, st)                                                                            \
     {                                                                                                     \
         _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
     }
+#define EF_Q4U_STAGE(COMPUTE, slot, next_slot, st)                                                        \
+    {                                                                                                     \
+        EF_Q4U_SHARE(next_slot, (st) + 1)                                                                 \
+        COMPUTE(slot, st)                                                                                 \
+        EF_Q4U_LOAD(slot, (st) + D)                                                                       \
+        __syncthreads();                                                                                  \
+    }
+#define EF_Q4U_RUN(COMPUTE)                                                                               \
+    {                                                                                                     \
+        _Pragma("unroll") for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_LOAD(ring_, ring_)               \
+        EF_Q4U_SHARE(0, 0)                                                                                \
+        __syncthreads();                                                                                  \
+        int st = 0;                                                                                       \
+        for (; st + D <= nloc; st += D) {                                                                 \
+            _Pragma("unroll") for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_STAGE(COMPUTE, ring_, (ring_ + 1) % D, st + ring_) \
+        }                                                                                                 \
+        _Pragma("unroll") for (int ring_ = 0; ring_ < D - 1; ++ring_)                                     \
+            if (st + ring_ < nloc) EF_Q4U_STAGE(COMPUTE, ring_, ring_ + 1, st + ring_)                    \
+    }
+
+// K loop of the first half for NTL live token tiles of a pass of four: stages [k0, k0 + nloc) of 64 inputs each, `xs` the
+// LDS ring of the four waves that share these stages.  The number of live tiles is the same for a whole workgroup.
+template <int TT, int NTL, int D, bool PAIRS>
+__device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, const uint16_t *__restrict__ sA,
+                                             const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int k0, int nloc,
+                                             int wave, int lane, floatx16 (&G)[TT], floatx16 (&U)[TT]) {
+    u32x4_t qa[D], qb[D], xr[D][NTL];
+    uint16_t sa[D], sb[D];
+    q4_half2 f1_, f3_;
     // The MFMAs of a k-step are issued between the vector instructions that dequantise the next
     // k-step's fragments (one MFMA, then a share of the ~40 vector instructions), so the matrix
     // cores work while the wave converts: a wave issues in order and has the SIMD to itself, nothing
     // else would overlap the two.
 #define EF_Q4U_COMPUTE(slot, st)                                                                          \
     {                                                                                                     \
-        const q4_half2 f1_ = q4_scale(sa[slot]), f3_ = q4_scale(sb[slot]);                                \
+        if (EF_Q4U_SCALES(slot)) { f1_ = q4_scale(sa[slot]); f3_ = q4_scale(sb[slot]); }                   \
         u32x4_t xb_[NTL][4];                                                                              \
         _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt)                                                \
             _Pragma("unroll") for (int j = 0; j < (NTL > 2 ? 1 : 4); ++j) xb_[tt][j] = xs[(st) & (kQ4Lds - 1)][tt * 4 + j][lane]; \
@@ -125,33 +170,72 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
             a1_ = n1_; a3_ = n3_;                                                                         \
         }                                                                                                 \
     }
-    // one stage: hand the next stage's token fragments to the workgroup, compute this one, refill the
-    // register slot just used, barrier (the next stage's fragments are visible; this stage's LDS
-    // buffer is overwritten three stages from now)
-#define EF_Q4U_STAGE(slot, next_slot, st)                                                                 \
-    {                                                                                                     \
-        EF_Q4U_SHARE(next_slot, (st) + 1)                                                                 \
-        EF_Q4U_COMPUTE(slot, st)                                                                          \
-        EF_Q4U_LOAD(slot, (st) + D)                                                                       \
-        __syncthreads();                                                                                  \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_LOAD(ring_, ring_)
-    EF_Q4U_SHARE(0, 0)
-    __syncthreads();
-    int st = 0;
-    for (; st + D <= nloc; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4U_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < nloc) EF_Q4U_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_Q4U_LOAD
-#undef EF_Q4U_SHARE
+    EF_Q4U_RUN(EF_Q4U_COMPUTE)
 #undef EF_Q4U_COMPUTE
-#undef EF_Q4U_STAGE
 }
+
+// K loop of the first half for a pass of one or two token tiles whose last one is half live, NH half tiles of 16 tokens: as
+// q4_up_stream, with the matrix work in steps of 16 tokens (G, U: [row half][half tile]).  Most experts of a decode batch have
+// no more than 16 tokens, and these kernels are bound by conversion and matrix work that hardly overlap (eight Mixtral-shaped
+// experts, 64 tokens, first half 137 us: its loads alone 92, its arithmetic alone 88, of that the conversions alone 60 and the
+// matrix instructions alone 58).  The codes of two k-steps are regrouped by rows before they are converted (one lane exchange
+// per pair of dwords), so the instruction of 16 rows x 16 tokens takes 32 inputs of a quad's row; the token fragments are read
+// from LDS in the same order of inputs.  Two layers, with 32 x 32 x 16 for all: 8 / 30 / 64 tokens on eight Mixtral-shaped
+// experts 313 -> 297 / 364 -> 338 / 395 -> 366 us, 100 tokens on 64 DeepSeek-shaped 203 -> 195.  A whole number of tiles
+// keeps the larger instruction: the same matrix time, fewer instructions (as half tiles 64 tokens on two experts 189 -> 192).
+template <int TT, int NH, int D, bool PAIRS>
+__device__ __forceinline__ void q4_up_stream16(const uint4 *__restrict__ w13, const uint16_t *__restrict__ sA,
+                                               const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int k0, int nloc,
+                                               int wave, int lane, floatx4_t (&G)[2][2 * TT - 1], floatx4_t (&U)[2][2 * TT - 1]) {
+    constexpr int NTL = (NH + 1) / 2;
+    u32x4_t qa[D], qb[D], xr[D][NTL];
+    uint16_t sa[D], sb[D];
+    uint32_t f_[4];   // scales of the current stages: matrix, row half
+    const int rd = ((lane >> 4) & 1) * 64 + (lane >> 5) * 32 + (lane & 15);   // inputs of quarter l / 16: fragment l / 16 % 2, half l / 32
+    // operand x of a stage: k-steps 2 (x / 4) and the next, matrix and row half x % 4; the conversion of operand x + 1 is
+    // issued between the matrix instructions of operand x
+#define EF_Q4U_COMPUTE(slot, st)                                                                          \
+    {                                                                                                     \
+        u32x4_t xb_[NH][2];                                                                               \
+        _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                    \
+            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
+                xb_[h][p] = (&xs[(st) & (kQ4Lds - 1)][(h >> 1) * 4 + 2 * p][0])[rd + 16 * (h & 1)];       \
+        uint32_t cd_[8]; /* codes of operand x */                                                         \
+        if (EF_Q4U_SCALES(slot)) {                                                                        \
+            const uint32_t fa_ = __builtin_bit_cast(uint32_t, q4_scale(sa[slot])), fb_ = __builtin_bit_cast(uint32_t, q4_scale(sb[slot])); \
+            split_rows(fa_, fa_, f_[0], f_[1]);                                                           \
+            split_rows(fb_, fb_, f_[2], f_[3]);                                                           \
+        }                                                                                                 \
+        _Pragma("unroll") for (int p = 0; p < 2; ++p) {                                                   \
+            split_rows(qa[slot][2 * p], qa[slot][2 * p + 1], cd_[4 * p], cd_[4 * p + 1]);                 \
+            split_rows(qb[slot][2 * p], qb[slot][2 * p + 1], cd_[4 * p + 2], cd_[4 * p + 3]);             \
+        }                                                                                                 \
+        u32x4_t w_ = dequant_q4(cd_[0], __builtin_bit_cast(q4_half2, f_[0]));                                     \
+        _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                                   \
+            u32x4_t n_ = w_;                                                                              \
+            if (x < 7) n_ = dequant_q4(cd_[x + 1], __builtin_bit_cast(q4_half2, f_[(x + 1) & 3]));        \
+            _Pragma("unroll") for (int h = 0; h < NH; ++h) {                                              \
+                if (x & 2) U[x & 1][h] = mfma16h(w_, xb_[h][x >> 2], U[x & 1][h]);                        \
+                else G[x & 1][h] = mfma16h(w_, xb_[h][x >> 2], G[x & 1][h]);                              \
+            }                                                                                             \
+            if (x < 7) {                                                                                  \
+                _Pragma("unroll") for (int q_ = 0; q_ < NH; ++q_) {                                       \
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
+                    __builtin_amdgcn_sched_group_barrier(0x002, (14 + NH - 1) / NH, 0);                   \
+                }                                                                                         \
+            }                                                                                             \
+            w_ = n_;                                                                                      \
+        }                                                                                                 \
+    }
+    EF_Q4U_RUN(EF_Q4U_COMPUTE)
+#undef EF_Q4U_COMPUTE
+}
+
+#undef EF_Q4U_RUN
+#undef EF_Q4U_STAGE
+#undef EF_Q4U_SHARE
+#undef EF_Q4U_LOAD
+#undef EF_Q4U_SCALES
 
 // ------------------------------------------------------------------------------------------
 // first half: act = silu(X W1^T) * (X W3^T).  Workgroup = (group, pass of TT token tiles, four
@@ -195,24 +279,78 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
     const uint4 *w13 = reinterpret_cast<const uint4 *>(blob) + (size_t)rb * nq * 128 + lane;
     const uint16_t *sA = reinterpret_cast<const uint16_t *>(blob + (size_t)3 * d * F / 2) +
                          (size_t)rb * (d >> 7) * 64 + (lane & 31);
+    // live half tiles of 16 tokens (passes of one or two tiles work in those; of a half live tile they read the tokens that
+    // exist twice, the same cache lines)
+    const int nh = min((gt.count[grp] - pass * TT * kTile + 15) >> 4, 2 * TT);
     // this wave's share of the token fragments of a stage: k-step `wave` of each tile (tiles past the
     // group's last one repeat it; their results are dropped)
     const uint4 *xsrc[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u)
-        xsrc[u] = xp + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 64 + lane;
+        xsrc[u] = xp + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 64 +
+                  (TT < 4 && nh == 2 * u + 1 ? lane & ~16 : lane);
+
+    if constexpr (TT < 4) if (nh & 1) {
+        constexpr int HT = 2 * TT - 1;   // half tiles of a pass with a half live tile
+        floatx4_t G[2][HT], U[2][HT];   // [row half][half tile of 16 tokens]
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int h = 0; h < HT; ++h) G[r][h] = U[r][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        if (TT == 1 || nh == 1) q4_up_stream16<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+        else q4_up_stream16<TT, 2 * TT - 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+
+        if constexpr (KH == 2) {
+            // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
+            floatx4_t *red = reinterpret_cast<floatx4_t *>(&xs[0][0][0][0]) + (size_t)wave * (4 * HT) * 64 + lane;
+            static_assert(sizeof(xs) >= (size_t)4 * (4 * HT) * 64 * sizeof(floatx4_t), "partial sums fit the ring's space");
+            if (kh == 1) {
+#pragma unroll
+                for (int r = 0; r < 2; ++r)
+#pragma unroll
+                    for (int h = 0; h < HT; ++h) {
+                        red[((r * HT + h) * 2) * 64] = G[r][h];
+                        red[((r * HT + h) * 2 + 1) * 64] = U[r][h];
+                    }
+            }
+            __syncthreads();
+            if (kh == 1) return;
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int h = 0; h < HT; ++h) {
+                    G[r][h] += red[((r * HT + h) * 2) * 64];
+                    U[r][h] += red[((r * HT + h) * 2 + 1) * 64];
+                }
+        }
+        // a lane holds four F-values of one token in each row half: half of its 16 bytes of the paired-order fragment (fp16)
+        // of that row half, rows 4 (l / 16) .. + 3 being elements 4 (l / 32) .. + 3 of half l / 16 % 2
+        const int nkb2 = F >> 4, p = lane >> 4;
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+            if (h >= nh) break;
+            uint2 *dst = reinterpret_cast<uint2 *>(act + gt.act_off[grp] + ((size_t)(pass * TT + (h >> 1)) * nkb2 + rb * 2) * 64 +
+                                                   (p & 1) * 32 + 16 * (h & 1) + (lane & 15)) + (p >> 1);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                float v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = q4_saturate(G[r][h][q] / (1.f + __expf(-G[r][h][q])) * U[r][h][q]);
+                dst[(size_t)r * 128] = make_uint2(__builtin_bit_cast(uint32_t, q4_half2{(_Float16)v[0], (_Float16)v[1]}),
+                                                  __builtin_bit_cast(uint32_t, q4_half2{(_Float16)v[2], (_Float16)v[3]}));
+            }
+        }
+        return;
+    }
 
     floatx16 G[TT], U[TT];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
 
-    // Groups of one live token tile take a loop of their own: half of the matrix-core work, LDS reads and token loads.
-    // In a launch of passes of two most experts have one (eight Mixtral-shaped experts, 64 tokens: 157 -> 131 us; passes
-    // of one tile for everybody instead dequantise twice where there are two: 412 against 399 us for two layers).
-    if (TT == 1 || ntl == 1) q4_up_stream<TT, 1, D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-    else if (TT == 2 || ntl == 2) q4_up_stream<TT, (TT > 1 ? 2 : 1), D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-    else if (ntl == 3) q4_up_stream<TT, (TT > 2 ? 3 : TT), D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-    else q4_up_stream<TT, TT, D>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    if (TT == 1 || ntl == 1) q4_up_stream<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    else if (TT == 2 || ntl == 2) q4_up_stream<TT, (TT > 1 ? 2 : 1), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    else if (ntl == 3) q4_up_stream<TT, (TT > 2 ? 3 : TT), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    else q4_up_stream<TT, TT, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
 
     if constexpr (KH == 2) {
         // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
@@ -287,14 +425,7 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     return hipGetLastError();
 }
 
-// K loop of the second half, as q4_up_stream: stages [q0, q1) of the nq stages of F
-template <int TT, int NTL, int D, int CBW>
-__device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, size_t qstride,
-                                               const uint16_t *__restrict__ sB, size_t sstride,
-                                               const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
-                                               int q1, int wave, int lane, floatx16 (&acc)[CBW][TT]) {
-    u32x4_t qw[D][CBW], ar[D][NTL];
-    uint16_t sc[D][CBW];
+// The K loops of the second half, as those of the first
 #define EF_Q4D_LOAD(slot, kq)                                                                             \
     {                                                                                                     \
         const int kc_ = min((kq), nq - 1);                                                                \
@@ -311,6 +442,34 @@ __device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, si
     {                                                                                                     \
         _Pragma("unroll") for (int u = 0; u < NTL; ++u) as[(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = ar[slot][u]; \
     }
+#define EF_Q4D_STAGE(COMPUTE, slot, next_slot, st)                                                        \
+    {                                                                                                     \
+        EF_Q4D_SHARE(next_slot, (st) + 1)                                                                 \
+        COMPUTE(slot, st)                                                                                 \
+        EF_Q4D_LOAD(slot, (st) + D)                                                                       \
+        __syncthreads();                                                                                  \
+    }
+#define EF_Q4D_RUN(COMPUTE)                                                                               \
+    {                                                                                                     \
+        _Pragma("unroll") for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_LOAD(ring_, q0 + ring_)          \
+        EF_Q4D_SHARE(0, q0)                                                                               \
+        __syncthreads();                                                                                  \
+        int st = q0;                                                                                      \
+        for (; st + D <= q1; st += D) {                                                                   \
+            _Pragma("unroll") for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_STAGE(COMPUTE, ring_, (ring_ + 1) % D, st + ring_) \
+        }                                                                                                 \
+        _Pragma("unroll") for (int ring_ = 0; ring_ < D - 1; ++ring_)                                     \
+            if (st + ring_ < q1) EF_Q4D_STAGE(COMPUTE, ring_, ring_ + 1, st + ring_)                      \
+    }
+
+// K loop of the second half for passes of four token tiles, as q4_up_stream: stages [q0, q1) of the nq stages of F
+template <int TT, int NTL, int D, int CBW>
+__device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, size_t qstride,
+                                               const uint16_t *__restrict__ sB, size_t sstride,
+                                               const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
+                                               int q1, int wave, int lane, floatx16 (&acc)[CBW][TT]) {
+    u32x4_t qw[D][CBW], ar[D][NTL];
+    uint16_t sc[D][CBW];
     // as in the first half: the MFMAs of one weight fragment are issued between the vector
     // instructions that dequantise the next one
 #define EF_Q4D_COMPUTE(slot, st)                                                                          \
@@ -335,30 +494,57 @@ __device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, si
             w_ = n_;                                                                                      \
         }                                                                                                 \
     }
-#define EF_Q4D_STAGE(slot, next_slot, st)                                                                 \
-    {                                                                                                     \
-        EF_Q4D_SHARE(next_slot, (st) + 1)                                                                 \
-        EF_Q4D_COMPUTE(slot, st)                                                                          \
-        EF_Q4D_LOAD(slot, (st) + D)                                                                       \
-        __syncthreads();                                                                                  \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_LOAD(ring_, q0 + ring_)
-    EF_Q4D_SHARE(0, q0)
-    __syncthreads();
-    int st = q0;
-    for (; st + D <= q1; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4D_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < q1) EF_Q4D_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_Q4D_LOAD
-#undef EF_Q4D_SHARE
+    EF_Q4D_RUN(EF_Q4D_COMPUTE)
 #undef EF_Q4D_COMPUTE
-#undef EF_Q4D_STAGE
 }
+
+// passes of one or two token tiles, as q4_up_stream16 (acc: [column block][half of its columns][half tile])
+template <int TT, int NH, int D, int CBW>
+__device__ __forceinline__ void q4_down_stream16(const uint4 *__restrict__ w2q, size_t qstride,
+                                                 const uint16_t *__restrict__ sB, size_t sstride,
+                                                 const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
+                                                 int q1, int wave, int lane, floatx4_t (&acc)[CBW][2][2 * TT - 1]) {
+    constexpr int NTL = (NH + 1) / 2;
+    u32x4_t qw[D][CBW], ar[D][NTL];
+    uint16_t sc[D][CBW];
+    const int rd = ((lane >> 4) & 1) * 64 + (lane >> 5) * 32 + (lane & 15);
+    // operand x of a stage: column block x / 4, k-steps 2 (x / 2 % 2) and the next, half x % 2 of the block's columns
+#define EF_Q4D_COMPUTE(slot, st)                                                                          \
+    {                                                                                                     \
+        u32x4_t af_[NH][2];                                                                               \
+        _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                    \
+            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
+                af_[h][p] = (&as[(st) & (kQ4Lds - 1)][(h >> 1) * 4 + 2 * p][0])[rd + 16 * (h & 1)];       \
+        uint32_t f_[2 * CBW], cd_[4 * CBW]; /* scales; codes of operand x */                              \
+        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw) {                                              \
+            const uint32_t fs_ = __builtin_bit_cast(uint32_t, q4_scale(sc[slot][cw]));                    \
+            split_rows(fs_, fs_, f_[2 * cw], f_[2 * cw + 1]);                                             \
+            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
+                split_rows(qw[slot][cw][2 * p], qw[slot][cw][2 * p + 1], cd_[4 * cw + 2 * p], cd_[4 * cw + 2 * p + 1]); \
+        }                                                                                                 \
+        u32x4_t w_ = dequant_q4(cd_[0], __builtin_bit_cast(q4_half2, f_[0]));                             \
+        _Pragma("unroll") for (int x = 0; x < 4 * CBW; ++x) {                                             \
+            const int y_ = x + 1;                                                                         \
+            u32x4_t n_ = w_;                                                                              \
+            if (y_ < 4 * CBW) n_ = dequant_q4(cd_[y_], __builtin_bit_cast(q4_half2, f_[2 * (y_ >> 2) + (y_ & 1)])); \
+            _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                \
+                acc[x >> 2][x & 1][h] = mfma16h(w_, af_[h][(x >> 1) & 1], acc[x >> 2][x & 1][h]);         \
+            if (y_ < 4 * CBW) {                                                                           \
+                _Pragma("unroll") for (int q_ = 0; q_ < NH; ++q_) {                                       \
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
+                    __builtin_amdgcn_sched_group_barrier(0x002, (14 + NH - 1) / NH, 0);                   \
+                }                                                                                         \
+            }                                                                                             \
+            w_ = n_;                                                                                      \
+        }                                                                                                 \
+    }
+    EF_Q4D_RUN(EF_Q4D_COMPUTE)
+#undef EF_Q4D_COMPUTE
+}
+#undef EF_Q4D_RUN
+#undef EF_Q4D_STAGE
+#undef EF_Q4D_SHARE
+#undef EF_Q4D_LOAD
 
 // ------------------------------------------------------------------------------------------
 // second half: Y = act W2^T.  Workgroup = (group, pass of TT token tiles, eight consecutive
@@ -367,7 +553,7 @@ __device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, si
 // Each K-slice writes its own partial Y plane; the un-permute sums the planes in order.
 // ------------------------------------------------------------------------------------------
 template <int TT>
-__global__ __launch_bounds__(256, TT == 4 ? 2 : 1) void ffn_down_q4_kernel(GroupTable gt, const uint4 *__restrict__ act,
+__global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, const uint4 *__restrict__ act,
                                                              float *__restrict__ Y, int d,
                                                              long long y_plane) {
     constexpr int D = TT == 4 ? 3 : kQ4Depth, CBW = 2;
@@ -394,10 +580,40 @@ __global__ __launch_bounds__(256, TT == 4 ? 2 : 1) void ffn_down_q4_kernel(Group
     const uint4 *w2q = reinterpret_cast<const uint4 *>(blob + (size_t)d * F) + (size_t)cbc * qstride + lane;
     const uint16_t *sB = reinterpret_cast<const uint16_t *>(blob + (size_t)3 * d * F / 2 + (size_t)d * F / 32) +
                          (size_t)cbc * sstride + (lane & 31);
+    const int nh = min((gt.count[grp] - pass * TT * kTile + 15) >> 4, 2 * TT);   // as in the first half
     const uint4 *asrc[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u)
-        asrc[u] = act + gt.act_off[grp] + (size_t)(pass * TT + min(u, ntl - 1)) * nkb * 64 + lane;
+        asrc[u] = act + gt.act_off[grp] + (size_t)(pass * TT + min(u, ntl - 1)) * nkb * 64 +
+                  (TT < 4 && nh == 2 * u + 1 ? lane & ~16 : lane);
+
+    float *Yp = Y + (size_t)kslice * y_plane;
+    if constexpr (TT < 4) if (nh & 1) {
+        constexpr int HT = 2 * TT - 1;
+        floatx4_t acc[CBW][2][HT];   // [column block][half of its columns][half tile of 16 tokens]
+#pragma unroll
+        for (int cw = 0; cw < CBW; ++cw)
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int h = 0; h < HT; ++h) acc[cw][r][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        if (TT == 1 || nh == 1) q4_down_stream16<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+        else q4_down_stream16<TT, 2 * TT - 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+
+        if (!valid) return;
+        // a lane holds token l % 16 of a half tile and four consecutive output columns per accumulator: 16-byte stores
+#pragma unroll
+        for (int h = 0; h < HT; ++h) {
+            const int tl = pass * TT * kTile + 16 * h + (lane & 15);
+            if (h >= nh || tl >= gt.count[grp]) continue;
+            float *row = Yp + (size_t)(gt.row_offset[grp] + tl) * d + cb0 * 32 + 4 * (lane >> 4);
+#pragma unroll
+            for (int cw = 0; cw < CBW; ++cw)
+#pragma unroll
+                for (int r = 0; r < 2; ++r) *reinterpret_cast<floatx4_t *>(row + 32 * cw + 16 * r) = acc[cw][r][h];
+        }
+        return;
+    }
 
     floatx16 acc[CBW][TT];
 #pragma unroll
@@ -412,7 +628,6 @@ __global__ __launch_bounds__(256, TT == 4 ? 2 : 1) void ffn_down_q4_kernel(Group
 
     if (!valid) return;
     const int g = lane >> 5;
-    float *Yp = Y + (size_t)kslice * y_plane;
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
         if (tt >= ntl) break;

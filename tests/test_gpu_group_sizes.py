@@ -23,6 +23,7 @@ SIZES = {
     "second passes": [129, 160, 193, 224, 225, 32, 1, 161],
     "tiled beside streamed": [320, 300, 33, 1, 100, 513, 64, 0],
     "three live tiles last": [350, 449, 257, 480, 0, 97, 289, 1],
+    "half live tiles": [15, 17, 33, 48, 47, 49, 34, 16],
 }
 
 
