@@ -9,13 +9,20 @@
 // fragments and every wave reads all of them from LDS, so L2 serves them once per workgroup.  Weights
 // still stream straight from HBM into operand registers (1 KiB fragments, nontemporal), a register ring
 // of three stages per wave, one barrier per stage of four k-blocks.
+//
+// Passes of two, four or eight tiles.  A second pass over a group's weights is read from HBM again: the two are not in step,
+// and what the 64 workgroups of an XCD have in flight alone fills its L2 (numbering them so that both passes over a row block
+// run on one XCD side by side changed nothing).  Eight tiles are 256 accumulator registers and 64 matrix instructions per
+// stage and wave, 1 us for the 32 KiB of weights that a compute unit gets in 1.3 us at 6.3 TB/s: still bound by HBM
+// (Mixtral-shaped 300 tokens, groups of up to six tiles, two layers 1219 -> 1110 us).
 #include "ef_device.h"
 #include "ef_kernels.h"
 
 namespace ef {
 
 constexpr int kShDepth = 3;   // register ring: stages in flight per wave (one workgroup per CU); the variants that
-                              // fit two workgroups per CU (<= 256 registers) keep two stages
+                              // fit two workgroups per CU (<= 256 registers) keep two stages (passes of eight with two and
+                              // three: the same time)
 constexpr int kShLds = 4;     // LDS ring of shared token / activation fragments (stages, power of two)
 
 // K loop of the first half for NTL live token tiles of a pass of TT (the same number for the whole workgroup): the token
@@ -24,7 +31,7 @@ constexpr int kShLds = 4;     // LDS ring of shared token / activation fragments
 template <int TT, int NTL, int D>
 __device__ __forceinline__ void shared_up_stream(const uint4 *__restrict__ w1, const uint4 *__restrict__ w3,
                                                  const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int nq, int wave,
-                                                 int lane, floatx16 (&G)[TT], floatx16 (&U)[TT]) {
+                                                 int lane, floatx16 (&G)[NTL], floatx16 (&U)[NTL]) {
     u32x4_t wa[D][4], wb[D][4], xr[D][NTL];
     // every load is unconditional (past the end the last stage is re-read, in bounds).  The token fragments are
     // requested before the weights: they are handed to the workgroup one stage before the weights of their
@@ -33,11 +40,11 @@ __device__ __forceinline__ void shared_up_stream(const uint4 *__restrict__ w1, c
     {                                                                                                    \
         const int kc_ = min((kq), nq - 1);                                                               \
         _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                  \
-            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64);   \
+            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64 + lane); \
         __builtin_amdgcn_sched_barrier(0);                                                               \
         _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            wa[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w1 + (size_t)(4 * kc_ + j) * 64)); \
-            wb[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w3 + (size_t)(4 * kc_ + j) * 64)); \
+            wa[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w1 + (size_t)(4 * kc_ + j) * 64 + lane)); \
+            wb[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w3 + (size_t)(4 * kc_ + j) * 64 + lane)); \
         }                                                                                                \
     }
 #define EF_SHU_SHARE(slot, st)                                                                           \
@@ -82,6 +89,37 @@ __device__ __forceinline__ void shared_up_stream(const uint4 *__restrict__ w1, c
 #undef EF_SHU_STAGE
 }
 
+// A pass with NTL live tiles or more: the loop for its number of them, and its activations (dst: those of the wave's row
+// block and the pass's first tile).  The accumulators live in here: none are held, or merged, for tiles a pass does not have.
+template <int TT, int NTL, int D>
+__device__ __forceinline__ void shared_up_pass(const uint4 *__restrict__ w1, const uint4 *__restrict__ w3,
+                                               const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int nq, int wave,
+                                               int lane, int ntl, uint4 *__restrict__ dst, int nkb2) {
+    if constexpr (NTL < TT)
+        if (ntl != NTL) return shared_up_pass<TT, NTL + 1, D>(w1, w3, xsrc, xs, nq, wave, lane, ntl, dst, nkb2);
+    floatx16 G[NTL], U[NTL];
+#pragma unroll
+    for (int tt = 0; tt < NTL; ++tt) { zero16(G[tt]); zero16(U[tt]); }
+    shared_up_stream<TT, NTL, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
+
+    // a lane holds 16 F-values of one token: the two paired-order fragments the second half consumes
+#pragma unroll
+    for (int tt = 0; tt < NTL; ++tt) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            uint32_t pk[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
+                const float v0 = g0 / (1.f + __expf(-g0)) * U[tt][8 * s + 2 * q];
+                const float v1 = g1 / (1.f + __expf(-g1)) * U[tt][8 * s + 2 * q + 1];
+                pk[q] = pack_act2(v0, v1);
+            }
+            dst[((size_t)tt * nkb2 + s) * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // first half: act = silu(X W1^T) * (X W3^T).  Workgroup = (group, pass of TT token tiles, four
 // consecutive 32-row blocks of F), wave = one row block, whole K range in stages of four k-blocks.
@@ -97,49 +135,23 @@ __global__ __launch_bounds__(256, OCC) void ffn_gate_up_shared_kernel(GroupTable
     const int F = gt.F[grp];
     const int rbw = (F >> 5) >> 2;               // workgroups per pass (F is a multiple of 128)
     const int pass = local / rbw;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int rb = (local % rbw) * 4 + wave;
     int ntl = gt.n_tiles[grp] - pass * TT;
     if (ntl > TT) ntl = TT;
     const int nkb = d >> 4, nq = d >> 6;         // d is a multiple of 64: whole stages
 
-    const uint4 *w1 = reinterpret_cast<const uint4 *>(gt.blob[grp]) + (size_t)rb * 2 * nkb * 64 + lane;
+    const uint4 *w1 = reinterpret_cast<const uint4 *>(gt.blob[grp]) + (size_t)rb * 2 * nkb * 64;
     const uint4 *w3 = w1 + (size_t)nkb * 64;
     // this wave's share of the token fragments of a stage: k-block `wave` of each tile (tiles past the
     // group's last one repeat it; their results are dropped)
     const uint4 *xsrc[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u)
-        xsrc[u] = xp + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 64 + lane;
+        xsrc[u] = xp + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 64;
 
-    floatx16 G[TT], U[TT];
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
-
-    if (TT == 1 || ntl == 1) shared_up_stream<TT, 1, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
-    else if (TT == 2 || ntl == 2) shared_up_stream<TT, 2, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
-    else if (ntl == 3) shared_up_stream<TT, (TT > 2 ? 3 : TT), D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
-    else shared_up_stream<TT, TT, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
-
-    // a lane holds 16 F-values of one token: the two paired-order fragments the second half consumes
-    const int nkb2 = F >> 4;
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if (tt >= ntl) break;
-        uint4 *dst = act + gt.act_off[grp] + ((size_t)(pass * TT + tt) * nkb2 + rb * 2) * 64 + lane;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            uint32_t pk[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
-                const float v0 = g0 / (1.f + __expf(-g0)) * U[tt][8 * s + 2 * q];
-                const float v1 = g1 / (1.f + __expf(-g1)) * U[tt][8 * s + 2 * q + 1];
-                pk[q] = pack_act2(v0, v1);
-            }
-            dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-        }
-    }
+    uint4 *dst = act + gt.act_off[grp] + ((size_t)pass * TT * (F >> 4) + rb * 2) * 64 + lane;
+    shared_up_pass<TT, 1, D>(w1, w3, xsrc, xs, nq, wave, lane, ntl, dst, F >> 4);
 }
 
 hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *xp,
@@ -159,6 +171,8 @@ hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int ti
         hipLaunchKernelGGL((ffn_gate_up_shared_kernel<4, 2, 2>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
     else if (tiles_per_pass == 4)
         hipLaunchKernelGGL((ffn_gate_up_shared_kernel<4, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
+    else if (tiles_per_pass == 8)
+        hipLaunchKernelGGL((ffn_gate_up_shared_kernel<8, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -167,18 +181,18 @@ hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int ti
 template <int TT, int NTL, int D, int CBW>
 __device__ __forceinline__ void shared_down_stream(const uint4 *__restrict__ w2, size_t cb_stride,
                                                    const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
-                                                   int q1, int wave, int lane, floatx16 (&acc)[CBW][TT]) {
+                                                   int q1, int wave, int lane, floatx16 (&acc)[CBW][NTL]) {
     u32x4_t wq[D][CBW][4], ar[D][NTL];
 #define EF_SHD_LOAD(slot, kq)                                                                            \
     {                                                                                                    \
         const int kc_ = min((kq), nq - 1);                                                               \
         _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                  \
-            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64);   \
+            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64 + lane); \
         __builtin_amdgcn_sched_barrier(0);                                                               \
         _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                               \
             _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                \
                 wq[slot][cw][j] = __builtin_nontemporal_load(                                            \
-                    reinterpret_cast<const u32x4_t *>(w2 + cw * cb_stride + (size_t)(4 * kc_ + j) * 64)); \
+                    reinterpret_cast<const u32x4_t *>(w2 + cw * cb_stride + (size_t)(4 * kc_ + j) * 64 + lane)); \
     }
 #define EF_SHD_SHARE(slot, st)                                                                           \
     {                                                                                                    \
@@ -219,6 +233,34 @@ __device__ __forceinline__ void shared_down_stream(const uint4 *__restrict__ w2,
 #undef EF_SHD_STAGE
 }
 
+// as shared_up_pass.  row: the lane's first token and column; rows: tokens from that one on that the group has (0: drop all)
+template <int TT, int NTL, int D, int CBW>
+__device__ __forceinline__ void shared_down_pass(const uint4 *__restrict__ w2, size_t cb_stride, const uint4 *const (&asrc)[TT],
+                                                 u32x4_t (*as)[TT * 4][64], int nq, int q0, int q1, int wave, int lane, int ntl,
+                                                 int rows, float *__restrict__ row, int d) {
+    if constexpr (NTL < TT)
+        if (ntl != NTL)
+            return shared_down_pass<TT, NTL + 1, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, ntl, rows, row, d);
+    floatx16 acc[CBW][NTL];
+#pragma unroll
+    for (int cw = 0; cw < CBW; ++cw)
+#pragma unroll
+        for (int tt = 0; tt < NTL; ++tt) zero16(acc[cw][tt]);
+    shared_down_stream<TT, NTL, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
+#pragma unroll
+    for (int tt = 0; tt < NTL; ++tt) {
+        // the product is formed transposed (W2 fragment first: the operand layouts are mirror images), so a lane
+        // holds token lane % 32 and four consecutive output columns per accumulator quad: 16-byte stores
+        if (tt * kTile >= rows) break;
+#pragma unroll
+        for (int cw = 0; cw < CBW; ++cw)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<float4 *>(row + (size_t)tt * kTile * d + cw * 32 + 8 * q) =
+                    make_float4(acc[cw][tt][4 * q], acc[cw][tt][4 * q + 1], acc[cw][tt][4 * q + 2], acc[cw][tt][4 * q + 3]);
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // second half: Y = act W2^T.  Workgroup = (group, pass of TT token tiles, eight consecutive
 // 32-column blocks of d, one of the group's K-slices), wave = two column blocks.  Activations (fp16) are operand
@@ -238,7 +280,7 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
     const int ncb = d >> 5, ncq = (ncb + 7) >> 3;
     const int ksg = gt.ksg[grp], kslice = local % ksg;
     const int cq = (local / ksg) % ncq, pass = (local / ksg) / ncq;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int cb0 = cq * 8 + wave * CBW;
     const bool valid = cb0 < ncb;                 // d is a multiple of 64: both column blocks or none
     const int cbc = valid ? cb0 : 0;              // waves past the last column load block 0 and drop the result
@@ -250,43 +292,16 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
 
     const size_t cb_stride = (size_t)nkb * 64;
     const uint4 *w2 = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(gt.blob[grp]) +
-                                                      (size_t)4 * d * F) + (size_t)cbc * cb_stride + lane;
+                                                      (size_t)4 * d * F) + (size_t)cbc * cb_stride;
     const uint4 *asrc[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u)
-        asrc[u] = act + gt.act_off[grp] + (size_t)(pass * TT + min(u, ntl - 1)) * nkb * 64 + lane;
+        asrc[u] = act + gt.act_off[grp] + (size_t)(pass * TT + min(u, ntl - 1)) * nkb * 64;
 
-    floatx16 acc[CBW][TT];
-#pragma unroll
-    for (int cw = 0; cw < CBW; ++cw)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
-
-    if (TT == 1 || ntl == 1) shared_down_stream<TT, 1, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
-    else if (TT == 2 || ntl == 2) shared_down_stream<TT, 2, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
-    else if (ntl == 3) shared_down_stream<TT, (TT > 2 ? 3 : TT), D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
-    else shared_down_stream<TT, TT, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
-
-    if (!valid) return;
-    const int g = lane >> 5;
-    float *Yp = Y + (size_t)kslice * y_plane;
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if (tt >= ntl) break;
-        // the product is formed transposed (W2 fragment first: the operand layouts are mirror images), so a lane
-        // holds token lane % 32 and four consecutive output columns per accumulator quad: 16-byte stores
-        const int tl = (pass * TT + tt) * kTile + (lane & 31);
-        if (tl >= gt.count[grp]) continue;
-        float *row = Yp + (size_t)(gt.row_offset[grp] + tl) * d;
-#pragma unroll
-        for (int cw = 0; cw < CBW; ++cw) {
-            const int col = (cb0 + cw) * 32 + 4 * g;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4 *>(row + col + 8 * q) =
-                    make_float4(acc[cw][tt][4 * q], acc[cw][tt][4 * q + 1], acc[cw][tt][4 * q + 2], acc[cw][tt][4 * q + 3]);
-        }
-    }
+    // this lane's part of its token's row: lane % 32 of the pass's first tile
+    const int t0 = pass * TT * kTile + (lane & 31);
+    float *row = Y + (size_t)kslice * y_plane + (size_t)(gt.row_offset[grp] + t0) * d + cb0 * 32 + 4 * (lane >> 5);
+    shared_down_pass<TT, 1, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, ntl, valid ? gt.count[grp] - t0 : 0, row, d);
 }
 
 hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act,
@@ -305,6 +320,8 @@ hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles
         return launch_done(ffn_down_shared_kernel<4, 2, 2>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
         return launch_done(ffn_down_shared_kernel<4, kShDepth, 1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
+    else if (tiles_per_pass == 8)
+        return launch_done(ffn_down_shared_kernel<8, kShDepth, 1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     return hipErrorInvalidValue;
 }
 

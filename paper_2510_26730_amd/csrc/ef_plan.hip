@@ -193,12 +193,21 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 }
 
 // Token tiles per pass over a streamed group's weights, for a launch whose largest group has `max_tiles` and whose first
-// half would have `wgs_of_four` workgroups in passes of four.  16-bit: groups of three or more tiles (too few for the tiled
-// kernels) take passes of four, which halves the re-reads of their weights.  4-bit: passes of four dequantise half as
+// half would have `wgs_of_four` workgroups in passes of four, beside `tiled_wgs` of a tiled one.  16-bit: groups of three or
+// more tiles (too few for the tiled kernels) take passes of four, which halves the re-reads of their weights, and where the
+// largest has five or more and the chip has more workgroups than compute units, streamed or tiled, passes of eight: no group
+// reads its weights twice (two layers, passes of four / eight: Mixtral-shaped 300 / 350 / 700 tokens 1219 / 1110, 1278 / 1139,
+// 1619 / 1480 us, two experts 200 tokens 556 / 454; DeepSeek-shaped 1056 tokens 711 / 694, on 16 experts with 385 tiled
+// workgroups 551 / 524).  With fewer every workgroup has a unit to itself, and the longer ones end the launch (Qwen-shaped
+// on 12 experts, 121 streamed and 231 tiled, 640 tokens 357 / 413; DeepSeek-shaped on 16, 176 and 198, 600 tokens 372 / 380;
+// d = 512, 56 and 40, 700 tokens 147 / 155).  4-bit: passes of four dequantise half as
 // often, but a pass is twice as long; they pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes
 // of two / four: Mixtral-shaped 200 tokens, 1008 workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515;
 // Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-shaped 300 tokens, 671, 289 / 312).
-int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four) {
+int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_wgs) {
+    if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_wgs > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
+        c->tune.lds_shared != 0 && c->cfg.d_ff % 128 == 0 && c->cfg.d_ff_shared % 128 == 0)
+        return 8;
     if (max_tiles >= 3 && c->tune.passes_of_four != 0 && (!c->q4 || wgs_of_four >= 896)) return 4;
     return max_tiles >= 2 ? 2 : 1;
 }
@@ -408,7 +417,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     // 4-bit groups of a tiled one's size stream because of what the whole layer holds; a phase that has one keeps to the
     // layer's pass width (for which the K slices of the second half were chosen) and does not cut the first half's K range
     // in two, whatever else is resident: such a group's sums do not depend on the phase it runs in
-    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four);
+    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, tiled_up_wgs);
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;
@@ -417,9 +426,9 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     const int want_waves = c->tune.up_want_waves, nkb = d / 16;
     while (ks < 4 && units * ks < want_waves && nkb / (ks * 2) >= 16) ks *= 2;
     if (c->tune.up_k_slices > 0) ks = c->tune.up_k_slices;
-    // passes of four tiles: the kernels whose four waves share the token / activation fragments through LDS
+    // passes of four tiles and more: the kernels whose four waves share the token / activation fragments through LDS
     // (per-wave copies of them would be twice the weights' bytes from L2)
-    bool shared = tpp == 4 && !c->q4 && c->tune.lds_shared != 0;
+    bool shared = tpp >= 4 && !c->q4 && c->tune.lds_shared != 0;
     for (int i = 0; i < n && shared; ++i) shared = gu.F[i] % 128 == 0;
     int wg_gu = 0, wg_dn = 0;
     for (int i = 0; i < n; ++i) {
@@ -588,7 +597,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             // passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
             // less (two layers: Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens
             // 1560 -> 1459); a launch of their own is passes of four too
-            if (c->tune.passes_of_four == 0 || tiles_per_pass(c, 4, four_all) == 4 ||
+            if (c->tune.passes_of_four == 0 || tiles_per_pass(c, 4, four_all, 0) == 4 ||
                 (four_all >= 512 && four_tiled * 4 <= four_all))
                 use_tiled = false;
         } else if (!c->q4 && wg_up < 64 && four_all - four_tiled >= 128 && c->tune.passes_of_four != 0 &&
@@ -624,12 +633,12 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
         if (has_shared && streams(c->cfg.d_ff_shared, T, false)) see(c->cfg.d_ff_shared, T);
-        tpp = tiles_per_pass(c, tmax, wgs_of_four);
+        tpp = tiles_per_pass(c, tmax, wgs_of_four, use_tiled ? tiled_up_wgs : 0);
         double stream_work = 0.0;     // workgroups times their k-blocks
         double stream_bytes = 0.0;    // weights of the streamed groups, as often as their passes read them
         auto add_base = [&](int F, int nt) {
             const int wgs = c->q4 ? ef::ffn_down_q4_wgs(d, nt, tpp, 1)
-                                  : tpp == 4 ? ef::ffn_down_shared_wgs(d, nt, tpp, 1) : ef::ffn_down_wgs(d, nt, tpp, 1);
+                                  : tpp >= 4 ? ef::ffn_down_shared_wgs(d, nt, tpp, 1) : ef::ffn_down_wgs(d, nt, tpp, 1);
             base_wgs += wgs;
             stream_work += (double)wgs * (F / 16);
             stream_bytes += (c->q4 ? 1.55 : 6.0) * d * F * ((nt + tpp - 1) / tpp);
@@ -643,14 +652,15 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 add_base(c->cfg.d_ff, nt);
             }
         if (has_shared && streams(c->cfg.d_ff_shared, T, false)) add_base(c->cfg.d_ff_shared, (T + ef::kTile - 1) / ef::kTile);
-        // the LDS-shared kernels (passes of four tiles) run two workgroups per compute unit, beside a tiled launch one (there
+        // the LDS-shared kernels run two workgroups per compute unit in passes of four, beside a tiled launch one (there
         // twice the workgroups only cost planes: DeepSeek-shaped 1056 tokens 772 -> 750 us for two layers, Mixtral-shaped 700
-        // tokens 1655 -> 1625)
-        const int want = c->tune.down_want_wgs > 0 ? c->tune.down_want_wgs : (tpp == 4 && !c->q4 && !use_tiled) ? 512 : 256;
+        // tokens 1655 -> 1625); in passes of eight they run one, but two shorter rounds are better than one (Mixtral-shaped
+        // 300 / 350 tokens 1111 / 1140 us, for 256 workgroups 1133 / 1185)
+        const int want = c->tune.down_want_wgs > 0 ? c->tune.down_want_wgs : (tpp >= 4 && !c->q4 && !use_tiled) ? 512 : 256;
         const int nkb_min = std::min(c->cfg.d_ff, has_shared ? c->cfg.d_ff_shared : c->cfg.d_ff) / 16;
         // a slice keeps >= 32 fragments per wave (bf16: four waves split it again), >= 6 quads (4-bit), or >= 8
         // stages of four fragments (LDS-shared kernels: a wave walks the whole slice)
-        const int units = c->q4 ? nkb_min / 4 / 6 : tpp == 4 ? nkb_min / 4 / 8 : nkb_min / 4 / 32;
+        const int units = c->q4 ? nkb_min / 4 / 6 : tpp >= 4 ? nkb_min / 4 / 8 : nkb_min / 4 / 32;
         while (ksg < 8 && base_wgs * ksg < want && units / (ksg * 2) >= 1 && y_plane * (ksg * 2) <= c->y_floats)
             ksg *= 2;
         // 4-bit: two workgroups per compute unit (their waves stall at different times) while the planes this adds

@@ -99,6 +99,19 @@ def test_group_sizes_of_the_shared_forms(oracle_mod, tune):
     run_groups(oracle_mod, cfg, SIZES["second passes"], False, tune)
 
 
+@pytest.mark.parametrize("d,F,sizes", [
+    (256, 2432, SIZES["second passes"]),                       # 266 workgroups in passes of four
+    (320, 4224, [256, 255, 97, 64, 33, 129, 1, 0]),            # 330; an odd number of stages, waves past the last column
+    (256, 2816, [320, 320, 320, 320, 320, 320, 288, 161]),     # 44 beside 308 tiled
+])
+def test_passes_of_eight(oracle_mod, d, F, sizes):
+    """One to eight live tiles in passes of eight, full and ragged last tiles, K slices of unequal length."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_eight", d=d, F=F, F_shared=0, k=1)
+    out = run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=1))
+    same = run_groups(None, cfg, sizes, False, dict(down_k_slices=3))
+    assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums
+
+
 @pytest.mark.parametrize("sizes,F", [([257, 300, 288, 320, 352, 290, 383, 289], 4864),   # 912 workgroups in passes of four
                                      ([140, 320, 160, 150, 3, 97, 33, 129], 4736)])      # 518, one group of ten tiles
 def test_q4_large_groups_do_not_depend_on_phases(sizes, F):
