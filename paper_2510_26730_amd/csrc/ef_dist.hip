@@ -190,8 +190,8 @@ __global__ __launch_bounds__(64 * kDistSmallWaves) void dist_small_kernel(const 
 // ------------------------------------------------------------------------------------------
 // Gram blocks of batches between the two sizes above and below (kDistSmallMaxTokens to kDistBlockMaxTokens): too few
 // 256 x 256 (or 128 x 256) blocks to fill the chip, each walking all of d alone: 25 workgroups and 49 us at T = 1056,
-// d = 2048.  Here a workgroup owns a block of 32B x 32B pairs (B = 1 or 2) and its four waves a quarter of d each: their
-// partial products meet in LDS in a fixed order.  Rows are read as they are, whole 128-byte lines by eight lanes each,
+// d = 2048.  Here a workgroup owns a block of 32B x 32B pairs (B = 1 or 2) and its NW = 4 or 8 waves a part of d each: their
+// partial products meet in LDS in a fixed order, and every wave turns its share of them into distances.  Rows are read as they are, whole 128-byte lines by eight lanes each,
 // and turned into operand fragments through a wave's own LDS buffer, pieces of a row rotated by an exclusive or so that
 // neither side meets bank conflicts (read straight into operand registers, 32 lines per load, the address path bound the
 // kernel: T = 1056, d = 2048 26.6 against 18.8 us for the call; T = 2048, d = 4096 119 and 66).  No packed copy; the norms
@@ -206,15 +206,15 @@ __device__ __forceinline__ float diag_of(const floatx16 &m, int dv) {
     for (int v = 1; v < 16; ++v) r = dv == v ? m[v] : r;
     return r;
 }
-template <int B, int R>
-__global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__restrict__ h, int T, int d,
+template <int B, int R, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void dist_block_kernel(const uint16_t *__restrict__ h, int T, int d,
                                                             float *__restrict__ part, int t_pad) {
     constexpr int U = 4;   // k-steps (16 columns each) per stage
     constexpr int TILE = 256;   // 16-byte units of a tile's stage: 32 rows x 128 bytes
     // a stage buffer per wave; the partial products take its place afterwards
-    __shared__ __attribute__((aligned(16))) u32x4_t lds[4][2 * B * TILE];
-    __shared__ float nrm[4][2 * B][32];
-    __shared__ float csum[2][32];
+    __shared__ __attribute__((aligned(16))) u32x4_t lds[NW][2 * B * TILE];
+    __shared__ float nrm[NW][2 * B][32];
+    __shared__ float csum[NW][32];
     static_assert(sizeof(lds[0]) >= sizeof(float) * B * B * 16 * 64, "a wave's partial products fit its stage buffer");
     // block t of the upper triangle, column by column: IB <= JB
     const int t = blockIdx.x;
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
     const int IB = t - JB * (JB + 1) / 2;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int g = lane >> 5, c = lane & 31;
-    const int n = (d >> 4) >> 2, k0 = wave * n;   // d is a multiple of 64: equal quarters
+    const int n = (d >> 4) / NW, k0 = wave * n;   // d is a multiple of 16 NW: equal parts
     // global load u of a tile's stage: rows 8u .. 8u+7, eight lanes to a row's 128 bytes
     const int lr = lane >> 3, lc = lane & 7;
     // of row tiles, then column tiles; rows past the last token read the last one (16-byte units: T d / 8 fits 32 bits)
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
     u32x4_t f[R][2 * B][U];
 #define EF_DISTB_LOAD(f_, kb)                                                                             \
     {                                                                                                     \
-        const unsigned ch_ = min(2 * (kb) + lc, 2 * n - 1); /* past the quarter's end its last piece again */  \
+        const unsigned ch_ = min(2 * (kb) + lc, 2 * n - 1); /* past the part's end its last piece again */  \
         _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                                 \
             _Pragma("unroll") for (int u = 0; u < U; ++u)                                                 \
                 f_[a][u] = h4[min((a < B ? row0 : col0) + (unsigned)((a % B) * kTile + 8 * u) * stride, last) + ch_]; \
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
     // compiler (no wait and no instruction: the hardware keeps a wave's LDS operations in order)
 #define EF_DISTB_STAGE(f_, kb)                                                                            \
     {                                                                                                     \
-        if ((kb) + U > n) { /* the quarter ends inside the stage: zeros past its end */                   \
+        if ((kb) + U > n) { /* the part ends inside the stage: zeros past its end */                   \
             const bool past_ = 2 * (kb) + lc >= 2 * n;                                                    \
             _Pragma("unroll") for (int a = 0; a < 2 * B; ++a)                                             \
                 _Pragma("unroll") for (int u = 0; u < U; ++u) f_[a][u] = past_ ? u32x4_t{0, 0, 0, 0} : f_[a][u]; \
@@ -317,33 +317,40 @@ __global__ __launch_bounds__(256, 2) void dist_block_kernel(const uint16_t *__re
         for (int a = 0; a < 2 * B; ++a) nrm[wave][a][c] = diag[a];
     }
     __syncthreads();
-    const int a = B == 2 ? wave >> 1 : 0, b = B == 2 ? wave & 1 : 0;   // this wave's tile of the block
-    float sum = 0.f;
+    // every wave takes its share of the block's elements, all of one tile: VW rows of 32 columns in each lane half
+    constexpr int VW = B * B * 16 / NW;
+    const int tile = wave * VW >> 4, a = tile / B, b = tile % B;
     const int j = (JB * B + b) * kTile + c;
-    if (B == 2 || wave == 0) {
-        const float nj = ((nrm[0][B + b][c] + nrm[1][B + b][c]) + nrm[2][B + b][c]) + nrm[3][B + b][c];
+    // the waves' parts as a tree: half the roundings of a chain
+    auto over_waves = [](auto part_of) {
+        const float lo = (part_of(0) + part_of(1)) + (part_of(2) + part_of(3));
+        return NW == 4 ? lo : lo + ((part_of(4 % NW) + part_of(5 % NW)) + (part_of(6 % NW) + part_of(7 % NW)));
+    };
+    const float nj = over_waves([&](int w) { return nrm[w][B + b][c]; });
+    float sum = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v >> 2) + 4 * g + (v & 3), i = (IB * B + a) * kTile + r;
-            const int q = (a * B + b) * 16 + v;
-            const float ip = ((red[0][q][lane] + red[1][q][lane]) + red[2][q][lane]) + red[3][q][lane];
-            const float ni = ((nrm[0][a][r] + nrm[1][a][r]) + nrm[2][a][r]) + nrm[3][a][r];
-            if (i < j && j < T) {
-                const float dd = ni + nj - 2.f * ip;
-                sum += __builtin_sqrtf(fmaxf(dd, 0.f));
-            }
+    for (int u = 0; u < VW; ++u) {
+        const int q = wave * VW + u, v = q & 15;
+        const int r = 8 * (v >> 2) + 4 * g + (v & 3), i = (IB * B + a) * kTile + r;
+        const float ip = over_waves([&](int w) { return red[w][q][lane]; }), ni = over_waves([&](int w) { return nrm[w][a][r]; });
+        if (i < j && j < T) {
+            const float dd = ni + nj - 2.f * ip;
+            sum += __builtin_sqrtf(fmaxf(dd, 0.f));
         }
-        sum += __shfl_xor(sum, 32);
     }
-    if (B == 2) {   // one partial per 64 rows: the upper 32 rows' sums come over LDS
-        if (a == 1 && g == 0) csum[b][c] = sum;
-        __syncthreads();
-        if (a == 1) return;
-        sum += csum[b][c];
-    } else if (wave != 0) {
-        return;
+    sum += __shfl_xor(sum, 32);
+    if (g == 0) csum[wave][c] = sum;
+    __syncthreads();
+    // one partial per block of rows: the waves' sums in ascending order
+    if (threadIdx.x < B * 32) {
+        const int bb = threadIdx.x >> 5;
+        float total = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+            if ((w * VW >> 4) % B == bb) total += csum[w][c];
+        const int jj = (JB * B + bb) * kTile + c;
+        if (jj < t_pad) part[(size_t)IB * t_pad + jj] = total;
     }
-    if (g == 0 && j < t_pad) part[(size_t)IB * t_pad + j] = sum;
 }
 
 // Per-token sums over the row blocks and their total, for the batches of the two kernels above: one workgroup, since a
@@ -691,8 +698,15 @@ hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, fl
     if (!dist_needs_packed(T, form)) {
         const bool wide = dist_block_wide(T);
         const int nb = (T + (wide ? 63 : 31)) / (wide ? 64 : 32), blocks = nb * (nb + 1) / 2;
-        if (wide) hipLaunchKernelGGL((dist_block_kernel<2, 1>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);
-        else hipLaunchKernelGGL((dist_block_kernel<1, 2>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);
+        // a block's d over eight waves while every block has a compute unit to itself: half the stages one after the other
+        // (the call, four / eight waves, d = 2048 / 4096: T = 1056 21.3 / 19.5, 1100 31.5 / 27.5, 700 13.1 / 13.0 and 18.4 /
+        // 16.6 us); with more blocks two of four waves share a unit as well and add up fewer partials (T = 900 17.2 / 19.5,
+        // T = 1500 31 / 34.5)
+        const bool eight = blocks <= 256 && d % 128 == 0;
+        if (wide && eight) hipLaunchKernelGGL((dist_block_kernel<2, 1, 8>), dim3(blocks), dim3(512), 0, s, h, T, d, scratch, t_pad);
+        else if (wide) hipLaunchKernelGGL((dist_block_kernel<2, 1, 4>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);
+        else if (eight) hipLaunchKernelGGL((dist_block_kernel<1, 2, 8>), dim3(blocks), dim3(512), 0, s, h, T, d, scratch, t_pad);
+        else hipLaunchKernelGGL((dist_block_kernel<1, 2, 4>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);
         hipLaunchKernelGGL(dist_sum_kernel<float>, dim3(1), dim3(1024), 0, s, scratch, T, t_pad, wide ? 64 : 32, tok_dist, dist);
         return hipGetLastError();
     }

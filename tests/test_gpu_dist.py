@@ -164,6 +164,12 @@ def test_forms_by_batch_size_match_oracle(oracle_mod, T, d):
     assert np.array_equal(tok, tok2) and tot == tot2, "not bit-reproducible"
 
 
+@pytest.mark.parametrize("T,d", [(704, 128), (705, 128), (700, 384), (1408, 384), (1409, 128), (1400, 192)])
+def test_blocks_of_four_and_eight_waves_match_oracle(oracle_mod, T, d):
+    """Both sides of 256 blocks of either size, d of one k-step and of three per wave, and one that eight waves cannot share."""
+    test_forms_by_batch_size_match_oracle(oracle_mod, T, d)
+
+
 @pytest.mark.parametrize("T,d", [(64, 4096), (100, 4096), (256, 2048), (500, 4096), (960, 2048), (1056, 2048), (1500, 4096)])
 def test_distances_do_not_drift(oracle_mod, T, d):
     """The mean relative error of the distances stays below a quarter of one fp32 rounding (2^-26 = 1.5e-8): rounding to
