@@ -25,82 +25,98 @@ constexpr int kShDepth = 3;   // register ring: stages in flight per wave (one w
                               // three: the same time)
 constexpr int kShLds = 4;     // LDS ring of shared token / activation fragments (stages, power of two)
 
-// K loop of the first half for NTL live token tiles of a pass of TT (the same number for the whole workgroup): the token
-// loads, LDS traffic and matrix-core work of tiles that do not exist are left out (Mixtral-shaped chunk of 300 tokens,
-// passes of one to four live tiles: first half 369 -> 360 us, second 227 -> 207 us).
-template <int TT, int NTL, int D>
-__device__ __forceinline__ void shared_up_stream(const uint4 *__restrict__ w1, const uint4 *__restrict__ w3,
-                                                 const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int nq, int wave,
-                                                 int lane, floatx16 (&G)[NTL], floatx16 (&U)[NTL]) {
-    u32x4_t wa[D][4], wb[D][4], xr[D][NTL];
+template <bool HALF>
+__device__ __forceinline__ floatx16 shared_mfma(u32x4_t a, u32x4_t b, floatx16 c) {
+    return HALF ? mfma32h(a, b, c) : mfma32v(a, b, c);
+}
+
+// K loop of either half for NTL live token tiles of a pass of TT (the same number for the whole workgroup; loads, LDS traffic
+// and matrix-core work of tiles that do not exist are left out): stages [q0, q1) of four k-blocks, two weight streams per
+// wave (wa: W1 or the first column block of W2, wb: W3 or the second).  src: the tiles' fragments.  Every pointer is uniform.
+//
+// A wave issues in order, and with one wave per SIMD nothing covers what it waits for, so each of the stage's 4 NTL pairs of
+// matrix instructions (64 cycles) carries what would otherwise be a wait or a burst: the LDS read of the fragment three
+// pairs on, and at most two of the global loads that refill the stage's registers as they fall free.  Against all reads just
+// ahead of their use and all loads at the stage's end, two layers: Mixtral-shaped 300 / 700 / 1500 tokens 1102 / 1087, 1442 /
+// 1385, 2342 / 2285 us, two experts 200 tokens 450 / 425, d = 512 130 tokens 103 / 96; DeepSeek- and Qwen-shaped the same.
+template <int TT, int NTL, int D, bool HALF>
+__device__ __forceinline__ void shared_stream(const char *__restrict__ wa, const char *__restrict__ wb,
+                                              const char *const (&src)[TT], u32x4_t (*xs)[TT * 4][64], int q0, int q1, int wave,
+                                              int lane, floatx16 (&A)[NTL], floatx16 (&B)[NTL]) {
+    constexpr int N = 4 * NTL, LA = 3;
+    u32x4_t fa[D][4], fb[D][4], xr[D][NTL], xb[LA + 1];
+    const unsigned wo = lane * 16, xo = wave * 1024 + lane * 16;   // this wave loads k-block `wave` of each tile
     // every load is unconditional (past the end the last stage is re-read, in bounds).  The token fragments are
     // requested before the weights: they are handed to the workgroup one stage before the weights of their
     // stage are used, and loads return in issue order, so waiting for them must not mean waiting for those weights
-#define EF_SHU_LOAD(slot, kq)                                                                            \
+#define EF_SH_STAGE_AT(st) ((unsigned)min((st), q1 - 1) * 4096u)
+#define EF_SH_X(slot, u, at) xr[slot][u] = *reinterpret_cast<const u32x4_t *>(src[u] + (xo + (at)));
+#define EF_SH_W(f, p, j, at) f = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>((p) + (wo + (at)) + 1024 * (j)));
+    // one stage: hand the next stage's token fragments to the workgroup, compute this one while its registers are
+    // refilled, barrier (the next stage's fragments are visible; this stage's LDS buffer is overwritten three stages on)
+#define EF_SH_STAGE(slot, next_slot, st)                                                                 \
     {                                                                                                    \
-        const int kc_ = min((kq), nq - 1);                                                               \
-        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                  \
-            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(xsrc[u] + (size_t)(4 * kc_ + wave) * 64 + lane); \
+        const unsigned at_ = EF_SH_STAGE_AT((st) + D);                                                   \
+        u32x4_t(*const now_)[64] = xs[(st) & (kShLds - 1)];                                              \
+        _Pragma("unroll") for (int i = 0; i < LA; ++i) xb[i] = now_[i % NTL * 4 + i / NTL][lane];        \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[((st) + 1) & (kShLds - 1)][u * 4 + wave][lane] = xr[next_slot][u]; \
         __builtin_amdgcn_sched_barrier(0);                                                               \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            wa[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w1 + (size_t)(4 * kc_ + j) * 64 + lane)); \
-            wb[slot][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w3 + (size_t)(4 * kc_ + j) * 64 + lane)); \
+        _Pragma("unroll") for (int i = 0; i < N; ++i) {                                                  \
+            const int j = i / NTL, tt = i % NTL, n = i + LA;                                             \
+            if (n < N) xb[n % (LA + 1)] = now_[n % NTL * 4 + n / NTL][lane];                             \
+            A[tt] = shared_mfma<HALF>(fa[slot][j], xb[i % (LA + 1)], A[tt]);                             \
+            if (j == 0) EF_SH_X(slot, tt, at_)                                                           \
+            if (j > 0 && tt == 0) EF_SH_W(fa[slot][j - 1], wa, j - 1, at_)                               \
+            if (j > 0 && tt == (NTL > 1 ? 1 : 0)) EF_SH_W(fb[slot][j - 1], wb, j - 1, at_)               \
+            B[tt] = shared_mfma<HALF>(fb[slot][j], xb[i % (LA + 1)], B[tt]);                             \
+            __builtin_amdgcn_sched_barrier(0);                                                           \
         }                                                                                                \
-    }
-#define EF_SHU_SHARE(slot, st)                                                                           \
-    {                                                                                                    \
-        _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[(st) & (kShLds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
-    }
-#define EF_SHU_COMPUTE(slot, st)                                                                         \
-    {                                                                                                    \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) {                                         \
-                const u32x4_t xb_ = xs[(st) & (kShLds - 1)][tt * 4 + j][lane];                           \
-                G[tt] = mfma32v(wa[slot][j], xb_, G[tt]);                                                \
-                U[tt] = mfma32v(wb[slot][j], xb_, U[tt]);                                                \
-            }                                                                                            \
-        }                                                                                                \
-    }
-    // one stage: hand the next stage's token fragments to the workgroup, compute this one, refill the
-    // register slot just used, barrier (the next stage's fragments are visible; this stage's LDS
-    // buffer is overwritten three stages from now)
-#define EF_SHU_STAGE(slot, next_slot, st)                                                                \
-    {                                                                                                    \
-        EF_SHU_SHARE(next_slot, (st) + 1)                                                                \
-        EF_SHU_COMPUTE(slot, st)                                                                         \
-        EF_SHU_LOAD(slot, (st) + D)                                                                      \
+        EF_SH_W(fa[slot][3], wa, 3, at_)                                                                 \
+        EF_SH_W(fb[slot][3], wb, 3, at_)                                                                 \
         __syncthreads();                                                                                 \
     }
 #pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_SHU_LOAD(ring_, ring_)
-    EF_SHU_SHARE(0, 0)
-    __syncthreads();
-    int st = 0;
-    for (; st + D <= nq; st += D) {
+    for (int r = 0; r < D; ++r) {
+        const unsigned at = EF_SH_STAGE_AT(q0 + r);
 #pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_SHU_STAGE(ring_, (ring_ + 1) % D, st + ring_)
+        for (int u = 0; u < NTL; ++u) EF_SH_X(r, u, at)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            EF_SH_W(fa[r][j], wa, j, at)
+            EF_SH_W(fb[r][j], wb, j, at)
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < nq) EF_SHU_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_SHU_LOAD
-#undef EF_SHU_SHARE
-#undef EF_SHU_COMPUTE
-#undef EF_SHU_STAGE
+    for (int u = 0; u < NTL; ++u) xs[q0 & (kShLds - 1)][u * 4 + wave][lane] = xr[0][u];
+    __syncthreads();
+    int st = q0;
+    for (; st + D <= q1; st += D) {
+#pragma unroll
+        for (int r = 0; r < D; ++r) EF_SH_STAGE(r, (r + 1) % D, st + r)
+    }
+#pragma unroll
+    for (int r = 0; r < D - 1; ++r)
+        if (st + r < q1) EF_SH_STAGE(r, r + 1, st + r)
+#undef EF_SH_STAGE_AT
+#undef EF_SH_X
+#undef EF_SH_W
+#undef EF_SH_STAGE
 }
 
 // A pass with NTL live tiles or more: the loop for its number of them, and its activations (dst: those of the wave's row
 // block and the pass's first tile).  The accumulators live in here: none are held, or merged, for tiles a pass does not have.
 template <int TT, int NTL, int D>
-__device__ __forceinline__ void shared_up_pass(const uint4 *__restrict__ w1, const uint4 *__restrict__ w3,
-                                               const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int nq, int wave,
+__device__ __forceinline__ void shared_up_pass(const char *__restrict__ w1, const char *__restrict__ w3,
+                                               const char *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int nq, int wave,
                                                int lane, int ntl, uint4 *__restrict__ dst, int nkb2) {
     if constexpr (NTL < TT)
         if (ntl != NTL) return shared_up_pass<TT, NTL + 1, D>(w1, w3, xsrc, xs, nq, wave, lane, ntl, dst, nkb2);
     floatx16 G[NTL], U[NTL];
 #pragma unroll
     for (int tt = 0; tt < NTL; ++tt) { zero16(G[tt]); zero16(U[tt]); }
-    shared_up_stream<TT, NTL, D>(w1, w3, xsrc, xs, nq, wave, lane, G, U);
+    shared_stream<TT, NTL, D, false>(w1, w3, xsrc, xs, 0, nq, wave, lane, G, U);
 
     // a lane holds 16 F-values of one token: the two paired-order fragments the second half consumes
 #pragma unroll
@@ -141,14 +157,14 @@ __global__ __launch_bounds__(256, OCC) void ffn_gate_up_shared_kernel(GroupTable
     if (ntl > TT) ntl = TT;
     const int nkb = d >> 4, nq = d >> 6;         // d is a multiple of 64: whole stages
 
-    const uint4 *w1 = reinterpret_cast<const uint4 *>(gt.blob[grp]) + (size_t)rb * 2 * nkb * 64;
-    const uint4 *w3 = w1 + (size_t)nkb * 64;
+    const char *w1 = reinterpret_cast<const char *>(gt.blob[grp]) + (size_t)rb * 2 * nkb * 1024;
+    const char *w3 = w1 + (size_t)nkb * 1024;
     // this wave's share of the token fragments of a stage: k-block `wave` of each tile (tiles past the
     // group's last one repeat it; their results are dropped)
-    const uint4 *xsrc[TT];
+    const char *xsrc[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u)
-        xsrc[u] = xp + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 64;
+        xsrc[u] = reinterpret_cast<const char *>(xp) + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 1024;
 
     uint4 *dst = act + gt.act_off[grp] + ((size_t)pass * TT * (F >> 4) + rb * 2) * 64 + lane;
     shared_up_pass<TT, 1, D>(w1, w3, xsrc, xs, nq, wave, lane, ntl, dst, F >> 4);
@@ -177,83 +193,28 @@ hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int ti
     return hipGetLastError();
 }
 
-// K loop of the second half, as shared_up_stream: stages [q0, q1) of the nq stages of F
-template <int TT, int NTL, int D, int CBW>
-__device__ __forceinline__ void shared_down_stream(const uint4 *__restrict__ w2, size_t cb_stride,
-                                                   const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
-                                                   int q1, int wave, int lane, floatx16 (&acc)[CBW][NTL]) {
-    u32x4_t wq[D][CBW][4], ar[D][NTL];
-#define EF_SHD_LOAD(slot, kq)                                                                            \
-    {                                                                                                    \
-        const int kc_ = min((kq), nq - 1);                                                               \
-        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                  \
-            ar[slot][u] = *reinterpret_cast<const u32x4_t *>(asrc[u] + (size_t)(4 * kc_ + wave) * 64 + lane); \
-        __builtin_amdgcn_sched_barrier(0);                                                               \
-        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                               \
-            _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                \
-                wq[slot][cw][j] = __builtin_nontemporal_load(                                            \
-                    reinterpret_cast<const u32x4_t *>(w2 + cw * cb_stride + (size_t)(4 * kc_ + j) * 64 + lane)); \
-    }
-#define EF_SHD_SHARE(slot, st)                                                                           \
-    {                                                                                                    \
-        _Pragma("unroll") for (int u = 0; u < NTL; ++u) as[(st) & (kShLds - 1)][u * 4 + wave][lane] = ar[slot][u]; \
-    }
-#define EF_SHD_COMPUTE(slot, st)                                                                         \
-    {                                                                                                    \
-        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                                                  \
-            _Pragma("unroll") for (int tt = 0; tt < NTL; ++tt) {                                         \
-                const u32x4_t af_ = as[(st) & (kShLds - 1)][tt * 4 + j][lane];                           \
-                _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw)                                       \
-                    acc[cw][tt] = mfma32h(wq[slot][cw][j], af_, acc[cw][tt]);                            \
-            }                                                                                            \
-        }                                                                                                \
-    }
-#define EF_SHD_STAGE(slot, next_slot, st)                                                                \
-    {                                                                                                    \
-        EF_SHD_SHARE(next_slot, (st) + 1)                                                                \
-        EF_SHD_COMPUTE(slot, st)                                                                         \
-        EF_SHD_LOAD(slot, (st) + D)                                                                      \
-        __syncthreads();                                                                                 \
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D; ++ring_) EF_SHD_LOAD(ring_, q0 + ring_)
-    EF_SHD_SHARE(0, q0)
-    __syncthreads();
-    int st = q0;
-    for (; st + D <= q1; st += D) {
-#pragma unroll
-        for (int ring_ = 0; ring_ < D; ++ring_) EF_SHD_STAGE(ring_, (ring_ + 1) % D, st + ring_)
-    }
-#pragma unroll
-    for (int ring_ = 0; ring_ < D - 1; ++ring_)
-        if (st + ring_ < q1) EF_SHD_STAGE(ring_, ring_ + 1, st + ring_)
-#undef EF_SHD_LOAD
-#undef EF_SHD_SHARE
-#undef EF_SHD_COMPUTE
-#undef EF_SHD_STAGE
-}
-
 // as shared_up_pass.  row: the lane's first token and column; rows: tokens from that one on that the group has (0: drop all)
-template <int TT, int NTL, int D, int CBW>
-__device__ __forceinline__ void shared_down_pass(const uint4 *__restrict__ w2, size_t cb_stride, const uint4 *const (&asrc)[TT],
-                                                 u32x4_t (*as)[TT * 4][64], int nq, int q0, int q1, int wave, int lane, int ntl,
+template <int TT, int NTL, int D>
+__device__ __forceinline__ void shared_down_pass(const char *__restrict__ w2a, const char *__restrict__ w2b,
+                                                 const char *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int q0, int q1,
+                                                 int wave, int lane, int ntl,
                                                  int rows, float *__restrict__ row, int d) {
     if constexpr (NTL < TT)
         if (ntl != NTL)
-            return shared_down_pass<TT, NTL + 1, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, ntl, rows, row, d);
-    floatx16 acc[CBW][NTL];
+            return shared_down_pass<TT, NTL + 1, D>(w2a, w2b, asrc, as, q0, q1, wave, lane, ntl, rows, row, d);
+    floatx16 acc[2][NTL];
 #pragma unroll
-    for (int cw = 0; cw < CBW; ++cw)
+    for (int cw = 0; cw < 2; ++cw)
 #pragma unroll
         for (int tt = 0; tt < NTL; ++tt) zero16(acc[cw][tt]);
-    shared_down_stream<TT, NTL, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, acc);
+    shared_stream<TT, NTL, D, true>(w2a, w2b, asrc, as, q0, q1, wave, lane, acc[0], acc[1]);
 #pragma unroll
     for (int tt = 0; tt < NTL; ++tt) {
         // the product is formed transposed (W2 fragment first: the operand layouts are mirror images), so a lane
         // holds token lane % 32 and four consecutive output columns per accumulator quad: 16-byte stores
         if (tt * kTile >= rows) break;
 #pragma unroll
-        for (int cw = 0; cw < CBW; ++cw)
+        for (int cw = 0; cw < 2; ++cw)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 *reinterpret_cast<float4 *>(row + (size_t)tt * kTile * d + cw * 32 + 8 * q) =
@@ -271,7 +232,6 @@ template <int TT, int D, int OCC>
 __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt, const uint4 *__restrict__ act,
                                                                  float *__restrict__ Y, int d,
                                                                  long long y_plane) {
-    constexpr int CBW = 2;
     __shared__ __attribute__((aligned(16))) u32x4_t as[kShLds][TT * 4][64];
     const int wg = blockIdx.x;
     int grp = 0;
@@ -281,7 +241,7 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
     const int ksg = gt.ksg[grp], kslice = local % ksg;
     const int cq = (local / ksg) % ncq, pass = (local / ksg) / ncq;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int cb0 = cq * 8 + wave * CBW;
+    const int cb0 = cq * 8 + wave * 2;
     const bool valid = cb0 < ncb;                 // d is a multiple of 64: both column blocks or none
     const int cbc = valid ? cb0 : 0;              // waves past the last column load block 0 and drop the result
     const int F = gt.F[grp];
@@ -290,18 +250,17 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
     int ntl = gt.n_tiles[grp] - pass * TT;
     if (ntl > TT) ntl = TT;
 
-    const size_t cb_stride = (size_t)nkb * 64;
-    const uint4 *w2 = reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(gt.blob[grp]) +
-                                                      (size_t)4 * d * F) + (size_t)cbc * cb_stride;
-    const uint4 *asrc[TT];
+    const char *w2a = reinterpret_cast<const char *>(gt.blob[grp]) + (size_t)4 * d * F + (size_t)cbc * nkb * 1024;
+    const char *w2b = w2a + (size_t)nkb * 1024;
+    const char *asrc[TT];
 #pragma unroll
     for (int u = 0; u < TT; ++u)
-        asrc[u] = act + gt.act_off[grp] + (size_t)(pass * TT + min(u, ntl - 1)) * nkb * 64;
+        asrc[u] = reinterpret_cast<const char *>(act + gt.act_off[grp]) + (size_t)(pass * TT + min(u, ntl - 1)) * nkb * 1024;
 
     // this lane's part of its token's row: lane % 32 of the pass's first tile
     const int t0 = pass * TT * kTile + (lane & 31);
     float *row = Y + (size_t)kslice * y_plane + (size_t)(gt.row_offset[grp] + t0) * d + cb0 * 32 + 4 * (lane >> 5);
-    shared_down_pass<TT, 1, D, CBW>(w2, cb_stride, asrc, as, nq, q0, q1, wave, lane, ntl, valid ? gt.count[grp] - t0 : 0, row, d);
+    shared_down_pass<TT, 1, D>(w2a, w2b, asrc, as, q0, q1, wave, lane, ntl, valid ? gt.count[grp] - t0 : 0, row, d);
 }
 
 hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act,
