@@ -47,6 +47,12 @@ __device__ __forceinline__ uint32_t pack_act2(float v0, float v1) {
     return __builtin_bit_cast(uint32_t, half2_t{(_Float16)v0, (_Float16)v1});
 }
 
+// silu(g) * u.  The reciprocal is the hardware's (1 ulp, as the exponential beside it): an IEEE division is ten instructions
+// more per element, and the product is rounded to 11 bits next (relative error of a layer against 64 bits 2.072e-4 either
+// way).  256 x 256 tiles end in 128 elements per lane: Mixtral-shaped 8192 tokens 9269 -> 9148 us for two layers, DeepSeek-
+// shaped 2500 tokens 1061 -> 1046, Qwen-shaped 4-bit 640 tokens 382 -> 375.  exp(-g) = inf gives 0 as the division does.
+__device__ __forceinline__ float silu_mul(float g, float u) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u; }
+
 // streaming (read-once) 16-byte load: keeps expert weights from displacing reused data in L2
 __device__ __forceinline__ uint4 load_stream(const uint4 *p) {
     u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));

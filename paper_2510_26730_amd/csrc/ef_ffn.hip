@@ -297,8 +297,8 @@ __global__ __launch_bounds__(256) void ffn_gate_up_kernel(GroupTable gt, const u
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
-                    const float v0 = g0 / (1.f + __expf(-g0)) * U[tt][8 * s + 2 * q];
-                    const float v1 = g1 / (1.f + __expf(-g1)) * U[tt][8 * s + 2 * q + 1];
+                    const float v0 = silu_mul(g0, U[tt][8 * s + 2 * q]);
+                    const float v1 = silu_mul(g1, U[tt][8 * s + 2 * q + 1]);
                     pk[q] = pack_act2(v0, v1);
                 }
                 dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);

@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
             for (int r = 0; r < 2; ++r) {
                 float v[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = q4_saturate(G[r][h][q] / (1.f + __expf(-G[r][h][q])) * U[r][h][q]);
+                for (int q = 0; q < 4; ++q) v[q] = q4_saturate(silu_mul(G[r][h][q], U[r][h][q]));
                 dst[(size_t)r * 128] = make_uint2(__builtin_bit_cast(uint32_t, q4_half2{(_Float16)v[0], (_Float16)v[1]}),
                                                   __builtin_bit_cast(uint32_t, q4_half2{(_Float16)v[2], (_Float16)v[3]}));
             }
@@ -388,8 +388,8 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
-                const float v0 = g0 / (1.f + __expf(-g0)) * U[tt][8 * s + 2 * q];
-                const float v1 = g1 / (1.f + __expf(-g1)) * U[tt][8 * s + 2 * q + 1];
+                const float v0 = silu_mul(g0, U[tt][8 * s + 2 * q]);
+                const float v1 = silu_mul(g1, U[tt][8 * s + 2 * q + 1]);
                 pk[q] = __builtin_bit_cast(uint32_t, q4_half2{(_Float16)q4_saturate(v0), (_Float16)q4_saturate(v1)});
             }
             dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);

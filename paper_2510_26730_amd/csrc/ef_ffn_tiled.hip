@@ -97,8 +97,8 @@ __global__ __launch_bounds__(256, 1) void ffn_gate_up_tiled_kernel(GroupTable gt
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float g0 = acc[2 * h][j][8 * s + 2 * q], g1 = acc[2 * h][j][8 * s + 2 * q + 1];
-                    const float v0 = g0 / (1.f + __expf(-g0)) * acc[2 * h + 1][j][8 * s + 2 * q];
-                    const float v1 = g1 / (1.f + __expf(-g1)) * acc[2 * h + 1][j][8 * s + 2 * q + 1];
+                    const float v0 = silu_mul(g0, acc[2 * h + 1][j][8 * s + 2 * q]);
+                    const float v1 = silu_mul(g1, acc[2 * h + 1][j][8 * s + 2 * q + 1]);
                     pk[q] = pack_act2(v0, v1);
                 }
                 dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
