@@ -716,6 +716,32 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                                      (ks - 1) * plane_s;
                     if (ks == 1 || t < best - 1e-9) { best = t; ksg_tiled = ks; }
                 }
+                // A shared FFN beside routed groups has a K of its own: with a slice count of its own too, both kinds end at
+                // about the same time (K 5632 and 1408 in three slices each are 59 and 15 stages on 240 workgroups, in four
+                // and one 44 each on 152).  Within one round of workgroups, where the longest decides; a workgroup costs 10 us
+                // of a compute unit whatever its length.  Two layers, one count / two: Qwen-shaped on 12 experts 400 / 560 /
+                // 640 / 800 / 1000 / 1200 tokens 309 / 301, 333 / 319, 349 / 341, 429 / 419, 493 / 464, 616 / 550, on 60 1000
+                // tokens 679 / 618; DeepSeek-shaped on 16 300 / 400 / 600 tokens 322 / 313, 340 / 327, 363 / 348.  Not where
+                // the tiled first half takes nearly all compute units of its one round: the streamed one then runs behind it,
+                // and the more even workgroups wait for it (680 / 720 tokens on 12 experts 372 / 381, 386 / 405).
+                const int nt_shared = has_shared ? (T + ef::kTile - 1) / ef::kTile : 0;
+                if (c->tune.down_split_slice_counts != 0 && (tiled_up_wgs <= 220 || tiled_up_wgs > 256) && has_shared &&
+                    takes_tiled(c, c->cfg.d_ff_shared, nt_shared, false, early)) {
+                    const int units_s = ef::ffn_tiled_units(d / 256, nt_shared, 1), units_r = (int)tiled_dn_wgs - units_s;
+                    const int stages_s = c->cfg.d_ff_shared / 32, stages_r = c->cfg.d_ff / 32;
+                    const double wg_s = 10e-6 / 256.0;
+                    best += (double)tiled_dn_wgs * ksg_tiled * wg_s;
+                    for (int kr = 1; kr <= 8 && units_r > 0; ++kr)
+                        for (int kh = 1; kh <= 8; ++kh) {
+                            if (kr == kh || units_r * kr + units_s * kh > 256 || y_plane * std::max(kr, kh) > c->y_floats ||
+                                (kr > 1 && stages_r / kr < 16) || (kh > 1 && stages_s / kh < 16))
+                                continue;
+                            const double longest = std::max((double)stages_r / kr, (double)stages_s / kh);
+                            const double planes_s = ((double)(tiled_rows - T) * (kr - 1) + (double)T * (kh - 1)) * d * 8.0 / 5e12;
+                            const double t = std::max(up_s + longest * 0.77e-6, stream_s) + planes_s + (units_r * kr + units_s * kh) * wg_s;
+                            if (t < best - 1e-9) { best = t; ksg_tiled = kr; split_expert = -1; split_ksg = kh; }
+                        }
+                }
             }
             if (c->tune.down_split_slice_counts == 0) ksg = ksg_tiled;   // one slice count for both launches
         }
@@ -732,7 +758,10 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 ++ksg_shared;
         }
         int forced = c->tune.down_k_slices;
-        if (forced >= 1 && forced <= 8 && y_plane * forced <= c->y_floats) ksg = ksg_shared = ksg_tiled = forced;
+        if (forced >= 1 && forced <= 8 && y_plane * forced <= c->y_floats) {
+            ksg = ksg_shared = ksg_tiled = forced;
+            split_expert = kNoSplit;
+        }
         // A tiled second half of more than one round of workgroups over the compute units ends in a round that is
         // partly empty (1056 workgroups: four rounds and an eighth; every compute unit holds one at a time).  The
         // layer's last tiled group (the one with the least work; the highest expert among equals) is cut into K

@@ -155,6 +155,17 @@ def test_wide_shared_ffn_takes_slices_of_its_own(oracle_mod, sizes, q4):
     assert not np.array_equal(out, same)
 
 
+@pytest.mark.parametrize("F,F_shared,ks", [(512, 2048, 0), (1024, 2048, 0), (512, 4096, 0), (512, 2048, 2)])
+def test_tiled_shared_ffn_takes_slices_of_its_own(oracle_mod, F, F_shared, ks):
+    """A tiled shared FFN of two to eight times the experts' width beside tiled and streamed groups: slice counts of their
+    own in the second half, and one count for all where it is forced."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_own", d=256, F=F, F_shared=F_shared, k=1)
+    sizes = [330, 321, 40, 33, 1, 0, 100, 31]
+    out = run_groups(oracle_mod, cfg, sizes, False, dict(down_k_slices=ks), expect=dict(ffn_up=1, ffn_up_tiled=1))
+    same = run_groups(None, cfg, sizes, False, dict(down_split_slice_counts=0))
+    assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums
+
+
 @pytest.mark.parametrize("tens,early", [(4, True), (5, False), (6, True)])
 def test_nine_tiles_join_the_tiled_launch_unless_they_fill_the_chip(oracle_mod, tens, early):
     """A group of nine tiles (44 units of a first half) beside `tens` groups of ten in the tiled launch: 220 units in all, from
