@@ -497,7 +497,8 @@ typedef struct ef_tuning {
                                         fullest one least full (1); 0: all groups start on XCD 0 */
     int32_t overlap_tiled;           /* 0/1: a phase's tiled launches run on a side stream beside its streamed ones (1) */
     int32_t sort_groups;             /* 0/1: groups with the most work first in a launch (1) */
-    int32_t passes_of_four;          /* 0/1: streamed groups of >= 3 token tiles take passes of four tiles (1) */
+    int32_t passes_of_four;          /* 0/1: streamed groups of >= 3 token tiles take passes of four tiles, 16-bit ones of >= 5
+                                        passes of eight where the chip has more workgroups than compute units (1) */
     int32_t lds_shared;              /* 0/1: ... through the kernels whose waves share fragments in LDS (1) */
     int32_t lds_shared_occupancy;    /* workgroups per compute unit of those kernels: 1, 2, or 0 = two for a launch of more
                                         workgroups than compute units (d_model > 2048: than two per unit) beside at most
@@ -509,7 +510,7 @@ typedef struct ef_tuning {
     int32_t down_k_slices;           /* 0 = auto, else 1..8: K-slice planes of the second half (both launches) */
     int32_t down_slices_by_longest_k; /* 0/1: the tiled second half sizes its slices by the group with the longest K (1) */
     int32_t down_split_slice_counts; /* 0/1: the streamed and the tiled launch of a layer choose their slice counts
-                                        separately, and a streamed shared FFN its own (1) */
+                                        separately, and a shared FFN its own (1) */
     int32_t gate_k_split;            /* 0 = auto, else 1..16: workgroups sharing the K range of one (tile, gate group) */
     int32_t gate_token_split;        /* 0/1: the gate's second step may split a tile's tokens over workgroups (1) */
     int32_t gate_fused_finish;       /* 0/1: decode-sized batches fuse the gate's second step with the grouping (1) */
