@@ -46,17 +46,17 @@ __device__ __forceinline__ void shared_stream(const char *__restrict__ wa, const
     constexpr int N = 4 * NTL, LA = 3;
     u32x4_t fa[D][4], fb[D][4], xr[D][NTL], xb[LA + 1];
     const unsigned wo = lane * 16, xo = wave * 1024 + lane * 16;   // this wave loads k-block `wave` of each tile
+    const int last = shared_last_stage(q1);
     // every load is unconditional (past the end the last stage is re-read, in bounds).  The token fragments are
     // requested before the weights: they are handed to the workgroup one stage before the weights of their
     // stage are used, and loads return in issue order, so waiting for them must not mean waiting for those weights
-#define EF_SH_STAGE_AT(st) ((unsigned)min((st), q1 - 1) * 4096u)
 #define EF_SH_X(slot, u, at) xr[slot][u] = *reinterpret_cast<const u32x4_t *>(src[u] + (xo + (at)));
 #define EF_SH_W(f, p, j, at) f = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>((p) + (wo + (at)) + 1024 * (j)));
     // one stage: hand the next stage's token fragments to the workgroup, compute this one while its registers are
     // refilled, barrier (the next stage's fragments are visible; this stage's LDS buffer is overwritten three stages on)
 #define EF_SH_STAGE(slot, next_slot, st)                                                                 \
     {                                                                                                    \
-        const unsigned at_ = EF_SH_STAGE_AT((st) + D);                                                   \
+        const unsigned at_ = shared_stage_offset((st) + D, last);                                        \
         u32x4_t(*const now_)[64] = xs[(st) & (kShLds - 1)];                                              \
         _Pragma("unroll") for (int i = 0; i < LA; ++i) xb[i] = now_[i % NTL * 4 + i / NTL][lane];        \
         _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[((st) + 1) & (kShLds - 1)][u * 4 + wave][lane] = xr[next_slot][u]; \
@@ -77,7 +77,7 @@ __device__ __forceinline__ void shared_stream(const char *__restrict__ wa, const
     }
 #pragma unroll
     for (int r = 0; r < D; ++r) {
-        const unsigned at = EF_SH_STAGE_AT(q0 + r);
+        const unsigned at = shared_stage_offset(q0 + r, last);
 #pragma unroll
         for (int u = 0; u < NTL; ++u) EF_SH_X(r, u, at)
         __builtin_amdgcn_sched_barrier(0);
@@ -99,7 +99,6 @@ __device__ __forceinline__ void shared_stream(const char *__restrict__ wa, const
 #pragma unroll
     for (int r = 0; r < D - 1; ++r)
         if (st + r < q1) EF_SH_STAGE(r, r + 1, st + r)
-#undef EF_SH_STAGE_AT
 #undef EF_SH_X
 #undef EF_SH_W
 #undef EF_SH_STAGE
@@ -246,7 +245,7 @@ __global__ __launch_bounds__(256, OCC) void ffn_down_shared_kernel(GroupTable gt
     const int cbc = valid ? cb0 : 0;              // waves past the last column load block 0 and drop the result
     const int F = gt.F[grp];
     const int nkb = F >> 4, nq = F >> 6;          // F is a multiple of 128: whole stages
-    const int q0 = (int)((long long)kslice * nq / ksg), q1 = (int)((long long)(kslice + 1) * nq / ksg);
+    const int q0 = shared_slice_begin(nq, ksg, kslice), q1 = shared_slice_begin(nq, ksg, kslice + 1);
     int ntl = gt.n_tiles[grp] - pass * TT;
     if (ntl > TT) ntl = TT;
 
@@ -268,7 +267,7 @@ hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles
     if (total_wgs <= 0) return hipSuccess;
     if (d % 64 != 0) return hipErrorInvalidValue;
     for (int i = 0; i < gt.n_groups; ++i)
-        if (gt.F[i] % 128 != 0 || gt.n_tiles[i] <= 0 || gt.ksg[i] < 1 ||
+        if (gt.F[i] % 128 != 0 || gt.n_tiles[i] <= 0 || gt.ksg[i] < 1 || gt.ksg[i] > gt.F[i] / 64 ||
             gt.wg_start[i + 1] - gt.wg_start[i] != ffn_down_shared_wgs(d, gt.n_tiles[i], tiles_per_pass, gt.ksg[i]))
             return hipErrorInvalidValue;
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;

@@ -219,6 +219,17 @@ inline int ffn_gate_up_shared_wgs(int F, int n_tiles, int tiles_per_pass) {
 inline int ffn_down_shared_wgs(int d, int n_tiles, int tiles_per_pass, int ksg) {
     return ((d / 32 + 7) / 8) * ((n_tiles + tiles_per_pass - 1) / tiles_per_pass) * ksg;
 }
+// Their K loops walk stages of 64 columns.  A K slice of the second half is the stages [begin(slice), begin(slice + 1)); a
+// group takes at most one slice per stage (more would be planes of zeros).  Loads run ahead of the loop without a test: past
+// the slice's end they read its last stage again, in an empty slice stage 0, so no load leaves the group's stages.
+inline __host__ __device__ int shared_slice_begin(int stages, int slices, int slice) {
+    return (int)((long long)slice * stages / slices);
+}
+inline __host__ __device__ int shared_last_stage(int end) { return end > 0 ? end - 1 : 0; }
+inline __host__ __device__ unsigned shared_stage_offset(int stage, int last) {   // bytes: four fragments of 1 KiB
+    return (unsigned)(stage < last ? stage : last) * 4096u;
+}
+inline int ffn_down_shared_slices(int F, int wanted) { return wanted < F / 64 ? wanted : F / 64; }
 hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *xp,
                                      void *act, int d, hipStream_t s);
 hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles_per_pass, int occ, const void *act, float *y,

@@ -230,6 +230,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     // weight-streaming kernels; at most two launches per FFN half
     ef::GroupTable gu{}, big{};
     ef::DequantTable dq{};
+    int streamed[ef::kMaxGroups];   // expert of each group of `gu`
     int n = 0, nb = 0, max_tiles = 1;
     bool large = false;   // 4-bit: a streamed group has a tiled one's size
     const bool allow_tiled = use_tiled;
@@ -272,6 +273,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             dq.F[nb] = F; dq.src[nb] = blob; dq.dst[nb] = copy;
             blob = copy;
         }
+        if (!tiled) streamed[i] = pg.expert;
         const bool split = tiled && split_expert != kNoSplit && pg.expert == split_expert;
         if (split) split_grp = nb;
         (pg.expert < 0 ? planes.shared : planes.routed[pg.expert]) =
@@ -435,6 +437,10 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
         gu.wg_start[i] = wg_gu;
         dn.wg_start[i] = wg_dn;
         if (shared) {
+            if (const int ksg = ef::ffn_down_shared_slices(gu.F[i], gu.ksg[i]); ksg < gu.ksg[i]) {
+                gu.ksg[i] = dn.ksg[i] = ksg;
+                (streamed[i] < 0 ? planes.shared : planes.routed[streamed[i]]) = (uint8_t)ksg;
+            }
             wg_gu += ef::ffn_gate_up_shared_wgs(gu.F[i], gu.n_tiles[i], tpp);
             wg_dn += ef::ffn_down_shared_wgs(d, gu.n_tiles[i], tpp, gu.ksg[i]);
             continue;

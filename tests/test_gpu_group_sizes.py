@@ -99,6 +99,19 @@ def test_group_sizes_of_the_shared_forms(oracle_mod, tune):
     run_groups(oracle_mod, cfg, SIZES["second passes"], False, tune)
 
 
+@pytest.mark.parametrize("F,F_shared,tune", [(128, 0, dict(down_k_slices=3)), (256, 0, dict(down_k_slices=8)),
+                                             (384, 128, dict(down_k_slices=7)), (512, 256, dict(down_k_slices=8)),
+                                             (128, 2048, dict(down_split_slice_counts=0))], ids=str)
+def test_more_slices_than_stages(oracle_mod, F, F_shared, tune):
+    """A slice count above the F / 64 stages of the second half's K range, forced or taken over from a wide tiled shared FFN:
+    a group takes one slice per stage, and the forced count gives the same sums as that one."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_slices", d=256, F=F, F_shared=F_shared, k=1)
+    sizes = [97, 65, 31, 0, 1, 5, 0, 1] if F_shared < 1024 else [97, 128, 65, 7, 1, 0, 0, 2]
+    out = run_groups(oracle_mod, cfg, sizes, False, tune)
+    if not F_shared:
+        assert np.array_equal(out, run_groups(None, cfg, sizes, False, dict(down_k_slices=F // 64)))
+
+
 @pytest.mark.parametrize("d,F,sizes", [
     (256, 2432, SIZES["second passes"]),                       # 266 workgroups in passes of four
     (320, 4224, [256, 255, 97, 64, 33, 129, 1, 0]),            # 330; an odd number of stages, waves past the last column
