@@ -47,11 +47,16 @@ __device__ __forceinline__ uint32_t pack_act2(float v0, float v1) {
     return __builtin_bit_cast(uint32_t, half2_t{(_Float16)v0, (_Float16)v1});
 }
 
-// silu(g) * u.  The reciprocal is the hardware's (1 ulp, as the exponential beside it): an IEEE division is ten instructions
-// more per element, and the product is rounded to 11 bits next (relative error of a layer against 64 bits 2.072e-4 either
-// way).  256 x 256 tiles end in 128 elements per lane: Mixtral-shaped 8192 tokens 9269 -> 9148 us for two layers, DeepSeek-
-// shaped 2500 tokens 1061 -> 1046, Qwen-shaped 4-bit 640 tokens 382 -> 375.  exp(-g) = inf gives 0 as the division does.
-__device__ __forceinline__ float silu_mul(float g, float u) { return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u; }
+// silu(g) * u.  The quotient g / (1 + exp(-g)) is an IEEE division's (at most 0.5000003 units in the last place off, with a
+// reciprocal one unit off) in five instructions instead of ten: one correction by the residual (Markstein's) behind the
+// hardware's reciprocal, then the fixup for infinities and NaN.  Where the denominator reaches 2^126 (g below -87.3) the
+// reciprocal is 0, and so is the quotient, which is below 2^-119 there.  256 x 256 tiles end in 128 elements per lane; two
+// layers, IEEE division / this: Mixtral-shaped 8192 tokens 9375 / 9297 us, DeepSeek-shaped 1056 697.9 / 696.0.  The bare
+// product with the reciprocal (9242 us) is up to 3.4 units off.
+__device__ __forceinline__ float silu_mul(float g, float u) {
+    const float den = 1.f + __expf(-g), r = __builtin_amdgcn_rcpf(den), q = g * r;
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, den, g), r, q), den, g) * u;
+}
 
 // streaming (read-once) 16-byte load: keeps expert weights from displacing reused data in L2
 __device__ __forceinline__ uint4 load_stream(const uint4 *p) {
