@@ -193,7 +193,7 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 }
 
 // Token tiles per pass over a streamed group's weights, for a launch whose largest group has `max_tiles` and whose first
-// half would have `wgs_of_four` workgroups in passes of four, beside `tiled_wgs` of a tiled one.  16-bit: groups of three or
+// half would have `wgs_of_four` workgroups in passes of four, beside `tiled_units` of a tiled one.  16-bit: groups of three or
 // more tiles (too few for the tiled kernels) take passes of four, which halves the re-reads of their weights, and where the
 // largest has five or more and the chip has more workgroups than compute units, streamed or tiled, passes of eight: no group
 // reads its weights twice (two layers, passes of four / eight: Mixtral-shaped 300 / 350 / 700 tokens 1219 / 1110, 1278 / 1139,
@@ -204,8 +204,8 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 // often, but a pass is twice as long; they pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes
 // of two / four: Mixtral-shaped 200 tokens, 1008 workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515;
 // Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-shaped 300 tokens, 671, 289 / 312).
-int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_wgs) {
-    if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_wgs > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
+int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_units) {
+    if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_units > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
         c->tune.lds_shared != 0 && c->cfg.d_ff % 128 == 0 && c->cfg.d_ff_shared % 128 == 0)
         return 8;
     if (max_tiles >= 3 && c->tune.passes_of_four != 0 && (!c->q4 || wgs_of_four >= 896)) return 4;
@@ -335,7 +335,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     }
     side.forked = *forked = forks;
     hipStream_t gs = forks ? c->side_stream : s;   // of the streamed launches
-    int tiled_up_wgs = 0, tiled_dn_wgs = 0;
+    int tiled_up_wgs = 0, tiled_dn_wgs = 0, tiled_units = 0;   // units: workgroups that do not exit at once
     double tb_up = 0.0, tb_dn = 0.0, tf_up = 0.0, tf_dn = 0.0;
     ef::GroupTable bdn = big;
     if (nb > 0) {
@@ -370,7 +370,9 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
                 continue;
             }
             const int ks = i == split_grp ? split_ksg : ksg_tiled;
-            big.xcd_rot[i] = place(ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1), load_up);
+            const int units = ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1);
+            tiled_units += units;
+            big.xcd_rot[i] = place(units, load_up);
             bdn.xcd_rot[i] = place(ef::ffn_tiled_units(d / 256, big.n_tiles[i], ks), load_dn);
             wg_up += ef::ffn_gate_up_tiled_wgs(big.F[i], big.n_tiles[i]);
             wg_dn += ef::ffn_down_tiled_wgs(d, big.n_tiles[i], ks);
@@ -419,7 +421,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     // 4-bit groups of a tiled one's size stream because of what the whole layer holds; a phase that has one keeps to the
     // layer's pass width (for which the K slices of the second half were chosen) and does not cut the first half's K range
     // in two, whatever else is resident: such a group's sums do not depend on the phase it runs in
-    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, tiled_up_wgs);
+    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, tiled_units);
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;

@@ -2,7 +2,9 @@
 the CPU oracle.  The routing is the caller's (ef_moe_ffn takes ids, weights and permutation), so each expert gets exactly
 the tokens the case names.  Bounds as in the other parity tests: max-abs 2e-2, relative L2 1e-2 (one fp16 rounding of the
 intermediate activation; observed relative L2 2e-4)."""
+import contextlib
 import dataclasses
+import re
 
 import numpy as np
 import pytest
@@ -27,9 +29,10 @@ SIZES = {
 }
 
 
-def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=None):
+def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=None, forms=None):
     """Output of the layer; compared with the oracle if one is given.  slots: fewer cache slots than experts, all empty.
-    expect: launches of kernel kinds; flops: their algorithmic flops."""
+    expect: launches of kernel kinds; flops: their algorithmic flops; forms: template arguments of the LDS-shared kernels that
+    ran (token tiles per pass, register ring, workgroups per compute unit), the same in both halves."""
     T, E = sum(sizes), cfg.E
     st = LayerStack(cfg, 1, slots_total=slots or E, max_tokens=T, q4=q4, flags=ef.EF_FLAG_PROFILE if expect else 0)
     try:
@@ -51,8 +54,12 @@ def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=
         dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
         out = torch.full((T, cfg.d), float("nan"), dtype=torch.float32, device="cuda")
         hd, d_ids, d_w, d_off, d_perm, d_inv = dev_u16(h), dev(ids), dev(w), dev(offsets), dev(perm), dev(inv)
-        ef.ef_moe_ffn(st.ctx, 0, hd, T, d_ids, d_w, counts, d_off, d_perm, d_inv, out, torch.cuda.current_stream())
-        torch.cuda.synchronize()
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) if forms else contextlib.nullcontext() as prof:
+            ef.ef_moe_ffn(st.ctx, 0, hd, T, d_ids, d_w, counts, d_off, d_perm, d_inv, out, torch.cuda.current_stream())
+            torch.cuda.synchronize()
+        if forms:
+            ran = [m.groups() for m in (re.search(r"ffn_(gate_up|down)_shared_kernel<([\d, ]+)>", e.name) for e in prof.events()) if m]
+            assert sorted(ran) == sorted((half, form) for half in ("down", "gate_up") for form in forms), ran
         if expect:
             launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
             assert {k: launches[k] for k in expect} == expect
@@ -123,6 +130,16 @@ def test_passes_of_eight(oracle_mod, d, F, sizes):
     out = run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=1))
     same = run_groups(None, cfg, sizes, False, dict(down_k_slices=3))
     assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums
+
+
+@pytest.mark.parametrize("large,form", [(5, "4, 2, 2"), (6, "8, 3, 1")])
+def test_pass_width_beside_tiled_groups(oracle_mod, large, form):
+    """Groups of 17 token tiles, 51 units of a tiled first half each on 56 workgroups (an XCD's share is rounded up): five of
+    them are a round of the compute units (255), six are more.  The streamed group of six tiles takes passes of four beside
+    the first, of eight beside the second."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_units", d=256, F=2176, F_shared=0, k=1)
+    sizes = [513] * large + [161, 1] + [0] * (6 - large)
+    run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=1, ffn_up_tiled=1), forms=[form])
 
 
 @pytest.mark.parametrize("sizes,F", [([257, 300, 288, 320, 352, 290, 383, 289], 4864),   # 912 workgroups in passes of four
