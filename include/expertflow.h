@@ -500,10 +500,11 @@ typedef struct ef_tuning {
     int32_t passes_of_four;          /* 0/1: streamed groups of >= 3 token tiles take passes of four tiles, 16-bit ones of >= 5
                                         passes of eight where the chip has more workgroups than compute units (1) */
     int32_t lds_shared;              /* 0/1: ... through the kernels whose waves share fragments in LDS (1) */
-    int32_t lds_shared_occupancy;    /* workgroups per compute unit of those kernels: 1, 2, or 0 = two for a launch of more
-                                        workgroups than compute units (d_model > 2048: than two per unit) beside at most
-                                        half a round of tiled ones, for one of fewer beside more than a round, and for
-                                        few short ones (0) */
+    int32_t lds_shared_occupancy;    /* 1, 2: passes of four only, that many workgroups of those kernels per compute unit.
+                                        0 = passes of eight where the rule above takes them (one per unit), else two for a
+                                        launch of more workgroups than compute units (d_model > 2048: than two per unit)
+                                        beside at most half a round of tiled ones, for one of fewer beside more than a
+                                        round, and for few short ones (0) */
     int32_t up_want_waves;           /* >= 1: the streamed first half splits K inside a workgroup below this many waves (640) */
     int32_t up_k_slices;             /* 0 = auto, else 1, 2 or 4 */
     int32_t down_want_wgs;           /* 0 = auto (256; 512 for the LDS-shared kernels), else >= 1: target of the K-slice split */

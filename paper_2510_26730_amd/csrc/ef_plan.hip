@@ -200,13 +200,13 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 // 1619 / 1480 us, two experts 200 tokens 556 / 454; DeepSeek-shaped 1056 tokens 711 / 694, on 16 experts with 385 tiled
 // workgroups 551 / 524).  With fewer every workgroup has a unit to itself, and the longer ones end the launch (Qwen-shaped
 // on 12 experts, 121 streamed and 231 tiled, 640 tokens 357 / 413; DeepSeek-shaped on 16, 176 and 198, 600 tokens 372 / 380;
-// d = 512, 56 and 40, 700 tokens 147 / 155).  4-bit: passes of four dequantise half as
+// d = 512, 56 and 40, 700 tokens 147 / 155).  A set lds_shared_occupancy asks for a form of the passes of four.  4-bit: passes of four dequantise half as
 // often, but a pass is twice as long; they pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes
 // of two / four: Mixtral-shaped 200 tokens, 1008 workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515;
 // Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-shaped 300 tokens, 671, 289 / 312).
 int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_units) {
     if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_units > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
-        c->tune.lds_shared != 0 && c->cfg.d_ff % 128 == 0 && c->cfg.d_ff_shared % 128 == 0)
+        c->tune.lds_shared != 0 && c->tune.lds_shared_occupancy == 0 && c->cfg.d_ff % 128 == 0 && c->cfg.d_ff_shared % 128 == 0)
         return 8;
     if (max_tiles >= 3 && c->tune.passes_of_four != 0 && (!c->q4 || wgs_of_four >= 896)) return 4;
     return max_tiles >= 2 ? 2 : 1;

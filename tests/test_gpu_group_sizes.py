@@ -132,6 +132,13 @@ def test_passes_of_eight(oracle_mod, d, F, sizes):
     assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums
 
 
+@pytest.mark.parametrize("occupancy,form", [(0, "8, 3, 1"), (1, "4, 3, 1"), (2, "4, 2, 2")])
+def test_a_set_occupancy_asks_for_a_form_of_passes_of_four(occupancy, form):
+    """266 workgroups in passes of four, groups of up to eight tiles: passes of eight unless a form of the others is set."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_forms", d=256, F=2432, F_shared=0, k=1)
+    run_groups(None, cfg, SIZES["second passes"], False, dict(lds_shared_occupancy=occupancy), forms=[form])
+
+
 @pytest.mark.parametrize("large,form", [(5, "4, 2, 2"), (6, "8, 3, 1")])
 def test_pass_width_beside_tiled_groups(oracle_mod, large, form):
     """Groups of 17 token tiles, 51 units of a tiled first half each on 56 workgroups (an XCD's share is rounded up): five of
