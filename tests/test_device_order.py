@@ -24,6 +24,6 @@ def test_distance_blocks_order_their_operand_exchange():
     """Each stage of the distance blocks passes operands between lanes through the wave's own LDS buffer: ordered after
     the writes and again before the next stage overwrites them."""
     kernels = {n: body for n, body in device_functions("ef_dist.hip").items() if "dist_block_kernel" in n}
-    assert len(kernels) == 2
+    assert len(kernels) == 4      # blocks of 32 x 32 and 64 x 64, four and eight waves
     for name, body in kernels.items():
         assert body.count("wave_lds_sync") >= 2, name
