@@ -10,7 +10,7 @@
 // still stream straight from HBM into operand registers (1 KiB fragments, nontemporal), a register ring
 // of three stages per wave, one barrier per stage of four k-blocks.
 //
-// Passes of two, four or eight tiles.  A second pass over a group's weights is read from HBM again: the two are not in step,
+// Passes of four or eight tiles.  A second pass over a group's weights is read from HBM again: the two are not in step,
 // and what the 64 workgroups of an XCD have in flight alone fills its L2 (numbering them so that both passes over a row block
 // run on one XCD side by side changed nothing).  Eight tiles are 256 accumulator registers and 64 matrix instructions per
 // stage and wave, 1 us for the 32 KiB of weights that a compute unit gets in 1.3 us at 6.3 TB/s: still bound by HBM
@@ -180,9 +180,7 @@ hipError_t launch_ffn_gate_up_shared(const GroupTable &gt, int total_wgs, int ti
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *x = reinterpret_cast<const uint4 *>(xp);
     uint4 *a = reinterpret_cast<uint4 *>(act);
-    if (tiles_per_pass == 2)
-        hipLaunchKernelGGL((ffn_gate_up_shared_kernel<2, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
-    else if (tiles_per_pass == 4 && occ == 2)
+    if (tiles_per_pass == 4 && occ == 2)
         hipLaunchKernelGGL((ffn_gate_up_shared_kernel<4, 2, 2>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
     else if (tiles_per_pass == 4)
         hipLaunchKernelGGL((ffn_gate_up_shared_kernel<4, kShDepth, 1>), dim3(total_wgs), dim3(256), 0, s, gt, x, a, d);
@@ -272,9 +270,7 @@ hipError_t launch_ffn_down_shared(const GroupTable &gt, int total_wgs, int tiles
             return hipErrorInvalidValue;
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *a = reinterpret_cast<const uint4 *>(act);
-    if (tiles_per_pass == 2)
-        return launch_done(ffn_down_shared_kernel<2, kShDepth, 1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
-    else if (tiles_per_pass == 4 && occ == 2)
+    if (tiles_per_pass == 4 && occ == 2)
         return launch_done(ffn_down_shared_kernel<4, 2, 2>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
     else if (tiles_per_pass == 4)
         return launch_done(ffn_down_shared_kernel<4, kShDepth, 1>, dim3(total_wgs), dim3(256), done, s, gt, a, y, d, y_plane);
