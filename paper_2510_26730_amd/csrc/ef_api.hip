@@ -229,6 +229,12 @@ static hipError_t q4_stage_reserve(ef_ctx *c, int min_units) {
     return e;
 }
 
+// A pair that times what lies between its records.  As the read markers (ef_create), without a system-scope release.
+static hipError_t create_timing_pair(EfEventPair &p) {
+    const hipError_t e = hipEventCreateWithFlags(&p.a, hipEventDisableSystemFence);
+    return e != hipSuccess ? e : hipEventCreateWithFlags(&p.b, hipEventDisableSystemFence);
+}
+
 extern "C" int ef_create(const ef_config *cfg, ef_ctx **out) {
     if (!cfg || !out) return fail(nullptr, EF_EINVAL, "ef_create: null argument");
     *out = nullptr;
@@ -367,10 +373,8 @@ extern "C" int ef_create(const ef_config *cfg, ef_ctx **out) {
     else if (g.flags & EF_FLAG_PROFILE_FFN_UP) c->profile_mask = 1u << EF_K_FFN_UP;
     if (c->profile_mask) c->prof_ring.resize(1024);
     for (auto *ring : {&c->stall_ring, &c->layer_ring, &c->prof_ring})
-        for (auto &p : *ring) {
-            if ((e = hipEventCreateWithFlags(&p.a, hipEventDisableSystemFence)) != hipSuccess) return bail(e, "event");
-            if ((e = hipEventCreateWithFlags(&p.b, hipEventDisableSystemFence)) != hipSuccess) return bail(e, "event");
-        }
+        for (auto &p : *ring)
+            if ((e = create_timing_pair(p)) != hipSuccess) return bail(e, "event");
     if (copy_engine_start(c) != EF_OK) {
         std::string keep = thread_error();
         ef_destroy(c);
@@ -641,10 +645,7 @@ extern "C" int ef_set_profile(ef_ctx *c, unsigned kinds_mask) {
     poll_prof(c, true);
     if (kinds_mask && c->prof_ring.empty()) {
         c->prof_ring.resize(1024);
-        for (auto &p : c->prof_ring) {
-            EF_HIP(c, hipEventCreate(&p.a));
-            EF_HIP(c, hipEventCreate(&p.b));
-        }
+        for (auto &p : c->prof_ring) EF_HIP(c, create_timing_pair(p));
     }
     c->profile_mask = kinds_mask & 0x3FFu;
     return EF_OK;
