@@ -119,17 +119,23 @@ def test_more_slices_than_stages(oracle_mod, F, F_shared, tune):
         assert np.array_equal(out, run_groups(None, cfg, sizes, False, dict(down_k_slices=F // 64)))
 
 
-@pytest.mark.parametrize("d,F,sizes", [
-    (256, 2432, SIZES["second passes"]),                       # 266 workgroups in passes of four
-    (320, 4224, [256, 255, 97, 64, 33, 129, 1, 0]),            # 330; an odd number of stages, waves past the last column
-    (256, 2816, [320, 320, 320, 320, 320, 320, 288, 161]),     # 44 beside 308 tiled
+@pytest.mark.parametrize("d,F,F_shared,sizes", [
+    (256, 2432, 0, SIZES["second passes"]),                       # 266 workgroups in passes of four
+    (320, 4224, 0, [256, 255, 97, 64, 33, 129, 1, 0]),            # 330; an odd number of stages, waves past the last column
+    (256, 2816, 0, [320, 320, 320, 320, 320, 320, 288, 161]),     # 44 beside 308 tiled
+    (320, 2432, 0, [288, 345, 512, 65, 96, 31, 0, 7]),            # 228 + 57: second passes of one, three and eight tiles
+    (256, 4096, 2816, [33, 40, 96, 65, 1, 7, 12, 11]),            # the shared FFN, nine tiles, streams with the experts
 ])
-def test_passes_of_eight(oracle_mod, d, F, sizes):
-    """One to eight live tiles in passes of eight, full and ragged last tiles, K slices of unequal length."""
-    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_eight", d=d, F=F, F_shared=0, k=1)
-    out = run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=1))
-    same = run_groups(None, cfg, sizes, False, dict(down_k_slices=3))
+def test_passes_of_eight(oracle_mod, d, F, F_shared, sizes):
+    """One to eight live tiles in passes of eight, first and second ones, full and ragged last tiles, K slices of unequal
+    length; and the bits of both forms of the passes of four."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_eight", d=d, F=F, F_shared=F_shared, k=1)
+    out = run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=1), forms=["8, 3, 1"])
+    same = run_groups(None, cfg, sizes, False, dict(down_k_slices=3), forms=["8, 3, 1"])
     assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums
+    for occupancy, form in ((1, "4, 3, 1"), (2, "4, 2, 2")):
+        four = run_groups(None, cfg, sizes, False, dict(down_k_slices=3, lds_shared_occupancy=occupancy), forms=[form])
+        assert np.array_equal(same, four)
 
 
 @pytest.mark.parametrize("occupancy,form", [(0, "8, 3, 1"), (1, "4, 3, 1"), (2, "4, 2, 2")])

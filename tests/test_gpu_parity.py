@@ -434,20 +434,20 @@ def test_full_size_qwen_mixed_batch(oracle_mod, force_tiled):
         st.close()
 
 
-@pytest.mark.parametrize("streamed_form", ["shared4", "shared4_two_per_cu", "plain4", "plain2"])
+@pytest.mark.parametrize("streamed_form", ["shared8", "shared4", "shared4_two_per_cu", "plain4", "plain2"])
 def test_full_size_deepseek_prefill(oracle_mod, streamed_form):
     """DeepSeek-V2-Lite-shaped layer at its three batch shapes: 32 decode tokens, 1024 prefill tokens and
     the mixed 1056 (shared experts through the tiled kernels from 256 tokens on, routed experts
     streamed).  The routed experts of the larger batches hold 3-7 token tiles: by default they take passes of
-    four tiles through the kernels that share fragments in LDS (one workgroup per compute unit, or two with a
-    shorter register ring: the form taken beside a large tiled launch); the other two forms (plain kernels with
-    passes of four, or of two tiles) are forced through ef_set_tuning."""
+    eight tiles through the kernels that share fragments in LDS; the other forms (those kernels in passes of four, one
+    workgroup per compute unit or two with a shorter register ring, and the plain kernels with passes of four, or of
+    two tiles) are forced through ef_set_tuning."""
     cfg = synth.CONFIGS["deepseek_v2_lite"]
     st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=1056)
     try:
-        if streamed_form == "shared4_two_per_cu":
-            ef.ef_set_tuning(st.ctx, lds_shared_occupancy=2)
-        elif streamed_form != "shared4":
+        if streamed_form.startswith("shared4"):
+            ef.ef_set_tuning(st.ctx, lds_shared_occupancy=2 if streamed_form == "shared4_two_per_cu" else 1)
+        elif streamed_form != "shared8":
             ef.ef_set_tuning(st.ctx, lds_shared=0)
         if streamed_form == "plain2":
             ef.ef_set_tuning(st.ctx, passes_of_four=0)
@@ -458,16 +458,19 @@ def test_full_size_deepseek_prefill(oracle_mod, streamed_form):
             say(f"full size: DeepSeek-V2-Lite-shaped layer, T={T}, shared experts")
             res_now = ef.ef_cache_query(st.ctx, 0, cfg.E)
             _sampled_layer_check(oracle_mod, st, 0, synth.hidden(cfg, 0, T), T, 0.5, res_now, n_sample, seed)
-        if streamed_form == "shared4":
-            # which of the two LDS-sharing forms a launch takes depends on what else is in the launch (how many
-            # tiled workgroups run beside it), so the two must agree bit for bit: same sums in the same order
+        if streamed_form == "shared8":
+            # which of the LDS-sharing forms a launch takes depends on what else is in the launch (how many
+            # tiled workgroups run beside it), so they must agree bit for bit: same sums in the same order
             hd = dev_u16(synth.hidden(cfg, 0, 1056))
             r = st.route(0, hd, 1056, 0.5)
             outs = []
-            for occ in (1, 2):
+            for occ, form in ((0, "8, 3, 1"), (1, "4, 3, 1"), (2, "4, 2, 2")):
                 ef.ef_set_tuning(st.ctx, lds_shared_occupancy=occ)
-                outs.append(st.ffn(0, hd, 1056, r))
-            assert np.array_equal(outs[0], outs[1])
+                with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+                    outs.append(st.ffn(0, hd, 1056, r))
+                ran = [e.name for e in prof.events() if "_shared_kernel<" in e.name]
+                assert len(ran) == 2 and all(f"_shared_kernel<{form}>" in n for n in ran), ran
+            assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[1], outs[2])
     finally:
         st.close()
 
