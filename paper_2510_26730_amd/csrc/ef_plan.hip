@@ -193,19 +193,22 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 }
 
 // Token tiles per pass over a streamed group's weights, for a launch whose largest group has `max_tiles` and whose first
-// half would have `wgs_of_four` workgroups in passes of four, beside `tiled_units` of a tiled one.  16-bit: groups of three or
+// half would have `wgs_of_four` workgroups in passes of four, beside `tiled_wgs` of a tiled one.  16-bit: groups of three or
 // more tiles (too few for the tiled kernels) take passes of four, which halves the re-reads of their weights, and where the
-// largest has five or more and the chip has more workgroups than compute units, streamed or tiled, passes of eight: no group
-// reads its weights twice (two layers, passes of four / eight: Mixtral-shaped 300 / 350 / 700 tokens 1219 / 1110, 1278 / 1139,
-// 1619 / 1480 us, two experts 200 tokens 556 / 454; DeepSeek-shaped 1056 tokens 711 / 694, on 16 experts with 385 tiled
-// workgroups 551 / 524).  With fewer every workgroup has a unit to itself, and the longer ones end the launch (Qwen-shaped
-// on 12 experts, 121 streamed and 231 tiled, 640 tokens 357 / 413; DeepSeek-shaped on 16, 176 and 198, 600 tokens 372 / 380;
-// d = 512, 56 and 40, 700 tokens 147 / 155).  A set lds_shared_occupancy asks for a form of the passes of four.  4-bit: passes of four dequantise half as
-// often, but a pass is twice as long; they pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes
-// of two / four: Mixtral-shaped 200 tokens, 1008 workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515;
-// Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-shaped 300 tokens, 671, 289 / 312).
-int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_units) {
-    if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_units > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
+// largest has five or more and the chip has more workgroups than compute units, streamed or tiled, passes of eight: a group of
+// up to eight tiles reads its weights once (two layers, passes of four / eight: Mixtral-shaped 300 / 350 / 700 tokens 1219 /
+// 1110, 1278 / 1139, 1619 / 1480 us, two experts 200 tokens 556 / 454; DeepSeek-shaped 1056 tokens 711 / 694, on 16 experts
+// with 385 tiled workgroups 551 / 524).  With fewer every workgroup has a unit to itself, and the longer ones end the launch
+// (Qwen-shaped on 12 experts, 121 streamed and 231 tiled, 640 tokens 357 / 413; DeepSeek-shaped on 16, 176 and 198, 600 tokens
+// 372 / 380; d = 512, 56 and 40, 700 tokens 147 / 155).  Tiled workgroups are counted as they are launched, a multiple of
+// eight per group: with 240 to 256 that do not exit at once the streamed ones wait for units all the same (Qwen-shaped on 12
+// experts, 700 / 760 tokens 409 / 399, 434 / 420; DeepSeek-shaped on 16, 700 tokens 416 / 419).  A set lds_shared_occupancy
+// asks for a form of the passes of four.  4-bit: passes of four dequantise half as often, but a pass is twice as long; they
+// pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes of two / four: Mixtral-shaped 200 tokens, 1008
+// workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515; Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-
+// shaped 300 tokens, 671, 289 / 312).
+int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_wgs) {
+    if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_wgs > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
         c->tune.lds_shared != 0 && c->tune.lds_shared_occupancy == 0 && c->cfg.d_ff % 128 == 0 && c->cfg.d_ff_shared % 128 == 0)
         return 8;
     if (max_tiles >= 3 && c->tune.passes_of_four != 0 && (!c->q4 || wgs_of_four >= 896)) return 4;
@@ -335,7 +338,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     }
     side.forked = *forked = forks;
     hipStream_t gs = forks ? c->side_stream : s;   // of the streamed launches
-    int tiled_up_wgs = 0, tiled_dn_wgs = 0, tiled_units = 0;   // units: workgroups that do not exit at once
+    int tiled_up_wgs = 0, tiled_dn_wgs = 0;
     double tb_up = 0.0, tb_dn = 0.0, tf_up = 0.0, tf_dn = 0.0;
     ef::GroupTable bdn = big;
     if (nb > 0) {
@@ -370,9 +373,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
                 continue;
             }
             const int ks = i == split_grp ? split_ksg : ksg_tiled;
-            const int units = ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1);
-            tiled_units += units;
-            big.xcd_rot[i] = place(units, load_up);
+            big.xcd_rot[i] = place(ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1), load_up);
             bdn.xcd_rot[i] = place(ef::ffn_tiled_units(d / 256, big.n_tiles[i], ks), load_dn);
             wg_up += ef::ffn_gate_up_tiled_wgs(big.F[i], big.n_tiles[i]);
             wg_dn += ef::ffn_down_tiled_wgs(d, big.n_tiles[i], ks);
@@ -421,7 +422,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     // 4-bit groups of a tiled one's size stream because of what the whole layer holds; a phase that has one keeps to the
     // layer's pass width (for which the K slices of the second half were chosen) and does not cut the first half's K range
     // in two, whatever else is resident: such a group's sums do not depend on the phase it runs in
-    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, tiled_units);
+    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, tiled_up_wgs);
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;
@@ -565,7 +566,8 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
     // tokens 1560 / 1459, 2000 tokens on 16 experts 873 / 778; Qwen-shaped 3000 tokens 1120 / 1026.
     bool q4_expand = false;
     long long passes_of_four_dn = 0;   // workgroups of a second half of the tiled groups in passes of four
-    long long tiled_up_wgs = 0, tiled_dn_wgs = 0, tiled_rows = 0;
+    long long tiled_up_units = 0, tiled_up_wgs = 0;   // of the tiled first half; its launch rounds up to eight per group
+    long long tiled_dn_wgs = 0, tiled_rows = 0;
     int tiled_stages_min = 1 << 30;   // fewest K stages (32 columns each) among the tiled groups
     int tiled_stages_max = 0;         // ... and most
     if (T > 0 && c->tune.tiled != 0) {
@@ -574,6 +576,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             if (!takes_tiled(c, F, nt, routed, early)) return;
             wg_up += ef::ffn_tiled_units(F / 128, nt, 1);
+            tiled_up_wgs += ef::ffn_gate_up_tiled_wgs(F, nt);
             if (nt >= ef::kQ4ExpandTiles) wg_up_large += ef::ffn_tiled_units(F / 128, nt, 1);
             passes_of_four_dn += ef::ffn_down_q4_wgs(d, nt, 4, 1);
             wg_dn += ef::ffn_tiled_units(d / 256, nt, 1);
@@ -615,7 +618,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             // Qwen-shaped 260 tokens on 12 experts, 88 tiles, 290 / 348 us)
             use_tiled = false;
         }
-        tiled_up_wgs = wg_up;
+        tiled_up_units = wg_up;
         tiled_dn_wgs = wg_dn;
     }
     // K slices of the second half (one Y plane each, summed by the un-permute): the streamed launch and the tiled
@@ -626,7 +629,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         long long base_wgs = 0;
         double streamed_w2_bytes = 0.0;   // second-half weights of the routed groups that stream (4-bit blobs)
         // token tiles per pass of the streamed launch: from the groups that stream (the tiled ones have kernels of
-        // their own), with the same rule launch_phase applies to a phase's streamed groups
+        // their own), with the rule that launch_phase applies to a phase's groups
         int tmax = 1;
         long long wgs_of_four = 0;
         auto see = [&](int F, int cnt) {
@@ -716,7 +719,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 // 92 us where this says 35, so short ones count as hiding less than they do
                 const double unit_s = stages_ref * 0.77e-6;
                 const double plane_s = (double)tiled_rows * d * 8.0 / 5e12, stream_s = stream_bytes / 5.5e12;
-                const double up_s = (double)((tiled_up_wgs + 255) / 256) * (d / 32) * 0.6e-6;
+                const double up_s = (double)((tiled_up_units + 255) / 256) * (d / 32) * 0.6e-6;
                 double best = 0.0;
                 for (int ks = 1; ks <= 8; ++ks) {
                     if (ks > 1 && (stages_ref / ks < 16 || y_plane * ks > c->y_floats)) break;
@@ -733,7 +736,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 // the tiled first half takes nearly all compute units of its one round: the streamed one then runs behind it,
                 // and the more even workgroups wait for it (680 / 720 tokens on 12 experts 372 / 381, 386 / 405).
                 const int nt_shared = has_shared ? (T + ef::kTile - 1) / ef::kTile : 0;
-                if (c->tune.down_split_slice_counts != 0 && (tiled_up_wgs <= 220 || tiled_up_wgs > 256) && has_shared &&
+                if (c->tune.down_split_slice_counts != 0 && (tiled_up_units <= 220 || tiled_up_units > 256) && has_shared &&
                     takes_tiled(c, c->cfg.d_ff_shared, nt_shared, false, early)) {
                     const int units_s = ef::ffn_tiled_units(d / 256, nt_shared, 1), units_r = (int)tiled_dn_wgs - units_s;
                     const int stages_s = c->cfg.d_ff_shared / 32, stages_r = c->cfg.d_ff / 32;

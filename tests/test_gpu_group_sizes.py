@@ -145,11 +145,10 @@ def test_a_set_occupancy_asks_for_a_form_of_passes_of_four(occupancy, form):
     run_groups(None, cfg, SIZES["second passes"], False, dict(lds_shared_occupancy=occupancy), forms=[form])
 
 
-@pytest.mark.parametrize("large,form", [(5, "4, 2, 2"), (6, "8, 3, 1")])
+@pytest.mark.parametrize("large,form", [(4, "4, 3, 1"), (5, "8, 3, 1")])
 def test_pass_width_beside_tiled_groups(oracle_mod, large, form):
-    """Groups of 17 token tiles, 51 units of a tiled first half each on 56 workgroups (an XCD's share is rounded up): five of
-    them are a round of the compute units (255), six are more.  The streamed group of six tiles takes passes of four beside
-    the first, of eight beside the second."""
+    """Groups of 17 token tiles, 51 units of a tiled first half each on 56 workgroups (an XCD's share is rounded up): the
+    streamed group of six tiles takes passes of four beside four of them (224), of eight beside five (280; 255 units)."""
     cfg = dataclasses.replace(synth.CONFIGS["tiny"], name="groups_units", d=256, F=2176, F_shared=0, k=1)
     sizes = [513] * large + [161, 1] + [0] * (6 - large)
     run_groups(oracle_mod, cfg, sizes, False, {}, expect=dict(ffn_up=1, ffn_up_tiled=1), forms=[form])
