@@ -731,12 +731,11 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
                 // about the same time (K 5632 and 1408 in three slices each are 59 and 15 stages on 240 workgroups, in four
                 // and one 44 each on 152).  Within one round of workgroups, where the longest decides; a workgroup costs 10 us
                 // of a compute unit whatever its length.  Two layers, one count / two: Qwen-shaped on 12 experts 400 / 560 /
-                // 640 / 800 / 1000 / 1200 tokens 309 / 301, 333 / 319, 349 / 341, 429 / 419, 493 / 464, 616 / 550, on 60 1000
-                // tokens 679 / 618; DeepSeek-shaped on 16 300 / 400 / 600 tokens 322 / 313, 340 / 327, 363 / 348.  Not where
-                // the tiled first half takes nearly all compute units of its one round: the streamed one then runs behind it,
-                // and the more even workgroups wait for it (680 / 720 tokens on 12 experts 372 / 381, 386 / 405).
+                // 640 / 720 / 760 / 800 / 1000 / 1200 tokens 317 / 306, 332 / 317, 346 / 340, 402 / 396, 418 / 404, 424 / 413,
+                // 495 / 457, 609 / 529, on 60 1000 tokens 654 / 596; DeepSeek-shaped on 16 300 / 400 / 600 / 700 / 760 tokens
+                // 326 / 317, 344 / 332, 367 / 354, 424 / 390, 441 / 410.
                 const int nt_shared = has_shared ? (T + ef::kTile - 1) / ef::kTile : 0;
-                if (c->tune.down_split_slice_counts != 0 && (tiled_up_units <= 220 || tiled_up_units > 256) && has_shared &&
+                if (c->tune.down_split_slice_counts != 0 && has_shared &&
                     takes_tiled(c, c->cfg.d_ff_shared, nt_shared, false, early)) {
                     const int units_s = ef::ffn_tiled_units(d / 256, nt_shared, 1), units_r = (int)tiled_dn_wgs - units_s;
                     const int stages_s = c->cfg.d_ff_shared / 32, stages_r = c->cfg.d_ff / 32;
