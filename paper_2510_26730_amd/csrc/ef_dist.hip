@@ -702,9 +702,9 @@ hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, fl
         const bool wide = dist_block_wide(T);
         const int nb = (T + (wide ? 63 : 31)) / (wide ? 64 : 32), blocks = nb * (nb + 1) / 2;
         // a block's d over eight waves while every block has a compute unit to itself: half the stages one after the other
-        // (the call, four / eight waves, d = 2048 / 4096: T = 1056 21.3 / 19.5, 1100 31.5 / 27.5, 700 13.1 / 13.0 and 18.4 /
-        // 16.6 us); with more blocks two of four waves share a unit as well and add up fewer partials (T = 900 17.2 / 19.5,
-        // T = 1500 31 / 34.5)
+        // (the call, four / eight waves: d = 2048, T = 700 12.6 / 12.4, 1056 20.2 / 18.0 us; d = 4096, 700 17.1 / 16.5, 1100
+        // 30.7 / 26.3); with more blocks two of four waves share a unit as well and add up fewer partials (d = 2048, T = 900
+        // 16.0 / 18.3, 1500 28.2 / 32.7; d = 4096 23.0 / 26.7, 43.7 / 49.3)
         const bool eight = blocks <= 256 && d % 128 == 0;
         if (wide && eight) hipLaunchKernelGGL((dist_block_kernel<2, 1, 8>), dim3(blocks), dim3(512), 0, s, h, T, d, scratch, t_pad);
         else if (wide) hipLaunchKernelGGL((dist_block_kernel<2, 1, 4>), dim3(blocks), dim3(256), 0, s, h, T, d, scratch, t_pad);

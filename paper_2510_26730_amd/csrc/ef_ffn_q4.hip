@@ -425,7 +425,7 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     return hipGetLastError();
 }
 
-// The K loops of the second half, as those of the first
+// The K loops of the second half, as those of the first (a scale is loaded and converted for every stage)
 #define EF_Q4D_LOAD(slot, kq)                                                                             \
     {                                                                                                     \
         const int kc_ = min((kq), nq - 1);                                                                \

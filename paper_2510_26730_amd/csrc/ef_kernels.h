@@ -161,8 +161,9 @@ constexpr int kDistSmallMaxTokens = 256;
 constexpr int kDistBlockMaxTokens = 3584;   // the call at T = 3500: 87 / 148 us (d = 2048 / 4096) against 106 / 156 us
                                             // through 256 x 256 blocks; from T = 4096 on those are level or ahead
 inline bool dist_needs_packed(int T, int form) { return !(form == 0 && T <= kDistBlockMaxTokens); }
-// 64 x 64 blocks once there are enough of them for half of the compute units, else 32 x 32 (the call, d = 2048 /
-// 4096: T = 900 16.0 / 23.6 us with 32 x 32 against 19.5 / 30.2, T = 1200 22.7 / 33.2 against 20.4 / 30.5)
+// 64 x 64 blocks once there are enough of them for half of the compute units, else 32 x 32 (the call with four waves for
+// either, d = 2048 / 4096: T = 900 16.0 / 23.6 us with 32 x 32 against 19.5 / 30.2, T = 1200 22.7 / 33.2 against 20.4 /
+// 30.5; not measured again with the eight waves that blocks of 64 x 64 take up to T = 1408)
 inline bool dist_block_wide(int T) { return T > 960; }
 // `form`: 0 = by batch size, 1 = register-fed 128 x 256 Gram blocks, 2 = 256 x 256 blocks through LDS (same bits)
 hipError_t launch_token_dist(const uint16_t *h, int T, int d, const void *xp, float *scratch, float *tok_dist,
