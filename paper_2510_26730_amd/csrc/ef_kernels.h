@@ -13,7 +13,7 @@ constexpr int kMaxGroups = kMaxE + 1;  // routed experts + the dense shared FFN
 constexpr int kDownColBlocks = 2;      // 32-column blocks per wave in the second FFN half
 
 constexpr int kGroupSmallTiles = 4;    // token tiles the single-workgroup grouping kernel handles
-constexpr int kGroupLdsTiles = 64;     // ... and the single-launch one
+constexpr int kGroupSumsWords = 16384; // per-tile counts (tiles x experts) that the single-launch one adds up
 
 // Gate / predict launch: G gate matrices applied to the same hidden states.
 struct GateArgs {
@@ -97,7 +97,7 @@ constexpr size_t kFusedMaxLds = 48 * 1024;   // dynamic LDS of the fused kernel 
 size_t gate_fused_lds_bytes(int T, int G, int E, int gpw);
 hipError_t launch_gate_fused(const GateArgs &a, int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv_perm,
                              const GroupExport &ex, hipStream_t s);
-// n_hist > 0 (more than kGroupLdsTiles token tiles only): hist[j][E] = sums of the per-tile counts hist_tiles[j], j < n_hist
+// n_hist > 0 (more than kGroupSmallTiles token tiles only): hist[j][E] = sums of the per-tile counts hist_tiles[j], j < n_hist
 hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, int k, int E, int32_t *blockbase,
                         int32_t *counts, int32_t *offsets, int32_t *perm, int32_t *inv_perm,
                         const int32_t *hist_tiles, int n_hist, int32_t *hist, const GroupExport &ex, hipStream_t s);

@@ -82,7 +82,7 @@ int run_gates(ef_ctx *c, int layer, const void *hidden, int T, float beta, bool 
         // layer; a caller's is written by the scan of the per-tile counts where the call ends in one, and cleared here
         // for the gates' atomics otherwise (a launch of 4 us)
         if (He > 0 && !ex.host_meta && g0 == 0) {
-            if (do_route && total_gates <= per_launch && !a.two_step && ntiles > ef::kGroupLdsTiles)
+            if (do_route && total_gates <= per_launch && !a.two_step && ntiles > ef::kGroupSmallTiles)
                 hist_tiles = rs.blockcounts + (size_t)ntiles * E;
             else EF_HIP(c, ef::launch_fill_i32(pred_hist, He * E, 0, s));
         }

@@ -684,16 +684,27 @@ __device__ __forceinline__ int scan_expert_serial(int *cnt, int ntiles, int E, i
 // position is its expert's next free one plus the number of lower lanes with the same expert, and
 // the lowest such lane advances the expert's entry.  LDS operations of one wave execute in order,
 // so the chunks need no barrier between them.
-__device__ __forceinline__ void scatter_tile(const int32_t *__restrict__ ids, int T, int k, int b, int lane,
-                                             int *nxt, int32_t *__restrict__ perm,
-                                             int32_t *__restrict__ inv_perm) {
-    const int tok0 = b * kTile;
-    const int ntok = min(kTile, T - tok0);
-    const int a0 = tok0 * k, n = ntok * k;
-    for (int c0 = 0; c0 < n; c0 += 64) {
-        const int idx = c0 + lane;
+struct TileIds { int e[kTile * kMaxK / 64]; };
+// The ids of tile b, 64 per element (0 past the end): a round trip to memory that a kernel starts before it knows where they
+// go (64 experts, 32 tokens, one layer predicted, the call 19.3 -> 18.7 us).
+__device__ __forceinline__ TileIds tile_ids(const int32_t *__restrict__ ids, int T, int k, int b, int lane) {
+    const int n = min(kTile, T - b * kTile) * k;   // negative for a tile past the end
+    TileIds t;
+#pragma unroll
+    for (int c = 0; c < kTile * kMaxK / 64; ++c) {
+        const int idx = c * 64 + lane;
+        t.e[c] = idx < n ? ids[(size_t)b * kTile * k + idx] : 0;
+    }
+    return t;
+}
+__device__ __forceinline__ void scatter_tile(const TileIds &ids, int T, int k, int b, int lane, int *nxt,
+                                             int32_t *__restrict__ perm, int32_t *__restrict__ inv_perm) {
+    const int a0 = b * kTile * k, n = min(kTile, T - b * kTile) * k;
+#pragma unroll
+    for (int c = 0; c < kTile * kMaxK / 64; ++c) {
+        if (c * 64 >= n) break;
+        const int idx = c * 64 + lane, e = ids.e[c];
         const bool valid = idx < n;
-        const int e = valid ? ids[a0 + idx] : 0;
         unsigned long long same = __ballot(valid);
 #pragma unroll
         for (int bit = 0; bit < 6; ++bit) {
@@ -730,7 +741,7 @@ __device__ __forceinline__ void export_meta(const GroupExport &ex, const int *to
     for (int x = threadIdx.x; x < ex.n_clear; x += blockDim.x) ex.hist[x] = 0;   // ready for the next layer
 }
 
-// Larger batches than group_lds_kernel takes: one workgroup per expert forms the exclusive prefix of
+// Larger batches than group_sums_kernel takes: one workgroup per expert forms the exclusive prefix of
 // that expert's per-tile counts over the tiles (16 waves, a contiguous range of tiles each: totals first,
 // then the scan with the bases of the waves before), and leaves the expert's total in counts[e].  Further blocks of E
 // workgroups add up the per-tile counts of the look-ahead gates: their histograms need no fill before the gate launch
@@ -786,7 +797,8 @@ __global__ __launch_bounds__(64 * kScatterWaves) void group_scatter_kernel(const
                                                                            int32_t *__restrict__ inv_perm, GroupExport ex) {
     __shared__ int nxt[kScatterWaves][64];
     __shared__ int total[kMaxE];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, b = blockIdx.x * kScatterWaves + wave;
+    const TileIds mine = tile_ids(ids, T, k, b, lane);
     const int t = lane < E ? counts[lane] : 0;
     int incl = t;
 #pragma unroll
@@ -805,11 +817,10 @@ __global__ __launch_bounds__(64 * kScatterWaves) void group_scatter_kernel(const
         __syncthreads();
         export_meta(ex, total, E);
     }
-    const int b = blockIdx.x * kScatterWaves + wave;
     if (b >= ntiles) return;
     nxt[wave][lane] = (lane < E) ? (incl - t) + blockbase[(size_t)b * E + lane] : 0;
     wave_lds_sync();
-    scatter_tile(ids, T, k, b, lane, nxt[wave], perm, inv_perm);
+    scatter_tile(mine, T, k, b, lane, nxt[wave], perm, inv_perm);
 }
 
 // scan + scatter in one workgroup for up to kGroupSmallTiles token tiles (prefixes stay in LDS, one thread per expert)
@@ -824,6 +835,7 @@ __global__ __launch_bounds__(64 * kGroupSmallTiles) void group_small_kernel(cons
     __shared__ int offs[kMaxE + 1];
     __shared__ int nxt[kGroupSmallTiles][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const TileIds mine = tile_ids(ids, T, k, wave, lane);
     // one memory round trip brings the per-tile counts into LDS; the scan then runs from there, in place
     for (int x = threadIdx.x; x < ntiles * E; x += blockDim.x) base[x] = bc[x];
     __syncthreads();
@@ -852,37 +864,61 @@ __global__ __launch_bounds__(64 * kGroupSmallTiles) void group_small_kernel(cons
     if (wave < ntiles) {
         nxt[wave][lane] = (lane < E) ? offs[lane] + base[wave * E + lane] : 0;
         wave_lds_sync();
-        scatter_tile(ids, T, k, wave, lane, nxt[wave], perm, inv_perm);
+        scatter_tile(mine, T, k, wave, lane, nxt[wave], perm, inv_perm);
     }
 }
 
-// Scan and scatter in one launch of several workgroups for up to kGroupLdsTiles token tiles: every workgroup loads all
-// per-tile counts into LDS and forms the totals and the prefixes of its own four tiles itself (a lane per expert walks the
-// tiles), so no workgroup waits for another.  Bound by latency: one load, the walk, one load of the ids.  Against one
-// workgroup that scans and scatters every tile: 64 experts, 33 tiles 12 -> 7 us; beyond 64 tiles the walk costs more than a
-// second launch (125 tiles of 64 experts: 7 us more than scan + scatter).
-__global__ __launch_bounds__(64 * kScatterWaves) void group_lds_kernel(const int32_t *__restrict__ bc, int ntiles,
-                                                                       const int32_t *__restrict__ ids, int T, int k, int E,
-                                                                       int32_t *__restrict__ counts,
-                                                                       int32_t *__restrict__ offsets,
-                                                                       int32_t *__restrict__ perm,
-                                                                       int32_t *__restrict__ inv_perm, GroupExport ex) {
-    __shared__ int cnt[kGroupLdsTiles * kMaxE];
-    __shared__ int total[kMaxE];
+// Scan and scatter in one launch: every workgroup adds up the per-tile counts itself, all of them and those of the tiles
+// before its own four, so no workgroup waits for another; further workgroups add up the per-tile counts of the look-ahead
+// gates, one each.  Bound by latency: a thread takes one expert and every R-th tile, eight loads in flight, while the ids are
+// on their way too.  The whole routing call, one lane per expert walking LDS (up to 64 tiles) or scan + scatter before: 64
+// experts 1056 tokens 20.5 -> 17.8 us, 4096 45.8 -> 43.4, 8 experts 4096 20.0 -> 17.4, 32768 51.2 -> 48.7.  Up to 16384
+// counts: at that many every workgroup reads 64 KiB of them and is level with or ahead of the two launches (64 experts 8192
+// tokens 51.8 against 52.1, 8 experts 65536 97.5 / 99.6), beyond it behind (8 experts 100000 tokens 148.4 / 147.2, 60
+// experts 16000 tokens, two layers predicted, 133.0 / 130.4).
+__global__ __launch_bounds__(64 * kScatterWaves) void group_sums_kernel(const int32_t *__restrict__ bc, int ntiles,
+                                                                        const int32_t *__restrict__ ids, int T, int k, int E,
+                                                                        int32_t *__restrict__ counts,
+                                                                        int32_t *__restrict__ offsets,
+                                                                        int32_t *__restrict__ perm,
+                                                                        int32_t *__restrict__ inv_perm,
+                                                                        const int32_t *__restrict__ hist_tiles,
+                                                                        int32_t *__restrict__ hist, GroupExport ex) {
+    __shared__ int total[kMaxE], before[kMaxE];
     __shared__ int nxt[kScatterWaves][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int x = threadIdx.x; x < ntiles * E; x += blockDim.x) cnt[x] = bc[x];
-    __syncthreads();
-    const int b = blockIdx.x * kScatterWaves + wave;
-    int tot = 0, before = 0;   // this lane's expert: assignments in all tiles, and in the tiles before b
-    if (lane < E) {
-#pragma unroll 8
-        for (int t = 0; t < ntiles; ++t) {
-            const int v = cnt[t * E + lane];
-            tot += v;
-            before += t < b ? v : 0;
+    const int b0 = blockIdx.x * kScatterWaves, b = b0 + wave;
+    const int g = (int)blockIdx.x - (ntiles + kScatterWaves - 1) / kScatterWaves;   // >= 0: a look-ahead gate's histogram
+    if (g >= 0) bc = hist_tiles + (size_t)g * ntiles * E;
+    if (threadIdx.x < kMaxE) total[threadIdx.x] = before[threadIdx.x] = 0;
+    const TileIds mine = tile_ids(ids, T, k, b, lane);
+    int own[kScatterWaves - 1];   // this lane's expert in the workgroup's tiles before the wave's
+#pragma unroll
+    for (int j = 0; j < kScatterWaves - 1; ++j) own[j] = lane < E && j < wave ? bc[(size_t)min(b0 + j, ntiles - 1) * E + lane] : 0;
+    const int R = 64 * kScatterWaves / E, r = threadIdx.x / E, e = threadIdx.x - r * E;
+    int tot = 0, bef = 0;
+    for (int t0 = r; r < R && t0 < ntiles; t0 += 8 * R) {
+        int v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = bc[(size_t)min(t0 + q * R, ntiles - 1) * E + e];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int t = t0 + q * R;
+            tot += t < ntiles ? v[q] : 0;
+            bef += t < min(b0, ntiles) ? v[q] : 0;
         }
     }
+    __syncthreads();
+    if (r < R) {
+        atomicAdd(&total[e], tot);
+        atomicAdd(&before[e], bef);
+    }
+    __syncthreads();
+    if (g >= 0) {
+        if (threadIdx.x < (unsigned)E) hist[g * E + threadIdx.x] = total[threadIdx.x];
+        return;
+    }
+    tot = lane < E ? total[lane] : 0;
     int incl = tot;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -894,17 +930,18 @@ __global__ __launch_bounds__(64 * kScatterWaves) void group_lds_kernel(const int
             if (lane < E) {
                 counts[lane] = tot;
                 offsets[lane] = incl - tot;
-                total[lane] = tot;
             }
             if (lane == 63) offsets[E] = incl;
         }
-        __syncthreads();
         export_meta(ex, total, E);   // the host starts planning while the scatter below still runs
     }
     if (b >= ntiles) return;
-    nxt[wave][lane] = lane < E ? incl - tot + before : 0;
+    int at = lane < E ? incl - tot + before[lane] : 0;
+#pragma unroll
+    for (int j = 0; j < kScatterWaves - 1; ++j) at += own[j];
+    nxt[wave][lane] = at;
     wave_lds_sync();
-    scatter_tile(ids, T, k, b, lane, nxt[wave], perm, inv_perm);
+    scatter_tile(mine, T, k, b, lane, nxt[wave], perm, inv_perm);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1068,7 +1105,7 @@ __global__ __launch_bounds__(1024) void gate_finish_group_kernel(GateArgs a, int
     for (int b = wave; b < ntiles; b += NW) {
         nxt[wave][lane] = (lane < E) ? offs[lane] + base[b * E + lane] : 0;
         wave_lds_sync();
-        scatter_tile(s_ids, a.T, a.k, b, lane, nxt[wave], perm, inv_perm);
+        scatter_tile(tile_ids(s_ids, a.T, a.k, b, lane), a.T, a.k, b, lane, nxt[wave], perm, inv_perm);
     }
 }
 
@@ -1116,15 +1153,16 @@ hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, i
                         const int32_t *hist_tiles, int n_hist, int32_t *hist, const GroupExport &ex, hipStream_t s) {
     if (T <= 0) return hipSuccess;
     const int ntiles = (T + kTile - 1) / kTile;
-    if (n_hist > 0 && (ntiles <= kGroupLdsTiles || n_hist >= kMaxGates || !hist_tiles || !hist)) return hipErrorInvalidValue;
+    if (n_hist > 0 && (ntiles <= kGroupSmallTiles || n_hist >= kMaxGates || !hist_tiles || !hist)) return hipErrorInvalidValue;
     if (ntiles <= kGroupSmallTiles) {
         hipLaunchKernelGGL(group_small_kernel, dim3(1), dim3(64 * kGroupSmallTiles), 0, s, blockcounts, ntiles, ids, T, k, E,
                            counts, offsets, perm, inv_perm, ex);
         return hipGetLastError();
     }
-    if (ntiles <= kGroupLdsTiles) {
-        hipLaunchKernelGGL(group_lds_kernel, dim3((ntiles + kScatterWaves - 1) / kScatterWaves), dim3(64 * kScatterWaves), 0, s,
-                           blockcounts, ntiles, ids, T, k, E, counts, offsets, perm, inv_perm, ex);
+    if (ntiles * E <= kGroupSumsWords) {
+        hipLaunchKernelGGL(group_sums_kernel, dim3((ntiles + kScatterWaves - 1) / kScatterWaves + std::max(0, n_hist)),
+                           dim3(64 * kScatterWaves), 0, s, blockcounts, ntiles, ids, T, k, E, counts, offsets, perm, inv_perm,
+                           hist_tiles, hist, ex);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(group_scan_kernel, dim3(E, 1 + std::max(0, n_hist)), dim3(1024), 0, s, blockcounts, ntiles, E,

@@ -98,3 +98,12 @@ def test_histograms_from_per_tile_counts_at_their_limits(oracle_mod, T, H):
     an odd last tile, the widest look-ahead, more than one chunk of 64 tiles per wave (over 1024 tiles)."""
     cfg = shape("mixtral_prefill", name=f"gs_hist_{T}_{H}", d=256, F=32)
     test_streaming_gate_against_oracle(oracle_mod, cfg.name, cfg, T, H)
+
+
+@pytest.mark.parametrize("E,k,T,H", [(8, 2, 129, 1), (3, 1, 2049, 0), (60, 8, 1024, 1), (64, 6, 8192, 1), (64, 6, 8193, 1)],
+                         ids=lambda v: str(v))
+def test_grouping_by_sums_at_its_limits(oracle_mod, E, k, T, H):
+    """From five token tiles to 16384 per-tile counts one launch groups the tokens: the first such batch, an expert count that
+    leaves threads over, eight ids a token, the largest number of counts, and the first batch past it."""
+    cfg = shape("mixtral_prefill", name=f"gs_sums_{E}_{T}", d=256, E=E, k=k, F=32)
+    test_streaming_gate_against_oracle(oracle_mod, cfg.name, cfg, T, H)
