@@ -550,7 +550,7 @@ extern "C" int ef_layer_step(ef_ctx *c, int layer, const void *hidden, int T, fl
         hipEvent_t packed = c->forks && c->side_stream && c->tune.overlap_tiled != 0 ? next_fork_event(c) : nullptr;
         {
             KernelTimer kt(c, s, EF_K_PACK, 4.0 * rows * d + 4.0 * T * k);
-            EF_HIP(c, ef::launch_pack_x_dev(c->st_counts, c->st_offsets, E, has_shared, T, std::min(bound, c->max_tiles),
+            EF_HIP(c, ef::launch_pack_x_dev(c->st_counts, E, has_shared, T, std::min(bound, c->max_tiles),
                                             static_cast<const uint16_t *>(hidden), d, k, c->st_perm, c->xp, c->q4, packed, s));
         }
         if (packed) EF_HIP(c, hipStreamWaitEvent(c->side_stream, packed, 0));

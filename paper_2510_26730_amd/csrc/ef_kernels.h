@@ -105,7 +105,7 @@ hipError_t launch_group(const int32_t *blockcounts, const int32_t *ids, int T, i
 // is recorded as the launch's own completion
 hipError_t launch_pack_x(const PackTable &pt, int total_tiles, const uint16_t *h, int d, int k,
                          const int32_t *perm, void *xp, bool f16, hipStream_t s);
-hipError_t launch_pack_x_dev(const int32_t *counts, const int32_t *offsets, int E, bool has_shared, int T,
+hipError_t launch_pack_x_dev(const int32_t *counts, int E, bool has_shared, int T,
                              int max_tiles, const uint16_t *h, int d, int k, const int32_t *perm, void *xp,
                              bool f16, hipEvent_t done, hipStream_t s);
 hipError_t launch_ffn_gate_up(const GroupTable &gt, int total_wgs, int tiles_per_pass, int ks, const void *xp,

@@ -215,6 +215,27 @@ def test_drawn_shapes_full_layer(oracle_mod, cfg, T, beta):
         st.close()
 
 
+@pytest.mark.parametrize("k,Fs,slices", [(1, 0, 1), (2, 0, 3), (3, 512, 2), (4, 512, 8), (5, 0, 2), (8, 512, 8)],
+                         ids=lambda v: str(v))
+def test_unpermute_over_rows_and_planes(oracle_mod, k, Fs, slices):
+    """Every instance of the un-permute at both ends of its range of k, one plane to eight, with and without a shared row."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"unpermute{k}", cfg_id=930 + k, d=192, E=9, k=k, F=512, F_shared=Fs)
+    T = 37
+    say(f"un-permute k={k} Fs={Fs} slices={slices}")
+    st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=T)
+    try:
+        ef.ef_set_tuning(st.ctx, down_k_slices=slices)
+        h = synth.hidden(cfg, 6, T)
+        hd = dev_u16(h)
+        r = st.route(0, hd, T, 0.0)
+        out = st.ffn(0, hd, T, r)
+        full = oracle_layer(oracle_mod, st, 0, h, 0.0, np.zeros(cfg.E, dtype=np.uint8), forced_ids=to_np(r, T, k)["ids"])
+        e1, e2 = float_close(out, full["out"])
+        say(f"  max abs {e1:.2e}, rel l2 {e2:.2e}")
+    finally:
+        st.close()
+
+
 def test_shared_ffn_tiled_beside_streamed_routed_groups(oracle_mod):
     """A batch whose shared FFN (10 token tiles, K = 1024) takes the tiled kernels with two K slices while the
     routed experts (2-4 tiles, K = 128) stream with one: the un-permute sums a different number of planes per
