@@ -13,7 +13,8 @@
 // holds one matrix row (column) and therefore needs one scale per group, and in fp16: the codes
 // become the fp16 numbers 1024 + q (or 64 + q) by one bit operation, a packed subtraction gives q - 8 exactly and
 // a packed multiplication (q - 8) * s: three vector instructions per pair of weights where an fp32
-// route costs seven, which is what keeps these kernels on the memory side of the balance.  The
+// route costs seven, which is what keeps these kernels on the memory side of the balance.  Passes of up to
+// 48 tokens leave the scale to the sums (q4_stream16, q4_stream32).  The
 // matrix cores therefore run in fp16 (fp32 accumulation): the packed tokens of a 4-bit context and
 // the intermediate activations are fp16 fragments (tokens convert exactly from bf16 for
 // 2^-14 <= |x| < 65504).
@@ -34,7 +35,7 @@ typedef _Float16 q4_half8 __attribute__((ext_vector_type(8)));
 // t = 2, 3, and x >> 8 gives the other two pairs the same way (one shift per dword instead of three).  Minus
 // 1032 (72) is q - 8 exactly; times s rounds once to fp16 (11 significant bits for a 4-bit integer times an
 // 8-bit mantissa: relative error <= 2^-12).
-__device__ __forceinline__ u32x4_t dequant_q4(uint32_t x, q4_half2 s2) {
+__device__ __forceinline__ u32x4_t q4_codes(uint32_t x) {   // q - 8
     const q4_half2 off_lo = {(_Float16)-1032.f, (_Float16)-1032.f}, off_hi = {(_Float16)-72.f, (_Float16)-72.f};
     const uint32_t y = x >> 8;
     // the masks live in vector registers the compiler cannot see through: "and" and "or" then fit one
@@ -47,8 +48,17 @@ __device__ __forceinline__ u32x4_t dequant_q4(uint32_t x, q4_half2 s2) {
     u32x4_t out;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        const q4_half2 w = (__builtin_bit_cast(q4_half2, pr[p]) + ((p & 1) ? off_hi : off_lo)) * s2;
+        const q4_half2 w = __builtin_bit_cast(q4_half2, pr[p]) + ((p & 1) ? off_hi : off_lo);
         out[p] = __builtin_bit_cast(uint32_t, w);
+    }
+    return out;
+}
+__device__ __forceinline__ u32x4_t dequant_q4(uint32_t x, q4_half2 s2) {   // (q - 8) s
+    u32x4_t out = q4_codes(x);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const uint32_t c = out[p];   // (a bit cast of the element itself reads element 0)
+        out[p] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(q4_half2, c) * s2);
     }
     return out;
 }
@@ -174,68 +184,182 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
 #undef EF_Q4U_COMPUTE
 }
 
-// K loop of the first half for a pass of one or two token tiles whose last one is half live, NH half tiles of 16 tokens: as
-// q4_up_stream, with the matrix work in steps of 16 tokens (G, U: [row half][half tile]).  Most experts of a decode batch have
-// no more than 16 tokens, and these kernels are bound by conversion and matrix work that hardly overlap (eight Mixtral-shaped
-// experts, 64 tokens, first half 137 us: its loads alone 92, its arithmetic alone 88, of that the conversions alone 60 and the
-// matrix instructions alone 58).  The codes of two k-steps are regrouped by rows before they are converted (one lane exchange
+#undef EF_Q4U_RUN
+#undef EF_Q4U_STAGE
+#undef EF_Q4U_SHARE
+#undef EF_Q4U_LOAD
+#undef EF_Q4U_SCALES
+
+// ------------------------------------------------------------------------------------------
+// K loops of passes of up to 48 tokens, either half: sum_k x_k (q_k - 8) s as s (sum_k x_k (q_k - 8)) per block of the 128 inputs
+// that share a scale.  The operand is q - 8 alone, nine vector instructions per eight weights instead of thirteen, and the
+// weights' scales are read and converted once per block; the matrix cores sum a block from zero, and every second stage the
+// block's sums join the totals with one multiply-add per accumulator element, in 32 bits and with the scale as it is.  The
+// operands are swapped against the other passes (tokens are the rows), so a lane has one weight row and needs one scale.
+// Passes of 49 tokens and more keep (q - 8) s as the operand: tiles share its cost, and a block's accumulators beside those of
+// the totals would take the registers of the ring.
+//
+// Bound by the weight stream and what a wave's in-order issue leaves idle of it.  Two layers, before / after: eight
+// Mixtral-shaped experts 1 / 8 / 30 / 64 tokens 145.0 / 137.8, 270.8 / 254.4, 331.0 / 314.9, 361.2 / 338.8 us (the first
+// half's loads alone 91 of its 99 us at 64 tokens); DeepSeek-shaped 4 / 32 / 100 tokens 107.3 / 101.9, 146.6 / 140.6, 186.1 /
+// 181.2; Qwen-shaped 25 / 200 tokens 116.9 / 111.5, 219.0 / 214.1.  Raised codes 64 + q as the operand (seven instructions), 72
+// times the sum of the inputs taken off through LDS: 257.9 and 360.7 us at 8 and 64 tokens, and rounding errors of its own.
+// ------------------------------------------------------------------------------------------
+struct Q4Streams {                 // of one wave: two weight streams (W1 and W3, or two column blocks of W2) and their scales
+    const uint4 *wa, *wb;
+    const uint16_t *sa, *sb;
+    int wstep, sstep;              // 16-byte units per stage, scales per block of 128 inputs
+};
+// A stage is that of EF_Q4U_STAGE.  Even slots of the ring hold the first stage of a block, and only those load its scales:
+// the loops start at an even stage.
+#define EF_Q4_LOAD(slot, kq)                                                                              \
+    {                                                                                                     \
+        const int kc_ = min((kq), last);                                                                  \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u)                                                   \
+            xr[slot][u] = *reinterpret_cast<const u32x4_t *>(src[u] + (size_t)(4 * kc_ + wave) * 64);     \
+        __builtin_amdgcn_sched_barrier(0);                                                                \
+        qa[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w.wa + (size_t)kc_ * w.wstep)); \
+        qb[slot] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(w.wb + (size_t)kc_ * w.wstep)); \
+        if ((slot) % 2 == 0) {                                                                            \
+            sa[(slot) / 2] = w.sa[(size_t)(kc_ >> 1) * w.sstep];                                          \
+            sb[(slot) / 2] = w.sb[(size_t)(kc_ >> 1) * w.sstep];                                          \
+        }                                                                                                 \
+    }
+#define EF_Q4_SHARE(slot, st)                                                                             \
+    {                                                                                                     \
+        _Pragma("unroll") for (int u = 0; u < NTL; ++u) xs[(st) & (kQ4Lds - 1)][u * 4 + wave][lane] = xr[slot][u]; \
+    }
+#define EF_Q4_STAGE(COMPUTE, slot, next_slot, st)                                                         \
+    {                                                                                                     \
+        EF_Q4_SHARE(next_slot, (st) + 1)                                                                  \
+        COMPUTE(slot, st)                                                                                 \
+        EF_Q4_LOAD(slot, (st) + D)                                                                        \
+        __syncthreads();                                                                                  \
+    }
+#define EF_Q4_RUN(COMPUTE)                                                                                \
+    {                                                                                                     \
+        static_assert(D % 2 == 0, "even slots hold the first stage of a block");                          \
+        const int last = max(q1, 1) - 1;                                                                  \
+        _Pragma("unroll") for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4_LOAD(ring_, q0 + ring_)           \
+        EF_Q4_SHARE(0, q0)                                                                                \
+        __syncthreads();                                                                                  \
+        int st = q0;                                                                                      \
+        for (; st + D <= q1; st += D) {                                                                   \
+            _Pragma("unroll") for (int ring_ = 0; ring_ < D; ++ring_) EF_Q4_STAGE(COMPUTE, ring_, (ring_ + 1) % D, st + ring_) \
+        }                                                                                                 \
+        _Pragma("unroll") for (int ring_ = 0; ring_ < D - 2; ++ring_)                                     \
+            if (st + ring_ < q1) EF_Q4_STAGE(COMPUTE, ring_, ring_ + 1, st + ring_)                       \
+    }
+__device__ __forceinline__ float q4_scale_f32(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
+
+// NH half tiles of 16 tokens, an odd number: a last tile that is half live takes half the matrix work (most experts of a decode
+// batch have no more than 16 tokens).  The codes of two k-steps are regrouped by rows before they are converted (one lane exchange
 // per pair of dwords), so the instruction of 16 rows x 16 tokens takes 32 inputs of a quad's row; the token fragments are read
-// from LDS in the same order of inputs.  Two layers, with 32 x 32 x 16 for all: 8 / 30 / 64 tokens on eight Mixtral-shaped
-// experts 313 -> 297 / 364 -> 338 / 395 -> 366 us, 100 tokens on 64 DeepSeek-shaped 203 -> 195.  A whole number of tiles
-// keeps the larger instruction: the same matrix time, fewer instructions (as half tiles 64 tokens on two experts 189 -> 192).
-template <int TT, int NH, int D, bool PAIRS>
-__device__ __forceinline__ void q4_up_stream16(const uint4 *__restrict__ w13, const uint16_t *__restrict__ sA,
-                                               const uint4 *const (&xsrc)[TT], u32x4_t (*xs)[TT * 4][64], int k0, int nloc,
-                                               int wave, int lane, floatx4_t (&G)[2][2 * TT - 1], floatx4_t (&U)[2][2 * TT - 1]) {
+// from LDS in the same order of inputs.  A, B: [row half][half tile]; a lane holds row l % 16 of the half and tokens
+// 4 (l / 16) .. + 3.
+template <int TT, int NH, int D>
+__device__ __forceinline__ void q4_stream16(const Q4Streams &w, const uint4 *const (&src)[TT], u32x4_t (*xs)[TT * 4][64],
+                                            int q0, int q1, int wave, int lane,
+                                            floatx4_t (&A)[2][2 * TT - 1], floatx4_t (&B)[2][2 * TT - 1]) {
     constexpr int NTL = (NH + 1) / 2;
     u32x4_t qa[D], qb[D], xr[D][NTL];
-    uint16_t sa[D], sb[D];
-    uint32_t f_[4];   // scales of the current stages: matrix, row half
+    uint16_t sa[D / 2], sb[D / 2];
+    float f_[4];                      // scales of the current block: matrix, row half
+    floatx4_t bl_[4][NH];             // sums of the current block
+    const floatx4_t zero = {0.f, 0.f, 0.f, 0.f};
     const int rd = ((lane >> 4) & 1) * 64 + (lane >> 5) * 32 + (lane & 15);   // inputs of quarter l / 16: fragment l / 16 % 2, half l / 32
-    // operand x of a stage: k-steps 2 (x / 4) and the next, matrix and row half x % 4; the conversion of operand x + 1 is
-    // issued between the matrix instructions of operand x
-#define EF_Q4U_COMPUTE(slot, st)                                                                          \
+#define EF_Q4_COMPUTE(slot, st)                                                                           \
     {                                                                                                     \
         u32x4_t xb_[NH][2];                                                                               \
         _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                    \
             _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
                 xb_[h][p] = (&xs[(st) & (kQ4Lds - 1)][(h >> 1) * 4 + 2 * p][0])[rd + 16 * (h & 1)];       \
         uint32_t cd_[8]; /* codes of operand x */                                                         \
-        if (EF_Q4U_SCALES(slot)) {                                                                        \
-            const uint32_t fa_ = __builtin_bit_cast(uint32_t, q4_scale(sa[slot])), fb_ = __builtin_bit_cast(uint32_t, q4_scale(sb[slot])); \
-            split_rows(fa_, fa_, f_[0], f_[1]);                                                           \
-            split_rows(fb_, fb_, f_[2], f_[3]);                                                           \
+        if ((slot) % 2 == 0) {                                                                            \
+            uint32_t fl_[4];                                                                              \
+            const uint32_t fa_ = (uint32_t)sa[(slot) / 2] << 16, fb_ = (uint32_t)sb[(slot) / 2] << 16;    \
+            split_rows(fa_, fa_, fl_[0], fl_[1]);                                                         \
+            split_rows(fb_, fb_, fl_[2], fl_[3]);                                                         \
+            _Pragma("unroll") for (int i = 0; i < 4; ++i) f_[i] = __builtin_bit_cast(float, fl_[i]);      \
         }                                                                                                 \
         _Pragma("unroll") for (int p = 0; p < 2; ++p) {                                                   \
             split_rows(qa[slot][2 * p], qa[slot][2 * p + 1], cd_[4 * p], cd_[4 * p + 1]);                 \
             split_rows(qb[slot][2 * p], qb[slot][2 * p + 1], cd_[4 * p + 2], cd_[4 * p + 3]);             \
         }                                                                                                 \
-        u32x4_t w_ = dequant_q4(cd_[0], __builtin_bit_cast(q4_half2, f_[0]));                                     \
+        u32x4_t w_ = q4_codes(cd_[0]);                                                                   \
         _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                                   \
             u32x4_t n_ = w_;                                                                              \
-            if (x < 7) n_ = dequant_q4(cd_[x + 1], __builtin_bit_cast(q4_half2, f_[(x + 1) & 3]));        \
-            _Pragma("unroll") for (int h = 0; h < NH; ++h) {                                              \
-                if (x & 2) U[x & 1][h] = mfma16h(w_, xb_[h][x >> 2], U[x & 1][h]);                        \
-                else G[x & 1][h] = mfma16h(w_, xb_[h][x >> 2], G[x & 1][h]);                              \
-            }                                                                                             \
+            if (x < 7) n_ = q4_codes(cd_[x + 1]);                                                        \
+            _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                \
+                bl_[x & 3][h] = mfma16h(xb_[h][x >> 2], w_, (slot) % 2 == 0 && x < 4 ? zero : bl_[x & 3][h]); \
             if (x < 7) {                                                                                  \
                 _Pragma("unroll") for (int q_ = 0; q_ < NH; ++q_) {                                       \
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
-                    __builtin_amdgcn_sched_group_barrier(0x002, (14 + NH - 1) / NH, 0);                   \
+                    __builtin_amdgcn_sched_group_barrier(0x002, (10 + NH - 1) / NH, 0);                    \
                 }                                                                                         \
             }                                                                                             \
             w_ = n_;                                                                                      \
         }                                                                                                 \
+        if ((slot) % 2 == 1) {                                                                            \
+            _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                \
+                _Pragma("unroll") for (int r = 0; r < 2; ++r)                                             \
+                    _Pragma("unroll") for (int v = 0; v < 4; ++v) {                                       \
+                        A[r][h][v] = __builtin_fmaf(f_[r], bl_[r][h][v], A[r][h][v]);                     \
+                        B[r][h][v] = __builtin_fmaf(f_[2 + r], bl_[2 + r][h][v], B[r][h][v]);             \
+                    }                                                                                     \
+        }                                                                                                 \
     }
-    EF_Q4U_RUN(EF_Q4U_COMPUTE)
-#undef EF_Q4U_COMPUTE
+    EF_Q4_RUN(EF_Q4_COMPUTE)
+#undef EF_Q4_COMPUTE
 }
 
-#undef EF_Q4U_RUN
-#undef EF_Q4U_STAGE
-#undef EF_Q4U_SHARE
-#undef EF_Q4U_LOAD
-#undef EF_Q4U_SCALES
+// One whole tile of 32 tokens (as two half tiles: the same matrix time, more instructions).  A lane holds row l % 32 and, in element v, token 8 (v / 4) + 4 (l / 32) + v % 4.
+template <int TT, int D>
+__device__ __forceinline__ void q4_stream32(const Q4Streams &w, const uint4 *const (&src)[TT], u32x4_t (*xs)[TT * 4][64],
+                                            int q0, int q1, int wave, int lane, floatx16 &A, floatx16 &B) {
+    constexpr int NTL = 1;
+    u32x4_t qa[D], qb[D], xr[D][NTL];
+    uint16_t sa[D / 2], sb[D / 2];
+    float fa_ = 0.f, fb_ = 0.f;
+    floatx16 ba_, bb_, zero;
+    zero16(zero);
+    zero16(ba_);
+    zero16(bb_);
+#define EF_Q4_COMPUTE(slot, st)                                                                           \
+    {                                                                                                     \
+        u32x4_t xb_[4];                                                                                   \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) xb_[j] = xs[(st) & (kQ4Lds - 1)][j][lane];          \
+        if ((slot) % 2 == 0) {                                                                            \
+            fa_ = q4_scale_f32(sa[(slot) / 2]);                                                           \
+            fb_ = q4_scale_f32(sb[(slot) / 2]);                                                           \
+        }                                                                                                 \
+        u32x4_t w_ = q4_codes(qa[slot][0]);                                                              \
+        _Pragma("unroll") for (int x = 0; x < 8; ++x) {                                                   \
+            u32x4_t n_ = w_;                                                                              \
+            if (x < 7) n_ = q4_codes(((x + 1) & 1) ? qb[slot][(x + 1) >> 1] : qa[slot][(x + 1) >> 1]);   \
+            if (x & 1) bb_ = mfma32h(xb_[x >> 1], w_, (slot) % 2 == 0 && x < 2 ? zero : bb_);             \
+            else ba_ = mfma32h(xb_[x >> 1], w_, (slot) % 2 == 0 && x < 2 ? zero : ba_);                   \
+            if (x < 7) {                                                                                  \
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                        \
+                __builtin_amdgcn_sched_group_barrier(0x002, 10, 0);                                        \
+            }                                                                                             \
+            w_ = n_;                                                                                      \
+        }                                                                                                 \
+        if ((slot) % 2 == 1) {                                                                            \
+            _Pragma("unroll") for (int v = 0; v < 16; ++v) {                                              \
+                A[v] = __builtin_fmaf(fa_, ba_[v], A[v]);                                                 \
+                B[v] = __builtin_fmaf(fb_, bb_[v], B[v]);                                                 \
+            }                                                                                             \
+        }                                                                                                 \
+    }
+    EF_Q4_RUN(EF_Q4_COMPUTE)
+#undef EF_Q4_COMPUTE
+}
+#undef EF_Q4_RUN
+#undef EF_Q4_STAGE
+#undef EF_Q4_SHARE
+#undef EF_Q4_LOAD
+
 
 // ------------------------------------------------------------------------------------------
 // first half: act = silu(X W1^T) * (X W3^T).  Workgroup = (group, pass of TT token tiles, four
@@ -290,15 +414,52 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
         xsrc[u] = xp + (size_t)(gt.tile_start[grp] + pass * TT + min(u, ntl - 1)) * nkb * 64 +
                   (TT < 4 && nh == 2 * u + 1 ? lane & ~16 : lane);
 
-    if constexpr (TT < 4) if (nh & 1) {
+    if constexpr (TT < 4) if (nh < 4) {
+        const Q4Streams w = {w13, w13 + 64, sA, sA + 32, 128, 64};
         constexpr int HT = 2 * TT - 1;   // half tiles of a pass with a half live tile
+        // where a lane's row f (0 .. 31) of the row block goes: half f / 16 of the paired-order fragments, lanes of half f / 4 % 2,
+        // element 4 (f / 8 % 2) + f % 4
+        uint16_t *out = reinterpret_cast<uint16_t *>(act + gt.act_off[grp] + ((size_t)pass * TT * (F >> 4) + rb * 2) * 64) +
+                        ((lane >> 2) & 1) * 256 + ((lane >> 3) & 1) * 4 + (lane & 3);
+        const size_t tile_halves = (size_t)(F >> 4) * 512;
+        auto put = [&](uint16_t *at, float g, float u) {
+            *at = __builtin_bit_cast(uint16_t, (_Float16)q4_saturate(silu_mul(g, u)));
+        };
+        if (nh == 2) {
+            floatx16 G, U;
+            zero16(G);
+            zero16(U);
+            q4_stream32<TT, D>(w, xsrc, xs[kh], k0, k0 + nloc, wave, lane, G, U);
+            if constexpr (KH == 2) {
+                float4 *red = reinterpret_cast<float4 *>(&xs[0][0][0][0]) + (size_t)wave * 8 * 64 + lane;
+                if (kh == 1) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        red[q * 64] = make_float4(G[4 * q], G[4 * q + 1], G[4 * q + 2], G[4 * q + 3]);
+                        red[(4 + q) * 64] = make_float4(U[4 * q], U[4 * q + 1], U[4 * q + 2], U[4 * q + 3]);
+                    }
+                }
+                __syncthreads();
+                if (kh == 1) return;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 g = red[q * 64], u = red[(4 + q) * 64];
+                    G[4 * q] += g.x; G[4 * q + 1] += g.y; G[4 * q + 2] += g.z; G[4 * q + 3] += g.w;
+                    U[4 * q] += u.x; U[4 * q + 1] += u.y; U[4 * q + 2] += u.z; U[4 * q + 3] += u.w;
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                put(out + ((lane >> 4) & 1) * 512 + (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * 8, G[v], U[v]);
+            return;
+        }
         floatx4_t G[2][HT], U[2][HT];   // [row half][half tile of 16 tokens]
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int h = 0; h < HT; ++h) G[r][h] = U[r][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-        if (TT == 1 || nh == 1) q4_up_stream16<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-        else q4_up_stream16<TT, 2 * TT - 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+        if (TT == 1 || nh == 1) q4_stream16<TT, 1, D>(w, xsrc, xs[kh], k0, k0 + nloc, wave, lane, G, U);
+        else q4_stream16<TT, 2 * TT - 1, D>(w, xsrc, xs[kh], k0, k0 + nloc, wave, lane, G, U);
 
         if constexpr (KH == 2) {
             // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
@@ -323,22 +484,14 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
                     U[r][h] += red[((r * HT + h) * 2 + 1) * 64];
                 }
         }
-        // a lane holds four F-values of one token in each row half: half of its 16 bytes of the paired-order fragment (fp16)
-        // of that row half, rows 4 (l / 16) .. + 3 being elements 4 (l / 32) .. + 3 of half l / 16 % 2
-        const int nkb2 = F >> 4, p = lane >> 4;
 #pragma unroll
         for (int h = 0; h < HT; ++h) {
             if (h >= nh) break;
-            uint2 *dst = reinterpret_cast<uint2 *>(act + gt.act_off[grp] + ((size_t)(pass * TT + (h >> 1)) * nkb2 + rb * 2) * 64 +
-                                                   (p & 1) * 32 + 16 * (h & 1) + (lane & 15)) + (p >> 1);
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                float v[4];
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = q4_saturate(silu_mul(G[r][h][q], U[r][h][q]));
-                dst[(size_t)r * 128] = make_uint2(__builtin_bit_cast(uint32_t, q4_half2{(_Float16)v[0], (_Float16)v[1]}),
-                                                  __builtin_bit_cast(uint32_t, q4_half2{(_Float16)v[2], (_Float16)v[3]}));
-            }
+                for (int v = 0; v < 4; ++v)
+                    put(out + (h >> 1) * tile_halves + r * 512 + (16 * (h & 1) + 4 * (lane >> 4) + v) * 8, G[r][h][v], U[r][h][v]);
         }
         return;
     }
@@ -347,7 +500,8 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
 
-    if (TT == 1 || ntl == 1) q4_up_stream<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+    if constexpr (TT == 1) return;
+    if (TT == 4 && ntl == 1) q4_up_stream<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
     else if (TT == 2 || ntl == 2) q4_up_stream<TT, (TT > 1 ? 2 : 1), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
     else if (ntl == 3) q4_up_stream<TT, (TT > 2 ? 3 : TT), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
     else q4_up_stream<TT, TT, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
@@ -408,8 +562,8 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *x = reinterpret_cast<const uint4 *>(xp);
     uint4 *a = reinterpret_cast<uint4 *>(act);
-    // two K halves per workgroup when each half keeps a few stages (d / 64 stages in all, an even number)
-    const bool halves = k_halves && (d >> 6) % 2 == 0 && (d >> 6) >= 8;
+    // two K halves per workgroup when each half keeps a few stages and whole blocks of 128 inputs
+    const bool halves = k_halves && (d >> 6) % 4 == 0 && (d >> 6) >= 8;
     // more workgroups than compute units: two of them per unit instead (whole K range each, the short register ring);
     // their waves stall at different times, where the halves of one workgroup meet at the same barriers
     // (seven Mixtral-shaped experts: 127 against 135 us, Qwen-shaped batch 52 against 60 us)
@@ -498,49 +652,6 @@ __device__ __forceinline__ void q4_down_stream(const uint4 *__restrict__ w2q, si
 #undef EF_Q4D_COMPUTE
 }
 
-// passes of one or two token tiles, as q4_up_stream16 (acc: [column block][half of its columns][half tile])
-template <int TT, int NH, int D, int CBW>
-__device__ __forceinline__ void q4_down_stream16(const uint4 *__restrict__ w2q, size_t qstride,
-                                                 const uint16_t *__restrict__ sB, size_t sstride,
-                                                 const uint4 *const (&asrc)[TT], u32x4_t (*as)[TT * 4][64], int nq, int q0,
-                                                 int q1, int wave, int lane, floatx4_t (&acc)[CBW][2][2 * TT - 1]) {
-    constexpr int NTL = (NH + 1) / 2;
-    u32x4_t qw[D][CBW], ar[D][NTL];
-    uint16_t sc[D][CBW];
-    const int rd = ((lane >> 4) & 1) * 64 + (lane >> 5) * 32 + (lane & 15);
-    // operand x of a stage: column block x / 4, k-steps 2 (x / 2 % 2) and the next, half x % 2 of the block's columns
-#define EF_Q4D_COMPUTE(slot, st)                                                                          \
-    {                                                                                                     \
-        u32x4_t af_[NH][2];                                                                               \
-        _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                    \
-            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
-                af_[h][p] = (&as[(st) & (kQ4Lds - 1)][(h >> 1) * 4 + 2 * p][0])[rd + 16 * (h & 1)];       \
-        uint32_t f_[2 * CBW], cd_[4 * CBW]; /* scales; codes of operand x */                              \
-        _Pragma("unroll") for (int cw = 0; cw < CBW; ++cw) {                                              \
-            const uint32_t fs_ = __builtin_bit_cast(uint32_t, q4_scale(sc[slot][cw]));                    \
-            split_rows(fs_, fs_, f_[2 * cw], f_[2 * cw + 1]);                                             \
-            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
-                split_rows(qw[slot][cw][2 * p], qw[slot][cw][2 * p + 1], cd_[4 * cw + 2 * p], cd_[4 * cw + 2 * p + 1]); \
-        }                                                                                                 \
-        u32x4_t w_ = dequant_q4(cd_[0], __builtin_bit_cast(q4_half2, f_[0]));                             \
-        _Pragma("unroll") for (int x = 0; x < 4 * CBW; ++x) {                                             \
-            const int y_ = x + 1;                                                                         \
-            u32x4_t n_ = w_;                                                                              \
-            if (y_ < 4 * CBW) n_ = dequant_q4(cd_[y_], __builtin_bit_cast(q4_half2, f_[2 * (y_ >> 2) + (y_ & 1)])); \
-            _Pragma("unroll") for (int h = 0; h < NH; ++h)                                                \
-                acc[x >> 2][x & 1][h] = mfma16h(w_, af_[h][(x >> 1) & 1], acc[x >> 2][x & 1][h]);         \
-            if (y_ < 4 * CBW) {                                                                           \
-                _Pragma("unroll") for (int q_ = 0; q_ < NH; ++q_) {                                       \
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                    \
-                    __builtin_amdgcn_sched_group_barrier(0x002, (14 + NH - 1) / NH, 0);                   \
-                }                                                                                         \
-            }                                                                                             \
-            w_ = n_;                                                                                      \
-        }                                                                                                 \
-    }
-    EF_Q4D_RUN(EF_Q4D_COMPUTE)
-#undef EF_Q4D_COMPUTE
-}
 #undef EF_Q4D_RUN
 #undef EF_Q4D_STAGE
 #undef EF_Q4D_SHARE
@@ -556,7 +667,9 @@ template <int TT>
 __global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, const uint4 *__restrict__ act,
                                                              float *__restrict__ Y, int d,
                                                              long long y_plane) {
-    constexpr int D = TT == 4 ? 3 : kQ4Depth, CBW = 2;
+    // passes of one with a ring of four fit three workgroups per compute unit (six: two; DeepSeek-shaped 32 tokens 144.3 -> 141.1
+    // us for two layers)
+    constexpr int D = TT == 4 ? 3 : 4, CBW = 2;
     __shared__ __attribute__((aligned(16))) u32x4_t as[kQ4Lds][TT * 4][64];
     const int wg = blockIdx.x;
     int grp = 0;
@@ -571,7 +684,8 @@ __global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, cons
     const int cbc = valid ? cb0 : 0;              // waves past the last column load block 0 and drop the result
     const int F = gt.F[grp];
     const int nkb = F >> 4, nq = F >> 6;
-    const int q0 = (int)((long long)kslice * nq / ksg), q1 = (int)((long long)(kslice + 1) * nq / ksg);
+    // whole blocks of 128 inputs (two stages)
+    const int q0 = (int)((long long)kslice * (nq >> 1) / ksg) * 2, q1 = (int)((long long)(kslice + 1) * (nq >> 1) / ksg) * 2;
     int ntl = gt.n_tiles[grp] - pass * TT;
     if (ntl > TT) ntl = TT;
 
@@ -588,32 +702,50 @@ __global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, cons
                   (TT < 4 && nh == 2 * u + 1 ? lane & ~16 : lane);
 
     float *Yp = Y + (size_t)kslice * y_plane;
-    if constexpr (TT < 4) if (nh & 1) {
+    if constexpr (TT < 4) if (nh < 4) {
         constexpr int HT = 2 * TT - 1;
-        floatx4_t acc[CBW][2][HT];   // [column block][half of its columns][half tile of 16 tokens]
+        const Q4Streams w = {w2q, w2q + qstride, sB, sB + sstride, 64, 32};
+        const int t0 = pass * TT * kTile, rows = gt.count[grp] - t0;
+        float *row = Yp + (size_t)(gt.row_offset[grp] + t0) * d + cb0 * 32;
+        if (nh == 2) {
+            floatx16 a, b;
+            zero16(a);
+            zero16(b);
+            q4_stream32<TT, D>(w, asrc, as, q0, q1, wave, lane, a, b);
+            if (!valid) return;
 #pragma unroll
-        for (int cw = 0; cw < CBW; ++cw)
+            for (int v = 0; v < 16; ++v) {
+                const int t = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                if (t >= rows) continue;
+                row[(size_t)t * d + (lane & 31)] = a[v];
+                row[(size_t)t * d + 32 + (lane & 31)] = b[v];
+            }
+            return;
+        }
+        floatx4_t a[2][HT], b[2][HT];   // [half of the block's columns][half tile of 16 tokens]
 #pragma unroll
-            for (int r = 0; r < 2; ++r)
+        for (int r = 0; r < 2; ++r)
 #pragma unroll
-                for (int h = 0; h < HT; ++h) acc[cw][r][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-        if (TT == 1 || nh == 1) q4_down_stream16<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
-        else q4_down_stream16<TT, 2 * TT - 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+            for (int h = 0; h < HT; ++h) a[r][h] = b[r][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+        if (TT == 1 || nh == 1) q4_stream16<TT, 1, D>(w, asrc, as, q0, q1, wave, lane, a, b);
+        else q4_stream16<TT, 2 * TT - 1, D>(w, asrc, as, q0, q1, wave, lane, a, b);
 
         if (!valid) return;
-        // a lane holds token l % 16 of a half tile and four consecutive output columns per accumulator: 16-byte stores
 #pragma unroll
-        for (int h = 0; h < HT; ++h) {
-            const int tl = pass * TT * kTile + 16 * h + (lane & 15);
-            if (h >= nh || tl >= gt.count[grp]) continue;
-            float *row = Yp + (size_t)(gt.row_offset[grp] + tl) * d + cb0 * 32 + 4 * (lane >> 4);
+        for (int h = 0; h < HT; ++h)
 #pragma unroll
-            for (int cw = 0; cw < CBW; ++cw)
+            for (int v = 0; v < 4; ++v) {
+                const int t = 16 * h + 4 * (lane >> 4) + v;
+                if (h >= nh || t >= rows) continue;
 #pragma unroll
-                for (int r = 0; r < 2; ++r) *reinterpret_cast<floatx4_t *>(row + 32 * cw + 16 * r) = acc[cw][r][h];
-        }
+                for (int r = 0; r < 2; ++r) {
+                    row[(size_t)t * d + 16 * r + (lane & 15)] = a[r][h][v];
+                    row[(size_t)t * d + 32 + 16 * r + (lane & 15)] = b[r][h][v];
+                }
+            }
         return;
     }
+    if constexpr (TT == 1) return;
 
     floatx16 acc[CBW][TT];
 #pragma unroll
@@ -621,7 +753,7 @@ __global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, cons
 #pragma unroll
         for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
 
-    if (TT == 1 || ntl == 1) q4_down_stream<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+    if (TT == 4 && ntl == 1) q4_down_stream<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
     else if (TT == 2 || ntl == 2) q4_down_stream<TT, (TT > 1 ? 2 : 1), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
     else if (ntl == 3) q4_down_stream<TT, (TT > 2 ? 3 : TT), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
     else q4_down_stream<TT, TT, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);

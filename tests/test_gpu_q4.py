@@ -75,6 +75,22 @@ def test_q4_layer_matches_oracle(oracle_mod, name, kw, T):
         st.close()
 
 
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 31, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("d,F,slices", [(512, 384, 0), (384, 384, 2), (640, 128, 8)])
+def test_q4_group_sizes_at_half_tiles(oracle_mod, T, d, F, slices):
+    """Two experts that every token takes, so a group is the whole batch: both sides of each half tile of 16 tokens, K ranges in
+    halves and whole, three blocks of 128 inputs in two slices and one in eight (seven of them empty)."""
+    cfg = q4_shape("tiny", name=f"q4_half_tiles_{d}_{F}", d=d, F=F, E=2, k=2)
+    st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=64, q4=True)
+    try:
+        ef.ef_set_tuning(st.ctx, down_k_slices=slices)
+        for e in range(cfg.E):
+            ef.ef_cache_swap_in(st.ctx, 0, e, 0, 0)
+        layer_check(oracle_mod, st, synth.hidden(cfg, 0, T), T, 0.0, ef.ef_cache_query(st.ctx, 0, cfg.E))
+    finally:
+        st.close()
+
+
 def test_q4_misses_are_swapped_in(oracle_mod):
     """Two of eight experts resident: the others are fetched (4-bit blobs) inside the FFN call."""
     cfg = q4_shape("tiny", name="tiny_q4", d=512, F=1024)
