@@ -207,11 +207,18 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 // pay from 7/4 rounds of two workgroups per compute unit on (two layers, passes of two / four: Mixtral-shaped 200 tokens, 1008
 // workgroups, 574 / 538 us; DeepSeek-shaped 1000 tokens, 1085, 564 / 515; Qwen-shaped 640 tokens, 835, 408 / 442; DeepSeek-
 // shaped 300 tokens, 671, 289 / 312).
-int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long tiled_wgs) {
+// Passes of one although some group has two tiles (4-bit): their kernels fit three workgroups per compute unit and issue less,
+// while second passes re-read no more than 16 MiB of first-half codes (`wgs_second` of their workgroups; two layers, passes of
+// two / one: DeepSeek-shaped 36 / 52 tokens 147.8 / 141.0, 156.5 / 152.0, on 16 experts 52 / 60 136.9 / 131.3, 139.3 / 138.1;
+// Qwen-shaped 36 / 60 147.2 / 137.2, 151.9 / 147.9, on 12 experts 60 tokens 134.2 / 128.8; Mixtral-shaped, 56 MiB per second
+// pass, 48 tokens on four experts 224.2 / 258.8, on eight 338.0 / 357.7).
+constexpr long long kSecondPassWeights = 16ll << 20;
+int tiles_per_pass(const ef_ctx *c, int max_tiles, long long wgs_of_four, long long wgs_second, long long tiled_wgs) {
     if (max_tiles >= 5 && (wgs_of_four > 256 || tiled_wgs > 256) && c->tune.passes_of_four != 0 && !c->q4 &&
         c->tune.lds_shared != 0 && c->tune.lds_shared_occupancy == 0 && c->cfg.d_ff % 128 == 0 && c->cfg.d_ff_shared % 128 == 0)
         return 8;
     if (max_tiles >= 3 && c->tune.passes_of_four != 0 && (!c->q4 || wgs_of_four >= 896)) return 4;
+    if (max_tiles == 2 && c->q4 && wgs_second * c->cfg.d_model <= kSecondPassWeights / 128) return 1;
     return max_tiles >= 2 ? 2 : 1;
 }
 
@@ -417,12 +424,15 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     if (rc) return rc;
     if (n == 0) return tiled_down();
     ef::GroupTable dn = gu;
-    long long wgs_of_four = 0;
-    for (int i = 0; i < n; ++i) wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
+    long long wgs_of_four = 0, wgs_second = 0;
+    for (int i = 0; i < n; ++i) {
+        wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
+        if (gu.n_tiles[i] > 1) wgs_second += gu.F[i] / 128;
+    }
     // 4-bit groups of a tiled one's size stream because of what the whole layer holds; a phase that has one keeps to the
     // layer's pass width (for which the K slices of the second half were chosen) and does not cut the first half's K range
     // in two, whatever else is resident: such a group's sums do not depend on the phase it runs in
-    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, tiled_up_wgs);
+    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, wgs_second, tiled_up_wgs);
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;
@@ -608,7 +618,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
             // passes of four for all groups alike (tiles_per_pass), or tiled groups that are a quarter of the workgroups or
             // less (two layers: Mixtral-shaped 700 tokens 1245 -> 1188 us, DeepSeek-shaped 300 tokens 315 -> 286, 4000 tokens
             // 1560 -> 1459); a launch of their own is passes of four too
-            if (c->tune.passes_of_four == 0 || tiles_per_pass(c, 4, four_all, 0) == 4 ||
+            if (c->tune.passes_of_four == 0 || tiles_per_pass(c, 4, four_all, 0, 0) == 4 ||
                 (four_all >= 512 && four_tiled * 4 <= four_all))
                 use_tiled = false;
         } else if (!c->q4 && wg_up < 64 && four_all - four_tiled >= 128 && c->tune.passes_of_four != 0 &&
@@ -631,11 +641,12 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         // token tiles per pass of the streamed launch: from the groups that stream (the tiled ones have kernels of
         // their own), with the rule that launch_phase applies to a phase's groups
         int tmax = 1;
-        long long wgs_of_four = 0;
+        long long wgs_of_four = 0, wgs_second = 0;
         auto see = [&](int F, int cnt) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
             tmax = std::max(tmax, nt);
             wgs_of_four += (long long)(F / 128) * ((nt + 3) / 4);
+            if (nt > 1) wgs_second += F / 128;
         };
         auto streams = [&](int F, int cnt, bool routed) {
             const int nt = (cnt + ef::kTile - 1) / ef::kTile;
@@ -644,7 +655,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         for (int e = 0; e < E; ++e)
             if (counts_host[e] > 0 && streams(c->cfg.d_ff, counts_host[e], true)) see(c->cfg.d_ff, counts_host[e]);
         if (has_shared && streams(c->cfg.d_ff_shared, T, false)) see(c->cfg.d_ff_shared, T);
-        tpp = tiles_per_pass(c, tmax, wgs_of_four, use_tiled ? tiled_up_wgs : 0);
+        tpp = tiles_per_pass(c, tmax, wgs_of_four, wgs_second, use_tiled ? tiled_up_wgs : 0);
         double stream_work = 0.0;     // workgroups times their k-blocks
         double stream_bytes = 0.0;    // weights of the streamed groups, as often as their passes read them
         auto add_base = [&](int F, int nt) {
