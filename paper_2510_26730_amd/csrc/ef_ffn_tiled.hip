@@ -36,7 +36,9 @@ __global__ __launch_bounds__(256, 1) void ffn_gate_up_tiled_kernel(GroupTable gt
                                                                     uint4 *__restrict__ act, int d) {
     constexpr bool kSwapOperands = false;
     __shared__ __attribute__((aligned(16))) u32x4_t lds[kTileStages][kStageFrags][64];
-    const int wg = blockIdx.x;
+    const bool in_order = gt.xcd_rot[0] == kTiledInOrder;   // a workgroup per unit; an XCD takes one contiguous share
+    const int b = blockIdx.x, n = gridDim.x;
+    const int wg = in_order ? (b & 7) * (n >> 3) + min(b & 7, n & 7) + (b >> 3) : b;
     int grp = 0;
     while (grp + 1 < gt.n_groups && gt.wg_start[grp + 1] <= wg) ++grp;
     const int local = wg - gt.wg_start[grp];
@@ -44,7 +46,8 @@ __global__ __launch_bounds__(256, 1) void ffn_gate_up_tiled_kernel(GroupTable gt
     const int ntiles = gt.n_tiles[grp];
     const int mpanels = (ntiles + 7) >> 3;
     TiledUnit unit;
-    if (!tiled_pick(local, gt.xcd_rot[grp], F >> 7, mpanels, 1, unit)) return;
+    if (in_order) unit = tiled_unit(local, F >> 7, mpanels);
+    else if (!tiled_pick(local, gt.xcd_rot[grp], F >> 7, mpanels, 1, unit)) return;
     const int rb0 = unit.np * 4, t0 = unit.mp * 8;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS DMA targets go through M0
@@ -111,10 +114,13 @@ hipError_t launch_ffn_gate_up_tiled(const GroupTable &gt, int total_wgs, const v
                                     bool f16, hipStream_t s) {
     if (total_wgs <= 0) return hipSuccess;
     // the kernel's index mapping and the grid must come from the same workgroup count per group
-    for (int i = 0; i < gt.n_groups; ++i)
-        if (gt.wg_start[i + 1] - gt.wg_start[i] != ffn_gate_up_tiled_wgs(gt.F[i], gt.n_tiles[i]) ||
+    const bool in_order = gt.n_groups > 0 && gt.xcd_rot[0] == kTiledInOrder;
+    for (int i = 0; i < gt.n_groups; ++i) {
+        const int units = ffn_tiled_units(gt.F[i] / 128, gt.n_tiles[i], 1);
+        if (gt.wg_start[i + 1] - gt.wg_start[i] != (in_order ? units : ffn_tiled_wgs(units)) ||
             !ffn_tiled_ok(d, gt.F[i], gt.n_tiles[i]))
             return hipErrorInvalidValue;
+    }
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     if (f16)
         hipLaunchKernelGGL(ffn_gate_up_tiled_kernel<true>, dim3(total_wgs), dim3(256), 0, s, gt,

@@ -57,7 +57,8 @@ struct GroupTable {
     int ksg[kMaxGroups];           // streamed second half: K slices of the group (one Y plane each); a whole word comes with
                                    // the scalar loads of the other fields, a byte is a vector load of its own ahead of
                                    // everything else (4-bit Mixtral-shaped decode of one token 149.6 against 148.6 us)
-    int xcd_rot[kMaxGroups];       // tiled kernels: the XCD (0..7) that takes the first eighth of the group's units
+    int xcd_rot[kMaxGroups];       // tiled kernels: the XCD (0..7) that takes the first eighth of the group's units, or
+                                   // kTiledInOrder
 };
 
 // Optional hand-over of counts and predicted histograms to the host (host-mapped memory): every word is
@@ -204,6 +205,14 @@ inline __host__ __device__ TiledUnit tiled_unit(int u, int npanels, int mpanels)
 inline int ffn_tiled_units(int npanels, int n_tiles, int slices) { return npanels * ((n_tiles + 7) / 8) * slices; }
 // every XCD gets the same number of workgroups; those past an XCD's share of units exit at once
 inline int ffn_tiled_wgs(int n_units) { return (n_units + 7) / 8 * 8; }
+// A first half of at most a round of units (one per compute unit) takes them in order over all groups instead, an even share of
+// the launch per XCD: that XCD's units come from one or two groups and share most of their panels, where an eighth of a small
+// group is three units of a weight panel and up to three token panels each (374 units: 423 -> 261 MB past L2).  Two layers:
+// DeepSeek-shaped 400 / 700 tokens 479.9 -> 470.0 / 590.9 -> 581.7 us, Qwen-shaped on 12 experts 640 tokens 340.3 -> 337.2.
+// Above a round the last units of an XCD's share run alone (DeepSeek-shaped on 16 experts 1700 tokens 654 -> 734), and second
+// halves, whose units differ in length, lose as much as they gain.
+constexpr int kTiledInOrder = -1;        // xcd_rot of every group of such a launch
+constexpr int kTiledInOrderUnits = 256;
 inline int ffn_gate_up_tiled_wgs(int F, int n_tiles) { return ffn_tiled_wgs(ffn_tiled_units(F / 128, n_tiles, 1)); }
 inline int ffn_down_tiled_wgs(int d, int n_tiles, int slices) { return ffn_tiled_wgs(ffn_tiled_units(d / 256, n_tiles, slices)); }
 

@@ -200,7 +200,7 @@ bool early_tiled(const ef_ctx *c, const int32_t *counts_host, bool has_shared, i
 // 1110, 1278 / 1139, 1619 / 1480 us, two experts 200 tokens 556 / 454; DeepSeek-shaped 1056 tokens 711 / 694, on 16 experts
 // with 385 tiled workgroups 551 / 524).  With fewer every workgroup has a unit to itself, and the longer ones end the launch
 // (Qwen-shaped on 12 experts, 121 streamed and 231 tiled, 640 tokens 357 / 413; DeepSeek-shaped on 16, 176 and 198, 600 tokens
-// 372 / 380; d = 512, 56 and 40, 700 tokens 147 / 155).  Tiled workgroups are counted as they are launched, a multiple of
+// 372 / 380; d = 512, 56 and 40, 700 tokens 147 / 155).  Tiled workgroups are counted as a multiple of
 // eight per group: with 240 to 256 that do not exit at once the streamed ones wait for units all the same (Qwen-shaped on 12
 // experts, 700 / 760 tokens 409 / 399, 434 / 420; DeepSeek-shaped on 16, 700 tokens 416 / 419).  A set lds_shared_occupancy
 // asks for a form of the passes of four.  4-bit: passes of four dequantise half as often, but a pass is twice as long; they
@@ -371,6 +371,9 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             }
             return best;
         };
+        int units_up = 0;
+        for (int i = 0; i < nb; ++i) units_up += ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1);
+        const bool in_order = rot_on && units_up <= ef::kTiledInOrderUnits;
         for (int i = 0; i < nb; ++i) {
             big.wg_start[i] = wg_up;
             bdn.wg_start[i] = wg_dn;
@@ -380,13 +383,15 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
                 continue;
             }
             const int ks = i == split_grp ? split_ksg : ksg_tiled;
-            big.xcd_rot[i] = place(ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1), load_up);
+            const int nu = ef::ffn_tiled_units(big.F[i] / 128, big.n_tiles[i], 1);
+            big.xcd_rot[i] = in_order ? ef::kTiledInOrder : place(nu, load_up);
             bdn.xcd_rot[i] = place(ef::ffn_tiled_units(d / 256, big.n_tiles[i], ks), load_dn);
-            wg_up += ef::ffn_gate_up_tiled_wgs(big.F[i], big.n_tiles[i]);
+            wg_up += in_order ? nu : ef::ffn_tiled_wgs(nu);
+            tiled_up_wgs += ef::ffn_tiled_wgs(nu);   // what the rules below count, whatever the order
             wg_dn += ef::ffn_down_tiled_wgs(d, big.n_tiles[i], ks);
         }
         big.wg_start[nb] = wg_up;
-        tiled_up_wgs = wg_up;
+        if (c->q4 && !expand) tiled_up_wgs = wg_up;
         bdn.wg_start[nb] = wg_dn;
         tiled_dn_wgs = wg_dn;
         alg_bytes(big, nb, tb_up, tb_dn);
@@ -406,7 +411,7 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
             dq.n = nb;
             EF_HIP(c, ef::launch_dequant_q4(dq, d, s));
         }
-        EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, tiled_up_wgs, c->xp, c->act, d, c->q4, s));
+        EF_HIP(c, ef::launch_ffn_gate_up_tiled(big, big.wg_start[nb], c->xp, c->act, d, c->q4, s));
         return EF_OK;
     };
     auto tiled_down = [&]() -> int {

@@ -231,3 +231,14 @@ def test_q4_two_large_groups_are_expanded(sizes, expanded):
     out = run_groups(None, cfg, sizes, True, {}, expect=dict(ffn_up=int(not expanded), ffn_up_tiled=int(expanded)))
     other = run_groups(None, cfg, sizes, True, dict(q4_expand_min_units=1 << 20 if expanded else 0))
     assert np.linalg.norm(out - other) <= 1e-3 * np.linalg.norm(other)
+
+
+@pytest.mark.parametrize("F,sizes", [(384, [350, 449, 320, 480, 0, 600, 1, 7]), (128, [300] * 8), (2048, [512] * 8),
+                                     (2048, [512] * 7 + [600])], ids=["33 units", "16 units", "256 units", "272 units"])
+def test_tiled_first_half_in_unit_order(oracle_mod, F, sizes):
+    """Up to 256 units the tiled first half takes them in order, uneven shares per XCD among them; past that, and without
+    tiled_xcd_rotation, an eighth of every group.  The order changes no bit."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"in_order_{F}_{sum(sizes)}", d=256, E=8, k=1, F=F)
+    a = run_groups(oracle_mod if F < 2048 else None, cfg, sizes, False, {})
+    b = run_groups(None, cfg, sizes, False, {"tiled_xcd_rotation": 0})
+    assert np.array_equal(a, b)
