@@ -494,7 +494,8 @@ typedef struct ef_tuning {
     int32_t tiled_min_up_wgs;        /* >= 1: ... and only if the tiled first-half launch has this many workgroups (1) */
     int32_t tiled_min_down_wgs;      /* >= 1: ... and the second-half launch this many (1) */
     int32_t tiled_xcd_rotation;      /* 0/1: each tiled group's units, an eighth per XCD, start on the XCD that leaves the
-                                        fullest one least full (1); 0: all groups start on XCD 0 */
+                                        fullest one least full, and a first half of one round takes contiguous shares of
+                                        all its units (1); 0: all groups start on XCD 0 */
     int32_t overlap_tiled;           /* 0/1: a phase's streamed launches run on a side stream beside its tiled ones (1) */
     int32_t sort_groups;             /* 0/1: groups with the most work first in a launch (1) */
     int32_t passes_of_four;          /* 0/1: streamed groups of >= 3 token tiles take passes of four tiles, 16-bit ones of >= 5

@@ -40,7 +40,7 @@ struct GateArgs {
     float *part;                   // two_step: [tiles][groups][ksplit][32][32 * column blocks] partial logits
     int stream;                    // 1: launches that qualify (gate_stream_ok) take the streaming form of the kernel
     int32_t *hist_tiles;           // null, or [G-1][ntiles][E]: gates 1.. leave per-tile counts here and `hist` alone
-                                   // (one-step launches with gate 0 = the current layer; group_scan_kernel adds them up)
+                                   // (one-step launches with gate 0 = the current layer; the grouping adds them up)
 };
 
 // Grouped FFN launch: one group per active expert (+ one for the dense shared FFN).

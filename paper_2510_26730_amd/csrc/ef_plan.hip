@@ -79,8 +79,8 @@ int run_gates(ef_ctx *c, int layer, const void *hidden, int T, float beta, bool 
         }
         a.two_step = (a.ksplit > 1 || a.tsplit > 1) ? 1 : 0;
         // histograms of the look-ahead: the library's own buffer is left zeroed by the hand-over step of the previous
-        // layer; a caller's is written by the scan of the per-tile counts where the call ends in one, and cleared here
-        // for the gates' atomics otherwise (a launch of 4 us)
+        // layer; a caller's is written by the grouping, which adds per-tile counts up, from five tiles on, and cleared
+        // here for the gates' atomics otherwise (a launch of 4 us)
         if (He > 0 && !ex.host_meta && g0 == 0) {
             if (do_route && total_gates <= per_launch && !a.two_step && ntiles > ef::kGroupSmallTiles)
                 hist_tiles = rs.blockcounts + (size_t)ntiles * E;
