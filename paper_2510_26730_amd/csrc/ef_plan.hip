@@ -429,15 +429,14 @@ int launch_phase(ef_ctx *c, int layer, const std::vector<PhaseGroup> &groups, co
     if (rc) return rc;
     if (n == 0) return tiled_down();
     ef::GroupTable dn = gu;
-    long long wgs_of_four = 0, wgs_second = 0;
-    for (int i = 0; i < n; ++i) {
-        wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
-        if (gu.n_tiles[i] > 1) wgs_second += gu.F[i] / 128;
-    }
-    // 4-bit groups of a tiled one's size stream because of what the whole layer holds; a phase that has one keeps to the
-    // layer's pass width (for which the K slices of the second half were chosen) and does not cut the first half's K range
-    // in two, whatever else is resident: such a group's sums do not depend on the phase it runs in
-    const int tpp = large ? tpp_layer : tiles_per_pass(c, max_tiles, wgs_of_four, wgs_second, tiled_up_wgs);
+    long long wgs_of_four = 0;
+    for (int i = 0; i < n; ++i) wgs_of_four += (long long)(gu.F[i] / 128) * ((gu.n_tiles[i] + 3) / 4);
+    // 4-bit: passes of four, and full ones of two, multiply with weights rounded to fp16, all others with the codes, so every
+    // phase keeps to the layer's width whatever is resident (a width of one where a phase has no second tile is the same
+    // arithmetic as two).  Groups of a tiled one's size stream because of what the whole layer holds; a phase that has one
+    // does not cut the first half's K range in two either: such a group's sums do not depend on the phase it runs in
+    const int tpp = !c->q4 ? tiles_per_pass(c, max_tiles, wgs_of_four, 0, tiled_up_wgs)
+                           : tpp_layer == 2 && max_tiles == 1 ? 1 : tpp_layer;
     // K slices inside a workgroup of the first half: split while the launch has too few waves to
     // keep enough weight bytes in flight, as long as a slice keeps >= 16 fragments
     long long units = 0;
@@ -644,7 +643,7 @@ extern "C" int ef_moe_ffn(ef_ctx *c, int layer, const void *hidden, int T, const
         long long base_wgs = 0;
         double streamed_w2_bytes = 0.0;   // second-half weights of the routed groups that stream (4-bit blobs)
         // token tiles per pass of the streamed launch: from the groups that stream (the tiled ones have kernels of
-        // their own), with the rule that launch_phase applies to a phase's groups
+        // their own), with the rule that launch_phase applies to a phase's groups (16-bit; 4-bit phases take this width)
         int tmax = 1;
         long long wgs_of_four = 0, wgs_second = 0;
         auto see = [&](int F, int cnt) {

@@ -29,10 +29,11 @@ SIZES = {
 }
 
 
-def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=None, forms=None):
+def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=None, forms=None, q4_forms=None):
     """Output of the layer; compared with the oracle if one is given.  slots: fewer cache slots than experts, all empty.
     expect: launches of kernel kinds; flops: their algorithmic flops; forms: template arguments of the LDS-shared kernels that
-    ran (token tiles per pass, register ring, workgroups per compute unit), the same in both halves."""
+    ran (token tiles per pass, register ring, workgroups per compute unit), the same in both halves; q4_forms: of the 4-bit
+    first halves that ran (token tiles per pass, parts of the K range, workgroups per compute unit)."""
     T, E = sum(sizes), cfg.E
     st = LayerStack(cfg, 1, slots_total=slots or E, max_tokens=T, q4=q4, flags=ef.EF_FLAG_PROFILE if expect else 0)
     try:
@@ -54,12 +55,15 @@ def run_groups(oracle_mod, cfg, sizes, q4, tune, slots=None, expect=None, flops=
         dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
         out = torch.full((T, cfg.d), float("nan"), dtype=torch.float32, device="cuda")
         hd, d_ids, d_w, d_off, d_perm, d_inv = dev_u16(h), dev(ids), dev(w), dev(offsets), dev(perm), dev(inv)
-        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) if forms else contextlib.nullcontext() as prof:
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) if forms or q4_forms else contextlib.nullcontext() as prof:
             ef.ef_moe_ffn(st.ctx, 0, hd, T, d_ids, d_w, counts, d_off, d_perm, d_inv, out, torch.cuda.current_stream())
             torch.cuda.synchronize()
         if forms:
             ran = [m.groups() for m in (re.search(r"ffn_(gate_up|down)_shared_kernel<([\d, ]+)>", e.name) for e in prof.events()) if m]
             assert sorted(ran) == sorted((half, form) for half in ("down", "gate_up") for form in forms), ran
+        if q4_forms:
+            ran = [m.group(1) for m in (re.search(r"ffn_gate_up_q4_kernel<([\d, ]+)>", e.name) for e in prof.events()) if m]
+            assert sorted(ran) == sorted(q4_forms), ran
         if expect:
             launches = dict(zip(ef.EF_KERNELS, ef.ef_get_stats(st.ctx)["kernel_launches"]))
             assert {k: launches[k] for k in expect} == expect
@@ -241,4 +245,20 @@ def test_tiled_first_half_in_unit_order(oracle_mod, F, sizes):
     cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"in_order_{F}_{sum(sizes)}", d=256, E=8, k=1, F=F)
     a = run_groups(oracle_mod if F < 2048 else None, cfg, sizes, False, {})
     b = run_groups(None, cfg, sizes, False, {"tiled_xcd_rotation": 0})
+    assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("d,F,sizes,form", [
+    (2048, 1024, [33, 48, 49, 50, 63, 64, 57, 40], "1, 2, 1"),       # second passes re-read 16 MiB of codes: passes of one
+    (2048, 1152, [33, 48, 49, 50, 63, 64, 57, 40], "2, 2, 1"),       # 18 MiB
+    (2048, 1024, [97, 50, 64, 33, 49, 16, 0, 5], "2, 2, 1"),         # a group of four tiles beside
+    (256, 14336, [97, 128, 65, 96, 33, 1, 64, 127], "4, 1, 2"),      # 896 workgroups in passes of four
+])
+def test_q4_results_do_not_depend_on_what_is_resident(oracle_mod, d, F, sizes, form):
+    """Passes of four, and of two over 49 tokens and more, multiply with weights rounded to fp16, narrower ones with the codes:
+    the width is the layer's, so the bits are the same with every expert resident (one phase) and through a single cache slot
+    (one expert per phase)."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"groups_width_{d}_{F}", d=d, F=F, F_shared=0, k=1)
+    a = run_groups(oracle_mod, cfg, sizes, True, {}, q4_forms=[form])
+    b = run_groups(None, cfg, sizes, True, {}, slots=1)
     assert np.array_equal(a, b)
