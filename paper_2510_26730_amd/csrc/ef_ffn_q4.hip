@@ -390,15 +390,14 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
     const int F = gt.F[grp];
     const int rbw = (F >> 5) >> 2;               // workgroups per pass (F is a multiple of 128)
     const int pass = local / rbw;
-    const int wave = (threadIdx.x >> 6) & 3, kh = threadIdx.x >> 8, lane = threadIdx.x & 63;
+    const int wave = (threadIdx.x >> 6) & 3, lane = threadIdx.x & 63;
+    // scalar where it bounds the K loop; undivided ranges keep vector addresses (0 spelled out: <4, 1, 2> 71.4 -> 72.3 us for
+    // 20 tiles of 5632 x 2048)
+    const int kh = KH == 1 ? threadIdx.x >> 8 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
     const int rb = (local % rbw) * 4 + wave;
     int ntl = gt.n_tiles[grp] - pass * TT;
     if (ntl > TT) ntl = TT;
     const int nkb = d >> 4, nq = d >> 6;
-    // stages [k0, k0 + nloc) of this wave's half (the launcher checks that the halves are equal: every wave
-    // passes the same barriers)
-    const int nloc = nq / KH, k0 = kh * nloc;
-
     const char *blob = reinterpret_cast<const char *>(gt.blob[grp]);
     const uint4 *w13 = reinterpret_cast<const uint4 *>(blob) + (size_t)rb * nq * 128 + lane;
     const uint16_t *sA = reinterpret_cast<const uint16_t *>(blob + (size_t)3 * d * F / 2) +
@@ -406,6 +405,15 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
     // live half tiles of 16 tokens (passes of one or two tiles work in those; of a half live tile they read the tokens that
     // exist twice, the same cache lines)
     const int nh = min((gt.count[grp] - pass * TT * kTile + 15) >> 4, 2 * TT);
+    // Stages [k0, k0 + nloc) of this wave's half.  The loops that put the scale on the sums take whole blocks of 128 inputs,
+    // the lower half the odd one; the upper half then waits at as many barriers more (`even`: barriers count waves), so every
+    // wave passes the same number.
+    const int cut = KH == 1 ? nq : TT < 4 && nh < 4 ? ((nq >> 1) + 1) / 2 * 2 : nq / 2;
+    const int k0 = kh * cut, nloc = KH == 2 && kh ? nq - cut : cut;
+    auto even = [&] {
+        if constexpr (KH == 2)
+            for (int i = nloc; i < cut; ++i) __syncthreads();
+    };
     // this wave's share of the token fragments of a stage: k-step `wave` of each tile (tiles past the
     // group's last one repeat it; their results are dropped)
     const uint4 *xsrc[TT];
@@ -430,6 +438,7 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
             zero16(G);
             zero16(U);
             q4_stream32<TT, D>(w, xsrc, xs[kh], k0, k0 + nloc, wave, lane, G, U);
+            even();
             if constexpr (KH == 2) {
                 float4 *red = reinterpret_cast<float4 *>(&xs[0][0][0][0]) + (size_t)wave * 8 * 64 + lane;
                 if (kh == 1) {
@@ -460,6 +469,7 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
             for (int h = 0; h < HT; ++h) G[r][h] = U[r][h] = floatx4_t{0.f, 0.f, 0.f, 0.f};
         if (TT == 1 || nh == 1) q4_stream16<TT, 1, D>(w, xsrc, xs[kh], k0, k0 + nloc, wave, lane, G, U);
         else q4_stream16<TT, 2 * TT - 1, D>(w, xsrc, xs[kh], k0, k0 + nloc, wave, lane, G, U);
+        even();
 
         if constexpr (KH == 2) {
             // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
@@ -562,8 +572,10 @@ hipError_t launch_ffn_gate_up_q4(const GroupTable &gt, int total_wgs, int tiles_
     if (gt.wg_start[gt.n_groups] != total_wgs) return hipErrorInvalidValue;
     const uint4 *x = reinterpret_cast<const uint4 *>(xp);
     uint4 *a = reinterpret_cast<uint4 *>(act);
-    // two K halves per workgroup when each half keeps a few stages and whole blocks of 128 inputs
-    const bool halves = k_halves && (d >> 6) % 4 == 0 && (d >> 6) >= 8;
+    // two K halves per workgroup when each half keeps a few stages (d / 64 in all, an even number; whole range / halves of an odd
+    // number of 128-input blocks, eight experts of F = 2048, two layers: d = 640 16 / 200 tokens 78.1 / 76.9, 100.0 / 96.9 us,
+    // d = 1920 95.7 / 92.5, 135.7 / 130.7)
+    const bool halves = k_halves && (d >> 6) >= 8;
     // more workgroups than compute units: two of them per unit instead (whole K range each, the short register ring);
     // their waves stall at different times, where the halves of one workgroup meet at the same barriers
     // (seven Mixtral-shaped experts: 127 against 135 us, Qwen-shaped batch 52 against 60 us)

@@ -262,3 +262,16 @@ def test_q4_results_do_not_depend_on_what_is_resident(oracle_mod, d, F, sizes, f
     a = run_groups(oracle_mod, cfg, sizes, True, {}, q4_forms=[form])
     b = run_groups(None, cfg, sizes, True, {}, slots=1)
     assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("d", [512, 640, 768, 896, 1280])
+@pytest.mark.parametrize("sizes,form", [([1, 15, 16, 17, 31, 32, 0, 30], "1, 2, 1"), ([97, 33, 47, 48, 49, 63, 64, 1], "2, 2, 1")],
+                         ids=["passes of one", "passes of two"])
+def test_q4_k_range_in_halves(oracle_mod, d, sizes, form):
+    """A first half of few workgroups cuts its K range in two, whole and half tiles, passes of two (the largest group has four
+    tiles) on both sides of 48 tokens: halves of 4, 6 and 10 stages (one turn of the register ring, a turn and a tail, two and a
+    tail) and, of an odd number of 128-input blocks, 6 + 4 and 8 + 6 (full passes of two: 5 + 5 and 7 + 7)."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"groups_halves_{d}", d=d, F=256, F_shared=0, k=1)
+    out = run_groups(oracle_mod, cfg, sizes, True, {}, q4_forms=[form])
+    same = run_groups(None, cfg, sizes, True, dict(down_k_slices=2), q4_forms=[form])
+    assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums

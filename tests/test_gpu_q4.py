@@ -58,8 +58,8 @@ def layer_check(oracle_mod, st, h, T, beta, res, toks=None):
     ("tiny", dict(d=512, F=1024), 37),           # ragged tile
     ("tiny", dict(d=128, F=128), 5),             # one quad pair per row block, one scale group
     ("tiny", dict(d=384, F=640), 200),           # several passes of two tiles, odd quad counts per K slice
-    ("tiny", dict(d=640, F=256), 70),            # K halves of five stages: one full turn of the register ring and a tail
-    ("tiny", dict(d=896, F=128), 33),            # K halves of seven stages
+    ("tiny", dict(d=640, F=256), 70),            # K halves of six and four stages: a turn of the register ring with a tail and one without
+    ("tiny", dict(d=896, F=128), 33),            # K halves of eight and six stages
     ("deepseek_v2_lite", dict(d=256, F=128), 130),   # 64 experts, mostly tiny groups
 ])
 def test_q4_layer_matches_oracle(oracle_mod, name, kw, T):
@@ -79,7 +79,8 @@ def test_q4_layer_matches_oracle(oracle_mod, name, kw, T):
 @pytest.mark.parametrize("d,F,slices", [(512, 384, 0), (384, 384, 2), (640, 128, 8)])
 def test_q4_group_sizes_at_half_tiles(oracle_mod, T, d, F, slices):
     """Two experts that every token takes, so a group is the whole batch: both sides of each half tile of 16 tokens, K ranges in
-    halves and whole, three blocks of 128 inputs in two slices and one in eight (seven of them empty)."""
+    halves (equal ones, and of three and two blocks of 128 inputs) and whole, three blocks in two slices and one in eight (seven of
+    them empty).  A batch of two tiles takes passes of one here; test_q4_k_range_in_halves has the same sizes in passes of two."""
     cfg = q4_shape("tiny", name=f"q4_half_tiles_{d}_{F}", d=d, F=F, E=2, k=2)
     st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=64, q4=True)
     try:
