@@ -495,9 +495,15 @@ hipError_t launch_ffn_down(const GroupTable &gt, int total_wgs, int tiles_per_pa
 }
 
 // ------------------------------------------------------------------------------------------
-// weighted un-permute, at most KM experts per token: out[t] = sum_j w[t,j] * (sum over the K-slice planes of expert ids[t,j] of Y[inv_perm[t*k+j]])
+// weighted un-permute: out[t] = sum_j w[t,j] * (sum over the K-slice planes of expert ids[t,j] of Y[inv_perm[t*k+j]])
 //                               (+ the dense shared FFN's row of token t)
+// Two forms with the same sums in the same order (planes, then rows); launch_combine chooses.
 // ------------------------------------------------------------------------------------------
+
+// Few workgroups, bound by round trips to memory: what names the rows (at most KM) first, then the first two planes of every
+// row, then what is left plane by plane, a round trip each, where a walk over the rows takes up to two per row (six experts
+// and the shared FFN, 32 / 128 / 200 tokens: 5.6 -> 4.0, 6.0 -> 4.9, 6.8 -> 6.0 us; four, 128 / 200 tokens: 5.6 -> 4.9, 6.4 ->
+// 5.9; two: level).
 template <int KM>
 __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ Y, PlaneTable planes, long long y_plane,
                                                       const float *__restrict__ w, const int32_t *__restrict__ ids,
@@ -506,9 +512,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
     const int t = blockIdx.x;
     const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
     if (c >= d) return;
-    // What names the rows first, then the first two planes of every row, then what is left plane by plane: a round trip to
-    // memory each, where a walk over the rows takes up to two per row (six experts and the shared FFN, 32 tokens: 5.6 -> 4.0
-    // us; 8192 tokens of two experts, at memory rate, 94 us either way).  The order of the sums is planes, then rows.
     float wj[KM];
     const float *row[KM + 1];
     int np[KM + 1];
@@ -545,6 +548,43 @@ __global__ __launch_bounds__(256) void combine_kernel(const float *__restrict__ 
     *reinterpret_cast<float4 *>(out + (size_t)t * d + c) = acc;
 }
 
+// Workgroups on every SIMD: row by row in few registers, eight workgroups per compute unit hide each other's round trips.
+__global__ __launch_bounds__(256, 8) void combine_walk_kernel(const float *__restrict__ Y, PlaneTable planes, long long y_plane,
+                                                              const float *__restrict__ w, const int32_t *__restrict__ ids,
+                                                              const int32_t *__restrict__ inv_perm, int T, int k, int d,
+                                                              long long shared_row0, float *__restrict__ out) {
+    const int t = blockIdx.x;
+    const int c = (blockIdx.y * 256 + threadIdx.x) * 4;
+    if (c >= d) return;
+    auto sum_planes = [&](const float *row, int np) {
+        float4 y = *reinterpret_cast<const float4 *>(row);
+        for (int p = 1; p < np; ++p) {
+            const float4 z = *reinterpret_cast<const float4 *>(row + (size_t)p * y_plane);
+            y.x += z.x; y.y += z.y; y.z += z.z; y.w += z.w;
+        }
+        return y;
+    };
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int j = 0; j < k; ++j) {
+        const int a = t * k + j;
+        const float wj = w[a];
+        const float4 y = sum_planes(Y + (size_t)inv_perm[a] * d + c, planes.routed[ids[a]]);
+        acc.x += wj * y.x; acc.y += wj * y.y; acc.z += wj * y.z; acc.w += wj * y.w;
+    }
+    if (shared_row0 >= 0) {
+        const float4 y = sum_planes(Y + (size_t)(shared_row0 + t) * d + c, planes.shared);
+        acc.x += y.x; acc.y += y.y; acc.z += y.z; acc.w += y.w;
+    }
+    *reinterpret_cast<float4 *>(out + (size_t)t * d + c) = acc;
+}
+
+// Up to two workgroups per compute unit the row-by-row form is behind (above), from there on ahead: four experts 400 / 640 / 1000
+// tokens of 2048 columns 7.8 -> 7.0, 10.1 -> 9.2, 11.7 -> 10.5 us, six 550 / 850 / 1800 tokens 8.0 -> 7.1, 11.1 -> 9.3, 20.8 ->
+// 19.3, two experts 520 / 1000 tokens of 4096 11.6 -> 11.2, 19.1 -> 18.5, 8192 level.  Except where its rounds of eight workgroups per compute
+// unit end in one that is nearly empty (six experts, 2048 columns, 1020 tokens 10.8 / 12.4 us row by row / loads first, 1030 13.0 /
+// 12.5, 1150 13.8 / 13.6, 1200 level, 1280 14.6 / 15.5; 2040 21.9 / 22.6, 2060 23.1 / 22.4, 2200 25.3 / 24.4; 3120 35.1 / 33.7).
+static bool combine_walks(long long wgs) { return wgs > 512 && (wgs <= 2048 || (wgs - 1) % 2048 >= 320); }
+
 // `done` (may be null): an event that completes with this kernel.  It rides on the kernel's own completion
 // signal, which costs the stream nothing, where a separate event record behind the kernel costs 2-3 us.
 hipError_t launch_combine(const float *y, const PlaneTable &planes, long long y_plane, const float *w,
@@ -555,6 +595,7 @@ hipError_t launch_combine(const float *y, const PlaneTable &planes, long long y_
         return launch_done(kernel, dim3(T, (d + 1023) / 1024), dim3(256), done, s, y, planes, y_plane, w, ids, inv_perm, T, k, d,
                            shared_row0, out);
     };
+    if (combine_walks((long long)T * ((d + 1023) / 1024))) return go(combine_walk_kernel);
     return k <= 2 ? go(combine_kernel<2>) : k <= 4 ? go(combine_kernel<4>) : go(combine_kernel<kMaxK>);
 }
 

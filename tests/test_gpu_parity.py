@@ -236,6 +236,30 @@ def test_unpermute_over_rows_and_planes(oracle_mod, k, Fs, slices):
         st.close()
 
 
+@pytest.mark.parametrize("k,Fs", [(2, 0), (3, 256), (8, 256)], ids=lambda v: str(v))
+@pytest.mark.parametrize("T,walks", [(512, False), (513, True), (2048, True), (2049, False), (2368, False), (2369, True)])
+def test_unpermute_row_by_row_where_the_grid_fills_the_chip(oracle_mod, k, Fs, T, walks):
+    """A workgroup per token: up to two per compute unit, and up to 320 beyond a round of eight, the form that requests all rows
+    first; row by row otherwise.  The kernel's name says which ran."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"unpermute_forms{k}", cfg_id=940 + k, d=64, E=9, k=k, F=256, F_shared=Fs)
+    st = LayerStack(cfg, 1, slots_total=cfg.E, max_tokens=T)
+    try:
+        ef.ef_set_tuning(st.ctx, down_k_slices=2)
+        h = synth.hidden(cfg, 7, T)
+        hd = dev_u16(h)
+        r = st.route(0, hd, T, 0.0)
+        torch.cuda.synchronize()
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+            out = st.ffn(0, hd, T, r)
+        ran = ["combine_walk_kernel" in e.name for e in prof.events() if "combine_" in e.name]
+        assert ran == [walks]
+        full = oracle_layer(oracle_mod, st, 0, h, 0.0, np.zeros(cfg.E, dtype=np.uint8), forced_ids=to_np(r, T, k)["ids"])
+        e1, e2 = float_close(out, full["out"])
+        say(f"un-permute k={k} Fs={Fs} T={T}: max abs {e1:.2e}, rel l2 {e2:.2e}")
+    finally:
+        st.close()
+
+
 def test_shared_ffn_tiled_beside_streamed_routed_groups(oracle_mod):
     """A batch whose shared FFN (10 token tiles, K = 1024) takes the tiled kernels with two K slices while the
     routed experts (2-4 tiles, K = 128) stream with one: the un-permute sums a different number of planes per
