@@ -13,8 +13,8 @@
 // holds one matrix row (column) and therefore needs one scale per group, and in fp16: the codes
 // become the fp16 numbers 1024 + q (or 64 + q) by one bit operation, a packed subtraction gives q - 8 exactly and
 // a packed multiplication (q - 8) * s: three vector instructions per pair of weights where an fp32
-// route costs seven, which is what keeps these kernels on the memory side of the balance.  Passes of up to
-// 48 tokens leave the scale to the sums (q4_stream16, q4_stream32).  The
+// route costs seven, which is what keeps these kernels on the memory side of the balance.  Passes of one and
+// of two token tiles with up to 48 tokens leave the scale to the sums (q4_stream16, q4_stream32).  The
 // matrix cores therefore run in fp16 (fp32 accumulation): the packed tokens of a 4-bit context and
 // the intermediate activations are fp16 fragments (tokens convert exactly from bf16 for
 // 2^-14 <= |x| < 65504).
@@ -191,19 +191,22 @@ __device__ __forceinline__ void q4_up_stream(const uint4 *__restrict__ w13, cons
 #undef EF_Q4U_SCALES
 
 // ------------------------------------------------------------------------------------------
-// K loops of passes of up to 48 tokens, either half: sum_k x_k (q_k - 8) s as s (sum_k x_k (q_k - 8)) per block of the 128 inputs
-// that share a scale.  The operand is q - 8 alone, nine vector instructions per eight weights instead of thirteen, and the
-// weights' scales are read and converted once per block; the matrix cores sum a block from zero, and every second stage the
-// block's sums join the totals with one multiply-add per accumulator element, in 32 bits and with the scale as it is.  The
-// operands are swapped against the other passes (tokens are the rows), so a lane has one weight row and needs one scale.
-// Passes of 49 tokens and more keep (q - 8) s as the operand: tiles share its cost, and a block's accumulators beside those of
-// the totals would take the registers of the ring.
+// K loops of passes of one and two tiles with up to 48 tokens, either half: sum_k x_k (q_k - 8) s as s (sum_k x_k (q_k - 8))
+// per block of the 128 inputs that share a scale.  The operand is q - 8 alone, nine vector instructions per eight weights
+// instead of thirteen, and the weights' scales are read and converted once per block; the matrix cores sum a block from zero,
+// and every second stage the block's sums join the totals with one multiply-add per accumulator element, in 32 bits and with
+// the scale as it is.  The operands are swapped against the other passes (tokens are the rows), so a lane has one weight row
+// and needs one scale.  Passes of 49 tokens and more, and passes of four whatever their last one holds, keep (q - 8) s as the
+// operand: tiles share its cost, and a block's accumulators beside those of the totals would take the registers of the ring.
+// The two round differently, so the width of a layer's passes is chosen once for all of its phases (launch_phase).
 //
 // Bound by the weight stream and what a wave's in-order issue leaves idle of it.  Two layers, before / after: eight
-// Mixtral-shaped experts 1 / 8 / 30 / 64 tokens 145.0 / 137.8, 270.8 / 254.4, 331.0 / 314.9, 361.2 / 338.8 us (the first
-// half's loads alone 91 of its 99 us at 64 tokens); DeepSeek-shaped 4 / 32 / 100 tokens 107.3 / 101.9, 146.6 / 140.6, 186.1 /
-// 181.2; Qwen-shaped 25 / 200 tokens 116.9 / 111.5, 219.0 / 214.1.  Raised codes 64 + q as the operand (seven instructions), 72
-// times the sum of the inputs taken off through LDS: 257.9 and 360.7 us at 8 and 64 tokens, and rounding errors of its own.
+// Mixtral-shaped experts 1 / 8 / 30 / 64 tokens 145.0 / 137.8, 270.8 / 254.4, 331.0 / 314.9, 361.2 / 338.8 us (64 tokens: first
+// half 103 -> 100, its loads alone 91, second half 57 -> 51); DeepSeek-shaped 4 / 32 / 100 tokens 107.3 / 101.9, 146.6 / 140.6,
+// 186.1 / 181.2; Qwen-shaped 25 / 200 tokens 116.9 / 111.5, 219.0 / 214.1.  The block's sums cost registers: first halves of
+// passes of one need 155 instead of 117 to 123 and fit three waves per SIMD instead of four.  Raised codes 64 + q as the
+// operand (seven instructions), 72 times the sum of the inputs taken off through LDS: 257.9 and 360.7 us at 8 and 64 tokens,
+// and rounding errors of its own.
 // ------------------------------------------------------------------------------------------
 struct Q4Streams {                 // of one wave: two weight streams (W1 and W3, or two column blocks of W2) and their scales
     const uint4 *wa, *wb;
@@ -313,7 +316,8 @@ __device__ __forceinline__ void q4_stream16(const Q4Streams &w, const uint4 *con
 #undef EF_Q4_COMPUTE
 }
 
-// One whole tile of 32 tokens (as two half tiles: the same matrix time, more instructions).  A lane holds row l % 32 and, in element v, token 8 (v / 4) + 4 (l / 32) + v % 4.
+// One whole tile of 32 tokens (as two half tiles: the same matrix time, more instructions).  A lane holds row l % 32 and, in
+// element v, token 8 (v / 4) + 4 (l / 32) + v % 4.
 template <int TT, int D>
 __device__ __forceinline__ void q4_stream32(const Q4Streams &w, const uint4 *const (&src)[TT], u32x4_t (*xs)[TT * 4][64],
                                             int q0, int q1, int wave, int lane, floatx16 &A, floatx16 &B) {
@@ -506,57 +510,58 @@ __global__ __launch_bounds__(256 * KH, OCC) void ffn_gate_up_q4_kernel(GroupTabl
         return;
     }
 
-    floatx16 G[TT], U[TT];
+    if constexpr (TT > 1) {
+        floatx16 G[TT], U[TT];
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
+        for (int tt = 0; tt < TT; ++tt) { zero16(G[tt]); zero16(U[tt]); }
 
-    if constexpr (TT == 1) return;
-    if (TT == 4 && ntl == 1) q4_up_stream<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-    else if (TT == 2 || ntl == 2) q4_up_stream<TT, (TT > 1 ? 2 : 1), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-    else if (ntl == 3) q4_up_stream<TT, (TT > 2 ? 3 : TT), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
-    else q4_up_stream<TT, TT, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+        if (TT == 4 && ntl == 1) q4_up_stream<TT, 1, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+        else if (TT == 2 || ntl == 2) q4_up_stream<TT, 2, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+        else if (ntl == 3) q4_up_stream<TT, (TT > 2 ? 3 : TT), D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
+        else q4_up_stream<TT, TT, D, KH == 1>(w13, sA, xsrc, xs[kh], k0, nloc, wave, lane, G, U);
 
-    if constexpr (KH == 2) {
-        // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
-        float4 *red = reinterpret_cast<float4 *>(&xs[0][0][0][0]) + (size_t)wave * (2 * TT * 4) * 64 + lane;
-        static_assert(sizeof(xs) >= (size_t)4 * (2 * TT * 4) * 64 * sizeof(float4), "partial sums fit the ring's space");
-        if (kh == 1) {
+        if constexpr (KH == 2) {
+            // every stage ends with a barrier: the ring is no longer read.  Lower half + upper half, in this order.
+            float4 *red = reinterpret_cast<float4 *>(&xs[0][0][0][0]) + (size_t)wave * (2 * TT * 4) * 64 + lane;
+            static_assert(sizeof(xs) >= (size_t)4 * (2 * TT * 4) * 64 * sizeof(float4), "partial sums fit the ring's space");
+            if (kh == 1) {
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        red[((tt * 2) * 4 + q) * 64] = make_float4(G[tt][4 * q], G[tt][4 * q + 1], G[tt][4 * q + 2], G[tt][4 * q + 3]);
+                        red[((tt * 2 + 1) * 4 + q) * 64] = make_float4(U[tt][4 * q], U[tt][4 * q + 1], U[tt][4 * q + 2], U[tt][4 * q + 3]);
+                    }
+            }
+            __syncthreads();
+            if (kh == 1) return;
 #pragma unroll
             for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    red[((tt * 2) * 4 + q) * 64] = make_float4(G[tt][4 * q], G[tt][4 * q + 1], G[tt][4 * q + 2], G[tt][4 * q + 3]);
-                    red[((tt * 2 + 1) * 4 + q) * 64] = make_float4(U[tt][4 * q], U[tt][4 * q + 1], U[tt][4 * q + 2], U[tt][4 * q + 3]);
+                    const float4 g = red[((tt * 2) * 4 + q) * 64], u = red[((tt * 2 + 1) * 4 + q) * 64];
+                    G[tt][4 * q] += g.x; G[tt][4 * q + 1] += g.y; G[tt][4 * q + 2] += g.z; G[tt][4 * q + 3] += g.w;
+                    U[tt][4 * q] += u.x; U[tt][4 * q + 1] += u.y; U[tt][4 * q + 2] += u.z; U[tt][4 * q + 3] += u.w;
                 }
         }
-        __syncthreads();
-        if (kh == 1) return;
+        // a lane holds 16 F-values of one token: the two paired-order fragments (fp16) the second half consumes
+        const int nkb2 = F >> 4;
 #pragma unroll
-        for (int tt = 0; tt < TT; ++tt)
+        for (int tt = 0; tt < TT; ++tt) {
+            if (tt >= ntl) break;
+            uint4 *dst = act + gt.act_off[grp] + ((size_t)(pass * TT + tt) * nkb2 + rb * 2) * 64 + lane;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 g = red[((tt * 2) * 4 + q) * 64], u = red[((tt * 2 + 1) * 4 + q) * 64];
-                G[tt][4 * q] += g.x; G[tt][4 * q + 1] += g.y; G[tt][4 * q + 2] += g.z; G[tt][4 * q + 3] += g.w;
-                U[tt][4 * q] += u.x; U[tt][4 * q + 1] += u.y; U[tt][4 * q + 2] += u.z; U[tt][4 * q + 3] += u.w;
+            for (int s = 0; s < 2; ++s) {
+                uint32_t pk[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
+                    const float v0 = silu_mul(g0, U[tt][8 * s + 2 * q]);
+                    const float v1 = silu_mul(g1, U[tt][8 * s + 2 * q + 1]);
+                    pk[q] = __builtin_bit_cast(uint32_t, q4_half2{(_Float16)q4_saturate(v0), (_Float16)q4_saturate(v1)});
+                }
+                dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
             }
-    }
-    // a lane holds 16 F-values of one token: the two paired-order fragments (fp16) the second half consumes
-    const int nkb2 = F >> 4;
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if (tt >= ntl) break;
-        uint4 *dst = act + gt.act_off[grp] + ((size_t)(pass * TT + tt) * nkb2 + rb * 2) * 64 + lane;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            uint32_t pk[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float g0 = G[tt][8 * s + 2 * q], g1 = G[tt][8 * s + 2 * q + 1];
-                const float v0 = silu_mul(g0, U[tt][8 * s + 2 * q]);
-                const float v1 = silu_mul(g1, U[tt][8 * s + 2 * q + 1]);
-                pk[q] = __builtin_bit_cast(uint32_t, q4_half2{(_Float16)q4_saturate(v0), (_Float16)q4_saturate(v1)});
-            }
-            dst[(size_t)s * 64] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         }
     }
 }
@@ -680,7 +685,7 @@ __global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, cons
                                                              float *__restrict__ Y, int d,
                                                              long long y_plane) {
     // passes of one with a ring of four fit three workgroups per compute unit (six: two; DeepSeek-shaped 32 tokens 144.3 -> 141.1
-    // us for two layers)
+    // us for two layers); passes of two with six spill registers (DeepSeek-shaped 100 tokens 190 against 185.7)
     constexpr int D = TT == 4 ? 3 : 4, CBW = 2;
     __shared__ __attribute__((aligned(16))) u32x4_t as[kQ4Lds][TT * 4][64];
     const int wg = blockIdx.x;
@@ -757,36 +762,36 @@ __global__ __launch_bounds__(256, 2) void ffn_down_q4_kernel(GroupTable gt, cons
             }
         return;
     }
-    if constexpr (TT == 1) return;
+    if constexpr (TT > 1) {
+        floatx16 acc[CBW][TT];
+#pragma unroll
+        for (int cw = 0; cw < CBW; ++cw)
+#pragma unroll
+            for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
 
-    floatx16 acc[CBW][TT];
-#pragma unroll
-    for (int cw = 0; cw < CBW; ++cw)
-#pragma unroll
-        for (int tt = 0; tt < TT; ++tt) zero16(acc[cw][tt]);
+        if (TT == 4 && ntl == 1) q4_down_stream<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+        else if (TT == 2 || ntl == 2) q4_down_stream<TT, 2, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+        else if (ntl == 3) q4_down_stream<TT, (TT > 2 ? 3 : TT), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
+        else q4_down_stream<TT, TT, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
 
-    if (TT == 4 && ntl == 1) q4_down_stream<TT, 1, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
-    else if (TT == 2 || ntl == 2) q4_down_stream<TT, (TT > 1 ? 2 : 1), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
-    else if (ntl == 3) q4_down_stream<TT, (TT > 2 ? 3 : TT), D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
-    else q4_down_stream<TT, TT, D, CBW>(w2q, qstride, sB, sstride, asrc, as, nq, q0, q1, wave, lane, acc);
-
-    if (!valid) return;
-    const int g = lane >> 5;
+        if (!valid) return;
+        const int g = lane >> 5;
 #pragma unroll
-    for (int tt = 0; tt < TT; ++tt) {
-        if (tt >= ntl) break;
-        // the product is formed transposed (W2 fragment first: the operand layouts are mirror images), so a lane
-        // holds token lane % 32 and four consecutive output columns per accumulator quad: 16-byte stores
-        const int tl = (pass * TT + tt) * kTile + (lane & 31);
-        if (tl >= gt.count[grp]) continue;
-        float *row = Yp + (size_t)(gt.row_offset[grp] + tl) * d;
+        for (int tt = 0; tt < TT; ++tt) {
+            if (tt >= ntl) break;
+            // the product is formed transposed (W2 fragment first: the operand layouts are mirror images), so a lane
+            // holds token lane % 32 and four consecutive output columns per accumulator quad: 16-byte stores
+            const int tl = (pass * TT + tt) * kTile + (lane & 31);
+            if (tl >= gt.count[grp]) continue;
+            float *row = Yp + (size_t)(gt.row_offset[grp] + tl) * d;
 #pragma unroll
-        for (int cw = 0; cw < CBW; ++cw) {
-            const int col = (cb0 + cw) * 32 + 4 * g;
+            for (int cw = 0; cw < CBW; ++cw) {
+                const int col = (cb0 + cw) * 32 + 4 * g;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4 *>(row + col + 8 * q) =
-                    make_float4(acc[cw][tt][4 * q], acc[cw][tt][4 * q + 1], acc[cw][tt][4 * q + 2], acc[cw][tt][4 * q + 3]);
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4 *>(row + col + 8 * q) =
+                        make_float4(acc[cw][tt][4 * q], acc[cw][tt][4 * q + 1], acc[cw][tt][4 * q + 2], acc[cw][tt][4 * q + 3]);
+            }
         }
     }
 }

@@ -207,8 +207,11 @@ inline int ffn_tiled_units(int npanels, int n_tiles, int slices) { return npanel
 inline int ffn_tiled_wgs(int n_units) { return (n_units + 7) / 8 * 8; }
 // A first half of at most a round of units (one per compute unit) takes them in order over all groups instead, an even share of
 // the launch per XCD: that XCD's units come from one or two groups and share most of their panels, where an eighth of a small
-// group is three units of a weight panel and up to three token panels each (374 units: 423 -> 261 MB past L2).  Two layers:
-// DeepSeek-shaped 400 / 700 tokens 479.9 -> 470.0 / 590.9 -> 581.7 us, Qwen-shaped on 12 experts 640 tokens 340.3 -> 337.2.
+// group is three units of a weight panel and up to three token panels each (DeepSeek-shaped 400 / 700 tokens, 110 / 220 units:
+// 127 -> 78, 252 -> 142 MB past L2; Qwen-shaped 640 tokens, 231 units, 200 -> 130).  The kernel itself gains at 110 units (54 ->
+// 47 us) and not from 209 on (52 -> 55, 56 -> 57); the streamed one beside it gains, which gets the compute units and the bytes.
+// Two layers, eighths / in order: DeepSeek-shaped 300 / 400 / 700 tokens 463 / 456, 478 / 467, 584 / 575 us, on 16 experts 400
+// tokens 327 / 317, 600 level; Qwen-shaped on 12 experts 300 / 500 / 640 tokens 289 / 286, 312 / 308, 334 / 332, on 60 level.
 // Above a round the last units of an XCD's share run alone (DeepSeek-shaped on 16 experts 1700 tokens 654 -> 734), and second
 // halves, whose units differ in length, lose as much as they gain.
 constexpr int kTiledInOrder = -1;        // xcd_rot of every group of such a launch

@@ -275,3 +275,16 @@ def test_q4_k_range_in_halves(oracle_mod, d, sizes, form):
     out = run_groups(oracle_mod, cfg, sizes, True, {}, q4_forms=[form])
     same = run_groups(None, cfg, sizes, True, dict(down_k_slices=2), q4_forms=[form])
     assert np.linalg.norm(out - same) <= 1e-5 * np.linalg.norm(out)      # the order of 32-bit sums
+
+
+@pytest.mark.parametrize("d,F,sizes,form", [
+    (384, 256, [1, 15, 16, 17, 31, 32, 0, 30], "1, 1, 1"),           # six stages: too few for halves
+    (384, 256, [97, 33, 47, 48, 49, 63, 64, 1], "2, 1, 1"),
+    (384, 4736, [1, 15, 16, 17, 31, 32, 8, 30], "1, 1, 2"),          # 296 workgroups
+    (640, 4736, [33, 47, 48, 49, 63, 64, 34, 40], "2, 1, 2"),        # 296, second passes would re-read 23 MiB
+])
+def test_q4_undivided_k_range(oracle_mod, d, F, sizes, form):
+    """The other forms of the 4-bit first half, at the same sizes: a ring of six stages, one turn of it,
+    and for more workgroups than compute units one of four, a turn or two and a tail."""
+    cfg = dataclasses.replace(synth.CONFIGS["tiny"], name=f"groups_whole_{d}_{F}", d=d, F=F, F_shared=0, k=1)
+    run_groups(oracle_mod, cfg, sizes, True, {}, q4_forms=[form])
